@@ -46,6 +46,12 @@ typedef std::atomic<int> Tunable;
 
 constexpr int kMaxDevices = 64;
 
+// The 256 MB cache between the L2s and HBM.  Operands that are read once per call and are too large to be found there by the next call
+// (the vocabulary matrix, the K/V pages, the logits of a large batch) are read with nontemporal loads: they do not allocate on the way, and
+// a linear read of 2 GiB (windows of a 24 GiB buffer, so that none is cached) rises from 6.2-6.4 to 7.0-7.2 TB/s.  Operands that fit it keep
+// the ordinary loads: re-read within a short time they come from the cache, and nontemporal they would not.
+constexpr size_t kMemorySideCache = (size_t)256 << 20;
+
 // Compute units of the current device (256 if the runtime cannot say), cached per device ordinal.
 inline int device_cu_count()
 {
@@ -91,10 +97,13 @@ __device__ inline uint32_t f32_to_bf16_bits(float f) { return pack_bf16x2(f, 0.0
 // Written as inline assembly so that the compiler does not order it against later LDS reads by draining
 // the whole load queue: the kernel double-buffers and waits with explicit s_waitcnt vmcnt(n) instead.
 // M0 (the LDS base of the transfer) is an operand tied to that register: the compiler writes it and knows it is live.
+// STREAM: a nontemporal load, for bytes that are read once (see kMemorySideCache).
+template <bool STREAM = false>
 __device__ inline void lds_dma16(const void* g, void* lds_base)
 {
     const uint32_t m0v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_base;
-    asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(m0v) : "memory");
+    if constexpr (STREAM) asm volatile("global_load_lds_dwordx4 %0, off nt" ::"v"(g), "{m0}"(m0v) : "memory");
+    else asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(m0v) : "memory");
 }
 
 // Block summaries of the large-tile LM head (lm_head_mfma.hip): what acceptance needs from a row of logits without reading it again.  A

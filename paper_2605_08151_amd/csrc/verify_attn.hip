@@ -63,6 +63,7 @@ struct AttnParams {
     const int32_t* plan_items;
     int max_pages, num_pages, Hq, Hkv, G, M, max_kv_len, max_q_len, chunk_target, splits;
     float scale_log2e;
+    bool stream_kv;            // K/V pages by nontemporal loads (kMemorySideCache)
 };
 
 __device__ inline bool request_ok(int r0, int n, int c, const AttnParams& p)
@@ -134,7 +135,8 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     // ---- this wave's two pages of a step, K and V, HBM -> LDS (always 16 direct loads: positions past the
     // range read page 0 instead, so the wait counts below are constants) ----
     const int drow = lane >> 4, dpos = lane & 15;        // direct-load role: row within a group of 4, 16-byte position
-    auto issue_step = [&](int wbase, unsigned char* buf) {
+    auto issue_pages = [&](auto stream, int wbase, unsigned char* buf) {
+        constexpr bool kStream = decltype(stream)::value;
 #pragma unroll
         for (int pg = 0; pg < 2; ++pg) {
             const int t0 = wbase + pg * kP;
@@ -144,12 +146,16 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
             for (int q4 = 0; q4 < 4; ++q4) {
                 const int row = q4 * 4 + drow;             // slot in the page = key & 15
                 // K: chunk ch of a row is stored at position ch ^ (row & 15)
-                lds_dma16(p.k_cache + base + row * kD + ((dpos ^ row) << 3), buf + (pg * 16 + q4 * 4) * kRowBytes);
+                lds_dma16<kStream>(p.k_cache + base + row * kD + ((dpos ^ row) << 3), buf + (pg * 16 + q4 * 4) * kRowBytes);
                 // V: 32-byte chunk c of a row is stored at position c ^ (row & 7)
                 const int src16 = ((((dpos >> 1) ^ (row & 7)) << 1) | (dpos & 1));
-                lds_dma16(p.v_cache + base + row * kD + (src16 << 3), buf + (32 + pg * 16 + q4 * 4) * kRowBytes);
+                lds_dma16<kStream>(p.v_cache + base + row * kD + (src16 << 3), buf + (32 + pg * 16 + q4 * 4) * kRowBytes);
             }
         }
+    };
+    auto issue_step = [&](int wbase, unsigned char* buf) {
+        if (p.stream_kv) issue_pages(std::true_type{}, wbase, buf);
+        else issue_pages(std::false_type{}, wbase, buf);
     };
     const int wfirst = kbeg + wave * 32;
     if (wfirst < kend) issue_step(wfirst, sKV);           // in flight while Q is staged
@@ -553,7 +559,7 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
     // ---- stage st of the chunk (keys kbeg + 32 st ..): its 16 direct loads are dealt to the waves, kIssue each; slots past the
     // range read page 0 (never used), so that the wait counts are constants ----
     const int drow = lane >> 4, dpos = lane & 15;        // direct-load role: row within a group of 4, 16-byte position
-    auto issue_stage = [&](int st) {
+    auto issue_stage_as = [&](auto stream, int st) {
         unsigned char* buf = sRing + (st & (kRowsStages - 1)) * kRowsStageBytes;
         const int t0s = kbeg + st * 32;
 #pragma unroll
@@ -570,8 +576,12 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
             // K: 16-byte chunk ch of a row is stored at position ch ^ (row & 15); V: 32-byte chunk c at c ^ (row & 7)
             const int src16 = isv ? ((((dpos >> 1) ^ (row4 & 7)) << 1) | (dpos & 1)) : (dpos ^ row4);
             const uint16_t* src = (isv ? p.v_cache : p.k_cache) + base + row4 * kD + (src16 << 3);
-            lds_dma16(src, buf + (isv * 32 + pg * 16 + q4 * 4) * kRowBytes);
+            lds_dma16<decltype(stream)::value>(src, buf + (isv * 32 + pg * 16 + q4 * 4) * kRowBytes);
         }
+    };
+    auto issue_stage = [&](int st) {
+        if (p.stream_kv) issue_stage_as(std::true_type{}, st);
+        else issue_stage_as(std::false_type{}, st);
     };
     const int nst = (kend - kbeg + 31) >> 5;
     const bool wave_has_rows = wave * 16 < R;
@@ -1107,6 +1117,9 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
     p.scale_log2e = scale * 1.4426950408889634f;
     p.plan_hdr = nullptr; p.plan_req = nullptr; p.plan_items = nullptr;
     p.parent = parent;
+    // Every page is read by one workgroup only.  Measured nontemporal against ordinary, main kernel: 64 requests x 8 kv heads x 1-4k keys
+    // (677 MB) 140 -> 124 us, 256 x 256..32768 keys (0.8 GB) 180 -> 164 us, 84 MB no difference; 4 requests of <= 512 keys (0.7 MB, cached) 15 against 17 us.
+    p.stream_kv = (size_t)B * max_kv_len * Hkv * (2 * kRowBytes) > kMemorySideCache * 3 / 4;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     const AttnPlanCfg pc = attn_plan_cfg(B, Hq, Hkv, max_kv_len, max_q_len, NR, p.chunk_target);

@@ -1,0 +1,30 @@
+"""GPU parity at the lines of the launch rules: both sides of a rule on sizes against the CPU oracle, at sizes where the variant behind
+the line can go wrong.  Tolerances as in test_gpu_parity.py."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2605_08151_amd import workloads as wl  # noqa: E402
+from test_gpu_parity import _close, _oracle_attn, _step, sv  # noqa: E402,F401
+
+
+@pytest.mark.parametrize("gammas,Hq", [((0,), 8), ((4,), 32), ((0, 3, 8), 64)], ids=["decode", "two_tiles", "row_split"])
+def test_attention_streaming_and_cached_loads(sv, oracle, gammas, Hq):
+    """K/V by nontemporal loads where the stated bound exceeds 3/4 of the memory-side cache (here 3 requests x 8 kv heads x 16384 keys),
+    by ordinary loads up to it.  The loads bring the same bytes: same bits on both sides of the line."""
+    cfg = wl.VerifyConfig("stream", 71, 3, gammas, ("uniform", 200, 2500), Hq, 8, 64, 64, sigma_qkv=1.0)
+    b = wl.make_batch(cfg, device="cuda", with_lm_head=False)
+    table = torch.full((3, 1040), -1, dtype=torch.int32, device="cuda")
+    table[:, :b["page_table"].shape[1]] = b["page_table"]
+    outs = []
+    for bound in (16384, 16385):
+        step = _step(dict(b, max_kv_len=bound), cfg)
+        outs.append(step.attn(b["q"], b["k_cache"], b["v_cache"], table, b["seq_lens"], b["qo_indptr"], b["scale"]))
+        torch.cuda.synchronize()
+        assert int(step.status.cpu()) == 0
+    assert torch.equal(outs[0], outs[1])
+    _close(outs[1].float().cpu().numpy(), _oracle_attn(oracle, b), "stream", sharp=True)
