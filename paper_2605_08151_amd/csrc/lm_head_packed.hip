@@ -57,9 +57,10 @@ __global__ __launch_bounds__(256) void lm_head_pack_kernel(const uint16_t* __res
 // TM: 16-row tiles of hidden per row group (rows <= 16 TM); RS: slabs in the W register ring (1 in every launch: 2
 // measured 5 us slower at M = 160 and equal above); NW: waves (4 or 8); NT: nontemporal stores of the logits;
 // TN: panels per wave and pass (2 or 4: a pass is 16 NW TN entries wide);
+// SW: W by nontemporal loads (one row group and a matrix too large for the memory-side cache);
 // STATS: also leave per-block maxima for greedy acceptance.
 // ------------------------------------------------------------------------------------------------
-template <int TM, int RS, int NW, bool NT, int TN, bool STATS>
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW>
 __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
     int M_all, int H, int V, int n_panels, int panels_per_wg, bool vec_store, int groups, int rows_per_group,
@@ -129,8 +130,10 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
     };
     auto fetch_w = [&](int c, int slab) {             // chunk c of the ring <- k-tile 4 * slab + c % 4
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-            wreg[tn][c] = *reinterpret_cast<const u32x4*>(wptr[tn] + (size_t)(slab * 4 + (c & 3)) * 512);
+        for (int tn = 0; tn < TN; ++tn) {
+            const u32x4* src = reinterpret_cast<const u32x4*>(wptr[tn] + (size_t)(slab * 4 + (c & 3)) * 512);
+            if constexpr (SW) wreg[tn][c] = __builtin_nontemporal_load(src); else wreg[tn][c] = *src;
+        }
     };
     auto fetch_h = [&](int set, int k0) {
 #pragma unroll
@@ -344,21 +347,35 @@ static void packed_geometry(int V, int groups, int* ranges, int* per_range)
     *ranges = ((n_panels + *per_range - 1) / *per_range + 7) / 8 * 8;
 }
 
-template <int TM, int RS, int NW, bool NT, int TN, bool STATS = false>
-static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
-                         float* blk_max = nullptr, int32_t* blk_arg = nullptr)
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW>
+static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
+                            float* blk_max, int32_t* blk_arg)
 {
     constexpr int BM = TM * 16;
     const size_t smem = 2 * (size_t)BM * kPkHPitch + NW * 16 * (TN * 64 + 16) + (STATS ? (size_t)BM * NW * 8 : 0);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS>), smem, granted, "spec_lm_head_packed")) return rc;
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW>), smem, granted, "spec_lm_head_packed")) return rc;
     int ranges, per_range;
     packed_geometry(V, groups, &ranges, &per_range);
     const int ppr = (per_range + NW * TN - 1) / (NW * TN);
     const bool vec_store = (V % 4 == 0);
-    hipLaunchKernelGGL((lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS>), dim3(ranges * groups), dim3(64 * NW), smem, s, a, wp, c, M, H, V,
+    hipLaunchKernelGGL((lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW>), dim3(ranges * groups), dim3(64 * NW), smem, s, a, wp, c, M, H, V,
                        (V + 15) / 16, per_range, vec_store, groups, BM, blk_max, blk_arg, ranges * ppr, ppr);
     return SPEC_OK;
+}
+
+// W is read once when one row group covers the batch: nontemporal if the matrix is larger than what several calls in a row would find in the
+// memory-side cache (measured, V = 151936, H = 4096, 1.24 GB: M = 5 207 -> 191 us, M = 40 223 -> 208 us; V = 50021, H = 1280, 128 MB: 33 -> 31.5;
+// V = 32000, H = 1024, 66 MB, called again and again: 14 with ordinary loads, 19 without).  With several row groups the others read it from the L2.
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS = false>
+static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
+                         float* blk_max = nullptr, int32_t* blk_arg = nullptr)
+{
+    if constexpr (NT) {
+        if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8)
+            return launch_packed_as<TM, RS, NW, NT, TN, STATS, true>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
+    }
+    return launch_packed_as<TM, RS, NW, NT, TN, STATS, false>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
 }
 
 template <int TM>

@@ -28,3 +28,19 @@ def test_attention_streaming_and_cached_loads(sv, oracle, gammas, Hq):
         assert int(step.status.cpu()) == 0
     assert torch.equal(outs[0], outs[1])
     _close(outs[1].float().cpu().numpy(), _oracle_attn(oracle, b), "stream", sharp=True)
+
+
+@pytest.mark.parametrize("M", [1, 37, 160])
+@pytest.mark.parametrize("V", [196608, 196612, 196625])
+def test_packed_lm_head_streaming_and_cached_weights(sv, oracle, M, V):
+    """The vocabulary matrix by nontemporal loads above 3/8 of the memory-side cache (H = 256: more than 196608 entries)."""
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, 256), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, 256), generator=g, device="cuda").to(torch.bfloat16)
+    Wp = torch.empty(sv.spec_lm_head_packed_bytes(V, 256) // 2, dtype=torch.bfloat16, device="cuda")
+    sv.spec_lm_head_pack(W, Wp)
+    logits = torch.full((M, V), 7.0, device="cuda")
+    sv.spec_lm_head_packed(hidden, Wp, logits)
+    ref = oracle.lm_head(wl.bf16_bits(hidden), wl.bf16_bits(W))
+    err = np.abs(logits.cpu().numpy() - ref).max()
+    assert err <= 1e-5 * math.sqrt(256) * np.abs(ref).max(), err
