@@ -664,6 +664,8 @@ static int launch_skinny_auto(const uint16_t* a, const uint16_t* w, float* c, in
     return launch_skinny<TM, 1, 2, 1>(a, w, c, M, H, V, s);
 }
 
+bool lm_head_rows_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc);   // lm_head_packed.hip
+
 static bool skinny_applies(int M, int H)
 {
     const int force = g_lm_kernel;
@@ -719,7 +721,10 @@ extern "C" int spec_lm_head(const void* hidden, const void* W, float* logits, in
     const uint16_t* a = (const uint16_t*)hidden;
     const uint16_t* w = (const uint16_t*)W;
     const int force = g_lm_kernel;
-    if (skinny_applies(M, H)) {
+    int rows_rc = SPEC_OK;
+    if (force == 0 && lm_head_rows_dispatch(a, w, logits, M, H, V, s, &rows_rc)) {
+        if (rows_rc != SPEC_OK) return rows_rc;
+    } else if (skinny_applies(M, H)) {
         int rc;
         if (M <= 32) rc = launch_skinny_auto<2>(a, w, logits, M, H, V, s);
         else if (M <= 64) rc = launch_skinny_auto<4>(a, w, logits, M, H, V, s);

@@ -57,10 +57,11 @@ __global__ __launch_bounds__(256) void lm_head_pack_kernel(const uint16_t* __res
 // TM: 16-row tiles of hidden per row group (rows <= 16 TM); RS: slabs in the W register ring (1 in every launch: 2
 // measured 5 us slower at M = 160 and equal above); NW: waves (4 or 8); NT: nontemporal stores of the logits;
 // TN: panels per wave and pass (2 or 4: a pass is 16 NW TN entries wide);
+// ROWS: W row-major instead of packed: a load takes 128 bytes of 8 rows (whole lines) and weave_rows makes operands of two of them;
 // SW: W by nontemporal loads (one row group and a matrix too large for the memory-side cache);
 // STATS: also leave per-block maxima for greedy acceptance.
 // ------------------------------------------------------------------------------------------------
-template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW>
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW, bool ROWS>
 __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
     int M_all, int H, int V, int n_panels, int panels_per_wg, bool vec_store, int groups, int rows_per_group,
@@ -113,6 +114,7 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
         for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const uint16_t* wptr[TN];
+    const uint16_t* wptr_hi[ROWS ? TN : 1];
     u32x4 wreg[TN][kRing], hreg[2][H_LOADS];
     int wave_p0 = 0, wave_np = 0;
     auto open_pass = [&](int pass) {                  // the wave's panels of a pass and their stream pointers
@@ -125,15 +127,39 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
         for (int tn = 0; tn < TN; ++tn) {
             // panels past the wave's share re-read its last one (branch-free loop); their results are never stored
             const int p = wave_p0 + max(0, min(tn, wave_np - 1));
-            wptr[tn] = Wp + (size_t)p * 16 * H + lane * 8;
+            if constexpr (ROWS) {
+                // entries past V repeat the last one; which half of a row's 128 bytes the lane takes: see weave_rows
+                wptr[tn] = Wp + (size_t)min(p * 16 + (l16 & 7), V - 1) * H + (kg + (l16 & 8) / 2) * 8;
+                wptr_hi[tn] = Wp + (size_t)min(p * 16 + 8 + (l16 & 7), V - 1) * H + (kg + 4 - (l16 & 8) / 2) * 8;
+            } else {
+                wptr[tn] = Wp + (size_t)p * 16 * H + lane * 8;
+            }
         }
     };
     auto fetch_w = [&](int c, int slab) {             // chunk c of the ring <- k-tile 4 * slab + c % 4
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-            const u32x4* src = reinterpret_cast<const u32x4*>(wptr[tn] + (size_t)(slab * 4 + (c & 3)) * 512);
+            const uint16_t* at;
+            if constexpr (ROWS) at = ((c & 1) ? wptr_hi[tn] : wptr[tn]) + (size_t)(slab * 2 + ((c & 3) >> 1)) * 64;
+            else at = wptr[tn] + (size_t)(slab * 4 + (c & 3)) * 512;
+            const u32x4* src = reinterpret_cast<const u32x4*>(at);
             if constexpr (SW) wreg[tn][c] = __builtin_nontemporal_load(src); else wreg[tn][c] = *src;
         }
+    };
+    // (ROWS) Chunks c, c + 1 of the ring as loaded hold 128 bytes of rows 0..7 and of rows 8..15 of a panel: lane (l16, kg) of the first
+    // has row l16 % 8, 16-byte piece kg (l16 < 8) or 4 + kg (else); of the second row 8 + l16 % 8, piece 4 + kg or kg.  Here they become the
+    // operands of the k-tiles they cover: row l16, piece kg (a selection), and row l16, piece 4 + kg (selection, then a rotation by 8
+    // within the 16 lanes).
+    auto weave_rows = [&](int c) {
+        const bool low = l16 < 8;
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t a = wreg[tn][c][e], b = wreg[tn][c + 1][e];
+                wreg[tn][c][e] = low ? a : b;
+                wreg[tn][c + 1][e] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(low ? b : a), 0x128, 0xF, 0xF, false);   // row_ror:8
+            }
     };
     auto fetch_h = [&](int set, int k0) {
 #pragma unroll
@@ -217,6 +243,7 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
 #pragma unroll
                 for (int i = 0; i < 4 * TM; ++i) {
                     const int c = i / TM, tm = i % TM;
+                    if (ROWS && tm == 0 && (c & 1) == 0) weave_rows(par * 4 + c);
                     const bf16x8 h = hfq[i % kHfAhead];
                     if (i + kHfAhead < 4 * TM) hfq[i % kHfAhead] = hfrag(i + kHfAhead);
 #pragma unroll
@@ -347,19 +374,19 @@ static void packed_geometry(int V, int groups, int* ranges, int* per_range)
     *ranges = ((n_panels + *per_range - 1) / *per_range + 7) / 8 * 8;
 }
 
-template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW>
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW, bool ROWS>
 static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
                             float* blk_max, int32_t* blk_arg)
 {
     constexpr int BM = TM * 16;
     const size_t smem = 2 * (size_t)BM * kPkHPitch + NW * 16 * (TN * 64 + 16) + (STATS ? (size_t)BM * NW * 8 : 0);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW>), smem, granted, "spec_lm_head_packed")) return rc;
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW, ROWS>), smem, granted, ROWS ? "spec_lm_head" : "spec_lm_head_packed")) return rc;
     int ranges, per_range;
     packed_geometry(V, groups, &ranges, &per_range);
     const int ppr = (per_range + NW * TN - 1) / (NW * TN);
     const bool vec_store = (V % 4 == 0);
-    hipLaunchKernelGGL((lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW>), dim3(ranges * groups), dim3(64 * NW), smem, s, a, wp, c, M, H, V,
+    hipLaunchKernelGGL((lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW, ROWS>), dim3(ranges * groups), dim3(64 * NW), smem, s, a, wp, c, M, H, V,
                        (V + 15) / 16, per_range, vec_store, groups, BM, blk_max, blk_arg, ranges * ppr, ppr);
     return SPEC_OK;
 }
@@ -367,15 +394,26 @@ static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int
 // W is read once when one row group covers the batch: nontemporal if the matrix is larger than what several calls in a row would find in the
 // memory-side cache (measured, V = 151936, H = 4096, 1.24 GB: M = 5 207 -> 191 us, M = 40 223 -> 208 us; V = 50021, H = 1280, 128 MB: 33 -> 31.5;
 // V = 32000, H = 1024, 66 MB, called again and again: 14 with ordinary loads, 19 without).  With several row groups the others read it from the L2.
-template <int TM, int RS, int NW, bool NT, int TN, bool STATS = false>
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS = false, bool ROWS = false>
 static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
                          float* blk_max = nullptr, int32_t* blk_arg = nullptr)
 {
     if constexpr (NT) {
         if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8)
-            return launch_packed_as<TM, RS, NW, NT, TN, STATS, true>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
+            return launch_packed_as<TM, RS, NW, NT, TN, STATS, true, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
     }
-    return launch_packed_as<TM, RS, NW, NT, TN, STATS, false>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
+    return launch_packed_as<TM, RS, NW, NT, TN, STATS, false, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
+}
+
+// A vocabulary of at most 8 panels per CU (V <= 32768 on 256 CUs) is one pass of 4 waves with 2 panels each and a 2-slab ring; 8 waves would have one
+// panel each, their second slot re-reading it, and twice the LDS reads per panel.  Measured at V = 32000, 8 against 4 waves: H = 4096
+// M = 40 51.6 -> 47.8 us, M = 160 70 -> 60; H = 2048 M = 96 35.3 -> 32.6; row-major H = 4096 M = 5 64.6 -> 48.0, M = 160 89 -> 65.
+// With more panels 8 waves are ahead (V = 50021, H = 1280, M = 40: 27.5 against 30.5).
+static bool few_panels(int V)
+{
+    int ranges, per_range;
+    packed_geometry(V, 1, &ranges, &per_range);
+    return per_range <= 8;
 }
 
 template <int TM>
@@ -390,7 +428,32 @@ static int launch_packed_auto(const uint16_t* a, const uint16_t* wp, float* c, i
     // W ring is 5 us slower with either); at M = 40 both take 218 us; at M = 576 and 1152 8 waves are 5 % ahead
     if (g_lm_packed_waves == 4) return launch_packed<TM, 1, 4, true, 4>(a, wp, c, M, H, V, groups, s);
     if (groups > 2) return launch_packed<TM, 1, 8, false, 2>(a, wp, c, M, H, V, groups, s);
+    if (groups == 1 && few_panels(V)) return launch_packed<TM, 2, 4, true, 2>(a, wp, c, M, H, V, groups, s);
     return launch_packed<TM, 1, 8, true, 2>(a, wp, c, M, H, V, groups, s);
+}
+
+template <int TM>
+static int launch_rows(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s)
+{
+    if (few_panels(V)) return launch_packed<TM, 2, 4, true, 2, false, true>(a, w, c, M, H, V, 1, s);
+    return launch_packed<TM, 1, 8, true, 2, false, true>(a, w, c, M, H, V, 1, s);
+}
+
+// The same kernel on a row-major matrix, for spec_lm_head (M <= 160, H a multiple of 256).  Returns false if it does not take the shape.
+// Measured (V = 151936, H = 4096) against the 4-wave kernel of lm_head.hip, whose passes are half as wide: M = 5 227 -> 201 us,
+// M = 40 249 -> 218, M = 128 309 -> 278, M = 160 329 -> 298; V = 50021, H = 1280 (no whole quads to store) M = 96 45.1 -> 42.3.
+// Reading 64 bytes of each of 16 rows instead (no weaving, ordinary loads) costs the same from M = 96 on, and 222 against 199 us at M = 5.
+bool lm_head_rows_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc)
+{
+    if (M > kPkMaxRows || H % (2 * kPkSlab) != 0 || (size_t)V > ((size_t)1 << 32) / (4 * (size_t)(kPkMaxRows + 16))) return false;
+    switch ((M + 15) / 16) {
+        case 1: case 2: *rc = launch_rows<2>(a, w, c, M, H, V, s); break;
+        case 3: case 4: *rc = launch_rows<4>(a, w, c, M, H, V, s); break;
+        case 5: case 6: *rc = launch_rows<6>(a, w, c, M, H, V, s); break;
+        case 7: case 8: *rc = launch_rows<8>(a, w, c, M, H, V, s); break;
+        default: *rc = launch_rows<10>(a, w, c, M, H, V, s); break;
+    }
+    return true;
 }
 
 }  // namespace specv

@@ -44,3 +44,24 @@ def test_packed_lm_head_streaming_and_cached_weights(sv, oracle, M, V):
     ref = oracle.lm_head(wl.bf16_bits(hidden), wl.bf16_bits(W))
     err = np.abs(logits.cpu().numpy() - ref).max()
     assert err <= 1e-5 * math.sqrt(256) * np.abs(ref).max(), err
+
+
+@pytest.mark.parametrize("M", [1, 17, 80, 160])
+@pytest.mark.parametrize("V", [5, 4099, 32768, 32769, 70003])
+def test_row_major_lm_head_through_the_packed_kernel(sv, oracle, M, V):
+    """Up to 160 rows and H a multiple of 256 a row-major matrix goes through the packed kernel (128 bytes of 8 rows per load): last panels of
+    1 .. 15 entries, up to 8 panels per CU (4 waves) and more (8 waves).  Same order of additions as from packed weights: same bits."""
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, 512), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, 512), generator=g, device="cuda").to(torch.bfloat16)
+    logits = torch.full((M + 1, V), 7.0, device="cuda")
+    sv.spec_lm_head(hidden, W, logits[:M])
+    ref = oracle.lm_head(wl.bf16_bits(hidden), wl.bf16_bits(W))
+    err = np.abs(logits[:M].cpu().numpy() - ref).max()
+    assert err <= 1e-5 * math.sqrt(512) * np.abs(ref).max(), err
+    assert (logits[M] == 7.0).all()                        # nothing past the last row
+    Wp = torch.empty(sv.spec_lm_head_packed_bytes(V, 512) // 2, dtype=torch.bfloat16, device="cuda")
+    sv.spec_lm_head_pack(W, Wp)
+    packed = torch.empty((M, V), device="cuda")
+    sv.spec_lm_head_packed(hidden, Wp, packed)
+    assert torch.equal(packed, logits[:M])
