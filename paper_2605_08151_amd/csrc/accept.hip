@@ -6,16 +6,15 @@
 //   1. row_stats      grid (segments, rows): per 4096-logit segment the max, the lowest argmax, a NaN
 //                     flag and, for sampled requests, sum exp((l - max_seg)/T): in fp32 (an estimate good to
 //                     2^-16, the default) or in fp64.
-//   2. decide         one workgroup per request, one wave per row: merges the segments of each row; then every
+//   2. decide         merges the segments of each row, one wave per row; then every
 //                     draft's test is evaluated at once (prefix match, or u*q < p with a Philox uniform) and the
 //                     accepted length is the position of the first failure.  With fp32 sums the test is taken
 //                     against both ends of the interval p must lie in; where they disagree the row is summed
 //                     again in fp64 by the workgroup, so the outcome is always that of the fp64 definition.
-//                     Greedy requests are finished here.
-//   3a. bonus_z       (fp32 sums only) grid (segments, requests): fp64 segment sums of exp((l - m)/T) on the one
-//                     row per sampled request that the bonus token is drawn from.
-//   3. residual_sums  grid (segments, requests): for sampled requests, fp64 segment sums of the
-//                     residual max(0, p - q) (and of p) on that row.
+//                     Greedy requests are finished here.  A kernel of its own (one workgroup per request) for all-greedy
+//                     batches, else the first part of the next one.
+//   3. bonus          grid (segments, requests), on the one row per sampled request that the bonus token is drawn from: fp64 segment sums of
+//                     exp((l - m)/T) (only after fp32 sums), then, in a second launch, of the residual max(0, p - q) and of p.
 //   4. pick           one workgroup per request: inverse CDF over segment sums, then inside the segment.
 // The fp64 exponential over all M rows made row_stats ALU-bound (103 us against 59 us for the same scan without it,
 // B = 64, M = 576, V = 151936); only one row per request needs its normaliser to the last bit.
@@ -29,6 +28,7 @@ constexpr int kSeg = 4096;          // logits per segment
 constexpr int kThreads = 256;
 constexpr int kPerThread = kSeg / kThreads;   // 16
 constexpr int kMaxRows = 64;        // gamma_max + 1 <= 64
+constexpr size_t kFp64Entries = (size_t)8 << 20;   // M * V up to which every row of a sampled request is summed in fp64
 constexpr int kPickLds = 512;       // segment sums staged in LDS by the pick kernel (V <= 2M entries)
 
 // benchmark / test hook: 0 = automatic (on), 1 = on, 2 = off (fp64 sums over every row), 3 = on with an interval so wide
@@ -92,22 +92,53 @@ __device__ inline float philox_uniform(uint64_t seed, uint32_t round, uint32_t j
 }
 
 // ---- reductions --------------------------------------------------------------------------------
-__device__ inline void wave_max_arg(float& m, int& a)
+// Data-parallel-primitive steps: shifts by 1, 2, 4, 8 inside the 16-lane rows, then lane 15 of a row to the next row and lane 31 to the upper
+// half.  Applied in this order to an associative operation they leave an inclusive scan over the 64 lanes (the total in lane 63); lanes
+// without a source keep `none`.  Six instructions per word instead of six round trips through the LDS crossbar.
+template <int STEP>
+__device__ inline int scan_source(int none, int x)
 {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const float om = __shfl_xor(m, d, 64);
-        const int oa = __shfl_xor(a, d, 64);
-        if (om > m || (om == m && oa < a)) { m = om; a = oa; }
-    }
+    if constexpr (STEP < 4) return __builtin_amdgcn_update_dpp(none, x, 0x110 + (1 << STEP), 0xF, 0xF, false);   // row_shr
+    else if constexpr (STEP == 4) return __builtin_amdgcn_update_dpp(none, x, 0x142, 0xA, 0xF, false);           // row_bcast:15
+    else return __builtin_amdgcn_update_dpp(none, x, 0x143, 0xC, 0xF, false);                                    // row_bcast:31
 }
 
-__device__ inline double wave_sum(double x)
+template <int STEP>
+__device__ inline void max_arg_step(float& m, int& a)
 {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
-    return x;
+    const float om = __builtin_bit_cast(float, scan_source<STEP>(__builtin_bit_cast(int, -INFINITY), __builtin_bit_cast(int, m)));
+    const int oa = scan_source<STEP>(0x7FFFFFFF, a);
+    if (om > m || (om == m && oa < a)) { m = om; a = oa; }
 }
+
+// maximum over the wave and its lowest index, in every lane (m is never NaN)
+__device__ inline void wave_max_arg(float& m, int& a)
+{
+    max_arg_step<0>(m, a); max_arg_step<1>(m, a); max_arg_step<2>(m, a);
+    max_arg_step<3>(m, a); max_arg_step<4>(m, a); max_arg_step<5>(m, a);
+    m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, m), 63));
+    a = __builtin_amdgcn_readlane(a, 63);
+}
+
+template <int STEP>
+__device__ inline double sum_step(double x)
+{
+    return x + __hiloint2double(scan_source<STEP>(0, __double2hiint(x)), scan_source<STEP>(0, __double2loint(x)));
+}
+
+// inclusive prefix sums over the wave
+__device__ inline double wave_scan(double x)
+{
+    return sum_step<5>(sum_step<4>(sum_step<3>(sum_step<2>(sum_step<1>(sum_step<0>(x))))));
+}
+
+__device__ inline double lane_value(double x, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+// sum over the wave, in every lane (a fixed order of additions)
+__device__ inline double wave_sum(double x) { return lane_value(wave_scan(x), 63); }
 
 __device__ inline int find_request(const int32_t* __restrict__ qo_indptr, int B, int row)
 {
@@ -119,17 +150,32 @@ __device__ inline int find_request(const int32_t* __restrict__ qo_indptr, int B,
     return lo;
 }
 
+// Four consecutive values of a row.  A row starts at any multiple of 4 bytes (V need not be a multiple of 4); the hardware takes 16-byte
+// global loads at 4-byte alignment.
+typedef float f32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+
 // loads the 16 logits this thread owns in its segment; out-of-range slots read as -inf (STREAM: nontemporal loads)
 template <bool STREAM = false>
-__device__ inline void load_strided(const float* __restrict__ row, int v0, int vend, bool vec, int tid, float (&x)[kPerThread])
+__device__ inline void load_strided(const float* __restrict__ row, int v0, int vend, int tid, float (&x)[kPerThread])
 {
+    if (vend - v0 == kSeg) {                              // (the same for the whole workgroup: all segments of a row but its last)
+        const f32x4_at4* src = reinterpret_cast<const f32x4_at4*>(row + v0) + tid;
+        f32x4_at4 t[kPerThread / 4];
+#pragma unroll
+        for (int it = 0; it < kPerThread / 4; ++it) {
+            if constexpr (STREAM) t[it] = __builtin_nontemporal_load(src + it * kThreads); else t[it] = src[it * kThreads];
+        }
+#pragma unroll
+        for (int it = 0; it < kPerThread / 4; ++it) {
+            x[it * 4 + 0] = t[it].x; x[it * 4 + 1] = t[it].y; x[it * 4 + 2] = t[it].z; x[it * 4 + 3] = t[it].w;
+        }
+        return;
+    }
 #pragma unroll
     for (int it = 0; it < kPerThread / 4; ++it) {
         const int idx = v0 + (it * kThreads + tid) * 4;
-        if (vec && idx + 3 < vend) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(row + idx);
-            f32x4 t;
-            if constexpr (STREAM) t = __builtin_nontemporal_load(src); else t = *src;
+        if (idx + 3 < vend) {
+            const f32x4_at4 t = *reinterpret_cast<const f32x4_at4*>(row + idx);
             x[it * 4 + 0] = t.x; x[it * 4 + 1] = t.y; x[it * 4 + 2] = t.z; x[it * 4 + 3] = t.w;
         } else {
 #pragma unroll
@@ -195,7 +241,7 @@ constexpr int kSegPerWg = 1;        // consecutive segments one workgroup handle
 template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void accept_row_stats_kernel(
     const float* __restrict__ logits, const float* __restrict__ temperature,
-    const int32_t* __restrict__ qo_indptr, int B, int V, int nseg, bool vec,
+    const int32_t* __restrict__ qo_indptr, int B, int V, int nseg,
     AcceptWorkspace w, int32_t* __restrict__ stats, bool greedy_rows_covered, bool fp32_sums)
 {
     __shared__ float s_m[kSegPerWg][kThreads / 64];
@@ -211,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void accept_row_stats_kernel(
 #pragma unroll
     for (int q = 0; q < kSegPerWg; ++q) {
         const int v0 = (seg0 + q) * kSeg;
-        load_strided<STREAM>(lrow, min(v0, V), min(V, v0 + kSeg), vec, tid, x[q]);      // past the row: all -inf
+        load_strided<STREAM>(lrow, min(v0, V), min(V, v0 + kSeg), tid, x[q]);      // past the row: all -inf
     }
     const float T = temperature ? temperature[find_request(qo_indptr, B, row)] : 0.0f;   // null: every request greedy
     if (greedy_rows_covered && T == 0.0f) return;         // the decision reads the LM head's block statistics instead
@@ -303,32 +349,119 @@ struct AcceptSummary {
     int blocks;
 };
 
-constexpr int kDecideThreads = 1024;   // 16 waves: the rows of a request (gamma + 1 <= 16 in practice) are merged side by side
+// The arguments of the decision, of which every kernel below takes a copy.
+struct DecideArgs {
+    const float* logits;
+    const int32_t* tokens;
+    const float* draft_probs;
+    const float* temperature;
+    const uint64_t* seeds;
+    const int32_t* qo_indptr;
+    int32_t* accept_len;
+    int32_t* out_tokens;
+    uint8_t* rollback;
+    int32_t* stats;
+    int32_t* status_flags;
+    const float* blk_max;      // block maxima of the LM head (nblk > 0)
+    const int32_t* blk_arg;
+    AcceptSummary sum;
+    uint32_t round;
+    float band;
+    int M, V, nseg, gamma_max, nblk;
+};
 
-__global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(
-    const float* __restrict__ logits, const int32_t* __restrict__ tokens, const float* __restrict__ draft_probs,
-    const float* __restrict__ temperature, const uint64_t* __restrict__ seeds, uint32_t round,
-    const int32_t* __restrict__ qo_indptr, int32_t* __restrict__ accept_len, int32_t* __restrict__ out_tokens,
-    uint8_t* __restrict__ rollback, int32_t* __restrict__ stats, int M, int V, int nseg, int gamma_max,
-    AcceptWorkspace w, int32_t* __restrict__ status_flags,
-    const float* __restrict__ blk_max, const int32_t* __restrict__ blk_arg, int nblk, float band, AcceptSummary sum)
+// The row a sampled request's bonus token is drawn from, as the decision leaves it in LDS (row < 0: nothing to draw).
+struct BonusJob {
+    int row, qrow, onehot;
+    float u, t;
+    double m, z;               // z is an estimate when band > 0: the draw then sums the row itself
+};
+
+// Accepted length of request i, by a whole workgroup of THREADS threads.  `writer`: this workgroup writes the request's outputs (the decision
+// may be repeated by several workgroups, which all arrive at the same bits).  Visible to all threads after the caller's next barrier.
+template <int THREADS>
+__device__ void decide_request(const DecideArgs& d_, const AcceptWorkspace& w, int i, bool writer, BonusJob* s_job)
 {
+    const float* __restrict__ logits = d_.logits;
+    const int M = d_.M, V = d_.V, nseg = d_.nseg, gamma_max = d_.gamma_max, nblk = d_.nblk;
+    const AcceptSummary& sum = d_.sum;
     __shared__ double s_m[kMaxRows], s_z[kMaxRows];
     __shared__ int s_arg[kMaxRows], s_bad[kMaxRows];
-    const int i = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
-    const int r0 = qo_indptr[i], gamma = qo_indptr[i + 1] - r0 - 1;
-    int32_t* emit = out_tokens + (size_t)i * (gamma_max + 1);
-    for (int j = tid; j <= gamma_max; j += kDecideThreads) emit[j] = -1;
-    if (tid == 0) { w.job_row[i] = -1; accept_len[i] = 0; if (rollback) rollback[i] = 0; }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
+    const int r0 = d_.qo_indptr[i], gamma = d_.qo_indptr[i + 1] - r0 - 1;
+    int32_t* emit = d_.out_tokens + (size_t)i * (gamma_max + 1);
+    if (tid == 0) s_job->row = -1;
     if (gamma < 0 || gamma > gamma_max || r0 < 0 || r0 + gamma + 1 > M) {
-        if (tid == 0 && status_flags) atomicOr(status_flags, SPEC_FLAG_BAD_LENGTH);
+        if (writer) {
+            for (int j = tid; j <= gamma_max; j += THREADS) emit[j] = -1;
+            if (tid == 0) {
+                d_.accept_len[i] = 0;
+                if (d_.rollback) d_.rollback[i] = 0;
+                if (d_.status_flags) atomicOr(d_.status_flags, SPEC_FLAG_BAD_LENGTH);
+            }
+        }
         return;
     }
-    const float T = temperature[i];
+    const float T = d_.temperature[i];
     const double Td = (double)T;
     const bool from_blocks = nblk > 0 && T == 0.0f;        // greedy: maxima the LM head left per vocabulary block
-    for (int j = wave; j <= gamma; j += kDecideThreads / 64) {   // one wave per row
+    // The first 64 segments of up to kAhead rows per wave are requested before anything is waited for, together with what the tests need per
+    // draft (token, then its logit on the previous row and its draft probability, by gamma threads at once).
+    constexpr int kWaves = THREADS / 64, kAhead = THREADS >= 1024 ? 1 : 3;
+    const bool plain = sum.blocks == 0 && !from_blocks;
+    float first_m[kAhead];
+    int first_a[kAhead], first_bad[kAhead];
+    double first_z[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+        const int j = wave + k * kWaves;
+        const size_t o = (size_t)(r0 + j) * nseg + lane;
+        const bool on = plain && j <= gamma && lane < nseg;
+        first_m[k] = on ? w.seg_max[o] : -INFINITY;
+        first_a[k] = on ? w.seg_arg[o] : 0x7FFFFFFF;
+        first_bad[k] = on ? w.seg_bad[o] : 0;
+        first_z[k] = on && T > 0.0f ? w.seg_z[o] : 0.0;
+    }
+    __shared__ int s_tok[kMaxRows];
+    __shared__ float s_logit[kMaxRows], s_qd[kMaxRows];
+    if (tid >= 1 && tid <= gamma) {
+        const int d = d_.tokens[r0 + tid];
+        const bool ok = d >= 0 && d < V;
+        s_tok[tid] = d;
+        s_logit[tid] = (ok && T > 0.0f) ? logits[(size_t)(r0 + tid - 1) * V + d] : 0.0f;
+        s_qd[tid] = (ok && T > 0.0f && d_.draft_probs) ? d_.draft_probs[(size_t)(r0 - i + tid - 1) * V + d] : 1.0f;
+    }
+    // one row of the plain path: its first 64 segments as given, the others fetched here
+    auto merge_row = [&](int j, float m, int arg, int bad, double z) {
         const size_t base = (size_t)(r0 + j) * nseg;
+        const float m_first = m;
+        for (int s = lane + 64; s < nseg; s += 64) {
+            const float sm = w.seg_max[base + s];
+            const int sa = w.seg_arg[base + s];
+            bad |= w.seg_bad[base + s];
+            if (sm > m || (sm == m && sa < arg)) { m = sm; arg = sa; }
+        }
+        wave_max_arg(m, arg);
+        bad = __any(bad) || !(m > -INFINITY && m < INFINITY);
+        if (T > 0.0f && !bad) {
+            z = m_first > -INFINITY ? z * exp(((double)m_first - (double)m) / Td) : 0.0;
+            for (int s = lane + 64; s < nseg; s += 64) {
+                const float sm = w.seg_max[base + s];
+                if (sm > -INFINITY) z += w.seg_z[base + s] * exp(((double)sm - (double)m) / Td);
+            }
+            z = wave_sum(z);
+        }
+        if (lane == 0) { s_m[j] = (double)m; s_z[j] = z; s_arg[j] = arg; s_bad[j] = bad; }
+    };
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+        if (plain && wave + k * kWaves <= gamma) merge_row(wave + k * kWaves, first_m[k], first_a[k], first_bad[k], first_z[k]);
+    for (int j = wave + kAhead * kWaves; plain && j <= gamma; j += kWaves) {
+        const size_t o = (size_t)(r0 + j) * nseg + lane;
+        const bool on = lane < nseg;
+        merge_row(j, on ? w.seg_max[o] : -INFINITY, on ? w.seg_arg[o] : 0x7FFFFFFF, on ? w.seg_bad[o] : 0, on && T > 0.0f ? w.seg_z[o] : 0.0);
+    }
+    for (int j = wave; !plain && j <= gamma; j += kWaves) {   // block statistics of the LM head: one wave per row
         float m = -INFINITY;
         int arg = 0x7FFFFFFF, bad = 0;
         if (sum.blocks > 0) {
@@ -381,7 +514,7 @@ __global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(
             if (lane == 0) { s_m[j] = (double)m; s_z[j] = z; s_arg[j] = arg; s_bad[j] = bad; }
             continue;
         }
-        if (from_blocks) {
+        {
             // ~V/128 blocks per row: eight loads in flight per lane, or the walk is one memory latency per 64 blocks
             const size_t bb = (size_t)(r0 + j) * nblk;
             for (int s0 = lane; s0 < nblk; s0 += 64 * 8) {
@@ -390,8 +523,8 @@ __global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int s = s0 + 64 * u;
-                    sm[u] = s < nblk ? blk_max[bb + s] : -INFINITY;
-                    sa[u] = s < nblk ? blk_arg[bb + s] : 0x7FFFFFFF;
+                    sm[u] = s < nblk ? d_.blk_max[bb + s] : -INFINITY;
+                    sa[u] = s < nblk ? d_.blk_arg[bb + s] : 0x7FFFFFFF;
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
@@ -399,59 +532,33 @@ __global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(
                     if (sm[u] > m || (sm[u] == m && sa[u] < arg)) { m = sm[u]; arg = sa[u]; }
                 }
             }
-        } else
-        for (int s = lane; s < nseg; s += 64) {
-            const float sm = w.seg_max[base + s];
-            const int sa = w.seg_arg[base + s];
-            bad |= w.seg_bad[base + s];
-            if (sm > m || (sm == m && sa < arg)) { m = sm; arg = sa; }
         }
-        // (the first 64 segment sums are requested together with the maxima: one memory round trip for V <= 262144)
-        const double z_first = (T > 0.0f && lane < nseg) ? w.seg_z[base + lane] : 0.0;
-        const float m_first = lane < nseg ? w.seg_max[base + lane] : -INFINITY;
         wave_max_arg(m, arg);
         bad = __any(bad) || !(m > -INFINITY && m < INFINITY);
-        double z = 0.0;
-        if (T > 0.0f && !bad) {
-            if (m_first > -INFINITY) z = z_first * exp(((double)m_first - (double)m) / Td);
-            for (int s = lane + 64; s < nseg; s += 64) {
-                const float sm = w.seg_max[base + s];
-                if (sm > -INFINITY) z += w.seg_z[base + s] * exp(((double)sm - (double)m) / Td);
-            }
-            z = wave_sum(z);
-        }
-        if (lane == 0) { s_m[j] = (double)m; s_z[j] = z; s_arg[j] = arg; s_bad[j] = bad; }
-    }
-    // what the walk below needs per draft (token, its logit on the previous row, its draft probability) is
-    // fetched by gamma threads at once: one memory round trip instead of one per draft
-    __shared__ int s_tok[kMaxRows];
-    __shared__ float s_logit[kMaxRows], s_qd[kMaxRows];
-    if (tid >= 1 && tid <= gamma) {
-        const int d = tokens[r0 + tid];
-        const bool ok = d >= 0 && d < V;
-        s_tok[tid] = d;
-        s_logit[tid] = (ok && T > 0.0f) ? logits[(size_t)(r0 + tid - 1) * V + d] : 0.0f;
-        s_qd[tid] = (ok && T > 0.0f && draft_probs) ? draft_probs[(size_t)(r0 - i + tid - 1) * V + d] : 1.0f;
+        if (lane == 0) { s_m[j] = (double)m; s_z[j] = 0.0; s_arg[j] = arg; s_bad[j] = bad; }
     }
     __syncthreads();
 
     // Every wave evaluates the same tests on the same LDS data (so that the branches below are uniform for the whole
-    // workgroup); wave 0 alone writes.  Lane j looks at row j (its logits usable?) and at draft j (1 <= j <= gamma <= 63):
+    // workgroup); wave 0 of the writer alone writes.  Lane j looks at row j (its logits usable?) and at draft j (1 <= j <= gamma <= 63):
     // every draft's test is evaluated at once, and the accepted length is the number of drafts before the first that fails.
-    const bool w0 = wave == 0;
     const bool has_draft = lane >= 1 && lane <= gamma;
     const int d = has_draft ? s_tok[lane] : 0;
     int flags = 0;
     bool valid = (T >= 0.0f);
-    if (T > 0.0f && seeds == nullptr) { valid = false; flags |= SPEC_FLAG_NO_SEED; }
+    if (T > 0.0f && d_.seeds == nullptr) { valid = false; flags |= SPEC_FLAG_NO_SEED; }
     if (__any(lane <= gamma && s_bad[lane])) { valid = false; flags |= SPEC_FLAG_BAD_LOGITS; }
     if (__any(has_draft && (d < 0 || d >= V))) { valid = false; flags |= SPEC_FLAG_BAD_TOKEN; }
     if (!(T >= 0.0f)) flags |= SPEC_FLAG_BAD_LOGITS;
     if (!valid) {
-        if (tid == 0) {
-            if (rollback) rollback[i] = (uint8_t)(gamma > 0);
-            if (stats) { if (gamma > 0) atomicAdd(stats + 0, 1); }
-            if (status_flags && flags) atomicOr(status_flags, flags);
+        if (writer) {
+            for (int j = tid; j <= gamma_max; j += THREADS) emit[j] = -1;
+            if (tid == 0) {
+                d_.accept_len[i] = 0;
+                if (d_.rollback) d_.rollback[i] = (uint8_t)(gamma > 0);
+                if (d_.stats && gamma > 0) atomicAdd(d_.stats + 0, 1);
+                if (d_.status_flags && flags) atomicOr(d_.status_flags, flags);
+            }
         }
         return;
     }
@@ -466,20 +573,21 @@ __global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(
         // of the interval that fl32(e / Z) must lie in, and only where the two disagree is the row summed again in fp64,
         // by the whole workgroup.  The outcome is that of the exact test in every case.
         enum { kPass = 0, kFail = 1, kOpen = 2 };
-        const uint64_t seed = seeds[i];
+        const uint64_t seed = d_.seeds[i];
+        const float band = d_.band;
         int state = kPass;
         double e = 0.0;
         float x = 0.0f;
         if (has_draft) {
             e = exp(((double)s_logit[lane] - s_m[lane - 1]) / Td);
             const double zj = s_z[lane - 1];
-            const float u = philox_uniform(seed, round, (uint32_t)lane, 0u);
+            const float u = philox_uniform(seed, d_.round, (uint32_t)lane, 0u);
             x = (float)((double)u * (double)s_qd[lane]);
             const float p_lo = (float)(e / (zj * (1.0 + (double)band))), p_hi = (float)(e / (zj * (1.0 - (double)band)));
             state = x < p_lo ? kPass : (x < p_hi ? kOpen : kFail);
         }
         __shared__ int s_need;
-        __shared__ double s_exact, s_part[kDecideThreads / 64], s_tbl[64];
+        __shared__ double s_exact, s_part[THREADS / 64], s_tbl[64];
         bool table_loaded = false;
         for (;;) {
             const unsigned long long fails = __ballot(state == kFail), opens = __ballot(state == kOpen);
@@ -491,13 +599,13 @@ __global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(
             const float* lrow = logits + (size_t)(r0 + need) * V;
             const double mrow = s_m[need], inv_t = 1.0 / Td;
             double z = 0.0;
-            for (int v = tid; v < V; v += kDecideThreads) z += exp_bulk(((double)lrow[v] - mrow) * inv_t, s_tbl);
+            for (int v = tid; v < V; v += THREADS) z += exp_bulk(((double)lrow[v] - mrow) * inv_t, s_tbl);
             z = wave_sum(z);
             if (lane == 0) s_part[wave] = z;
             __syncthreads();
             if (tid == 0) {
                 double t = 0.0;
-                for (int k = 0; k < kDecideThreads / 64; ++k) t += s_part[k];
+                for (int k = 0; k < THREADS / 64; ++k) t += s_part[k];
                 s_exact = t; s_z[need] = t;
             }
             __syncthreads();
@@ -510,27 +618,45 @@ __global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(
         if (tid == 0) {
             // the bonus is drawn on the row that rejected (from the residual) or on the last row (from the target itself)
             const int jr = rejected_at ? rejected_at - 1 : gamma;
-            w.job_row[i] = r0 + jr;
-            w.job_qrow[i] = (rejected_at && draft_probs) ? (r0 - i + jr) : -1;
-            w.job_onehot[i] = (rejected_at && !draft_probs) ? s_tok[rejected_at] : -1;
-            w.job_u[i] = philox_uniform(seed, round, (uint32_t)(rejected_at ? rejected_at : gamma + 1), 1u);
-            w.job_m[i] = s_m[jr];
-            w.job_z[i] = s_z[jr];                         // (an estimate when band > 0: the draw then sums the row itself)
-            w.job_t[i] = T;
+            s_job->row = r0 + jr;
+            s_job->qrow = (rejected_at && d_.draft_probs) ? (r0 - i + jr) : -1;
+            s_job->onehot = (rejected_at && !d_.draft_probs) ? s_tok[rejected_at] : -1;
+            s_job->u = philox_uniform(seed, d_.round, (uint32_t)(rejected_at ? rejected_at : gamma + 1), 1u);
+            s_job->m = s_m[jr];
+            s_job->z = s_z[jr];
+            s_job->t = T;
         }
     }
-    if (!w0) return;
-    // lane j writes slot j: the accepted drafts, then (greedy) the bonus; sampled requests get theirs from the draw
-    if (lane < a) emit[lane] = s_tok[lane + 1];
-    else if (lane == a && bonus >= 0) emit[lane] = bonus;
+    if (!writer || wave != 0) return;
+    // lane j writes slot j: the accepted drafts, then (greedy) the bonus, then -1; sampled requests get their bonus from the draw
+    if (lane <= gamma_max) emit[lane] = lane < a ? s_tok[lane + 1] : (lane == a ? bonus : -1);
     if (lane == 0) {
-        accept_len[i] = a;
-        if (rollback) rollback[i] = (uint8_t)(a < gamma);
-        if (stats) {
-            if (a < gamma) atomicAdd(stats + 0, 1);
-            atomicAdd(stats + 1, a + 1);
+        d_.accept_len[i] = a;
+        if (d_.rollback) d_.rollback[i] = (uint8_t)(a < gamma);
+        if (d_.stats) {
+            if (a < gamma) atomicAdd(d_.stats + 0, 1);
+            atomicAdd(d_.stats + 1, a + 1);
         }
     }
+}
+
+constexpr int kDecideThreads = 1024;   // 16 waves: the rows of a request (gamma + 1 <= 16 in practice) are merged side by side
+
+__device__ inline void store_job(const AcceptWorkspace& w, int i, const BonusJob& j)
+{
+    w.job_row[i] = j.row;
+    if (j.row < 0) return;
+    w.job_qrow[i] = j.qrow; w.job_onehot[i] = j.onehot;
+    w.job_u[i] = j.u; w.job_t[i] = j.t; w.job_m[i] = j.m; w.job_z[i] = j.z;
+}
+
+__global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(DecideArgs d, AcceptWorkspace w)
+{
+    __shared__ BonusJob s_job;
+    decide_request<kDecideThreads>(d, w, blockIdx.x, true, &s_job);
+    if (!d.seeds) return;                                 // all greedy: nothing is drawn
+    __syncthreads();
+    if (threadIdx.x == 0) store_job(w, blockIdx.x, s_job);
 }
 
 // ---- 2b. greedy decision on a candidate tree ---------------------------------------------------
@@ -622,133 +748,115 @@ __device__ inline void residual_of(float l, float qv, double m, double inv_t, do
     rho = diff > 0.0f ? diff : 0.0f;
 }
 
-// What a workgroup needs to know about the row a request's bonus token is drawn from.  Every field is fetched before
-// the first is looked at (one memory round trip); for a request that draws nothing (row < 0) the rest is stale, unused.
-struct BonusJob {
-    int row, qrow, onehot;
-    double m, inv_t;
-    float u;
-};
-
+// The job as an earlier kernel left it.  Every field is fetched before the first is looked at (one memory round trip); for a request that
+// draws nothing (row < 0) the rest is stale, unused.
 __device__ inline BonusJob load_job(const AcceptWorkspace& w, int i)
 {
     BonusJob j;
     j.row = w.job_row[i]; j.qrow = w.job_qrow[i]; j.onehot = w.job_onehot[i];
-    j.m = w.job_m[i]; j.u = w.job_u[i];
-    j.inv_t = 1.0 / (double)w.job_t[i];
+    j.m = w.job_m[i]; j.u = w.job_u[i]; j.t = w.job_t[i]; j.z = w.job_z[i];
     return j;
 }
 
-// Z of the bonus row: either what the decision kernel left (sums_exact: every row's Z was summed in fp64), or the sum
-// of the per-segment fp64 sums of accept_bonus_z_kernel.  Lane s of wave 0 takes segments s, s + 64, ...; the butterfly
-// that follows adds in a fixed order, so every workgroup of a request arrives at the same bits.  Returned through LDS
-// (s_z), visible after the caller's next barrier.
-__device__ inline void stage_bonus_z(const AcceptWorkspace& w, int i, int nseg, bool z_from_segments, double* s_z, int tid)
+// Z of the bonus row from the per-segment fp64 sums that an accept_bonus_kernel<*, true> left.  Lane s of wave 0 takes segments s,
+// s + 64, ...; the butterfly that follows adds in a fixed order, so every workgroup of a request arrives at the same bits.  Returned
+// through LDS (s_z), visible after the caller's next barrier.
+__device__ inline void stage_bonus_z(const AcceptWorkspace& w, int i, int nseg, double* s_z, int tid)
 {
     if (tid >= 64) return;
     double z = 0.0;
-    if (z_from_segments) {
-        for (int s = tid; s < nseg; s += 64) z += w.job_zseg[(size_t)i * nseg + s];
-        z = wave_sum(z);
-    } else {
-        z = w.job_z[i];
-    }
+    for (int s = tid; s < nseg; s += 64) z += w.job_zseg[(size_t)i * nseg + s];
+    z = wave_sum(z);
     if (tid == 0) *s_z = z;
 }
 
-// ---- 3a. exact Z of the one row per request that the bonus is drawn from --------------------------
-// (only when the bulk sums were taken in fp32, see accept_row_stats_kernel)
-constexpr int kJobSegs = 1;         // consecutive segments per workgroup of the two bonus-row kernels (2 measured no faster:
-                                    // their time is launch + two memory round trips + the fp64 exponentials, all in one round)
-
-__global__ __launch_bounds__(kThreads) void accept_bonus_z_kernel(const float* __restrict__ logits, int V, int nseg, bool vec,
-                                                                  AcceptWorkspace w)
+// ---- 3. segment sums on the one row per request that the bonus is drawn from ----------------------
+// Grid (segments, requests).  ZSUM: fp64 sums of exp((l - m)/T), wanted when the decision had only an estimate of Z; else: fp64 sums of the
+// residual max(0, p - q) and of p, which need the exact Z (z_from_segments: from the launch before; else the job's).
+// DECIDE: every workgroup of a sampled request takes the decision by itself first (the first of them also writes the request's outputs and the
+// job): a launch less, for a batch that leaves the chip idle anyway (5 rows x 151936: decision, Z and
+// residual 18.1 us in three launches, 9.9 in this one; 13 mixed requests x 50021: 18.3 -> 9.7).
+// Thousands of workgroups deciding the same 64 or 128 requests cost more than the launch (B = 64, M = 576: 22 -> 32 us; M = 1204: 30 -> 46).
+template <bool DECIDE, bool ZSUM>
+__global__ __launch_bounds__(kThreads) void accept_bonus_kernel(DecideArgs d, AcceptWorkspace w, bool z_from_segments)
 {
-    __shared__ double s_part[kJobSegs][kThreads / 64];
-    __shared__ double s_tbl[64];
-    const int seg0 = blockIdx.x * kJobSegs, i = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const BonusJob job = load_job(w, i);
-    if (job.row < 0) return;
-    load_exp_table(s_tbl, tid);
-    float x[kJobSegs][kPerThread];
-#pragma unroll
-    for (int q = 0; q < kJobSegs; ++q) {
-        const int v0 = (seg0 + q) * kSeg;
-        load_strided(logits + (size_t)job.row * V, min(v0, V), min(V, v0 + kSeg), vec, tid, x[q]);   // past the row: all -inf
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kJobSegs; ++q) {
-        double z = 0.0;
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) z += exp_bulk(((double)x[q][k] - job.m) * job.inv_t, s_tbl);   // -inf slots add ~1e-304
-        z = wave_sum(z);
-        if (lane == 0) s_part[q][wave] = z;
-    }
-    __syncthreads();
-    if (tid < kJobSegs && seg0 + tid < nseg) {
-        double t = 0.0;
-        for (int k = 0; k < kThreads / 64; ++k) t += s_part[tid][k];
-        w.job_zseg[(size_t)i * nseg + seg0 + tid] = t;
-    }
-}
-
-// ---- 3. segment sums of the residual ---------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void accept_residual_sums_kernel(
-    const float* __restrict__ logits, const float* __restrict__ draft_probs, int V, int nseg, bool vec,
-    bool z_from_segments, AcceptWorkspace w)
-{
-    __shared__ double s_r[kJobSegs][kThreads / 64], s_p[kJobSegs][kThreads / 64];
+    __shared__ double s_r[kThreads / 64], s_p[kThreads / 64];
     __shared__ double s_tbl[64];
     __shared__ double s_z;
-    const int seg0 = blockIdx.x * kJobSegs, i = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const BonusJob job = load_job(w, i);
-    stage_bonus_z(w, i, nseg, z_from_segments, &s_z, tid);
-    if (job.row < 0) return;
-    load_exp_table(s_tbl, tid);
-    float x[kJobSegs][kPerThread], qv[kJobSegs][kPerThread];
-#pragma unroll
-    for (int q = 0; q < kJobSegs; ++q) {
-        const int v0 = min((seg0 + q) * kSeg, V), vend = min(V, v0 + kSeg);
-        load_strided(logits + (size_t)job.row * V, v0, vend, vec, tid, x[q]);
-        if (job.qrow >= 0) load_strided(draft_probs + (size_t)job.qrow * V, v0, vend, vec, tid, qv[q]);
+    __shared__ BonusJob s_job;
+    const int seg = blockIdx.x, i = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int V = d.V, nseg = d.nseg;
+    BonusJob job;
+    if constexpr (DECIDE) {
+        // a greedy request (or one with a temperature that makes no sense) draws nothing: its first workgroup decides and that is all
+        if (seg != 0 && !(d.temperature[i] > 0.0f)) return;
+        decide_request<kThreads>(d, w, i, seg == 0, &s_job);
+        __syncthreads();
+        job = s_job;
+        if (seg == 0 && tid == 0) store_job(w, i, job);
+    } else {
+        if constexpr (ZSUM) {
+            job.row = w.job_row[i]; job.m = w.job_m[i]; job.t = w.job_t[i];
+            asm volatile("" :: "s"(job.row), "s"(job.m), "s"(job.t));    // one round trip: not one for the row and another for the rest
+        } else {
+            job = load_job(w, i);
+            if (z_from_segments) stage_bonus_z(w, i, nseg, &s_z, tid);
+        }
     }
+    if (job.row < 0) return;
+    const double inv_t = 1.0 / (double)job.t;
+    const int v0 = seg * kSeg, vend = min(V, v0 + kSeg);
+    float x[kPerThread], qv[kPerThread];
+    load_strided(d.logits + (size_t)job.row * V, v0, vend, tid, x);               // past the row: all -inf
+    if constexpr (!ZSUM) {
+        if (job.qrow >= 0) load_strided<true>(d.draft_probs + (size_t)job.qrow * V, v0, vend, tid, qv);
+    }
+    load_exp_table(s_tbl, tid);
     __syncthreads();
-    const double z = s_z, rz = 1.0 / z;
+    double rs = 0.0, ps = 0.0;
+    if constexpr (ZSUM) {
 #pragma unroll
-    for (int q = 0; q < kJobSegs; ++q) {
-        const int v0 = (seg0 + q) * kSeg, vend = min(V, v0 + kSeg);
-        double rs = 0.0, ps = 0.0;
+        for (int k = 0; k < kPerThread; ++k) rs += exp_bulk(((double)x[k] - job.m) * inv_t, s_tbl);   // -inf slots add ~1e-304
+    } else {
+        const double z = z_from_segments ? s_z : job.z, rz = 1.0 / z;
 #pragma unroll
         for (int it = 0; it < kPerThread / 4; ++it)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int v = v0 + (it * kThreads + tid) * 4 + k;
                 if (v < vend) {
-                    const float qd = job.qrow >= 0 ? qv[q][it * 4 + k] : (v == job.onehot ? 1.0f : 0.0f);
+                    const float qd = job.qrow >= 0 ? qv[it * 4 + k] : (v == job.onehot ? 1.0f : 0.0f);
                     float p, rho;
-                    residual_of(x[q][it * 4 + k], qd, job.m, job.inv_t, z, rz, s_tbl, p, rho);
+                    residual_of(x[it * 4 + k], qd, job.m, inv_t, z, rz, s_tbl, p, rho);
                     rs += (double)rho;
                     ps += (double)p;
                 }
             }
-        rs = wave_sum(rs);
         ps = wave_sum(ps);
-        if (lane == 0) { s_r[q][wave] = rs; s_p[q][wave] = ps; }
+        if (lane == 0) s_p[wave] = ps;
     }
+    rs = wave_sum(rs);
+    if (lane == 0) s_r[wave] = rs;
     __syncthreads();
-    if (tid < kJobSegs && seg0 + tid < nseg) {
+    if (tid == 0) {
         double r = 0.0, p = 0.0;
-        for (int k = 0; k < kThreads / 64; ++k) { r += s_r[tid][k]; p += s_p[tid][k]; }
-        w.res_sum[(size_t)i * nseg + seg0 + tid] = r;
-        w.p_sum[(size_t)i * nseg + seg0 + tid] = p;
+        for (int k = 0; k < kThreads / 64; ++k) {
+            r += s_r[k];
+            if (!ZSUM) p += s_p[k];
+        }
+        if (ZSUM) {
+            w.job_zseg[(size_t)i * nseg + seg] = r;
+        } else {
+            w.res_sum[(size_t)i * nseg + seg] = r;
+            w.p_sum[(size_t)i * nseg + seg] = p;
+        }
     }
 }
 
 // ---- 4. inverse CDF ----------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void accept_pick_kernel(
     const float* __restrict__ logits, const float* __restrict__ draft_probs, const int32_t* __restrict__ accept_len,
-    int32_t* __restrict__ out_tokens, int V, int nseg, int gamma_max, bool vec, bool z_from_segments, AcceptWorkspace w)
+    int32_t* __restrict__ out_tokens, int V, int nseg, int gamma_max, bool z_from_segments, AcceptWorkspace w)
 {
     __shared__ int s_seg, s_use_p, s_best, s_last;
     __shared__ double s_before, s_target, s_wave[kThreads / 64], s_z;
@@ -766,8 +874,10 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(
             s_ps[s] = w.p_sum[(size_t)i * nseg + s];
         }
     }
-    stage_bonus_z(w, i, nseg, z_from_segments, &s_z, tid);
+    if (z_from_segments) stage_bonus_z(w, i, nseg, &s_z, tid);
+    else if (tid == 0) s_z = job.z;
     if (job.row < 0) return;
+    const double inv_t = 1.0 / (double)job.t;
     load_exp_table(s_tbl, tid);
     __syncthreads();
     if (wave == 0) {
@@ -789,23 +899,18 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(
         for (int base = 0; base < nseg && found < 0; base += 64) {
             const int s = base + lane;
             const double v = s < nseg ? seg_sum(s, use_p) : 0.0;
-            double incl = v;
-#pragma unroll
-            for (int dd = 1; dd < 64; dd <<= 1) {
-                const double up = __shfl_up(incl, dd, 64);
-                if (lane >= dd) incl += up;
-            }
+            const double incl = wave_scan(v);
             const unsigned long long over = __ballot(s < nseg && carry + incl > target);
             const unsigned long long pos = __ballot(s < nseg && v > 0.0);
             if (over) {
                 const int l = __ffsll((long long)over) - 1;
                 found = base + l;
-                before = carry + __shfl(incl - v, l, 64);
+                before = carry + lane_value(incl - v, l);
                 const unsigned long long pos_upto = pos & ((2ull << l) - 1ull);
                 if (pos_upto) last_pos = base + 63 - __clzll((long long)pos_upto);
             } else {
                 if (pos) last_pos = base + 63 - __clzll((long long)pos);
-                carry += __shfl(incl, 63, 64);
+                carry += lane_value(incl, 63);
             }
         }
         if (found < 0) {                                  // rounding ran the CDF out: last segment with weight
@@ -827,13 +932,13 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(
     const float* lrow = logits + (size_t)job.row * V;
     const float* qptr = qrow >= 0 ? draft_probs + (size_t)qrow * V : nullptr;
     float lv[kPerThread], qv[kPerThread];
-    if (vec && v0 + kPerThread <= V) {                     // (V % 4 == 0 and 16-byte aligned rows)
+    if (v0 + kPerThread <= V) {
 #pragma unroll
         for (int k4 = 0; k4 < kPerThread / 4; ++k4) {
-            const f32x4 t = *reinterpret_cast<const f32x4*>(lrow + v0 + 4 * k4);
+            const f32x4_at4 t = *reinterpret_cast<const f32x4_at4*>(lrow + v0 + 4 * k4);
             lv[4 * k4] = t.x; lv[4 * k4 + 1] = t.y; lv[4 * k4 + 2] = t.z; lv[4 * k4 + 3] = t.w;
-            f32x4 q4 = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (qptr) q4 = *reinterpret_cast<const f32x4*>(qptr + v0 + 4 * k4);
+            f32x4_at4 q4 = {0.f, 0.f, 0.f, 0.f};
+            if (qptr) q4 = *reinterpret_cast<const f32x4_at4*>(qptr + v0 + 4 * k4);
             qv[4 * k4] = q4.x; qv[4 * k4 + 1] = q4.y; qv[4 * k4 + 2] = q4.z; qv[4 * k4 + 3] = q4.w;
         }
     } else {
@@ -854,19 +959,14 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(
         if (v < V) {
             const float q = qptr ? qv[k] : (v == onehot ? 1.0f : 0.0f);
             float p, r;
-            residual_of(lv[k], q, job.m, job.inv_t, z, rz, s_tbl, p, r);
+            residual_of(lv[k], q, job.m, inv_t, z, rz, s_tbl, p, r);
             rho[k] = use_p ? p : r;
             if (rho[k] > 0.0f) my_last = v;
         }
         mine += (double)rho[k];
     }
     // exclusive prefix of the per-thread sums, in thread order
-    double incl = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double up = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += up;
-    }
+    const double incl = wave_scan(mine);
     if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
     double before = s_before;
@@ -894,14 +994,14 @@ namespace specv {
 // The scan of all M rows.  Logits that cannot all still be in the memory-side cache are read nontemporal (measured, V = 151936: M = 1204,
 // 732 MB 133 -> 110 us; M = 576 62 -> 58; M = 160, 97 MB 19.4 -> 17.9; below half the cache no difference).
 static void launch_row_stats(const float* logits, const float* temperature, const int32_t* qo_indptr, int B, int M, int V, int nseg,
-                             bool vec, const AcceptWorkspace& w, int32_t* stats, bool greedy_rows_covered, bool fp32_sums, hipStream_t s)
+                             const AcceptWorkspace& w, int32_t* stats, bool greedy_rows_covered, bool fp32_sums, hipStream_t s)
 {
     const dim3 grid((nseg + kSegPerWg - 1) / kSegPerWg, M);
     if ((size_t)M * V * 4 > kMemorySideCache / 4)
-        hipLaunchKernelGGL(accept_row_stats_kernel<true>, grid, dim3(kThreads), 0, s, logits, temperature, qo_indptr, B, V, nseg, vec, w,
+        hipLaunchKernelGGL(accept_row_stats_kernel<true>, grid, dim3(kThreads), 0, s, logits, temperature, qo_indptr, B, V, nseg, w,
                            stats, greedy_rows_covered, fp32_sums);
     else
-        hipLaunchKernelGGL(accept_row_stats_kernel<false>, grid, dim3(kThreads), 0, s, logits, temperature, qo_indptr, B, V, nseg, vec, w,
+        hipLaunchKernelGGL(accept_row_stats_kernel<false>, grid, dim3(kThreads), 0, s, logits, temperature, qo_indptr, B, V, nseg, w,
                            stats, greedy_rows_covered, fp32_sums);
 }
 }  // namespace specv
@@ -943,29 +1043,38 @@ static int accept_impl(const float* logits, const int32_t* tokens, const float* 
     if (workspace_bytes < need)
         return fail(SPEC_EWORKSPACE, "spec_accept: workspace %zu bytes, need %zu", workspace_bytes, need);
     carve(&w, (char*)workspace, B, M, nseg);
-    const bool vec = (V % 4 == 0) && aligned(logits, 16) && (!draft_probs || aligned(draft_probs, 16));
     hipStream_t s = (hipStream_t)stream;
     // Sampled requests: the bulk sums over all candidate rows in fp32 and an interval test, fp64 sums only on the row
-    // the bonus is drawn from (and on rows whose test the interval leaves open); or fp64 sums over every row.
+    // the bonus is drawn from (and on rows whose test the interval leaves open); or fp64 sums over every row, which for a small batch cost
+    // less (0.5 us per million entries) than the launch that sums the bonus rows (5 us).
     const int filter_mode = g_accept_filter;
-    const bool filter = seeds != nullptr && (filter_mode != 2 || sum.blocks > 0);   // block sums are estimates: the interval test is needed
+    const bool small = (size_t)M * V <= (size_t)kFp64Entries;
+    const bool filter = seeds != nullptr && ((filter_mode != 2 && !(filter_mode == 0 && small)) || sum.blocks > 0);   // block sums are estimates: the interval test is needed
     const float band = !filter ? 0.0f : (filter_mode == 3 ? 0.25f : 6.103515625e-05f);   // 2^-14; 0.25 leaves most tests open
+    DecideArgs d{};
+    d.logits = logits; d.tokens = tokens; d.draft_probs = draft_probs; d.temperature = temperature; d.seeds = seeds;
+    d.qo_indptr = qo_indptr; d.accept_len = accept_len; d.out_tokens = out_tokens; d.rollback = rollback; d.stats = stats;
+    d.status_flags = status_flags; d.blk_max = blk_max; d.blk_arg = blk_arg; d.sum = sum; d.round = round; d.band = band;
+    d.M = M; d.V = V; d.nseg = nseg; d.gamma_max = gamma_max; d.nblk = blocks;
     if (sum.blocks > 0 || (blocks > 0 && !seeds)) {
         // every row's summary is at hand (or: all greedy, seeds == NULL promises it, and every row's maxima are):
         // no row of logits is scanned
         if (stats) hipLaunchKernelGGL(accept_reset_stats_kernel, dim3(1), dim3(64), 0, s, stats, B);
     } else {
-        launch_row_stats(logits, temperature, qo_indptr, B, M, V, nseg, vec, w, stats, blocks > 0, filter, s);
+        launch_row_stats(logits, temperature, qo_indptr, B, M, V, nseg, w, stats, blocks > 0, filter, s);
     }
-    hipLaunchKernelGGL(accept_decide_kernel, dim3(B), dim3(kDecideThreads), 0, s, logits, tokens, draft_probs, temperature, seeds,
-                       round, qo_indptr, accept_len, out_tokens, rollback, stats, M, V, nseg, gamma_max, w, status_flags,
-                       blk_max, blk_arg, blocks, band, sum);
-    if (seeds) {   // seeds == NULL promises an all-greedy batch: nothing is ever drawn
-        if (filter) hipLaunchKernelGGL(accept_bonus_z_kernel, dim3((nseg + kJobSegs - 1) / kJobSegs, B), dim3(kThreads), 0, s, logits, V, nseg, vec, w);
-        hipLaunchKernelGGL(accept_residual_sums_kernel, dim3((nseg + kJobSegs - 1) / kJobSegs, B), dim3(kThreads), 0, s, logits, draft_probs, V,
-                           nseg, vec, filter, w);
+    // (seeds == NULL promises an all-greedy batch: nothing is ever drawn)
+    const dim3 per_segment(nseg, B);
+    if (seeds && !filter && small && blocks == 0) {
+        hipLaunchKernelGGL((accept_bonus_kernel<true, false>), per_segment, dim3(kThreads), 0, s, d, w, false);
+    } else {
+        hipLaunchKernelGGL(accept_decide_kernel, dim3(B), dim3(kDecideThreads), 0, s, d, w);
+        if (filter) hipLaunchKernelGGL((accept_bonus_kernel<false, true>), per_segment, dim3(kThreads), 0, s, d, w, false);
+        if (seeds) hipLaunchKernelGGL((accept_bonus_kernel<false, false>), per_segment, dim3(kThreads), 0, s, d, w, filter);
+    }
+    if (seeds) {
         hipLaunchKernelGGL(accept_pick_kernel, dim3(B), dim3(kThreads), 0, s, logits, draft_probs, accept_len,
-                           out_tokens, V, nseg, gamma_max, vec, filter, w);
+                           out_tokens, V, nseg, gamma_max, filter, w);
     }
     return check_launch("spec_accept");
 }
@@ -1076,9 +1185,8 @@ extern "C" int spec_accept_tree(const float* logits, const int32_t* tokens, cons
     if (workspace_bytes < need)
         return fail(SPEC_EWORKSPACE, "spec_accept_tree: workspace %zu bytes, need %zu", workspace_bytes, need);
     carve(&w, (char*)workspace, B, M, nseg);
-    const bool vec = (V % 4 == 0) && aligned(logits, 16);
     hipStream_t s = (hipStream_t)stream;
-    launch_row_stats(logits, nullptr, qo_indptr, B, M, V, nseg, vec, w, stats, false, false, s);
+    launch_row_stats(logits, nullptr, qo_indptr, B, M, V, nseg, w, stats, false, false, s);
     hipLaunchKernelGGL(accept_decide_tree_kernel, dim3(B), dim3(256), 0, s, tokens, parent, qo_indptr, accept_len, out_tokens,
                        path, rollback, stats, M, V, nseg, gamma_max, w, status_flags);
     return check_launch("spec_accept_tree");

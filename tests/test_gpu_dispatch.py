@@ -9,7 +9,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2605_08151_amd import workloads as wl  # noqa: E402
-from test_gpu_parity import _close, _oracle_attn, _step, sv  # noqa: E402,F401
+from test_gpu_parity import _accept_both, _assert_same, _close, _oracle_attn, _qo, _step, sv  # noqa: E402,F401
 
 
 @pytest.mark.parametrize("gammas,Hq", [((0,), 8), ((4,), 32), ((0, 3, 8), 64)], ids=["decode", "two_tiles", "row_split"])
@@ -65,3 +65,21 @@ def test_row_major_lm_head_through_the_packed_kernel(sv, oracle, M, V):
     packed = torch.empty((M, V), device="cuda")
     sv.spec_lm_head_packed(hidden, Wp, packed)
     assert torch.equal(packed, logits[:M])
+
+
+@pytest.mark.parametrize("V,B", [(1, 3), (4095, 5), (4096, 5), (4097, 5), (8193, 5), (50021, 7), (50021, 60)])
+def test_sampled_acceptance_of_small_batches(sv, oracle, V, B):
+    """Up to 8 Mi logits every row is summed in fp64 and the decision is taken by every workgroup of the residual launch (the last pair of sizes is
+    just beyond: 240 rows x 50021).  Rows that start at odd multiples of 4 bytes, last segments of 1, 4095 and 4096 entries."""
+    rng = np.random.default_rng(V + B)
+    gammas = np.full(B, 3)
+    gammas[::3] = 0
+    qo = _qo(gammas)
+    logits = rng.normal(0, 2.0, (qo[-1], V)).astype(np.float32)
+    cfg = wl.VerifyConfig("s", V, B, (3,), ("const", 1), 8, 1, 64, V)
+    dp, tokens = wl.draft_probs_noisy(cfg, torch.from_numpy(qo), torch.from_numpy(logits), noise_std=0.5)
+    temp = np.full(B, 0.8, np.float32)
+    temp[1::4] = 0.0
+    got, ref = _accept_both(sv, oracle, logits, tokens.numpy(), dp.numpy(), temp, rng.integers(0, 2 ** 63, B, dtype=np.uint64), 9, qo, 3)
+    _assert_same(got, ref, gammas)
+    assert got["status"] == 0
