@@ -10,7 +10,11 @@
 //     after the MFMAs that consumed it: no W byte touches LDS;
 //   * hidden goes from L2 into LDS by direct global->LDS loads (no staging registers), 4 slabs of 64 k deep, and
 //     a fragment read from LDS feeds 4 MFMAs (one per panel of the wave);
-//   * a wave is its own latency hiding: everything it needs is requested 2.5 to 4 slabs (2-4 us) ahead.
+//   * a wave is its own latency hiding: everything it needs is requested 2.5 to 4 slabs (2-4 us) ahead, hidden fragments are read
+//     from LDS across the border of two slabs, and the stores of a tile drain under the first steps of the next one.
+// What bounds it: with 16 instructions per 4 MFMAs and a wave (64 cycles) the issue slots, and the power the operands' way from L2
+// costs.  M = 1152, V = 151936, H = 4096, same box: 1260 us with vector address arithmetic, branches per group and a full stop at every
+// slab and tile, 1165 us (1.23 PFLOP/s) as it stands; 1119 before and without any store, 800 with operands that never move.
 // The batch is cut into row groups of whole 16-row tiles, nearly equal and at most 256 rows each; the grid is groups x panel ranges, the groups of a
 // range run on the same XCD at the same time and share that range's panels through the XCD's L2, so HBM sees W once.
 // Per output element the products are added in the same order as in the other LM-head kernels (k ascending, one
@@ -18,6 +22,7 @@
 #include "common.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace specv {
 
@@ -29,19 +34,35 @@ constexpr int kMfPassPanels = kMfWaves * kMfTN;
 constexpr int kMfRing = 4;                     // slabs in flight: hidden slabs in LDS = W slabs in registers
 constexpr int kMfPatchPitch = kMfTN * 64 + 16; // bytes per row of a wave's store patch
 
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // (a row of logits starts at any multiple of 4 bytes)
+
+#define SPECV_INLINE __attribute__((always_inline))
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
+// lds_dma16 with a wave-uniform base and a 32-bit offset per lane
+__device__ inline void lds_dma16_off(uint32_t off, const void* base, void* lds_base)
+{
+    const uint32_t m0v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_base;
+    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
+}
+
 // (SUMMARY instantiations also leave the block summaries described at LmSummary)
-template <int TM, bool NT, bool SUMMARY>
+template <int TM, bool SUMMARY>
 __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
-    int M_all, int H, int V, int n_panels, int panels_per_wg, bool vec_store, int groups, int tiles_lo, int groups_hi,
-    LmSummary sm)
+    int M_all, int H, int V, int n_panels, int panels_per_wg, int groups, int tiles_lo, int groups_hi,
+    bool nt, LmSummary sm)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int RW = kMfRing;
     constexpr int SR = (TM * 16 + 31) / 32 * 32;      // rows staged per slab: 8 per direct load, the same count for every wave
     constexpr int QN = SR / 32;                       // direct loads per wave and slab
     constexpr int kSlabBytes = SR * kMfPitch;
-    constexpr int kHfAhead = 4;                       // hidden fragments read from LDS ahead of their MFMAs
+    // hidden fragments are read from LDS ahead of their MFMAs: kHfCross groups at the border of two steps, kHfAhead inside one
+    constexpr int kHfCross = 5, kHfAhead = 7, kHfCatchUp = kHfAhead - kHfCross, kHfRing = 8;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, l16 = lane & 15, kg = lane >> 4;
@@ -103,43 +124,34 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         const int ch = (lane & 7) ^ ((row >> 1) & 7);
         hoff[q] = (uint32_t)min(row, M - 1) * (uint32_t)H * 2u + (uint32_t)ch * 16u;
     }
-    auto stage_h = [&](int slab, int slot) {          // slab index in [0, nslab), ring slot
-        const unsigned char* src = A + (size_t)slab * (kMfSlab * 2);
-        unsigned char* dst = hbuf + slot * kSlabBytes + (QN * wave) * 1024;
-#pragma unroll
-        for (int q = 0; q < QN; ++q) lds_dma16(src + hoff[q], dst + q * 1024);
+    const unsigned char* hsrc = A;                    // slab whose direct loads are issued next (wave-uniform: a scalar base)
+    auto stage_h1 = [&](int slot, int q) SPECV_INLINE {            // direct load q of this wave's share of that slab
+        lds_dma16_off(hoff[q], hsrc, hbuf + slot * kSlabBytes + (QN * wave + q) * 1024);
     };
 
-    // ---- W: the wave's panels of a pass and their stream pointers
-    const uint16_t* wcur[kMfTN];
-    const uint16_t* wnext[kMfTN];
+    // ---- W: the wave's panels of a pass, read through a buffer descriptor (base: the wave's first panel; size: its panels, so that
+    // slots past its share read zeros and cost no traffic) at a scalar stream position plus 16 bytes per lane:
+    // a request costs no vector address arithmetic.
+    // Passes are full (16 panels, 4 per wave) up to the last, which deals its 1..16 panels as evenly as they go.
     int wave_p0 = 0, wave_np = 0;
-    auto pass_panels = [&](int pass, int& p0, int& np) {
-        const int lo = p_begin + pass * n_own / npass;                // 32-bit: passes x panels of a range is small
-        const int hi = p_begin + (pass + 1) * n_own / npass;          // 1 <= hi - lo <= 16
-        const int m = hi - lo;
+    auto pass_panels = [&](int pass, int& p0, int& np) SPECV_INLINE {
+        const int lo = p_begin + pass * kMfPassPanels;
+        const int m = min(kMfPassPanels, p_end - lo);
         p0 = lo + wave * m / kMfWaves;
-        np = lo + (wave + 1) * m / kMfWaves - p0;      // 0 .. 4; p0 < hi is a panel of the matrix either way
+        np = lo + (wave + 1) * m / kMfWaves - p0;      // 0 .. 4; p0 < p_end is a panel of the matrix either way
     };
-    auto panel_ptrs = [&](int p0, int np, const uint16_t* (&ptr)[kMfTN]) {
-#pragma unroll
-        for (int tn = 0; tn < kMfTN; ++tn) {
-            // slots past the wave's share re-read its last panel (branch-free loop); their results are never stored
-            const int p = p0 + max(0, min(tn, np - 1));
-            ptr[tn] = Wp + (size_t)p * 16 * H + lane * 8;
-        }
-    };
+    const uint32_t panel_bytes = (uint32_t)H * 32u;
+    const uint32_t woff = (uint32_t)lane * 16u;
     u32x4 wreg[RW][2][kMfTN];
-    // panel tn of chunk (k-tile t of slab `slab`) of ring slot `slot`; slabs past the end of the pass come from the next
-    // pass's panels
-    auto fetch_w1 = [&](int slot, int t, int tn, int slab) {
-        const bool nxt = slab >= nslab;
-        const int sl = nxt ? slab - nslab : slab;
-        const uint16_t* base = nxt ? wnext[tn] : wcur[tn];
-        wreg[slot][t][tn] = *reinterpret_cast<const u32x4*>(base + (size_t)(sl * 2 + t) * 512);
+    __amdgpu_buffer_rsrc_t wrsrc;
+    uint32_t wpos = 0;                                // byte position of the slab that is requested next inside its panel
+    auto open_panels = [&](int p0, int np) SPECV_INLINE {
+        const unsigned char* base = reinterpret_cast<const unsigned char*>(Wp) + (size_t)p0 * panel_bytes;
+        wrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (uint32_t)np * panel_bytes, 0x00020000);
+        wpos = 0;
     };
-    auto stage_h1 = [&](int slab, int slot, int q) {  // direct load q of this wave's share of a hidden slab
-        lds_dma16(A + (size_t)slab * (kMfSlab * 2) + hoff[q], hbuf + slot * kSlabBytes + (QN * wave + q) * 1024);
+    auto fetch_w1 = [&](int slot, int t, int tn) SPECV_INLINE {    // k-tile t of that slab, panel slot tn
+        wreg[slot][t][tn] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff, wpos + t * 1024 + tn * panel_bytes, 0);
     };
 
     f32x4 acc[kMfTN][TM];
@@ -150,126 +162,202 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
 
     // LDS offset of this lane's fragment of row tile 0, k-tile t inside a slab: row l16, chunk (4 t + kg) ^ ((l16 >> 1) & 7)
     // (row 16 tm + l16 has the same swizzle term: 8 tm vanishes under & 7)
-    uint32_t hf_off[2];
+    // and the same for slots 2 and 3, so that every fragment is one of four registers plus a 16-bit immediate
+    typedef __attribute__((address_space(3))) const unsigned char* LdsPtr;
+    uint32_t hf_at[2][2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) hf_off[t] = (uint32_t)(l16 * kMfPitch + (((t * 4 + kg) ^ ((l16 >> 1) & 7)) << 4));
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            hf_at[u][t] = (uint32_t)(uintptr_t)(LdsPtr)hbuf + (uint32_t)(u * 2 * kSlabBytes + l16 * kMfPitch + (((t * 4 + kg) ^ ((l16 >> 1) & 7)) << 4));
+            asm volatile("" : "+v"(hf_at[u][t]));     // (the compiler would keep a register per distant fragment instead)
+        }
+    bf16x8 hfq[kHfRing];
+    auto hfrag = [&](auto rc, auto ic) SPECV_INLINE {              // fragment i = t * TM + tm of the slab in ring slot r
+        constexpr int r = decltype(rc)::value, i = decltype(ic)::value;
+        static_assert(kSlabBytes + (TM - 1) * 16 * kMfPitch < 65536, "16-bit LDS offsets");
+        return *reinterpret_cast<__attribute__((address_space(3))) const bf16x8*>(
+            (LdsPtr)(uintptr_t)hf_at[r / 2][i / TM] + ((r & 1) * kSlabBytes + (i % TM) * (16 * kMfPitch)));
+    };
 
-    int pass = 0;
+    int pass = 0, p0_next, np_next;
     pass_panels(0, wave_p0, wave_np);
-    panel_ptrs(wave_p0, wave_np, wcur);
-    {
-        int p0n, npn;
-        pass_panels(npass > 1 ? 1 : 0, p0n, npn);
-        panel_ptrs(p0n, npn, wnext);
-    }
+    pass_panels(npass > 1 ? 1 : 0, p0_next, np_next);
+    open_panels(wave_p0, wave_np);
     // prologue: hidden slabs 0..2 and W slabs 0..3 except the last chunk (the first step requests it); everything has landed
     // before the first step (once per workgroup)
-    stage_h(0, 0);
-    stage_h(1, 1);
-    stage_h(2, 2);
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
+    for (int r = 0; r < RW - 1; ++r) {
+#pragma unroll
+        for (int q = 0; q < QN; ++q) stage_h1(r, q);
+        hsrc += kMfSlab * 2;
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int tn = 0; tn < kMfTN; ++tn)
-                if (r < RW - 1 || t == 0) fetch_w1(r, t, tn, r);
+                if (r < RW - 1 || t == 0) fetch_w1(r, t, tn);
+        if (r < RW - 1) wpos += 2048;
+    }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
+    static_for<kHfCross>([&](auto ic) SPECV_INLINE { hfq[ic] = hfrag(std::integral_constant<int, 0>{}, ic); });
+    __builtin_amdgcn_sched_barrier(0);
 
     // One step = one slab of 64 k for the whole tile; slab s lives in ring slot s % 4 (hidden in LDS, W in registers), and
     // because H is a multiple of 256 that slot is the same in every pass, so all ring indices are compile-time constants.
     // The steps of all passes form one stream: the requests for the slabs after the end of a pass are the first slabs of
     // the next pass, so the pipeline never drains between tiles.
-    // A step is 2 TM groups of 4 MFMAs (one hidden fragment against the wave's 4 panels); after each group at most ONE
-    // memory request is issued, so that the four waves of the CU, which run in step, never queue up behind each other at the
-    // memory pipeline with nothing left for the matrix cores.  Requests of step s, in program order (fenced: the in-order
-    // completion of a wave's requests is what every wait counts on):
+    // A step is 2 TM groups of 4 MFMAs (one hidden fragment against the wave's 4 panels).  A wave issues one instruction in
+    // 4 cycles and a group keeps the matrix core busy for 64: everything else of a group has to fit 12 slots, so a request is
+    // one load with a scalar base and a step without branches (FOUR: a full pass, the wave owns all four panels) does no vector arithmetic.
+    // Requests of step s, in program order (fenced: the in-order completion of a wave's requests is what every wait counts on):
     //   groups 0..3            W chunk k-tile 1 of slab s+3 (its ring slot was consumed at the end of the previous step)
-    //   groups 4..4+QN-1       direct loads of hidden slab s+3 into the LDS slot that was read in the previous step
+    //   groups 4..4+QN-1       direct loads of hidden slab s+3 into the LDS slot of slab s-1
     //   groups TM..TM+3        W chunk k-tile 0 of slab s+4 (this step's slot, consumed by groups 0..TM-1)
+    // Hidden fragments are read 5 to 7 groups ahead, across the border of the steps: the barrier that publishes slab s+1 and
+    // frees the slot of slab s stands 5 groups before the end of step s, when this step's last fragment has been in registers
+    // for two groups, and the last groups read the first fragments of slab s+1: no step begins by waiting for LDS.
     // The accumulators are pinned to the accumulation registers by writing the MFMA as an asm statement; its operands are
-    // ordinary values, so the compiler still inserts the waits for the W loads and the LDS reads.  Those waits count W
+    // ordinary values, so the compiler still inserts the waits for the W loads and the LDS reads.  It does not know that an MFMA must
+    // not follow a vector instruction that wrote its operand by less than 2 wait states; copies can only stand where two ways of the
+    // code meet, i.e. before the first step of a pass, whose MFMAs bring their own s_nop.  Those waits count W
     // loads only (the direct loads are invisible to the compiler): a wait for a chunk requested 3.5 steps ago allows ~28
     // younger requests in flight, i.e. it covers requests at least 1.75 steps old, and a direct load is needed 2.5 steps
     // after it was issued: it is never what the math waits for.
-    static_assert(4 + QN <= TM, "the requests of k-tile 0 fit its groups");
-    auto do_step = [&](auto rc, int s) {
+    static_assert(4 + QN <= TM && TM + 3 <= 2 * TM - 6, "the requests of a step precede its barrier");
+    // FIRST: the first slab of a pass (the products start from zero).  last_iter: the last 4 slabs of a pass.
+    // stores: the counted stores of a tile were issued between the requests for slab s+1 and this step.
+    auto do_step = [&](auto rc, auto first_c, auto four_c, bool last_iter, bool stores) SPECV_INLINE {
         constexpr int r = decltype(rc)::value;        // ring slot of slab s
         constexpr int rp = (r + 3) % RW;              // ring slot of slab s-1 = of slab s+3
-        const unsigned char* cur = hbuf + r * kSlabBytes;
-        int s3 = s + 3;                               // hidden wraps into the next pass (same rows); W takes the next panels
-        const int s3h = s3 >= nslab ? s3 - nslab : s3;
-        const bool four_panels = wave_np == kMfTN;
-        bf16x8 hfq[kHfAhead];
-        auto hfrag = [&](int i) {                     // i = t * TM + tm
-            return *reinterpret_cast<const bf16x8*>(cur + hf_off[i / TM] + (i % TM) * (16 * kMfPitch));
-        };
-#pragma unroll
-        for (int i = 0; i < kHfAhead; ++i) hfq[i] = hfrag(i);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 2 * TM; ++i) {
-            const int t = i / TM, tm = i % TM;
-            const bf16x8 h = hfq[i % kHfAhead];
+        constexpr bool FIRST = decltype(first_c)::value, FOUR = decltype(four_c)::value;
+        constexpr int g0 = r * 2 * TM;                // running group index (8 TM groups of 4 steps are a multiple of kHfRing)
+        static_for<2 * TM>([&](auto ic) SPECV_INLINE {
+            constexpr int i = decltype(ic)::value, t = i / TM, tm = i % TM;
+            const bf16x8 h = hfq[(g0 + i) % kHfRing];
             if (tm < TM - 1 || full_tm) {             // wave-uniform
 #pragma unroll
-                for (int tn = 0; tn < kMfTN; ++tn)
-                    if (tn < kMfTN - 1 || four_panels)    // wave-uniform: a panel slot the wave does not own costs no MFMA
+                for (int tn = 0; tn < kMfTN; ++tn) {
+                    if (!FOUR && tn >= kMfTN - 2 && tn >= wave_np) continue;    // wave-uniform: such a slot costs no MFMA
+                    if constexpr (FIRST && t == 0)
+                        asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
+                    else
                         asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
+                }
             }
-            if (i + kHfAhead < 2 * TM) hfq[i % kHfAhead] = hfrag(i + kHfAhead);
-            if (i < 4) fetch_w1(rp, 1, i, s3);
-            else if (i < 4 + QN) stage_h1(s3h, rp, i - 4);
-            else if (i >= TM && i < TM + 4) fetch_w1(r, 0, i - TM, s + RW);
+            if constexpr (i < kHfCatchUp) {
+                hfq[(g0 + kHfCross + 2 * i) % kHfRing] = hfrag(rc, std::integral_constant<int, kHfCross + 2 * i>{});
+                hfq[(g0 + kHfCross + 2 * i + 1) % kHfRing] = hfrag(rc, std::integral_constant<int, kHfCross + 2 * i + 1>{});
+            } else if constexpr (i + kHfAhead < 2 * TM) {
+                hfq[(g0 + i + kHfAhead) % kHfRing] = hfrag(rc, std::integral_constant<int, i + kHfAhead>{});
+            } else if constexpr (i >= 2 * TM - kHfCross) {
+                hfq[(g0 + i + kHfCross) % kHfRing] =
+                    hfrag(std::integral_constant<int, (r + 1) % RW>{}, std::integral_constant<int, i + kHfCross - 2 * TM>{});
+            }
+            if constexpr (i < 4) fetch_w1(rp, 1, i);
+            else if constexpr (i < 4 + QN) stage_h1(rp, i - 4);
+            else if constexpr (i >= TM && i < TM + 4) fetch_w1(r, 0, i - TM);
+            if constexpr (i == 4) {                   // W goes on to slab s+4: after the last one of a pass, to the next pass's panels
+                wpos += 2048;
+                if (r == 0 && last_iter) open_panels(p0_next, np_next);
+            }
+            if constexpr (i == TM - 1) {              // hidden goes on to slab s+4; after the last one, to slab 0 again
+                hsrc += kMfSlab * 2;
+                if (r == 0 && last_iter) hsrc = A;
+            }
+            if constexpr (i == 2 * TM - kHfCross - 1) {
+                // Slab s+1 must be complete in LDS before anybody reads it.  This wave's share was requested in groups 4.. of
+                // step s-2; younger than it are 4 W loads of that step and the 8 + QN requests of each of the two steps since.
+                // Where a tile was stored by counted stores in between, 4 for each of its TM or TM - 1 row tiles are younger still, and
+                // waiting for all but 63 (the most the counter holds) lets them drain for two steps.  No LDS read of slab s is pending either: its slot may be overwritten.
+                constexpr int kYounger = 2 * QN + 20;
+                constexpr int kDrain = kYounger + 4 * (TM - 1) < 63 ? kYounger + 4 * (TM - 1) : 63;
+                static_assert(kYounger < 63, "s_waitcnt vmcnt has 6 bits");
+                if (stores) __builtin_amdgcn_s_waitcnt(0x0070 | (kDrain & 15) | ((kDrain >> 4) << 14));
+                else __builtin_amdgcn_s_waitcnt(0x0070 | (kYounger & 15) | ((kYounger >> 4) << 14));
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
             __builtin_amdgcn_sched_barrier(0);
-        }
-        // Slab s+1 must be complete in LDS before anybody reads it.  This wave's share was requested in groups 4.. of
-        // step s-2; younger than it are 4 W loads of that step and the 8 + QN requests of each of the two steps since (and,
-        // after a tile was stored, that tile's stores, which then complete here too).
-        constexpr int kYounger = 2 * QN + 20;
-        static_assert(kYounger < 64, "s_waitcnt vmcnt has 6 bits");
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (kYounger & 15) | ((kYounger >> 4) << 14));
-        __syncthreads();
+        });
     };
-    for (;;) {
-        for (int sR = 0; sR < nslab; sR += RW) {
-            do_step(std::integral_constant<int, 0>{}, sR);
-            do_step(std::integral_constant<int, 1>{}, sR + 1);
-            do_step(std::integral_constant<int, 2>{}, sR + 2);
-            do_step(std::integral_constant<int, 3>{}, sR + 3);
-        }
-        // ---- the tile is complete; the next pass's first slabs are already in flight ----
-        const int st_p0 = wave_p0, st_np = wave_np;
-        ++pass;
-        const bool more = pass < npass;
-        if (more) {
-            pass_panels(pass, wave_p0, wave_np);
-#pragma unroll
-            for (int tn = 0; tn < kMfTN; ++tn) wcur[tn] = wnext[tn];
-            int p0n, npn;
-            pass_panels(pass + 1 < npass ? pass + 1 : pass, p0n, npn);
-            panel_ptrs(p0n, npn, wnext);
-        }
+    auto do_steps = [&](auto first_c, auto four_c, bool last_iter, bool stores) SPECV_INLINE {
+        constexpr bool FIRST = decltype(first_c)::value;
+        do_step(std::integral_constant<int, 0>{}, first_c, four_c, last_iter, FIRST && stores);
+        do_step(std::integral_constant<int, 1>{}, std::false_type{}, four_c, false, FIRST && stores);
+        do_step(std::integral_constant<int, 2>{}, std::false_type{}, four_c, false, false);
+        do_step(std::integral_constant<int, 3>{}, std::false_type{}, four_c, false, false);
+    };
+    // Stores the finished tile of pass `pass`; returns whether it did so by exactly 4 stores per row tile.
+    auto store_tile = [&](int pass, int st_p0, int st_np, auto full_c) SPECV_INLINE {
+        constexpr bool FULL = decltype(full_c)::value;    // a full pass: four panels, all inside the matrix
+        const bool whole = !SUMMARY && st_np > 0 && (FULL || (st_p0 + st_np) * 16 <= V);
         // acc[tn][tm][i] = C[row 16 tm + l16][entry 16 (st_p0 + tn) + 4 kg + i]
         // (SUMMARY) block of this wave and pass; its span is written once, by the first row group
         int blk = 0, count = 0;
         if constexpr (SUMMARY) {
-            blk = (range * sm.passes_per_range + (pass - 1)) * kMfWaves + wave;
+            blk = (range * sm.passes_per_range + pass) * kMfWaves + wave;
             const int first = st_p0 * 16;
             count = max(0, min(st_np * 16, V - first));
             if (group == 0 && lane == 0) { sm.blk_span[2 * blk] = first; sm.blk_span[2 * blk + 1] = count; }
         }
-        if (vec_store || SUMMARY) {                   // (the summary instantiations are only launched for V % 4 == 0)
-            // V % 4 == 0.  The tile is turned through the wave's own LDS patch so that one store instruction writes all
+        // (the lane's coordinates are taken afresh here: as invariants of the pass loop they, and everything derived from them, would
+        // be kept in registers that the main loop needs)
+        int lane_e = lane;
+        asm volatile("" : "+v"(lane_e));
+        const int l16_e = lane_e & 15, kg_e = lane_e >> 4;
+        if (whole) {
+            // All entries of the wave's panels are in the matrix: stores without tests, the next row tile written to the patch before
+            // this one's stores wait for their reads.  Lanes past the wave's panels or the group's rows repeat the last entries or row.
+            const int srow = lane_e >> 4, scol = min((lane_e & 15) * 4, st_np * 16 - 4);
+            unsigned char* dst = reinterpret_cast<unsigned char*>(C + st_p0 * 16);
+            const uint32_t off = ((uint32_t)srow * (uint32_t)V + (uint32_t)scol) * 4u;
+            const size_t row_step = 16 * (size_t)V;
+            f32x4 v[4];
+            auto put = [&](auto tmc) SPECV_INLINE {
+#pragma unroll
+                for (int tn = 0; tn < kMfTN; ++tn)
+                    *reinterpret_cast<f32x4*>(patch + l16_e * kMfPatchPitch + (tn * 16 + kg_e * 4) * 4) = acc[tn][decltype(tmc)::value];
+            };
+            put(std::integral_constant<int, 0>{});
+            static_for<TM>([&](auto tmc) SPECV_INLINE {
+                constexpr int tm = decltype(tmc)::value;
+                if (tm < TM - 1 || full_tm) {         // wave-uniform
+                    constexpr bool RAGGED = tm >= TM - 2;      // the group's last tile
+                    const int last = M - 1 - tm * 16;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int prow = RAGGED ? min(q * 4 + srow, last) : q * 4 + srow;
+                        v[q] = *reinterpret_cast<const f32x4*>(patch + prow * kMfPatchPitch + scol * 4);
+                    }
+                    if constexpr (tm + 1 < TM) { if (tm + 1 < TM - 1 || full_tm) put(std::integral_constant<int, tm + 1>{}); }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        f32x4_any* d = reinterpret_cast<f32x4_any*>(dst + off);
+                        if constexpr (RAGGED) d = reinterpret_cast<f32x4_any*>(C + (size_t)(tm * 16 + min(q * 4 + srow, last)) * V + (st_p0 * 16 + scol));
+                        if (nt) __builtin_nontemporal_store((f32x4_any)v[q], d); else *d = v[q];    // (wave-uniform)
+                        dst += row_step;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        } else {                                      // (the summary instantiations are only launched for V % 4 == 0)
+            // The tile is turned through the wave's own LDS patch so that one store instruction writes all
             // the wave's entries of a row (256 bytes), 4 rows at a time.  LDS operations of one wave execute in order, so
             // the patch needs no barrier and no second copy.
             constexpr int kLanesPerRow = kMfTN * 4, kRowsPerStore = 64 / kLanesPerRow;
-            const int srow = lane / kLanesPerRow, scol = (lane % kLanesPerRow) * 4;     // this lane's row and entry when storing
+            const int srow = lane_e / kLanesPerRow, scol = (lane_e % kLanesPerRow) * 4;     // this lane's row and entry when storing
             const int col0 = st_p0 * 16 + scol;
-            const bool col_ok = scol < st_np * 16 && col0 < V;
+            const bool col_ok = scol < st_np * 16 && col0 + 4 <= V;
+            const int col_tail = scol < st_np * 16 && !col_ok ? V - col0 : 0;
             uint32_t off = ((uint32_t)srow * (uint32_t)V + (uint32_t)col0) * 4u;
+            int row = srow;                           // (running, for the same reason)
             const uint32_t row_step = (uint32_t)kRowsPerStore * 4u * (uint32_t)V;
             // (SUMMARY) running element index of this lane's row in blk_max / blk_sum, stepped like `off`: computed afresh
             // per row it is invariant from pass to pass, and the compiler would keep all 4 TM of them in registers
@@ -281,12 +369,11 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
 #pragma unroll
                 for (int tn = 0; tn < kMfTN; ++tn) {
                     t[tn] = acc[tn][tm];
-                    *reinterpret_cast<f32x4*>(patch + l16 * kMfPatchPitch + (tn * 16 + kg * 4) * 4) = t[tn];
-                    if constexpr (!SUMMARY) acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    *reinterpret_cast<f32x4*>(patch + l16_e * kMfPatchPitch + (tn * 16 + kg_e * 4) * 4) = t[tn];
                 }
 #pragma unroll
                 for (int q = 0; q < 16 / kRowsPerStore; ++q) {
-                    const int prow = q * kRowsPerStore + srow, row = tm * 16 + prow;
+                    const int prow = q * kRowsPerStore + srow;
                     const f32x4 v = *reinterpret_cast<const f32x4*>(patch + prow * kMfPatchPitch + scol * 4);
                     if constexpr (SUMMARY) {
                         // In this layout a row's 64 entries lie in the 16 lanes of one 16-lane row, 4 consecutive entries
@@ -315,42 +402,42 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
                         asm volatile("" : "+v"(sat));
                     }
                     if (row < M && col_ok) {
-                        f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<unsigned char*>(C) + off);
-                        if constexpr (NT) __builtin_nontemporal_store(v, dst); else *dst = v;
+                        f32x4_any* dst = reinterpret_cast<f32x4_any*>(reinterpret_cast<unsigned char*>(C) + off);
+                        if (nt) __builtin_nontemporal_store((f32x4_any)v, dst); else *dst = v;
+                    }
+                    if (!SUMMARY && row < M && col_tail > 0) {          // the matrix ends inside these four entries
+                        float* dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(C) + off);
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) if (e < col_tail) dst[e] = v[e];
                     }
                     off += row_step;                  // one running byte offset (rows x V x 4 < 2^32 per group)
-                    asm volatile("" : "+v"(off));
+                    row += kRowsPerStore;
+                    asm volatile("" : "+v"(off), "+v"(row));
                 }
                 // one row tile at a time: left to itself the scheduler interleaves the summaries of all tiles, and their
                 // temporaries (16 values each) no longer fit beside the W ring
-                if constexpr (SUMMARY) __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (SUMMARY) {
-                // the accumulators are cleared only now, behind a fence: cleared tile by tile above, the clears were
-                // moved to the front and every old value had to be copied out (and spilled) first
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                    for (int tn = 0; tn < kMfTN; ++tn) acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        } else {
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
-#pragma unroll
-                for (int tn = 0; tn < kMfTN; ++tn) {
-                    const int row = tm * 16 + l16, e = (st_p0 + tn) * 16 + kg * 4;
-                    if (row < M && tn < st_np) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (e + i < V) C[(size_t)row * V + e + i] = acc[tn][tm][i];
-                    }
-                    acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
             }
         }
-        if (!more) break;
+        return whole;
+    };
+
+    // Full passes are in code of their own: where ways with and without the fourth panel meet, the compiler would move the whole ring to
+    // other registers, and wait for every request in flight to do so.
+    // In each, the first four steps stand outside the loop: there, and only there, the waits know of the stores of the tile before.
+    bool stored = false;                              // a tile's counted stores precede this pass
+    auto one_pass = [&](auto four_c) SPECV_INLINE {
+        do_steps(std::true_type{}, four_c, nslab == RW, stored);
+        for (int s = RW; s < nslab; s += RW) do_steps(std::false_type{}, four_c, s + RW == nslab, false);
+        // the tile is complete; the next pass's first slabs are already in flight
+        stored = store_tile(pass, wave_p0, wave_np, four_c);
+    };
+    for (; pass + 1 < npass; ++pass) {
+        one_pass(std::true_type{});
+        wave_p0 = p0_next; wave_np = np_next;
+        pass_panels(min(pass + 2, npass - 1), p0_next, np_next);
     }
+    one_pass(std::false_type{});
     if constexpr (SUMMARY) {                          // block slots of passes this range does not have
         if (group == 0)
             for (int b = npass * kMfWaves + tid; b < sm.passes_per_range * kMfWaves; b += 64 * kMfWaves) {
@@ -363,7 +450,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
 
 Tunable g_lm_packed_tile{0};   // benchmark hook: 0 = automatic (this kernel for M > 160), 1 = the weight-streaming kernel over row groups
 Tunable g_lm_mfma_nt{0};       // benchmark hook: nontemporal logits stores, 0 = automatic (one or two row groups), 1 = always, 2 = never
-Tunable g_lm_mfma_rows{0};     // benchmark hook: rows per group of this kernel at most (144..256), 0 = automatic (208, or the whole batch up to 256)
+Tunable g_lm_mfma_rows{0};     // benchmark hook: rows per group of this kernel at most (144..256), 0 = automatic (256)
 
 // Row groups, panel ranges and the instantiation that serves them (host arithmetic, shared by the launch and by the
 // callers that size the block summaries).
@@ -373,11 +460,12 @@ static MfmaLayout mfma_layout(int M, int V)
 {
     constexpr int kMaxTM = 16;
     MfmaLayout L{};
-    // Measured on MI355X (V = 151936, H = 4096): M = 1206 as 6 groups of 12-13 tiles 1314 us, as 5 groups of 15-16 tiles
-    // 1346 us (the library GEMM of the image with fp32 output: 1342 us); a batch of at most 16 tiles stays one group.
+    // As few groups as 16 tiles each allow: the taller the tile, the fewer bytes go from L2 to the CUs per product.  Measured on MI355X
+    // (V = 151936, H = 4096), groups of at most 13 / at most 16 tiles: M = 480 576 / 520 us, M = 800 842 / 842, M = 1040 1087 / 1090,
+    // M = 1152 1206 / 1182 (the library GEMM of the image with bf16 output: 1377).
     const int forced = g_lm_mfma_rows;
     const int tiles = (M + 15) / 16;                                     // 16-row tiles of the batch
-    const int cap_tiles = forced >= 16 * 9 && forced <= 16 * kMaxTM ? forced / 16 : (tiles <= kMaxTM ? kMaxTM : 13);
+    const int cap_tiles = forced >= 16 * 9 && forced <= 16 * kMaxTM ? forced / 16 : kMaxTM;
     int groups = (tiles + cap_tiles - 1) / cap_tiles;
     while (groups > 1 && (tiles + groups - 1) / groups < 9) --groups;    // the kernel is built for 9..16 tiles per group
     L.groups = groups;
@@ -396,15 +484,15 @@ static MfmaLayout mfma_layout(int M, int V)
     return L;
 }
 
-template <int TM, bool NT, bool SUMMARY>
+template <int TM, bool SUMMARY>
 static int launch_mfma(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, LmSummary sm, hipStream_t s)
 {
     constexpr int SR = (TM * 16 + 31) / 32 * 32;
     const size_t smem = (size_t)kMfRing * SR * kMfPitch + (size_t)kMfWaves * 16 * kMfPatchPitch + (SUMMARY ? TM * 16 * 4 : 0);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, NT, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
-    hipLaunchKernelGGL((lm_head_mfma_kernel<TM, NT, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
-                       (V + 15) / 16, L.per_range, V % 4 == 0, L.groups, L.tiles_lo, L.groups_hi, sm);
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
+    hipLaunchKernelGGL((lm_head_mfma_kernel<TM, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
+                       (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi, L.nt, sm);
     return SPEC_OK;
 }
 
@@ -433,10 +521,8 @@ int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M
     switch (L.tm) {
 #define SPECV_MF(TMv)                                                                                             \
         case TMv:                                                                                                 \
-            if (summary) return L.nt ? launch_mfma<TMv, true, true>(a, wp, c, M, H, V, L, sm, s)                  \
-                                     : launch_mfma<TMv, false, true>(a, wp, c, M, H, V, L, sm, s);                \
-            return L.nt ? launch_mfma<TMv, true, false>(a, wp, c, M, H, V, L, sm, s)                              \
-                        : launch_mfma<TMv, false, false>(a, wp, c, M, H, V, L, sm, s);
+            return summary ? launch_mfma<TMv, true>(a, wp, c, M, H, V, L, sm, s)                                  \
+                           : launch_mfma<TMv, false>(a, wp, c, M, H, V, L, sm, s);
         SPECV_MF(9) SPECV_MF(10) SPECV_MF(11) SPECV_MF(12) SPECV_MF(13) SPECV_MF(14) SPECV_MF(15) SPECV_MF(16)
 #undef SPECV_MF
         default: break;

@@ -83,3 +83,31 @@ def test_sampled_acceptance_of_small_batches(sv, oracle, V, B):
     got, ref = _accept_both(sv, oracle, logits, tokens.numpy(), dp.numpy(), temp, rng.integers(0, 2 ** 63, B, dtype=np.uint64), 9, qo, 3)
     _assert_same(got, ref, gammas)
     assert got["status"] == 0
+
+
+@pytest.mark.parametrize("V,H", [(2000, 256), (33000, 512), (70003, 256), (139281, 256)])
+@pytest.mark.parametrize("M", [161, 256, 257, 466])
+def test_large_tile_lm_head_passes(sv, oracle, M, V, H):
+    """More than 160 rows: a range of one short pass, of full passes before it (whole tiles stored without tests, their stores pending
+    over the next steps), passes of as few slabs as the ring has, rows of logits that start at odd multiples of 4 bytes, whole and ragged row
+    tiles.  Same order of additions as the weight-streaming kernel over row groups: same bits."""
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, H), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, H), generator=g, device="cuda").to(torch.bfloat16)
+    Wp = torch.empty(sv.spec_lm_head_packed_bytes(V, H) // 2, dtype=torch.bfloat16, device="cuda")
+    sv.spec_lm_head_pack(W, Wp)
+    logits = torch.full((M + 1, V), 7.0, device="cuda")
+    sv.spec_lm_head_packed(hidden, Wp, logits[:M])
+    rows = torch.tensor(sorted({0, 15, 16, M // 2, M - 17, M - 1}), device="cuda")
+    ref = oracle.lm_head(wl.bf16_bits(hidden[rows]), wl.bf16_bits(W))
+    err = np.abs(logits[rows].cpu().numpy() - ref).max()
+    assert err <= 1e-5 * math.sqrt(H) * np.abs(ref).max(), err
+    assert (logits[M] == 7.0).all()                        # nothing past the last row
+    sv.spec_set_tuning("lm_packed_tile", 1)
+    try:
+        other = torch.empty((M, V), device="cuda")
+        sv.spec_lm_head_packed(hidden, Wp, other)
+        torch.cuda.synchronize()
+    finally:
+        sv.spec_set_tuning("lm_packed_tile", 0)
+    assert torch.equal(other, logits[:M])
