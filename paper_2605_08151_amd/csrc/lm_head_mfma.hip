@@ -20,6 +20,7 @@
 // Per output element the products are added in the same order as in the other LM-head kernels (k ascending, one
 // fp32 accumulator), so the logits are bit-identical to theirs.
 #include "common.h"
+#include "lm_head_tiles.h"
 
 #include <type_traits>
 #include <utility>
@@ -28,9 +29,6 @@ namespace specv {
 
 constexpr int kMfSlab = 64;                    // k per slab
 constexpr int kMfPitch = kMfSlab * 2;          // bytes per hidden row in LDS; 16-byte chunk c of row r sits at c ^ ((r >> 1) & 7)
-constexpr int kMfWaves = 4;
-constexpr int kMfTN = 4;                       // panels (16 vocabulary entries each) per wave
-constexpr int kMfPassPanels = kMfWaves * kMfTN;
 constexpr int kMfRing = 4;                     // slabs in flight: hidden slabs in LDS = W slabs in registers
 constexpr int kMfPatchPitch = kMfTN * 64 + 16; // bytes per row of a wave's store patch
 
@@ -129,29 +127,29 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         lds_dma16_off(hoff[q], hsrc, hbuf + slot * kSlabBytes + (QN * wave + q) * 1024);
     };
 
-    // ---- W: the wave's panels of a pass, read through a buffer descriptor (base: the wave's first panel; size: its panels, so that
-    // slots past its share read zeros and cost no traffic) at a scalar stream position plus 16 bytes per lane:
-    // a request costs no vector address arithmetic.
-    // Passes are full (16 panels, 4 per wave) up to the last, which deals its 1..16 panels as evenly as they go.
+    // ---- W: the wave's panels of a pass, read through a buffer descriptor at its first panel, at a scalar position (panel slot and
+    // place in the stream) plus 16 bytes per lane: a request costs no vector address arithmetic.
     int wave_p0 = 0, wave_np = 0;
     auto pass_panels = [&](int pass, int& p0, int& np) SPECV_INLINE {
-        const int lo = p_begin + pass * kMfPassPanels;
-        const int m = min(kMfPassPanels, p_end - lo);
-        p0 = lo + wave * m / kMfWaves;
-        np = lo + (wave + 1) * m / kMfWaves - p0;      // 0 .. 4; p0 < p_end is a panel of the matrix either way
+        const PanelShare s = mf_panel_share(p_begin, p_end, pass, wave);
+        p0 = s.p0;
+        np = s.np;
     };
     const uint32_t panel_bytes = (uint32_t)H * 32u;
     const uint32_t woff = (uint32_t)lane * 16u;
     u32x4 wreg[RW][2][kMfTN];
     __amdgpu_buffer_rsrc_t wrsrc;
     uint32_t wpos = 0;                                // byte position of the slab that is requested next inside its panel
+    uint32_t wslot[kMfTN];                            // mf_slot_bytes of the wave's panel slots
     auto open_panels = [&](int p0, int np) SPECV_INLINE {
         const unsigned char* base = reinterpret_cast<const unsigned char*>(Wp) + (size_t)p0 * panel_bytes;
-        wrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (uint32_t)np * panel_bytes, 0x00020000);
+        wrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (uint32_t)max(np, 1) * panel_bytes, 0x00020000);
         wpos = 0;
+#pragma unroll
+        for (int tn = 0; tn < kMfTN; ++tn) wslot[tn] = mf_slot_bytes(np, tn, panel_bytes);
     };
     auto fetch_w1 = [&](int slot, int t, int tn) SPECV_INLINE {    // k-tile t of that slab, panel slot tn
-        wreg[slot][t][tn] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff, wpos + t * 1024 + tn * panel_bytes, 0);
+        wreg[slot][t][tn] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff, wpos + t * 1024 + wslot[tn], 0);
     };
 
     f32x4 acc[kMfTN][TM];
@@ -452,36 +450,13 @@ Tunable g_lm_packed_tile{0};   // benchmark hook: 0 = automatic (this kernel for
 Tunable g_lm_mfma_nt{0};       // benchmark hook: nontemporal logits stores, 0 = automatic (one or two row groups), 1 = always, 2 = never
 Tunable g_lm_mfma_rows{0};     // benchmark hook: rows per group of this kernel at most (144..256), 0 = automatic (256)
 
-// Row groups, panel ranges and the instantiation that serves them (host arithmetic, shared by the launch and by the
-// callers that size the block summaries).
-struct MfmaLayout { int groups, tiles_lo, groups_hi, tm, ranges, per_range, passes_per_range, blocks; bool nt; };
+static MfmaLayout mfma_layout(int M, int V) { return mfma_layout_for(M, V, device_cu_count(), g_lm_mfma_rows); }
 
-static MfmaLayout mfma_layout(int M, int V)
+// nontemporal stores of the logits: with one or two row groups
+static bool mfma_nt(const MfmaLayout& L)
 {
-    constexpr int kMaxTM = 16;
-    MfmaLayout L{};
-    // As few groups as 16 tiles each allow: the taller the tile, the fewer bytes go from L2 to the CUs per product.  Measured on MI355X
-    // (V = 151936, H = 4096), groups of at most 13 / at most 16 tiles: M = 480 576 / 520 us, M = 800 842 / 842, M = 1040 1087 / 1090,
-    // M = 1152 1206 / 1182 (the library GEMM of the image with bf16 output: 1377).
-    const int forced = g_lm_mfma_rows;
-    const int tiles = (M + 15) / 16;                                     // 16-row tiles of the batch
-    const int cap_tiles = forced >= 16 * 9 && forced <= 16 * kMaxTM ? forced / 16 : kMaxTM;
-    int groups = (tiles + cap_tiles - 1) / cap_tiles;
-    while (groups > 1 && (tiles + groups - 1) / groups < 9) --groups;    // the kernel is built for 9..16 tiles per group
-    L.groups = groups;
-    L.tiles_lo = tiles / groups; L.groups_hi = tiles % groups;           // groups of tiles_lo + 1 first, then of tiles_lo
-    L.tm = L.tiles_lo + (L.groups_hi ? 1 : 0);
-    const int nt_forced = g_lm_mfma_nt;
-    L.nt = nt_forced == 1 || (nt_forced == 0 && groups <= 2);
-    // panel ranges: as many as there are CUs per row group, a multiple of 8 (one per XCD and step of the dealing)
-    const int cus = device_cu_count();
-    const int n_panels = (V + 15) / 16;
-    const int r0 = max(8, cus / groups / 8 * 8);
-    L.per_range = (n_panels + r0 - 1) / r0;
-    L.ranges = ((n_panels + L.per_range - 1) / L.per_range + 7) / 8 * 8;
-    L.passes_per_range = (L.per_range + kMfPassPanels - 1) / kMfPassPanels;
-    L.blocks = L.ranges * L.passes_per_range * kMfWaves;
-    return L;
+    const int forced = g_lm_mfma_nt;
+    return forced == 1 || (forced == 0 && L.groups <= 2);
 }
 
 template <int TM, bool SUMMARY>
@@ -492,7 +467,7 @@ static int launch_mfma(const uint16_t* a, const uint16_t* wp, float* c, int M, i
     static LdsGrantTable granted = {};
     if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
     hipLaunchKernelGGL((lm_head_mfma_kernel<TM, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
-                       (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi, L.nt, sm);
+                       (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi, mfma_nt(L), sm);
     return SPEC_OK;
 }
 

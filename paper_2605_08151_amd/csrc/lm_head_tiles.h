@@ -1,0 +1,64 @@
+// Row groups, panel ranges and panel shares of the large-tile LM head (lm_head_mfma.hip), and which bytes of the packed matrix a wave
+// requests for them.  Integer arithmetic only, without device types: the kernel, its launch and a CPU test that walks whole matrices share it.
+#pragma once
+
+#include <cstdint>
+
+namespace specv {
+
+constexpr int kMfWaves = 4;                    // waves per workgroup
+constexpr int kMfTN = 4;                       // panels (16 vocabulary entries each) per wave
+constexpr int kMfPassPanels = kMfWaves * kMfTN;
+
+// Row groups, panel ranges and the instantiation that serves them.
+struct MfmaLayout { int groups, tiles_lo, groups_hi, tm, ranges, per_range, passes_per_range, blocks; };
+
+// cap_rows: rows per group at most (144..256; anything else = 256).
+constexpr MfmaLayout mfma_layout_for(int M, int V, int cus, int cap_rows)
+{
+    constexpr int kMaxTM = 16;
+    MfmaLayout L{};
+    // As few groups as 16 tiles each allow: the taller the tile, the fewer bytes go from L2 to the CUs per product.  Measured on MI355X
+    // (V = 151936, H = 4096), groups of at most 13 / at most 16 tiles: M = 480 576 / 520 us, M = 800 842 / 842, M = 1040 1087 / 1090,
+    // M = 1152 1206 / 1182 (the library GEMM of the image with bf16 output: 1377).
+    const int tiles = (M + 15) / 16;                                     // 16-row tiles of the batch
+    const int cap_tiles = cap_rows >= 16 * 9 && cap_rows <= 16 * kMaxTM ? cap_rows / 16 : kMaxTM;
+    int groups = (tiles + cap_tiles - 1) / cap_tiles;
+    while (groups > 1 && (tiles + groups - 1) / groups < 9) --groups;    // the kernel is built for 9..16 tiles per group
+    L.groups = groups;
+    L.tiles_lo = tiles / groups;                                         // groups of tiles_lo + 1 first, then of tiles_lo
+    L.groups_hi = tiles % groups;
+    L.tm = L.tiles_lo + (L.groups_hi ? 1 : 0);
+    // panel ranges: as many as there are CUs per row group, a multiple of 8 (one per XCD and step of the dealing)
+    const int n_panels = (V + 15) / 16;
+    const int per_xcd = cus / groups / 8;
+    const int r0 = per_xcd > 0 ? per_xcd * 8 : 8;
+    L.per_range = (n_panels + r0 - 1) / r0;
+    L.ranges = ((n_panels + L.per_range - 1) / L.per_range + 7) / 8 * 8;
+    L.passes_per_range = (L.per_range + kMfPassPanels - 1) / kMfPassPanels;
+    L.blocks = L.ranges * L.passes_per_range * kMfWaves;
+    return L;
+}
+
+struct PanelShare { int p0, np; };             // first panel and number of panels, 0 .. 4; p0 is a panel of the range also where np == 0
+
+// What wave `wave` owns in pass `pass` of the range [p_begin, p_end): passes are full (16 panels, 4 per wave) up to the last, which deals
+// its 1..16 panels as evenly as they go.
+constexpr PanelShare mf_panel_share(int p_begin, int p_end, int pass, int wave)
+{
+    const int lo = p_begin + pass * kMfPassPanels;
+    const int m = p_end - lo < kMfPassPanels ? p_end - lo : kMfPassPanels;
+    const int first = wave * m / kMfWaves;
+    return {lo + first, (wave + 1) * m / kMfWaves - first};
+}
+
+// Byte distance of panel slot tn from the wave's first panel.  A slot past the wave's share repeats its last panel (the L2 or the
+// L1 has it, its products are never stored), so that every request lies inside the matrix by its address alone: a buffer
+// descriptor's bounds check does not cover the scalar offset.
+constexpr uint32_t mf_slot_bytes(int np, int tn, uint32_t panel_bytes)
+{
+    const int last = np > 0 ? np - 1 : 0;
+    return (uint32_t)(tn < last ? tn : last) * panel_bytes;
+}
+
+}  // namespace specv
