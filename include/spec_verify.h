@@ -96,7 +96,8 @@ int spec_version(void);
  *   "lm_packed_tile"   which kernel spec_lm_head_packed runs for M > 160: 0 = automatic (the large-tile MFMA-bound
  *                      kernel), 1 = the weight-streaming kernel over row groups of at most 160 rows.
  *   "lm_mfma_rows"     rows per row group of that large-tile kernel at most, 144..256; 0 = automatic.
- *   "lm_mfma_nt"       its logits stores nontemporal: 0 = automatic (one or two row groups), 1 = always, 2 = never.
+ *   "lm_mfma_nt"       its logits stores nontemporal: 0 = automatic (at most 416 rows and V a multiple of 16), 1 = always,
+ *                      2 = never.
  * A forced kernel that cannot take the shape falls back to the plain tiled one.  Unknown key: SPEC_EINVAL. */
 int spec_set_tuning(const char* key, int value);
 

@@ -47,12 +47,13 @@ __device__ inline void lds_dma16_off(uint32_t off, const void* base, void* lds_b
     asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
 }
 
-// (SUMMARY instantiations also leave the block summaries described at LmSummary)
-template <int TM, bool SUMMARY>
+// NT: nontemporal stores of the logits (a template argument: of two stores in the branches of a flag the compiler makes one ordinary store);
+// SUMMARY instantiations also leave the block summaries described at LmSummary.
+template <int TM, bool NT, bool SUMMARY>
 __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
     int M_all, int H, int V, int n_panels, int panels_per_wg, int groups, int tiles_lo, int groups_hi,
-    bool nt, LmSummary sm)
+    LmSummary sm)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int RW = kMfRing;
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
                     for (int q = 0; q < 4; ++q) {
                         f32x4_any* d = reinterpret_cast<f32x4_any*>(dst + off);
                         if constexpr (RAGGED) d = reinterpret_cast<f32x4_any*>(C + (size_t)(tm * 16 + min(q * 4 + srow, last)) * V + (st_p0 * 16 + scol));
-                        if (nt) __builtin_nontemporal_store((f32x4_any)v[q], d); else *d = v[q];    // (wave-uniform)
+                        if constexpr (NT) __builtin_nontemporal_store((f32x4_any)v[q], d); else *d = v[q];
                         dst += row_step;
                     }
                     __builtin_amdgcn_sched_barrier(0);
@@ -401,7 +402,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
                     }
                     if (row < M && col_ok) {
                         f32x4_any* dst = reinterpret_cast<f32x4_any*>(reinterpret_cast<unsigned char*>(C) + off);
-                        if (nt) __builtin_nontemporal_store((f32x4_any)v, dst); else *dst = v;
+                        if constexpr (NT) __builtin_nontemporal_store((f32x4_any)v, dst); else *dst = v;
                     }
                     if (!SUMMARY && row < M && col_tail > 0) {          // the matrix ends inside these four entries
                         float* dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(C) + off);
@@ -447,27 +448,31 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
 }
 
 Tunable g_lm_packed_tile{0};   // benchmark hook: 0 = automatic (this kernel for M > 160), 1 = the weight-streaming kernel over row groups
-Tunable g_lm_mfma_nt{0};       // benchmark hook: nontemporal logits stores, 0 = automatic (one or two row groups), 1 = always, 2 = never
+Tunable g_lm_mfma_nt{0};       // benchmark hook: nontemporal logits stores, 0 = automatic (see mfma_nt), 1 = always, 2 = never
 Tunable g_lm_mfma_rows{0};     // benchmark hook: rows per group of this kernel at most (144..256), 0 = automatic (256)
 
 static MfmaLayout mfma_layout(int M, int V) { return mfma_layout_for(M, V, device_cu_count(), g_lm_mfma_rows); }
 
-// nontemporal stores of the logits: with one or two row groups
-static bool mfma_nt(const MfmaLayout& L)
+// Nontemporal stores of the logits: nobody reads them before the next kernel, and they do not push the weight stream out of the caches.  Up to 416
+// rows, where that stream bounds the kernel (ordinary -> nontemporal, V = 151936, H = 4096: M = 192 294 -> 270 us, M = 257 370 -> 358,
+// M = 416 448 -> 450; M = 512 519 -> 522), and only where every row starts on a multiple of 64 bytes: elsewhere rows share their first and
+// last lines with their neighbours, and such lines are written to HBM in parts (H = 1280, M = 320: V = 50020 48 -> 56 us, V = 50021 48 -> 57;
+// V = 50016 46.8 -> 47.7).
+static bool mfma_nt(int M, int V)
 {
     const int forced = g_lm_mfma_nt;
-    return forced == 1 || (forced == 0 && L.groups <= 2);
+    return forced == 1 || (forced == 0 && M <= 416 && V % 16 == 0);
 }
 
-template <int TM, bool SUMMARY>
+template <int TM, bool NT, bool SUMMARY>
 static int launch_mfma(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, LmSummary sm, hipStream_t s)
 {
     constexpr int SR = (TM * 16 + 31) / 32 * 32;
     const size_t smem = (size_t)kMfRing * SR * kMfPitch + (size_t)kMfWaves * 16 * kMfPatchPitch + (SUMMARY ? TM * 16 * 4 : 0);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
-    hipLaunchKernelGGL((lm_head_mfma_kernel<TM, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
-                       (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi, mfma_nt(L), sm);
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, NT, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
+    hipLaunchKernelGGL((lm_head_mfma_kernel<TM, NT, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
+                       (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi, sm);
     return SPEC_OK;
 }
 
@@ -493,11 +498,14 @@ int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M
             return fail(SPEC_ESHAPE, "spec_lm_head_packed_summary: no block summaries for M=%d H=%d V=%d (V must be a multiple of 4)", M, H, V);
         sm = *summary; sm.blocks = L.blocks; sm.passes_per_range = L.passes_per_range;
     }
+    const bool nt = mfma_nt(M, V);
     switch (L.tm) {
 #define SPECV_MF(TMv)                                                                                             \
         case TMv:                                                                                                 \
-            return summary ? launch_mfma<TMv, true>(a, wp, c, M, H, V, L, sm, s)                                  \
-                           : launch_mfma<TMv, false>(a, wp, c, M, H, V, L, sm, s);
+            if (summary) return nt ? launch_mfma<TMv, true, true>(a, wp, c, M, H, V, L, sm, s)                    \
+                                   : launch_mfma<TMv, false, true>(a, wp, c, M, H, V, L, sm, s);                  \
+            return nt ? launch_mfma<TMv, true, false>(a, wp, c, M, H, V, L, sm, s)                                \
+                      : launch_mfma<TMv, false, false>(a, wp, c, M, H, V, L, sm, s);
         SPECV_MF(9) SPECV_MF(10) SPECV_MF(11) SPECV_MF(12) SPECV_MF(13) SPECV_MF(14) SPECV_MF(15) SPECV_MF(16)
 #undef SPECV_MF
         default: break;
