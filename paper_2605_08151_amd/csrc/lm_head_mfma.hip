@@ -431,12 +431,14 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         // the tile is complete; the next pass's first slabs are already in flight
         stored = store_tile(pass, wave_p0, wave_np, four_c);
     };
-    for (; pass + 1 < npass; ++pass) {
+    const int full = mf_full_passes(p_begin, p_end, V);
+    while (pass < full) {
         one_pass(std::true_type{});
+        ++pass;
         wave_p0 = p0_next; wave_np = np_next;
-        pass_panels(min(pass + 2, npass - 1), p0_next, np_next);
+        pass_panels(min(pass + 1, npass - 1), p0_next, np_next);
     }
-    one_pass(std::false_type{});
+    if (pass < npass) one_pass(std::false_type{});
     if constexpr (SUMMARY) {                          // block slots of passes this range does not have
         if (group == 0)
             for (int b = npass * kMfWaves + tid; b < sm.passes_per_range * kMfWaves; b += 64 * kMfWaves) {

@@ -52,6 +52,14 @@ constexpr PanelShare mf_panel_share(int p_begin, int p_end, int pass, int wave)
     return {lo + first, (wave + 1) * m / kMfWaves - first};
 }
 
+// Passes of the range that the kernel's code for full ones serves: 16 panels, all their entries in the matrix.  All passes, where the panels divide
+// and the last one is not padded, else all but the last (V = 32000, H = 4096, one full pass per range: M = 257 69 -> 62 us, M = 416 92 -> 87
+// against its code for any number of panels, which tests the wave's share in every group).
+constexpr int mf_full_passes(int p_begin, int p_end, int V)
+{
+    return (p_end - p_begin - (p_end * 16 > V ? 1 : 0)) / kMfPassPanels;
+}
+
 // Byte distance of panel slot tn from the wave's first panel.  A slot past the wave's share repeats its last panel (the L2 or the
 // L1 has it, its products are never stored), so that every request lies inside the matrix by its address alone: a buffer
 // descriptor's bounds check does not cover the scalar offset.

@@ -31,10 +31,14 @@ static int walk(int M, int V, int H, int cus, int cap)
         if (p_begin >= p_end) continue;
         const int npass = (p_end - p_begin + kMfPassPanels - 1) / kMfPassPanels;
         CHECK(npass <= L.passes_per_range, "M=%d V=%d: %d passes", M, V, npass);
+        const int full = mf_full_passes(p_begin, p_end, V);
+        CHECK(full == npass || full == npass - 1, "M=%d V=%d range %d: %d full of %d passes", M, V, range, full, npass);
+        CHECK(full == npass || (p_end - p_begin) % kMfPassPanels != 0 || p_end * 16 > V, "M=%d V=%d range %d: the last pass is a full one", M, V, range);
         for (int pass = 0; pass < npass; ++pass)
             for (int wave = 0; wave < kMfWaves; ++wave) {
                 const PanelShare s = mf_panel_share(p_begin, p_end, pass, wave);
                 CHECK(s.np >= 0 && s.np <= kMfTN && s.p0 >= p_begin && s.p0 + s.np <= p_end && s.p0 < p_end, "M=%d V=%d range %d pass %d wave %d: panels %d + %d", M, V, range, pass, wave, s.p0, s.np);
+                if (pass < full) CHECK(s.np == kMfTN && (s.p0 + s.np) * 16 <= V, "M=%d V=%d range %d pass %d wave %d: not a full pass", M, V, range, pass, wave);
                 for (int k = 0; k < s.np; ++k) ++owner[s.p0 + k];
                 for (int tn = 0; tn < kMfTN; ++tn) {
                     // the requests of a slot cover one whole panel, slab by slab
@@ -64,7 +68,7 @@ int main()
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_every_request_of_the_vocabulary_matrix_lies_inside_it(tmp_path):
-    """Every panel is owned by one wave of one pass, and the bytes that any panel slot of any wave requests (slots past a wave's share
+    """Every panel is owned by one wave of one pass, a full pass has four panels per wave and no entry past the matrix, and the bytes that any panel slot of any wave requests (slots past a wave's share
     included) are bytes of the packed matrix."""
     src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
     src.write_text(PROGRAM)
