@@ -13,27 +13,53 @@ constexpr int kMfPassPanels = kMfWaves * kMfTN;
 // Row groups, panel ranges and the instantiation that serves them.
 struct MfmaLayout { int groups, tiles_lo, groups_hi, tm, ranges, per_range, passes_per_range, blocks; };
 
-// cap_rows: rows per group at most (144..256; anything else = 256).
+// Panels of a range when `groups` row groups share the CUs: as many ranges as there are CUs per group, a multiple of 8 (one per XCD and step of
+// the dealing).
+constexpr int mf_per_range(int n_panels, int groups, int cus)
+{
+    const int per_xcd = cus / groups / 8;
+    const int r0 = per_xcd > 0 ? per_xcd * 8 : 8;
+    return (n_panels + r0 - 1) / r0;
+}
+
+// Time of a workgroup in units of half a row tile's products for one panel per wave: a pass costs as many panel slots as its fullest wave owns
+// (two at least), each 2 tm + 11 (the products, and the operands and the epilogue that do not depend on the rows).
+constexpr long mf_group_cost(int tiles, int groups, int n_panels, int cus)
+{
+    const int per_range = mf_per_range(n_panels, groups, cus), tm = (tiles + groups - 1) / groups;
+    const int rest = per_range % kMfPassPanels, last = (rest + kMfWaves - 1) / kMfWaves;
+    const long slots = (long)(per_range / kMfPassPanels) * kMfTN + (rest == 0 ? 0 : (last > 2 ? last : 2));
+    return slots * (2 * tm + 11);
+}
+
+// cap_rows: rows per group at most (144..256); anything else = automatic.
 constexpr MfmaLayout mfma_layout_for(int M, int V, int cus, int cap_rows)
 {
-    constexpr int kMaxTM = 16;
+    constexpr int kMinTM = 9, kMaxTM = 16;                               // the kernel is built for 9..16 tiles per group
     MfmaLayout L{};
-    // As few groups as 16 tiles each allow: the taller the tile, the fewer bytes go from L2 to the CUs per product.  Measured on MI355X
-    // (V = 151936, H = 4096), groups of at most 13 / at most 16 tiles: M = 480 576 / 520 us, M = 800 842 / 842, M = 1040 1087 / 1090,
-    // M = 1152 1206 / 1182 (the library GEMM of the image with bf16 output: 1377).
     const int tiles = (M + 15) / 16;                                     // 16-row tiles of the batch
-    const int cap_tiles = cap_rows >= 16 * 9 && cap_rows <= 16 * kMaxTM ? cap_rows / 16 : kMaxTM;
+    const int n_panels = (V + 15) / 16;
+    const bool forced = cap_rows >= 16 * kMinTM && cap_rows <= 16 * kMaxTM;
+    const int cap_tiles = forced ? cap_rows / 16 : kMaxTM;
     int groups = (tiles + cap_tiles - 1) / cap_tiles;
-    while (groups > 1 && (tiles + groups - 1) / groups < 9) --groups;    // the kernel is built for 9..16 tiles per group
+    while (groups > 1 && (tiles + groups - 1) / groups < kMinTM) --groups;
+    // As few groups as 16 tiles each allow: the taller the tile, the fewer bytes go from L2 to the CUs per product.  Measured on MI355X
+    // (V = 151936, H = 4096), groups of at most 13 / at most 16 tiles: M = 480 576 / 506 us, M = 768 788 / 773, M = 1024 1035 / 1004,
+    // M = 1152 1164 / 1151.  One or two more where that leaves the last pass of every range, or CUs, much emptier: 3 / 4 groups at V = 32000,
+    // H = 4096 (25 panels a range, 16 + 9 / 32): M = 640 166 / 137 us, M = 768 190 / 154; V = 64000, H = 1280: M = 704 137 / 126.
+    if (!forced) {
+        long best = mf_group_cost(tiles, groups, n_panels, cus) * 97 / 100;
+        const int fewest = groups;
+        for (int g = fewest + 1; g <= fewest + 2 && (tiles + g - 1) / g >= kMinTM; ++g) {
+            const long cost = mf_group_cost(tiles, g, n_panels, cus);
+            if (cost < best) { best = cost; groups = g; }
+        }
+    }
     L.groups = groups;
     L.tiles_lo = tiles / groups;                                         // groups of tiles_lo + 1 first, then of tiles_lo
     L.groups_hi = tiles % groups;
     L.tm = L.tiles_lo + (L.groups_hi ? 1 : 0);
-    // panel ranges: as many as there are CUs per row group, a multiple of 8 (one per XCD and step of the dealing)
-    const int n_panels = (V + 15) / 16;
-    const int per_xcd = cus / groups / 8;
-    const int r0 = per_xcd > 0 ? per_xcd * 8 : 8;
-    L.per_range = (n_panels + r0 - 1) / r0;
+    L.per_range = mf_per_range(n_panels, groups, cus);
     L.ranges = ((n_panels + L.per_range - 1) / L.per_range + 7) / 8 * 8;
     L.passes_per_range = (L.per_range + kMfPassPanels - 1) / kMfPassPanels;
     L.blocks = L.ranges * L.passes_per_range * kMfWaves;

@@ -20,7 +20,7 @@ using namespace specv;
 static int walk(int M, int V, int H, int cus, int cap)
 {
     const MfmaLayout L = mfma_layout_for(M, V, cus, cap);
-    CHECK(L.tm >= 9 && L.tm <= 16, "M=%d: %d tiles per group", M, L.tm);
+    CHECK(L.tm >= 9 && L.tm <= 16 && L.tm - L.tiles_lo <= 1, "M=%d: %d tiles per group", M, L.tm);
     CHECK(16 * (L.groups * L.tiles_lo + L.groups_hi) >= M && 16 * (L.groups * L.tiles_lo + L.groups_hi) < M + 16, "M=%d: rows", M);
     const int n_panels = (V + 15) / 16;
     const uint32_t panel_bytes = (uint32_t)H * 32u;
@@ -53,9 +53,22 @@ static int walk(int M, int V, int H, int cus, int cap)
     return 0;
 }
 
+// one more group where fewer leave much of a range's last pass, or of the chip, without panels; else as few as 16 tiles each allow
+static int groups_chosen()
+{
+    const struct { int M, V, groups; } expected[] = {
+        {188, 151936, 1}, {576, 151936, 3}, {1152, 151936, 5}, {640, 32000, 4}, {768, 32000, 4}, {512, 32000, 2}, {704, 64000, 4}, {1600, 151936, 8}};
+    for (const auto& e : expected) {
+        const int g = mfma_layout_for(e.M, e.V, 256, 0).groups;
+        CHECK(g == e.groups, "M=%d V=%d: %d groups", e.M, e.V, g);
+    }
+    return 0;
+}
+
 int main()
 {
-    const int Ms[] = {161, 192, 208, 209, 256, 257, 416, 417, 466, 576, 1152, 1204, 4000};
+    if (groups_chosen()) return 1;
+    const int Ms[] = {161, 192, 208, 209, 256, 257, 416, 417, 466, 576, 640, 1152, 1204, 1600, 4000};
     const int Vs[] = {1, 5, 16, 17, 999, 2000, 4095, 8200, 32000, 33000, 50021, 70003, 139281, 151936, 151937};
     const int Hs[] = {256, 1280, 4096}, cuss[] = {8, 64, 256, 304}, caps[] = {0, 144, 208, 256};
     for (int M : Ms) for (int V : Vs) for (int H : Hs) for (int cus : cuss) for (int cap : caps)
