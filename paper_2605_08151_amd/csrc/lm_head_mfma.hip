@@ -222,8 +222,9 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     // for two groups, and the last groups read the first fragments of slab s+1: no step begins by waiting for LDS.
     // The accumulators are pinned to the accumulation registers by writing the MFMA as an asm statement; its operands are
     // ordinary values, so the compiler still inserts the waits for the W loads and the LDS reads.  It does not know that an MFMA must
-    // not follow a vector instruction that wrote its operand by less than 2 wait states; copies can only stand where two ways of the
-    // code meet, i.e. before the first step of a pass, whose MFMAs bring their own s_nop.  Those waits count W
+    // not follow a vector instruction that wrote its operand by less than 2 wait states.  Before the first step of a pass, where copies do stand,
+    // the MFMAs bring their own s_nop; that nothing else is in the way, around the branches for the last row tile and for panel slots above all, is
+    // checked on the built code by a test (s_nops at those branches too: M = 768, V = 32000, H = 4096 161 -> 164 us, M = 1152 263 -> 279).  Those waits count W
     // loads only (the direct loads are invisible to the compiler): a wait for a chunk requested 3.5 steps ago allows ~28
     // younger requests in flight, i.e. it covers requests at least 1.75 steps old, and a direct load is needed 2.5 steps
     // after it was issued: it is never what the math waits for.
@@ -241,7 +242,8 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
             if (tm < TM - 1 || full_tm) {             // wave-uniform
 #pragma unroll
                 for (int tn = 0; tn < kMfTN; ++tn) {
-                    if (!FOUR && tn >= kMfTN - 2 && tn >= wave_np) continue;    // wave-uniform: such a slot costs no MFMA
+                    // wave-uniform: slots 2 and 3 cost no MFMA where the wave does not own them (0 and 1 are always computed)
+                    if (!FOUR && tn >= kMfTN - 2 && tn >= wave_np) continue;
                     if constexpr (FIRST && t == 0)
                         asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
                     else
