@@ -18,6 +18,7 @@
 //   Every chunk writes an unnormalised fp32 partial (O, running max, sum); a second kernel merges the
 //   partials of a row in split order (deterministic) and writes bf16.
 #include "common.h"
+#include "kv_stream.h"
 
 #include <cmath>
 #include <type_traits>
@@ -55,7 +56,7 @@ struct AttnParams {
     float* part_l;      // [M*Hq, splits]
     int32_t* status_flags;
     // balanced work list written by verify_attn_plan_kernel (all null when requests are split by the fixed
-    // chunk_target instead): hdr = {items, keys per chunk}; req[i] = {splits of request i, first partial slot};
+    // chunk_target instead): hdr = {items, keys per chunk, K/V too large for the memory-side cache}; req[i] = {splits of request i, first partial slot};
     // items[k] = {request, split, splits of the request, first partial slot}
     const int32_t* parent;     // tree verification: row-local parent of every candidate row ([M], -1 for a root), or null = chains
     const int32_t* plan_hdr;
@@ -63,8 +64,33 @@ struct AttnParams {
     const int32_t* plan_items;
     int max_pages, num_pages, Hq, Hkv, G, M, max_kv_len, max_q_len, chunk_target, splits;
     float scale_log2e;
-    bool stream_kv;            // K/V pages by nontemporal loads (kMemorySideCache)
+    int B;
+    float stream_keys;         // committed keys of the batch above which its K/V is too large for the memory-side cache (0: it never is)
 };
+
+// The kernels with STREAM read a chunk's pages by nontemporal loads where kv_stream.h says so.  kv_scan leaves this wave's part of the scan in LDS;
+// after a barrier kv_streams combines the parts (the same answer in every wave).  The scan costs about 1 us of a short call (28.2 -> 29.2); the work
+// list's kernel knows the batch's total and spares it where that is small.
+struct KvScanPart { float keys; int shared; };
+
+template <int NW>
+__device__ inline void kv_scan(const AttnParams& p, int i, int page, KvScanPart* parts)
+{
+    const KvScan s = kv_scan_part(p.seq_lens, p.page_table, p.max_pages, p.B, p.max_kv_len, i, page, threadIdx.x, NW * 64);
+    const bool shared = __any(s.shared);
+    const float keys = four_rows_sum(row16_sum(s.keys));
+    if ((threadIdx.x & 63) == 0) parts[threadIdx.x >> 6] = {keys, shared};
+}
+
+template <int NW>
+__device__ inline bool kv_streams(const AttnParams& p, const KvScanPart* parts)
+{
+    float keys = 0.0f;
+    int shared = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { keys += parts[w].keys; shared |= parts[w].shared; }
+    return __builtin_amdgcn_readfirstlane(keys > p.stream_keys && !shared);
+}
 
 __device__ inline bool request_ok(int r0, int n, int c, const AttnParams& p)
 {
@@ -73,8 +99,8 @@ __device__ inline bool request_ok(int r0, int n, int c, const AttnParams& p)
 
 // NR: 16-row query tiles per (request, kv head); NW: waves per workgroup (each owns 32 keys of a step);
 // FINAL: no request is split, so the workgroup normalises and writes bf16 itself (no partials, no merge kernel).
-// NBUF: K/V buffers per wave (2 = the next step's pages are in flight while this step is computed).
-template <int NR, int NW, int NBUF, bool FINAL>
+// NBUF: K/V buffers per wave (2 = the next step's pages are in flight while this step is computed); STREAM: see kv_stream.h.
+template <int NR, int NW, int NBUF, bool FINAL, bool STREAM>
 __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
 {
     constexpr int kThreads = NW * 64;
@@ -86,9 +112,11 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     const int l16 = lane & 15, g = lane >> 4;
     const int kvh = blockIdx.y;
     int split, i, ns_plan = 0, pb_plan = 0;
+    bool scan = STREAM;
     if (p.plan_items) {
         // one workgroup per item of the balanced list; the grid is sized from a host bound
         if ((int)blockIdx.x >= p.plan_hdr[0]) return;
+        scan = STREAM && p.plan_hdr[2];
         const int* it = p.plan_items + 4 * (size_t)blockIdx.x;
         i = __builtin_amdgcn_readfirstlane(it[0]);
         split = __builtin_amdgcn_readfirstlane(it[1]);
@@ -125,12 +153,19 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     // queue as the direct K/V loads and force them to drain. ----
     int bad_page = 0;
     const int npages = (kend - kbeg + kP - 1) / kP;
+    __shared__ KvScanPart s_scan[STREAM ? NW : 1];
+    int page0 = 0;                                        // (requested together with what the scan looks at: one round trip)
+    if (STREAM && scan) {
+        if (tid < npages) page0 = pt[kbeg / kP + tid];
+        kv_scan<NW>(p, i, kbeg / kP, s_scan);
+    }
     for (int pg = tid; pg < npages; pg += kThreads) {
-        int page = pt[kbeg / kP + pg];
+        int page = STREAM && scan && pg == tid ? page0 : pt[kbeg / kP + pg];
         if (page < 0 || page >= p.num_pages) { page = 0; bad_page = 1; }
         sPT[pg] = page;
     }
     __syncthreads();
+    const bool stream_kv = STREAM && scan && kv_streams<STREAM ? NW : 1>(p, s_scan);
 
     // ---- this wave's two pages of a step, K and V, HBM -> LDS (always 16 direct loads: positions past the
     // range read page 0 instead, so the wait counts below are constants) ----
@@ -154,7 +189,7 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
         }
     };
     auto issue_step = [&](int wbase, unsigned char* buf) {
-        if (p.stream_kv) issue_pages(std::true_type{}, wbase, buf);
+        if (STREAM && stream_kv) issue_pages(std::true_type{}, wbase, buf);
         else issue_pages(std::false_type{}, wbase, buf);
     };
     const int wfirst = kbeg + wave * 32;
@@ -456,7 +491,7 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
 constexpr int kRowsStageBytes = kWaveLds;      // 32 K rows + 32 V rows
 
 // RING: K/V stages per workgroup in LDS (RING - 1 of them in flight while one is computed)
-template <int NW, bool FINAL, int RING>
+template <int NW, bool FINAL, int RING, bool STREAM>
 __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void verify_attn_rows_kernel(AttnParams p)
 {
     constexpr int kRowsStages = RING;
@@ -469,8 +504,10 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
     const int l16 = lane & 15, g = lane >> 4;
     const int kvh = blockIdx.y;
     int split, i, ns_plan = 0, pb_plan = 0;
+    bool scan = STREAM;
     if (p.plan_items) {
         if ((int)blockIdx.x >= p.plan_hdr[0]) return;
+        scan = STREAM && p.plan_hdr[2];
         const int* it = p.plan_items + 4 * (size_t)blockIdx.x;
         i = __builtin_amdgcn_readfirstlane(it[0]);
         split = __builtin_amdgcn_readfirstlane(it[1]);
@@ -519,6 +556,8 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
         if (row_ok) v = *reinterpret_cast<const u32x4*>(p.q + rowhead * kD + (s * 4 + g) * 8);
         qf[s] = __builtin_bit_cast(bf16x8, v);
     }
+    __shared__ KvScanPart s_scan[STREAM ? NW : 1];
+    if (STREAM && scan) kv_scan<NW>(p, i, kbeg / kP, s_scan);            // (its loads fly with those of Q)
     const bool tree = p.parent != nullptr;
     int limit = row_ok ? (tree ? kend : min(c + qj + 1, kend)) : 0;      // the row sees key positions t < limit
     // tree verification: bit a of anc is set iff candidate a is on this row's path to the root (a chain: all ones)
@@ -548,6 +587,7 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
         sAnc[r] = m;
     }
     __syncthreads();                                      // page ids and masks visible
+    const bool stream_kv = STREAM && scan && kv_streams<STREAM ? NW : 1>(p, s_scan);
     // The Q fragments came by ordinary loads.  The compiler cannot see the direct loads below (inline assembly), and with
     // some of them always in flight (rings deeper than two) it would make the loop wait for "all loads" at the first use
     // of a fragment in every stage, which serialises the ring (measured 230 against 187 us).  Waiting once here and handing
@@ -580,7 +620,7 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
         }
     };
     auto issue_stage = [&](int st) {
-        if (p.stream_kv) issue_stage_as(std::true_type{}, st);
+        if (STREAM && stream_kv) issue_stage_as(std::true_type{}, st);
         else issue_stage_as(std::false_type{}, st);
     };
     const int nst = (kend - kbeg + 31) >> 5;
@@ -822,6 +862,7 @@ __global__ __launch_bounds__(1024) void verify_attn_plan_kernel(AttnParams p, in
         const int total = item0 + a;
         hdr[0] = total < max_items ? total : max_items;
         hdr[1] = c;
+        hdr[2] = T > p.stream_keys;
     }
     if (tid == 0 && any_bad && p.status_flags) atomicOr(p.status_flags, SPEC_FLAG_BAD_LENGTH);
 }
@@ -982,15 +1023,21 @@ static size_t attn_smem_bytes(int NR, int NW, int NBUF, int chunk_keys)
     return tiles > epi ? tiles : epi;
 }
 
-template <int NR, int NW, int NBUF, bool FINAL>
-static int launch_attn_one(const AttnParams& p, dim3 grid, hipStream_t s)
+template <int NR, int NW, int NBUF, bool FINAL, bool STREAM>
+static int launch_attn_one_as(const AttnParams& p, dim3 grid, hipStream_t s)
 {
     const size_t smem = attn_smem_bytes(NR, NW, NBUF, p.chunk_target < p.max_kv_len ? p.chunk_target : p.max_kv_len);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&verify_attn_kernel<NR, NW, NBUF, FINAL>), smem, granted,
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&verify_attn_kernel<NR, NW, NBUF, FINAL, STREAM>), smem, granted,
                                     "spec_verify_attn")) return rc;
-    hipLaunchKernelGGL((verify_attn_kernel<NR, NW, NBUF, FINAL>), grid, dim3(NW * 64), smem, s, p);
+    hipLaunchKernelGGL((verify_attn_kernel<NR, NW, NBUF, FINAL, STREAM>), grid, dim3(NW * 64), smem, s, p);
     return SPEC_OK;
+}
+
+template <int NR, int NW, int NBUF, bool FINAL>
+static int launch_attn_one(const AttnParams& p, dim3 grid, hipStream_t s)
+{
+    return p.stream_keys > 0.0f ? launch_attn_one_as<NR, NW, NBUF, FINAL, true>(p, grid, s) : launch_attn_one_as<NR, NW, NBUF, FINAL, false>(p, grid, s);
 }
 
 Tunable g_attn_rows_ring{0};  // benchmark hook: K/V stages per workgroup of the row-split kernel, 2 or 4; 0 = automatic
@@ -1000,22 +1047,23 @@ static size_t attn_rows_smem_bytes(int chunk_keys, int ring)
     return (size_t)ring * kRowsStageBytes + (size_t)(chunk_keys / kP + 1) * 4 + 64 * 4 + 8 + 8 * 16 * 8;
 }
 
-template <int NW, bool FINAL, int RING>
+template <int NW, bool FINAL, int RING, bool STREAM>
 static int launch_attn_rows_ring(const AttnParams& p, dim3 grid, hipStream_t s)
 {
     const size_t smem = attn_rows_smem_bytes(p.chunk_target < p.max_kv_len ? p.chunk_target : p.max_kv_len, RING);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&verify_attn_rows_kernel<NW, FINAL, RING>), smem, granted,
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&verify_attn_rows_kernel<NW, FINAL, RING, STREAM>), smem, granted,
                                     "spec_verify_attn")) return rc;
-    hipLaunchKernelGGL((verify_attn_rows_kernel<NW, FINAL, RING>), grid, dim3(NW * 64), smem, s, p);
+    hipLaunchKernelGGL((verify_attn_rows_kernel<NW, FINAL, RING, STREAM>), grid, dim3(NW * 64), smem, s, p);
     return SPEC_OK;
 }
 
 template <int NW, bool FINAL>
 static int launch_attn_rows(const AttnParams& p, dim3 grid, hipStream_t s)
 {
-    if (g_attn_rows_ring == 4) return launch_attn_rows_ring<NW, FINAL, 4>(p, grid, s);
-    return launch_attn_rows_ring<NW, FINAL, 2>(p, grid, s);
+    if (p.stream_keys > 0.0f)
+        return g_attn_rows_ring == 4 ? launch_attn_rows_ring<NW, FINAL, 4, true>(p, grid, s) : launch_attn_rows_ring<NW, FINAL, 2, true>(p, grid, s);
+    return g_attn_rows_ring == 4 ? launch_attn_rows_ring<NW, FINAL, 4, false>(p, grid, s) : launch_attn_rows_ring<NW, FINAL, 2, false>(p, grid, s);
 }
 
 // (the row-split kernel folds the scale into its exponentials, which needs a positive, finite scale)
@@ -1117,9 +1165,10 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
     p.scale_log2e = scale * 1.4426950408889634f;
     p.plan_hdr = nullptr; p.plan_req = nullptr; p.plan_items = nullptr;
     p.parent = parent;
-    // Every page is read by one workgroup only.  Measured nontemporal against ordinary, main kernel: 64 requests x 8 kv heads x 1-4k keys
-    // (677 MB) 140 -> 124 us, 256 x 256..32768 keys (0.8 GB) 180 -> 164 us, 84 MB no difference; 4 requests of <= 512 keys (0.7 MB, cached) 15 against 17 us.
-    p.stream_kv = (size_t)B * max_kv_len * Hkv * (2 * kRowBytes) > kMemorySideCache * 3 / 4;
+    p.B = B;
+    // where not even the stated bounds exceed 3/4 of the memory-side cache, the kernels without the choice run (0)
+    const size_t cached_keys = kMemorySideCache * 3 / 4 / (2 * kRowBytes);
+    p.stream_keys = (size_t)B * max_kv_len * Hkv > cached_keys ? (float)cached_keys / (float)Hkv : 0.0f;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     const AttnPlanCfg pc = attn_plan_cfg(B, Hq, Hkv, max_kv_len, max_q_len, NR, p.chunk_target);

@@ -14,8 +14,8 @@ from test_gpu_parity import _accept_both, _assert_same, _close, _oracle_attn, _q
 
 @pytest.mark.parametrize("gammas,Hq", [((0,), 8), ((4,), 32), ((0, 3, 8), 64)], ids=["decode", "two_tiles", "row_split"])
 def test_attention_streaming_and_cached_loads(sv, oracle, gammas, Hq):
-    """K/V by nontemporal loads where the stated bound exceeds 3/4 of the memory-side cache (here 3 requests x 8 kv heads x 16384 keys),
-    by ordinary loads up to it.  The loads bring the same bytes: same bits on both sides of the line."""
+    """Where the stated bound exceeds 3/4 of the memory-side cache (here 3 requests x 8 kv heads x 16384 keys) the kernels look at the batch before
+    they choose how to load K/V, up to it they do not (this batch is a small one, ordinary loads).  Same bits on both sides of the line."""
     cfg = wl.VerifyConfig("stream", 71, 3, gammas, ("uniform", 200, 2500), Hq, 8, 64, 64, sigma_qkv=1.0)
     b = wl.make_batch(cfg, device="cuda", with_lm_head=False)
     table = torch.full((3, 1040), -1, dtype=torch.int32, device="cuda")
@@ -28,6 +28,40 @@ def test_attention_streaming_and_cached_loads(sv, oracle, gammas, Hq):
         assert int(step.status.cpu()) == 0
     assert torch.equal(outs[0], outs[1])
     _close(outs[1].float().cpu().numpy(), _oracle_attn(oracle, b), "stream", sharp=True)
+
+
+@pytest.mark.parametrize("gammas,Hq", [((0,), 8), ((4,), 32), ((0, 3, 8), 64)], ids=["decode", "two_tiles", "row_split"])
+def test_attention_over_more_keys_than_the_cache_holds(sv, oracle, gammas, Hq):
+    """3 requests x 8 kv heads x 16450..16800 keys (more than 3/4 of the memory-side cache: nontemporal loads), each also alone under the same
+    bounds (ordinary loads) and all with the first pages of request 0 mapped into the others (a common prefix: ordinary loads where it is
+    shared).  Same cuts, so same bits alone and together."""
+    cfg = wl.VerifyConfig("many_keys", 72, 3, gammas, ("uniform", 16450, 16800), Hq, 8, 64, 64, sigma_qkv=1.0)
+    b = wl.make_batch(cfg, device="cuda", with_lm_head=False)
+    assert int(b["seq_lens"].sum()) * 8 * 512 > 192 << 20
+    sv.spec_set_tuning("attn_plan", 2)
+    sv.spec_set_tuning("attn_chunk", 2048)
+    try:
+        step = _step(b, cfg)
+        together = step.attn(b["q"], b["k_cache"], b["v_cache"], b["page_table"], b["seq_lens"], b["qo_indptr"], b["scale"]).clone()
+        qo = b["qo_indptr"].cpu().numpy()
+        for i in range(3):
+            one = slice(qo[i], qo[i + 1])
+            out, status = torch.empty_like(b["q"][one]), torch.zeros(1, dtype=torch.int32, device="cuda")
+            sv.spec_verify_attn(b["q"][one], b["k_cache"], b["v_cache"], b["page_table"][i:i + 1], b["seq_lens"][i:i + 1],
+                                torch.tensor([0, qo[i + 1] - qo[i]], dtype=torch.int32, device="cuda"), out, None, b["max_kv_len"],
+                                b["gamma_max"] + 1, b["scale"], status, step.attn_ws)
+            assert torch.equal(out, together[one]) and int(status.cpu()) == 0
+        _close(together.float().cpu().numpy(), _oracle_attn(oracle, b), "many keys", sharp=True)
+        table = b["page_table"].clone()
+        table[1:, :300] = table[0, :300]
+        shared = dict(b, page_table=table)
+        out = step.attn(b["q"], b["k_cache"], b["v_cache"], table, b["seq_lens"], b["qo_indptr"], b["scale"])
+        assert torch.equal(out[:qo[1]], together[:qo[1]])
+        _close(out.float().cpu().numpy(), _oracle_attn(oracle, shared), "shared prefix", sharp=True)
+        assert int(step.status.cpu()) == 0
+    finally:
+        sv.spec_set_tuning("attn_plan", 0)
+        sv.spec_set_tuning("attn_chunk", 0)
 
 
 @pytest.mark.parametrize("M", [1, 37, 160])
