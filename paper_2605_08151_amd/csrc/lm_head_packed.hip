@@ -391,15 +391,17 @@ static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int
     return SPEC_OK;
 }
 
-// W is read once when one row group covers the batch: nontemporal if the matrix is larger than what several calls in a row would find in the
-// memory-side cache (measured, V = 151936, H = 4096, 1.24 GB: M = 5 207 -> 191 us, M = 40 223 -> 208 us; V = 50021, H = 1280, 128 MB: 33 -> 31.5;
-// V = 32000, H = 1024, 66 MB, called again and again: 14 with ordinary loads, 19 without).  With several row groups the others read it from the L2.
+// W is read once when one row group covers the batch: nontemporal if the matrix is larger than the memory-side cache by so much that a call finds
+// little of it there from the call before.  Measured back to back, ordinary -> nontemporal, us: 1.16 GiB (V = 151936, H = 4096) M = 5 207 -> 191,
+// M = 40 223 -> 208; 390 MiB (100000, 2048) M = 1 68 -> 62.5, M = 80 77 -> 75.5; 312 MiB (64000, 2560) 55 -> 51, 60 -> 57; 296 MiB (151936, 1024)
+// no difference; 281 MiB (36000, 4096) 45 -> 47, 52 -> 59; 195 MiB (100000, 1024) M = 40 34 -> 38.  After 2 GiB of other reads, when nothing is
+// found, the two differ by 3 % up to 288 MiB.  With several row groups the others read W from the L2.
 template <int TM, int RS, int NW, bool NT, int TN, bool STATS = false, bool ROWS = false>
 static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
                          float* blk_max = nullptr, int32_t* blk_arg = nullptr)
 {
     if constexpr (NT) {
-        if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8)
+        if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 9 / 8)
             return launch_packed_as<TM, RS, NW, NT, TN, STATS, true, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
     }
     return launch_packed_as<TM, RS, NW, NT, TN, STATS, false, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);

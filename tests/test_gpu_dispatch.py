@@ -67,7 +67,7 @@ def test_attention_over_more_keys_than_the_cache_holds(sv, oracle, gammas, Hq):
 @pytest.mark.parametrize("M", [1, 37, 160])
 @pytest.mark.parametrize("V", [196608, 196612, 196625])
 def test_packed_lm_head_streaming_and_cached_weights(sv, oracle, M, V):
-    """The vocabulary matrix by nontemporal loads above 3/8 of the memory-side cache (H = 256: more than 196608 entries)."""
+    """Large vocabularies of a short matrix, last panels of 1, 4 and 16 entries.  (Ordinary loads: the line of the nontemporal ones is below.)"""
     g = torch.Generator(device="cuda").manual_seed(V + M)
     hidden = torch.randn((M, 256), generator=g, device="cuda").to(torch.bfloat16)
     W = torch.randn((V, 256), generator=g, device="cuda").to(torch.bfloat16)
@@ -99,6 +99,31 @@ def test_row_major_lm_head_through_the_packed_kernel(sv, oracle, M, V):
     packed = torch.empty((M, V), device="cuda")
     sv.spec_lm_head_packed(hidden, Wp, packed)
     assert torch.equal(packed, logits[:M])
+
+
+def _both_layouts(sv, hidden, W):
+    """logits of the row-major and of the packed matrix"""
+    M, V, H = hidden.shape[0], W.shape[0], W.shape[1]
+    logits, packed = torch.full((M, V), 7.0, device="cuda"), torch.full((M, V), 7.0, device="cuda")
+    sv.spec_lm_head(hidden, W, logits)
+    Wp = torch.empty(sv.spec_lm_head_packed_bytes(V, H) // 2, dtype=torch.bfloat16, device="cuda")
+    sv.spec_lm_head_pack(W, Wp)
+    sv.spec_lm_head_packed(hidden, Wp, packed)
+    return logits, packed
+
+
+@pytest.mark.parametrize("M", [1, 80, 160])
+@pytest.mark.parametrize("V", [147456, 147457])
+def test_packed_lm_head_at_the_line_of_its_nontemporal_loads(sv, oracle, M, V):
+    """The vocabulary matrix by nontemporal loads above 9/8 of the memory-side cache (H = 1024: more than 147456 entries)."""
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, 1024), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, 1024), generator=g, device="cuda").to(torch.bfloat16)
+    logits, packed = _both_layouts(sv, hidden, W)
+    rows = torch.tensor(sorted({0, M // 2, M - 1}), device="cuda")
+    ref = oracle.lm_head(wl.bf16_bits(hidden[rows]), wl.bf16_bits(W))
+    assert np.abs(packed[rows].cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(1024) * np.abs(ref).max()
+    assert torch.equal(packed, logits)
 
 
 @pytest.mark.parametrize("V,B", [(1, 3), (4095, 5), (4096, 5), (4097, 5), (8193, 5), (50021, 7), (50021, 60)])
