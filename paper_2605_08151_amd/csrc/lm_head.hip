@@ -619,10 +619,12 @@ static int launch_big2(const uint16_t* a, const uint16_t* w, float* c, int M, in
 }
 
 Tunable g_lm_kernel_waves{8};  // benchmark hook: waves per workgroup of the MFMA-bound kernel (4 or 8)
-Tunable g_lm_kernel{0};   // benchmark hook: 0 = automatic, 1 = weight-streaming, 2 = MFMA-bound with direct loads, 3 = plain tiled,
-                       // 8 = MFMA-bound with register staging (the automatic choice for M > 160),
-                       // 4 = weight-streaming with 8 waves (4 x 2) and a 2-slab ring, 5/6/7 = 4 waves with
-                       // 4-slab ring / 4-slab ring + paired refills / 2-slab ring + paired refills (the default)
+// benchmark hook: 0 = automatic, 1 = weight-streaming (this file's), 2 = MFMA-bound with direct loads, 3 = plain tiled, 8 = MFMA-bound with
+// register staging (the automatic choice for M > 160), 4 = weight-streaming with 8 waves (4 x 2) and a 2-slab ring, 5/6/7 = 4 waves with
+// 4-slab ring / 4-slab ring + paired refills / 2-slab ring + paired refills (what 0 and 1 run).
+// For M <= 160 the automatic choice is lm_head_rows_dispatch (lm_head_packed.hip) where that takes the shape; this file's weight-streaming kernel
+// serves the smaller vocabularies, and spec_lm_head_stats.
+Tunable g_lm_kernel{0};
 
 // vocabulary entries per workgroup and the grid of the weight-streaming kernel
 static void skinny_geometry(int V, int* cols, int* grid)

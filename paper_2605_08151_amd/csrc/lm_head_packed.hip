@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void lm_head_pack_kernel(const uint16_t* __res
 //     row, 128 or 256 bytes).  With one or two row groups they are stored nontemporal (nobody reads them before the
 //     next kernel; 263 against 280 us at M = 160); with many groups the L2 absorbs the writes better (1351 against
 //     1504 us at M = 1152).
-// TM: 16-row tiles of hidden per row group (rows <= 16 TM); RS: slabs in the W register ring (1 in every launch: 2
+// TM: 16-row tiles of hidden per row group (rows <= 16 TM); RS: slabs in the W register ring (1, or 2 with 4 waves of 2 panels: with 8 waves 2
 // measured 5 us slower at M = 160 and equal above); NW: waves (4 or 8); NT: nontemporal stores of the logits;
 // TN: panels per wave and pass (2 or 4: a pass is 16 NW TN entries wide);
 // ROWS: W row-major instead of packed: a load takes 128 bytes of 8 rows (whole lines) and weave_rows makes operands of two of them;
@@ -396,12 +396,14 @@ static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int
 // M = 40 223 -> 208; 390 MiB (100000, 2048) M = 1 68 -> 62.5, M = 80 77 -> 75.5; 312 MiB (64000, 2560) 55 -> 51, 60 -> 57; 296 MiB (151936, 1024)
 // no difference; 281 MiB (36000, 4096) 45 -> 47, 52 -> 59; 195 MiB (100000, 1024) M = 40 34 -> 38.  After 2 GiB of other reads, when nothing is
 // found, the two differ by 3 % up to 288 MiB.  With several row groups the others read W from the L2.
+// Row-major, only where rows lie a multiple of 4 KB apart (V = 151936 / 100000, M = 1: H = 4096 213 -> 204 / 150 -> 141, H = 2048 130 -> 128 /
+// 78 -> 73; but H = 2560 137 -> 142 / 93 -> 96, H = 5120 268 -> 273 / 177 -> 182).
 template <int TM, int RS, int NW, bool NT, int TN, bool STATS = false, bool ROWS = false>
 static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
                          float* blk_max = nullptr, int32_t* blk_arg = nullptr)
 {
     if constexpr (NT) {
-        if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 9 / 8)
+        if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 9 / 8 && (!ROWS || H % 2048 == 0))
             return launch_packed_as<TM, RS, NW, NT, TN, STATS, true, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
     }
     return launch_packed_as<TM, RS, NW, NT, TN, STATS, false, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
@@ -409,14 +411,15 @@ static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M,
 
 // A vocabulary of at most 8 panels per CU (V <= 32768 on 256 CUs) is one pass of 4 waves with 2 panels each and a 2-slab ring; 8 waves would have one
 // panel each, their second slot re-reading it, and twice the LDS reads per panel.  Measured at V = 32000, 8 against 4 waves: H = 4096
-// M = 40 51.6 -> 47.8 us, M = 160 70 -> 60; H = 2048 M = 96 35.3 -> 32.6; row-major H = 4096 M = 5 64.6 -> 48.0, M = 160 89 -> 65.
+// M = 40 51.6 -> 47.8 us, M = 160 70 -> 60; H = 2048 M = 96 35.3 -> 32.6; row-major H = 4096 M = 80 74 -> 48, M = 160 87 -> 61.
 // With more panels 8 waves are ahead (V = 50021, H = 1280, M = 40: 27.5 against 30.5).
-static bool few_panels(int V)
+static int panels_per_cu(int V)
 {
     int ranges, per_range;
     packed_geometry(V, 1, &ranges, &per_range);
-    return per_range <= 8;
+    return per_range;
 }
+static bool few_panels(int V) { return panels_per_cu(V) <= 8; }
 
 template <int TM>
 static int launch_packed_auto(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
@@ -441,13 +444,19 @@ static int launch_rows(const uint16_t* a, const uint16_t* w, float* c, int M, in
     return launch_packed<TM, 1, 8, true, 2, false, true>(a, w, c, M, H, V, 1, s);
 }
 
-// The same kernel on a row-major matrix, for spec_lm_head (M <= 160, H a multiple of 256).  Returns false if it does not take the shape.
-// Measured (V = 151936, H = 4096) against the 4-wave kernel of lm_head.hip, whose passes are half as wide: M = 5 227 -> 201 us,
-// M = 40 249 -> 218, M = 128 309 -> 278, M = 160 329 -> 298; V = 50021, H = 1280 (no whole quads to store) M = 96 45.1 -> 42.3.
+// The same kernel on a row-major matrix, for spec_lm_head (M <= 160, H a multiple of 256).  Returns false if it does not take the shape: the 4-wave
+// kernel of lm_head.hip, whose passes are half as wide, serves it then.
+// That one splits a small vocabulary over more waves, and with few rows over more workgroups.  Measured against it (4-wave -> this, us):
+//   12 panels per CU and more: V = 151936, H = 4096 M = 5 227 -> 201, M = 40 249 -> 218, M = 128 309 -> 278, M = 160 329 -> 298;
+//     V = 49152 M = 1 H = 1024 20.9 -> 20.2, H = 2048 33.9 -> 34.8, H = 4096 76 -> 74, M = 160 33.9 -> 29.7, 54.8 -> 48.2, 116 -> 97
+//   8 to 11: M = 80 V = 32768 H = 2048 26.1 -> 25.5, H = 4096 51.7 -> 48.9, V = 34000 39.3 -> 38.6, 78 -> 74, M = 160 51.7 -> 44.1, 104 -> 88; but
+//     M = 1 V = 32768 H = 2048 22.6 -> 24.1, V = 34000 29.1 -> 33.4, V = 40960 31.1 -> 33.9
+//   fewer: V = 24576 H = 2048 M = 1 18.9 -> 20.3, M = 160 28.9 -> 31.7; V = 16000, H = 1024 8.8 -> 11.6, 17.0 -> 19.0; V = 2000, H = 4096 21.9 -> 33.4
 // Reading 64 bytes of each of 16 rows instead (no weaving, ordinary loads) costs the same from M = 96 on, and 222 against 199 us at M = 5.
 bool lm_head_rows_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc)
 {
     if (M > kPkMaxRows || H % (2 * kPkSlab) != 0 || (size_t)V > ((size_t)1 << 32) / (4 * (size_t)(kPkMaxRows + 16))) return false;
+    if (panels_per_cu(V) < (M <= 64 ? 12 : 8)) return false;
     switch ((M + 15) / 16) {
         case 1: case 2: *rc = launch_rows<2>(a, w, c, M, H, V, s); break;
         case 3: case 4: *rc = launch_rows<4>(a, w, c, M, H, V, s); break;

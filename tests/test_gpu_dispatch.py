@@ -112,6 +112,34 @@ def _both_layouts(sv, hidden, W):
     return logits, packed
 
 
+@pytest.mark.parametrize("M", [1, 64, 65, 160])
+@pytest.mark.parametrize("V", [28672, 28673, 45056, 45057])
+def test_row_major_lm_head_at_the_lines_of_its_routes(sv, oracle, M, V):
+    """7 and 8, 11 and 12 panels per CU (of 256), up to 64 rows and more: the 4-wave kernel on one side, the packed kernel's row-major form on the other."""
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, 256), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, 256), generator=g, device="cuda").to(torch.bfloat16)
+    logits, packed = _both_layouts(sv, hidden, W)
+    ref = oracle.lm_head(wl.bf16_bits(hidden), wl.bf16_bits(W))
+    assert np.abs(logits.cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(256) * np.abs(ref).max()
+    assert torch.equal(packed, logits)
+
+
+@pytest.mark.parametrize("M", [5, 80, 160])
+@pytest.mark.parametrize("V,H", [(32000, 4864), (32767, 6144)])
+def test_few_panels_and_a_matrix_beyond_the_cache(sv, oracle, V, H, M):
+    """At most 8 panels per CU (4 waves, two slabs in the ring) and nontemporal weights: packed, and row-major where H is a multiple of 2048."""
+    assert V * H * 2 > 288 << 20
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, H), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, H), generator=g, device="cuda").to(torch.bfloat16)
+    logits, packed = _both_layouts(sv, hidden, W)
+    rows = torch.tensor(sorted({0, M // 2, M - 1}), device="cuda")
+    ref = oracle.lm_head(wl.bf16_bits(hidden[rows]), wl.bf16_bits(W))
+    assert np.abs(logits[rows].cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(H) * np.abs(ref).max()
+    assert torch.equal(packed, logits)
+
+
 @pytest.mark.parametrize("M", [1, 80, 160])
 @pytest.mark.parametrize("V", [147456, 147457])
 def test_packed_lm_head_at_the_line_of_its_nontemporal_loads(sv, oracle, M, V):
