@@ -81,7 +81,7 @@ int spec_version(void);
  *                      17..48 rows.
  *   "attn_rows_ring"   K/V stages (32 keys each) a workgroup of that kernel keeps in LDS: 2 (default) or 4.
  *   "accept_filter"    how spec_accept normalises the rows of sampled requests: 0 = automatic (2 for at most 8 Mi
- *                      logits, 1 above); 1 = fp32 sums over every row, an interval test, and fp64 sums only on the
+ *                      logits in at most 4096 rows, 1 above); 1 = fp32 sums over every row, an interval test, and fp64 sums only on the
  *                      row a bonus token is drawn from and on rows whose test the interval leaves open; 2 = fp64
  *                      sums over every row; 3 = as 1 with an interval so wide that most tests take the fp64 path (a
  *                      test hook).  Same integers in all.

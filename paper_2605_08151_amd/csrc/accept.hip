@@ -28,7 +28,11 @@ constexpr int kSeg = 4096;          // logits per segment
 constexpr int kThreads = 256;
 constexpr int kPerThread = kSeg / kThreads;   // 16
 constexpr int kMaxRows = 64;        // gamma_max + 1 <= 64
-constexpr size_t kFp64Entries = (size_t)8 << 20;   // M * V up to which every row of a sampled request is summed in fp64
+// Batches of which every row of a sampled request is summed in fp64 and whose decision is taken inside the residual launch: at most so many logits, and
+// so many rows (the decision's 4 waves per request are not enough for thousands of rows of a small vocabulary: V = 1000, 512 requests
+// x 16 rows 60 us with the launches apart, 66.5 in one; 256 x 16 44.5 / 44.7; 512 x 9 51.2 / 51.0; 512 x 5 45.4 / 40.5).
+constexpr size_t kFp64Entries = (size_t)8 << 20;
+constexpr int kFp64Rows = 4096;
 constexpr int kPickLds = 512;       // segment sums staged in LDS by the pick kernel (V <= 2M entries)
 
 // benchmark / test hook: 0 = automatic (on), 1 = on, 2 = off (fp64 sums over every row), 3 = on with an interval so wide
@@ -1048,7 +1052,7 @@ static int accept_impl(const float* logits, const int32_t* tokens, const float* 
     // the bonus is drawn from (and on rows whose test the interval leaves open); or fp64 sums over every row, which for a small batch cost
     // less (0.5 us per million entries) than the launch that sums the bonus rows (5 us).
     const int filter_mode = g_accept_filter;
-    const bool small = (size_t)M * V <= (size_t)kFp64Entries;
+    const bool small = (size_t)M * V <= kFp64Entries && M <= kFp64Rows;
     const bool filter = seeds != nullptr && ((filter_mode != 2 && !(filter_mode == 0 && small)) || sum.blocks > 0);   // block sums are estimates: the interval test is needed
     const float band = !filter ? 0.0f : (filter_mode == 3 ? 0.25f : 6.103515625e-05f);   // 2^-14; 0.25 leaves most tests open
     DecideArgs d{};

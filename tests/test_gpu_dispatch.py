@@ -154,10 +154,10 @@ def test_packed_lm_head_at_the_line_of_its_nontemporal_loads(sv, oracle, M, V):
     assert torch.equal(packed, logits)
 
 
-@pytest.mark.parametrize("V,B", [(1, 3), (4095, 5), (4096, 5), (4097, 5), (8193, 5), (50021, 7), (50021, 60)])
+@pytest.mark.parametrize("V,B", [(1, 3), (4095, 5), (4096, 5), (4097, 5), (8193, 5), (50021, 7), (50021, 60), (300, 1366), (300, 1367)])
 def test_sampled_acceptance_of_small_batches(sv, oracle, V, B):
-    """Up to 8 Mi logits every row is summed in fp64 and the decision is taken by every workgroup of the residual launch (the last pair of sizes is
-    just beyond: 240 rows x 50021).  Rows that start at odd multiples of 4 bytes, last segments of 1, 4095 and 4096 entries."""
+    """Up to 8 Mi logits every row is summed in fp64 and the decision is taken by every workgroup of the residual launch (180 rows x 50021
+    are just beyond), in up to 4096 rows (1366 requests have 4096, 1367 have 4100).  Rows that start at odd multiples of 4 bytes, last segments of 1, 4095 and 4096 entries."""
     rng = np.random.default_rng(V + B)
     gammas = np.full(B, 3)
     gammas[::3] = 0
