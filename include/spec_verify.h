@@ -91,7 +91,8 @@ int spec_version(void);
  *                      tiled, 4..7 = variants of 1 (wave count / register-ring depth; 7 = 1), 8 = MFMA-bound with
  *                      register staging.
  *   "lm_big_waves"     waves per workgroup of the MFMA-bound kernels of spec_lm_head: 4 or 8 (default).
- *   "lm_packed_waves"  waves per workgroup of the weight-streaming kernel of spec_lm_head_packed: 4 or 8 (default).
+ *   "lm_packed_waves"  waves per workgroup of the weight-streaming kernel of spec_lm_head_packed: 4 or 8; 0 = automatic (8, or
+ *                      4 of half the width where a CU has at most 8 panels of 16 entries).
  *   "lm_packed_wide"   that kernel with passes of 512 vocabulary entries over row groups of at most 80 rows:
  *                      0 = automatic (off), 1 = always, 2 = never.
  *   "lm_packed_tile"   which kernel spec_lm_head_packed runs for M > 160: 0 = automatic (the large-tile MFMA-bound

@@ -39,7 +39,7 @@ extern "C" int spec_version(void) { return 1000; }
 //   "lm_big_waves"  waves per workgroup of its MFMA-bound kernels (4 or 8)
 //   "attn_plan"   balanced work list of spec_verify_attn: 0 = automatic, 1 = always, 2 = never
 //   "attn_plan_waves"  work items per CU the list aims at (0 = automatic)
-//   "lm_packed_waves"  waves per workgroup of spec_lm_head_packed (4 or 8)
+//   "lm_packed_waves"  waves per workgroup of spec_lm_head_packed (4 or 8; 0 = automatic)
 extern "C" int spec_set_tuning(const char* key, int value)
 {
     if (key && std::strcmp(key, "attn_chunk") == 0) { specv::g_attn_chunk_override = value; return SPEC_OK; }
@@ -55,7 +55,7 @@ extern "C" int spec_set_tuning(const char* key, int value)
     if (key && std::strcmp(key, "lm_packed_tile") == 0) { specv::g_lm_packed_tile = value; return SPEC_OK; }
     if (key && std::strcmp(key, "lm_mfma_nt") == 0) { specv::g_lm_mfma_nt = value; return SPEC_OK; }
     if (key && std::strcmp(key, "lm_mfma_rows") == 0) { specv::g_lm_mfma_rows = value; return SPEC_OK; }
-    if (key && std::strcmp(key, "lm_packed_waves") == 0) { specv::g_lm_packed_waves = value == 4 ? 4 : 8; return SPEC_OK; }
+    if (key && std::strcmp(key, "lm_packed_waves") == 0) { specv::g_lm_packed_waves = value == 4 || value == 8 ? value : 0; return SPEC_OK; }
     return specv::fail(SPEC_EINVAL, "spec_set_tuning: unknown key '%s'", key ? key : "(null)");
 }
 

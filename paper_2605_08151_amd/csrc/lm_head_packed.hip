@@ -361,7 +361,7 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
 }
 
 Tunable g_lm_packed_wide{0};      // benchmark hook: 512-entry passes for M <= 160 (0 = automatic, 1 = always, 2 = never)
-Tunable g_lm_packed_waves{8};     // benchmark hook: waves per workgroup of the packed kernel (4 or 8)
+Tunable g_lm_packed_waves{0};     // benchmark hook: waves per workgroup of the packed kernel (4 or 8; 0 = automatic)
 
 // panel ranges and panels per range of a launch: ranges is a multiple of 8 (one per XCD and step of the dealing), as many
 // as there are CUs per row group; trailing ranges without panels are dropped 8 at a time
@@ -433,7 +433,7 @@ static int launch_packed_auto(const uint16_t* a, const uint16_t* wp, float* c, i
     // W ring is 5 us slower with either); at M = 40 both take 218 us; at M = 576 and 1152 8 waves are 5 % ahead
     if (g_lm_packed_waves == 4) return launch_packed<TM, 1, 4, true, 4>(a, wp, c, M, H, V, groups, s);
     if (groups > 2) return launch_packed<TM, 1, 8, false, 2>(a, wp, c, M, H, V, groups, s);
-    if (groups == 1 && few_panels(V)) return launch_packed<TM, 2, 4, true, 2>(a, wp, c, M, H, V, groups, s);
+    if (groups == 1 && g_lm_packed_waves != 8 && few_panels(V)) return launch_packed<TM, 2, 4, true, 2>(a, wp, c, M, H, V, groups, s);
     return launch_packed<TM, 1, 8, true, 2>(a, wp, c, M, H, V, groups, s);
 }
 
@@ -529,7 +529,7 @@ static int lm_head_packed_any(const char* who, const void* hidden, const void* W
     int rc;
     // Groups of at most 80 rows leave registers for 4 panels per wave: a pass is 512 entries wide, which halves the LDS
     // reads per MFMA and quarters the re-reads of hidden, at the price of W crossing L2 -> CU twice as often.
-    if (!blk_max && g_lm_packed_wide == 1 && g_lm_packed_waves == 8) {
+    if (!blk_max && g_lm_packed_wide == 1 && g_lm_packed_waves != 4) {
         groups = (M + kPkMaxRows / 2 - 1) / (kPkMaxRows / 2);
         tm = ((M + groups - 1) / groups + 15) / 16;                     // 1 .. 5
         if (groups > 2) rc = launch_packed<5, 1, 8, false, 4>(a, wp, logits, M, H, V, groups, s);

@@ -138,6 +138,12 @@ def test_few_panels_and_a_matrix_beyond_the_cache(sv, oracle, V, H, M):
     ref = oracle.lm_head(wl.bf16_bits(hidden[rows]), wl.bf16_bits(W))
     assert np.abs(logits[rows].cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(H) * np.abs(ref).max()
     assert torch.equal(packed, logits)
+    try:
+        for waves in (4, 8):
+            sv.spec_set_tuning("lm_packed_waves", waves)
+            assert torch.equal(_both_layouts(sv, hidden, W)[1], logits)
+    finally:
+        sv.spec_set_tuning("lm_packed_waves", 0)
 
 
 @pytest.mark.parametrize("M", [1, 80, 160])
