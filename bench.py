@@ -9,7 +9,7 @@ tokens/s (sum of accepted drafts + bonus tokens per wall-clock second) on the na
 hybrid ordinary-parallel mix, the largest one), the roofline figures of the dominant kernel measured with HIP
 events on the launch stream, per-call timings, the ceilings two probes measure on this chip (linear read, MFMA-only
 loop), short runs of the other workloads (`per_config`), and the CPU oracle timed on a bounded sample of the same
-workload on this box's host cores.
+workload on this machine's host cores.
 
 Other modes (no step is timed):
     python bench.py --peaks                      only the two probes, one JSON line
@@ -41,7 +41,7 @@ KERNEL_OF_CALL = {
     ("verify_attn", True): ("verify_attn_rows_kernel", "verify_attn_kernel"),
     ("verify_attn", False): ("verify_attn_rows_kernel", "verify_attn_kernel"),
     ("lm_head", True): ("lm_head_mfma_kernel", "lm_head_packed_kernel"),
-    ("lm_head", False): ("lm_head_big2_kernel", "lm_head_big_kernel", "lm_head_skinny_kernel", "lm_head_tiled_kernel"),
+    ("lm_head", False): ("lm_head_big2_kernel", "lm_head_big_kernel", "lm_head_packed_kernel(row-major)", "lm_head_skinny_kernel", "lm_head_tiled_kernel"),
     ("accept", True): ("accept_row_stats_kernel",), ("accept", False): ("accept_row_stats_kernel",),
     ("kv_commit", True): ("kv_commit_kernel",), ("kv_commit", False): ("kv_commit_kernel",),
 }
@@ -102,9 +102,16 @@ def algorithmic(cfg, b):
 
 
 def short_kernel_name(full: str) -> str:
-    """'void specv::lm_head_packed_kernel<10, 1, ...>(...)' -> 'lm_head_packed_kernel'"""
-    s = full.replace("void ", "").split("(")[0].split("<")[0]
-    return s.split("::")[-1].strip()
+    """'void specv::lm_head_mfma_kernel<13, false, false>(...)' -> 'lm_head_mfma_kernel'; instantiations that do different work in one run are
+    told apart: the packed LM head kernel on a row-major matrix, and the sums of exponentials before the residual sums of acceptance."""
+    s = full.replace("void ", "").split("(")[0]
+    name, _, args = s.partition("<")
+    name, args = name.split("::")[-1].strip(), [a.strip() for a in args.rstrip(">").split(",")]
+    if name == "lm_head_packed_kernel" and args[-1] == "true":
+        return name + "(row-major)"
+    if name == "accept_bonus_kernel":
+        return name + ("(exponentials)" if args[-1] == "true" else "(residual)")
+    return name
 
 
 def load_traffic(cfg_name, call, packed):
@@ -448,7 +455,7 @@ def cpu_model():
 
 
 def cpu_baseline(cfg, b, step, tokens, draft_probs, seeds, emitted_per_step, budget_s=8.0):
-    """Times the oracle as it stands on this box's host cores.  Each stage first runs on a small probe, then on
+    """Times the oracle as it stands on this machine's host cores.  Each stage first runs on a small probe, then on
     the largest slice of the real workload that the probe says fits ~budget_s seconds (the whole stage if it
     fits), and is extrapolated linearly to full size."""
     import numpy as np
@@ -524,11 +531,11 @@ def _algorithmic_by_kernel(cfg_name):
     alg = algorithmic(cfg, b)
     n_stoch = int((b["temperature"] > 0).sum())
     return {"verify_attn_kernel": alg["attn_bytes"] / 1e6, "verify_attn_rows_kernel": alg["attn_bytes"] / 1e6,
-            "lm_head_packed_kernel": alg["lm_bytes"] / 1e6,
+            "lm_head_packed_kernel": alg["lm_bytes"] / 1e6, "lm_head_packed_kernel(row-major)": alg["lm_bytes"] / 1e6,
             "lm_head_mfma_kernel": alg["lm_bytes"] / 1e6, "lm_head_big2_kernel": alg["lm_bytes"] / 1e6,
             "lm_head_skinny_kernel": alg["lm_bytes"] / 1e6,
             "accept_row_stats_kernel": b["M"] * cfg.V * 4 / 1e6,
-            "accept_residual_sums_kernel": n_stoch * 2 * cfg.V * 4 / 1e6}
+            "accept_bonus_kernel(exponentials)": n_stoch * cfg.V * 4 / 1e6, "accept_bonus_kernel(residual)": n_stoch * 2 * cfg.V * 4 / 1e6}
 
 
 def summarize_counters(args):
@@ -566,7 +573,7 @@ def summarize_counters(args):
     md = os.path.join(ROOT, "profiles", f"step_{name}_hbm_traffic.md")
     with open(md, "w") as o:
         o.write(f"# Verification step, workload '{name}': HBM traffic per launch from rocprofv3 counters\n\n")
-        o.write("Commands (on the MI355X box, from the repository root, one counter per run):\n\n")
+        o.write("Commands (on an MI355X, from the repository root, one counter per run):\n\n")
         o.write("    cd /tmp && export TMPDIR=/tmp && cd <repository root>; OUT=<a scratch directory>\n")
         for c in ("FETCH_SIZE", "WRITE_SIZE"):
             o.write(f"    rocprofv3 --pmc {c} --output-format csv -d $OUT/pmc_{c} -o {name} -- {cmd}\n")
@@ -616,7 +623,7 @@ def summarize_sq(args):
                      f"{a['SQ_LDS_IDX_ACTIVE']:.3e} | {a['SQ_LDS_BANK_CONFLICT'] / max(a['SQ_LDS_IDX_ACTIVE'], 1) * 100:.1f} % |\n"))
     with open(md, "w") as o:
         o.write(f"# Verification step, workload '{name}': wave, MFMA and LDS counters (rocprofv3 --pmc)\n\n")
-        o.write("Commands (on the MI355X box, from the repository root):\n\n")
+        o.write("Commands (on an MI355X, from the repository root):\n\n")
         o.write("    cd /tmp && export TMPDIR=/tmp && cd <repository root>; OUT=<a scratch directory>\n")
         o.write(f"    rocprofv3 --pmc {SQ_COUNTERS} --output-format csv -d $OUT/pmc_sq -o {name} -- {cmd}\n")
         o.write(f"    python3 bench.py --config {name} --summarize-sq $OUT/pmc_sq/{name}_counter_collection.csv\n\n")
@@ -635,8 +642,8 @@ def summarize_sq(args):
 def write_peaks_md(path, rec):
     p = rec["measured_peaks"]
     with open(path, "w") as o:
-        o.write("# Measured ceilings of the MI355X box (probes of the library, HIP events on the launch stream)\n\n")
-        o.write("Command (on the MI355X box, from the repository root; OUT = a scratch directory):\n\n    python3 bench.py --peaks --peaks-md $OUT/peaks.md\n\n")
+        o.write("# Measured ceilings of an MI355X (probes of the library, HIP events on the launch stream)\n\n")
+        o.write("Command (on an MI355X, from the repository root; OUT = a scratch directory):\n\n    python3 bench.py --peaks --peaks-md $OUT/peaks.md\n\n")
         o.write("| probe | measured | datasheet | ratio |\n|---|---|---|---|\n")
         hb, mf = rec["datasheet"]["hbm_GBs"], rec["datasheet"]["mfma_bf16_TFLOPs"]
         o.write(f"| linear read of 2 GiB (`spec_probe_read`, 16-byte loads, 4 KB per workgroup step), median | {p['hbm_linear_read_GBs']:.0f} GB/s | {hb:.0f} GB/s | {p['hbm_linear_read_GBs'] / hb:.3f} |\n")
@@ -659,7 +666,7 @@ def summarize_trace(args):
     md = os.path.join(ROOT, "profiles", f"step_{name}_kernel_trace.md")
     with open(md, "w") as o:
         o.write(f"# Verification step, workload '{name}': rocprofv3 kernel trace\n\n")
-        o.write("Command (on the MI355X box, from the repository root):\n\n")
+        o.write("Command (on an MI355X, from the repository root):\n\n")
         o.write(f"    OUT=<a scratch directory>; cd /tmp && export TMPDIR=/tmp && cd <repository root> && rocprofv3 --kernel-trace --stats --output-format csv "
                 f"-d $OUT/prof -o {name} -- {cmd}\n")
         o.write(f"    python3 bench.py --config {name} --summarize-trace $OUT/prof/{name}_kernel_stats.csv\n\n")
