@@ -646,7 +646,7 @@ def write_peaks_md(path, rec):
         o.write("Command (on an MI355X, from the repository root; OUT = a scratch directory):\n\n    python3 bench.py --peaks --peaks-md $OUT/peaks.md\n\n")
         o.write("| probe | measured | datasheet | ratio |\n|---|---|---|---|\n")
         hb, mf = rec["datasheet"]["hbm_GBs"], rec["datasheet"]["mfma_bf16_TFLOPs"]
-        o.write(f"| linear read of 2 GiB (`spec_probe_read`, 16-byte loads, 4 KB per workgroup step), median | {p['hbm_linear_read_GBs']:.0f} GB/s | {hb:.0f} GB/s | {p['hbm_linear_read_GBs'] / hb:.3f} |\n")
+        o.write(f"| linear read of 2 GiB (`spec_probe_read`, nontemporal 16-byte loads, a contiguous share per workgroup), median | {p['hbm_linear_read_GBs']:.0f} GB/s | {hb:.0f} GB/s | {p['hbm_linear_read_GBs'] / hb:.3f} |\n")
         o.write(f"| the same, best launch | {p['hbm_linear_read_GBs_best']:.0f} GB/s | {hb:.0f} GB/s | {p['hbm_linear_read_GBs_best'] / hb:.3f} |\n")
         o.write(f"| the same 2 GiB as 4 KB pages through an index list, in order (`spec_probe_read_pages`) | {p['hbm_4k_pages_in_order_GBs']:.0f} GB/s | {hb:.0f} GB/s | {p['hbm_4k_pages_in_order_GBs'] / hb:.3f} |\n")
         o.write(f"| 4 KB pages in a random permutation (what a paged K/V pool looks like) | {p['hbm_4k_pages_random_order_GBs']:.0f} GB/s | {hb:.0f} GB/s | {p['hbm_4k_pages_random_order_GBs'] / hb:.3f} |\n")
