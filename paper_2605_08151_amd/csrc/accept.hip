@@ -995,8 +995,9 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(
 }  // namespace specv
 
 namespace specv {
-// The scan of all M rows.  Logits that cannot all still be in the memory-side cache are read nontemporal (measured, V = 151936: M = 1204,
-// 732 MB 133 -> 110 us; M = 576 62 -> 58; M = 160, 97 MB 19.4 -> 17.9; below half the cache no difference).
+// The scan of all M rows.  From a quarter of the memory-side cache on, logits are read nontemporal.  Measured (V = 151936, ordinary -> nontemporal, scan and
+// decision alone, back to back / LM head, scan and decision): M = 80, 49 MB 14.1 -> 14.2 us / 83.3 -> 82.6; M = 120, 73 MB 16.5 -> 14.8 / 96.2 -> 94.7;
+// M = 240, 146 MB 26.6 -> 26.3 / 128 -> 124; M = 448, 272 MB 46.3 -> 47.3 / 198 -> 192; M = 576, 350 MB 65.9 -> 59.1 / 267 -> 246.
 static void launch_row_stats(const float* logits, const float* temperature, const int32_t* qo_indptr, int B, int M, int V, int nseg,
                              const AcceptWorkspace& w, int32_t* stats, bool greedy_rows_covered, bool fp32_sums, hipStream_t s)
 {

@@ -12,9 +12,10 @@
 //     a fragment read from LDS feeds 4 MFMAs (one per panel of the wave);
 //   * a wave is its own latency hiding: everything it needs is requested 2.5 to 4 slabs (2-4 us) ahead, hidden fragments are read
 //     from LDS across the border of two slabs, and the stores of a tile drain under the first steps of the next one.
-// What bounds it: with 16 instructions per 4 MFMAs and a wave (64 cycles) the issue slots, and the power the operands' way from L2
-// costs.  M = 1152, V = 151936, H = 4096, same box: 1260 us with vector address arithmetic, branches per group and a full stop at every
-// slab and tile, 1165 us (1.23 PFLOP/s) as it stands; 1119 before and without any store, 800 with operands that never move.
+// What bounds it: the issue slots (a wave issues 16 instructions in the time of 4 MFMAs, 64 cycles), and the power that the operands' way from L2
+// costs.  M = 1152, V = 151936, H = 4096 takes 1150-1190 us (1.2 PFLOP/s; 1240-1270 with vector address arithmetic, branches per group and a full stop at every
+// slab and tile); 1119 without any store of logits, 800 with operands that stay in registers.  With one row group (161..256 rows) it is the stream of W,
+// as in the weight-streaming kernel: M = 192 270 us, 4.9 TB/s.
 // The batch is cut into row groups of whole 16-row tiles, nearly equal and at most 256 rows each; the grid is groups x panel ranges, the groups of a
 // range run on the same XCD at the same time and share that range's panels through the XCD's L2, so HBM sees W once.
 // Per output element the products are added in the same order as in the other LM-head kernels (k ascending, one
