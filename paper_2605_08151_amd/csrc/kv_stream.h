@@ -13,30 +13,27 @@
 
 namespace specv {
 
-constexpr int kKvScanRequests = 1024;          // at most so many requests around its own are looked at by a workgroup
+constexpr int kKvScanRequests = 64;            // at most so many requests around its own are looked at by a workgroup: one per lane of a wave
 
 struct KvScan {
-    float keys;                                // committed keys of the requests looked at
-    bool shared;                               // another request maps the same page at the same place
+    float keys;                                // committed keys of the request looked at, times the requests each one looked at stands for
+    bool shared;                               // it maps the same page at the same place
 };
 
-// Part `part` of `parts` of the scan for request i, whose chunk starts at page index `page`: requests part, part + parts, ... of the window.
-constexpr KvScan kv_scan_part(const int32_t* seq_lens, const int32_t* page_table, int max_pages, int B, int max_kv_len, int i, int page, int part, int parts)
+// What lane `lane` looks at for request i, whose chunk starts at page index `page`.
+constexpr KvScan kv_scan_lane(const int32_t* seq_lens, const int32_t* page_table, int max_pages, int B, int max_kv_len, int i, int page, int lane)
 {
-    KvScan r{0.0f, false};
+    const int looked_at = B < kKvScanRequests ? B : kKvScanRequests;
     int first = i - kKvScanRequests / 2;
-    if (first > B - kKvScanRequests) first = B - kKvScanRequests;
+    if (first > B - looked_at) first = B - looked_at;
     if (first < 0) first = 0;
-    const int last = first + kKvScanRequests < B ? first + kKvScanRequests : B;
-    const int32_t own = page_table[(long)i * max_pages + page];
-    for (int j = first + part; j < last; j += parts) {
-        const int c = seq_lens[j];
-        const int32_t other = page_table[(long)j * max_pages + page];    // (requested together with the length)
-        const int keys = c < 0 ? 0 : (c < max_kv_len ? c : max_kv_len);
-        r.keys += (float)keys;
-        r.shared |= (j != i) & (other == own) & (page < keys / 16);       // (entries past a request's committed keys may be stale)
-    }
-    return r;
+    if (lane >= looked_at) return {0.0f, false};
+    const int j = first + lane;
+    const int32_t own = page_table[(long)i * max_pages + page], other = page_table[(long)j * max_pages + page];
+    const int c = seq_lens[j];
+    const int keys = c < 0 ? 0 : (c < max_kv_len ? c : max_kv_len);
+    // (entries past a request's committed keys may be stale)
+    return {(float)keys * ((float)B / (float)looked_at), j != i && other == own && page < keys / 16};
 }
 
 }  // namespace specv

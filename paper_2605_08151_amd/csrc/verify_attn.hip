@@ -68,28 +68,17 @@ struct AttnParams {
     float stream_keys;         // committed keys of the batch above which its K/V is too large for the memory-side cache (0: it never is)
 };
 
-// The kernels with STREAM read a chunk's pages by nontemporal loads where kv_stream.h says so.  kv_scan leaves this wave's part of the scan in LDS;
-// after a barrier kv_streams combines the parts (the same answer in every wave).  The scan costs about 1 us of a short call (28.2 -> 29.2); the work
-// list's kernel knows the batch's total and spares it where that is small.
-struct KvScanPart { float keys; int shared; };
-
+// The kernels with STREAM read a chunk's pages by nontemporal loads where kv_stream.h says so: the last wave looks (beside the first one's loads of the
+// chunk's page ids) and leaves the answer in LDS for the others behind the barrier that publishes those.  The work list's kernel knows the batch's total and
+// spares the look where that is small.
 template <int NW>
-__device__ inline void kv_scan(const AttnParams& p, int i, int page, KvScanPart* parts)
+__device__ inline void kv_scan(const AttnParams& p, int i, int page, bool total_known, int* answer)
 {
-    const KvScan s = kv_scan_part(p.seq_lens, p.page_table, p.max_pages, p.B, p.max_kv_len, i, page, threadIdx.x, NW * 64);
+    if (threadIdx.x < (NW - 1) * 64) return;
+    const KvScan s = kv_scan_lane(p.seq_lens, p.page_table, p.max_pages, p.B, p.max_kv_len, i, page, threadIdx.x - (NW - 1) * 64);
     const bool shared = __any(s.shared);
-    const float keys = four_rows_sum(row16_sum(s.keys));
-    if ((threadIdx.x & 63) == 0) parts[threadIdx.x >> 6] = {keys, shared};
-}
-
-template <int NW>
-__device__ inline bool kv_streams(const AttnParams& p, const KvScanPart* parts)
-{
-    float keys = 0.0f;
-    int shared = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { keys += parts[w].keys; shared |= parts[w].shared; }
-    return __builtin_amdgcn_readfirstlane(keys > p.stream_keys && !shared);
+    const float keys = total_known ? INFINITY : four_rows_sum(row16_sum(s.keys));
+    if (threadIdx.x == (NW - 1) * 64) *answer = keys > p.stream_keys && !shared;
 }
 
 __device__ inline bool request_ok(int r0, int n, int c, const AttnParams& p)
@@ -153,19 +142,15 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     // queue as the direct K/V loads and force them to drain. ----
     int bad_page = 0;
     const int npages = (kend - kbeg + kP - 1) / kP;
-    __shared__ KvScanPart s_scan[STREAM ? NW : 1];
-    int page0 = 0;                                        // (requested together with what the scan looks at: one round trip)
-    if (STREAM && scan) {
-        if (tid < npages) page0 = pt[kbeg / kP + tid];
-        kv_scan<NW>(p, i, kbeg / kP, s_scan);
-    }
+    __shared__ int s_stream;
+    if (STREAM && scan) kv_scan<NW>(p, i, kbeg / kP, p.plan_items != nullptr, &s_stream);
     for (int pg = tid; pg < npages; pg += kThreads) {
-        int page = STREAM && scan && pg == tid ? page0 : pt[kbeg / kP + pg];
+        int page = pt[kbeg / kP + pg];
         if (page < 0 || page >= p.num_pages) { page = 0; bad_page = 1; }
         sPT[pg] = page;
     }
     __syncthreads();
-    const bool stream_kv = STREAM && scan && kv_streams<STREAM ? NW : 1>(p, s_scan);
+    const bool stream_kv = STREAM && scan && __builtin_amdgcn_readfirstlane(s_stream);
 
     // ---- this wave's two pages of a step, K and V, HBM -> LDS (always 16 direct loads: positions past the
     // range read page 0 instead, so the wait counts below are constants) ----
@@ -556,8 +541,8 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
         if (row_ok) v = *reinterpret_cast<const u32x4*>(p.q + rowhead * kD + (s * 4 + g) * 8);
         qf[s] = __builtin_bit_cast(bf16x8, v);
     }
-    __shared__ KvScanPart s_scan[STREAM ? NW : 1];
-    if (STREAM && scan) kv_scan<NW>(p, i, kbeg / kP, s_scan);            // (its loads fly with those of Q)
+    __shared__ int s_stream;
+    if (STREAM && scan) kv_scan<NW>(p, i, kbeg / kP, p.plan_items != nullptr, &s_stream);    // (its loads fly with those of Q)
     const bool tree = p.parent != nullptr;
     int limit = row_ok ? (tree ? kend : min(c + qj + 1, kend)) : 0;      // the row sees key positions t < limit
     // tree verification: bit a of anc is set iff candidate a is on this row's path to the root (a chain: all ones)
@@ -587,7 +572,7 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
         sAnc[r] = m;
     }
     __syncthreads();                                      // page ids and masks visible
-    const bool stream_kv = STREAM && scan && kv_streams<STREAM ? NW : 1>(p, s_scan);
+    const bool stream_kv = STREAM && scan && __builtin_amdgcn_readfirstlane(s_stream);
     // The Q fragments came by ordinary loads.  The compiler cannot see the direct loads below (inline assembly), and with
     // some of them always in flight (rings deeper than two) it would make the loop wait for "all loads" at the first use
     // of a fragment in every stage, which serialises the ring (measured 230 against 187 us).  Waiting once here and handing
@@ -1166,9 +1151,11 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
     p.plan_hdr = nullptr; p.plan_req = nullptr; p.plan_items = nullptr;
     p.parent = parent;
     p.B = B;
-    // where not even the stated bounds exceed 3/4 of the memory-side cache, the kernels without the choice run (0)
-    const size_t cached_keys = kMemorySideCache * 3 / 4 / (2 * kRowBytes);
-    p.stream_keys = (size_t)B * max_kv_len * Hkv > cached_keys ? (float)cached_keys / (float)Hkv : 0.0f;
+    // Where not even the stated bounds exceed 3/4 of the memory-side cache, the kernels without the choice run (0).  The choice itself is for the keys
+    // there are, from half of that cache on (calls on three batches in turn, ordinary -> nontemporal: 82 MB 36.1 -> 36.7 us, 94 MB 47.4 -> 47.5, 168 MB
+    // 42 -> 40, 200 MB 61 -> 55.5 and, in a step with long contexts, 269 -> 263).
+    const size_t cache_keys = kMemorySideCache / (2 * kRowBytes);
+    p.stream_keys = (size_t)B * max_kv_len * Hkv > cache_keys * 3 / 4 ? (float)(cache_keys / 2) / (float)Hkv : 0.0f;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     const AttnPlanCfg pc = attn_plan_cfg(B, Hq, Hkv, max_kv_len, max_q_len, NR, p.chunk_target);

@@ -1,5 +1,5 @@
 """Which chunks the attention kernels read by nontemporal loads, on the CPU: a C++ program runs the kernels' own scan (csrc/kv_stream.h) over whole
-batches, all parts of it, and prints the answer per request and chunk.  No device code runs."""
+batches, all lanes of it, and prints the answer per request and chunk.  No device code runs."""
 import os
 import shutil
 import subprocess
@@ -16,8 +16,8 @@ PROGRAM = r"""
 
 int main()
 {
-    int B, max_pages, max_kv_len, parts, asked;
-    if (std::scanf("%d %d %d %d %d", &B, &max_pages, &max_kv_len, &parts, &asked) != 5) return 2;
+    int B, max_pages, max_kv_len, asked;
+    if (std::scanf("%d %d %d %d", &B, &max_pages, &max_kv_len, &asked) != 4) return 2;
     std::vector<int32_t> lens(B), table((size_t)B * max_pages);
     for (auto& x : lens) if (std::scanf("%d", &x) != 1) return 2;
     for (auto& x : table) if (std::scanf("%d", &x) != 1) return 2;
@@ -26,8 +26,8 @@ int main()
         if (std::scanf("%d %d", &i, &page) != 2) return 2;
         double keys = 0;
         bool shared = false;
-        for (int part = 0; part < parts; ++part) {
-            const specv::KvScan s = specv::kv_scan_part(lens.data(), table.data(), max_pages, B, max_kv_len, i, page, part, parts);
+        for (int lane = 0; lane < 64; ++lane) {
+            const specv::KvScan s = specv::kv_scan_lane(lens.data(), table.data(), max_pages, B, max_kv_len, i, page, lane);
             keys += s.keys;
             shared = shared || s.shared;
         }
@@ -45,9 +45,9 @@ def scan(tmp_path_factory):
     (d / "scan.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=address,undefined", "-I", CSRC, str(d / "scan.cpp"), "-o", str(d / "scan")], check=True)
 
-    def run(lens, table, max_kv_len, asked, parts=256):
+    def run(lens, table, max_kv_len, asked):
         B, max_pages = table.shape
-        words = [B, max_pages, max_kv_len, parts, len(asked), *lens, *table.ravel(), *np.ravel(asked)]
+        words = [B, max_pages, max_kv_len, len(asked), *lens, *table.ravel(), *np.ravel(asked)]
         out = subprocess.run([str(d / "scan")], input=" ".join(str(int(w)) for w in words), capture_output=True, text=True, check=True).stdout
         return [(int(a), b == "1") for a, b in (line.split() for line in out.splitlines())]
     return run
@@ -72,15 +72,17 @@ def test_pages_of_a_common_prefix_are_found(scan):
     table[1, 8:12] = [1, 2, 3, 4]
     table[4] = table[1]
     asked = [(i, page) for i in range(4) for page in range(12)]
-    for parts in (64, 320, 512):
-        got = [s for _, s in scan(lens, table, 4096, asked, parts)]
-        expect = [(i in (0, 2, 3) and page < 4) or (i in (2, 3) and page < 8) or (i == 1 and page < 1) for i, page in asked]
-        assert got == expect                               # (request 4 has one whole page, and it is request 1's)
+    got = [s for _, s in scan(lens, table, 4096, asked)]
+    expect = [(i in (0, 2, 3) and page < 4) or (i in (2, 3) and page < 8) or (i == 1 and page < 1) for i, page in asked]
+    assert got == expect                                   # (request 4 has one whole page, and it is request 1's)
 
 
-def test_large_batches_are_scanned_in_a_window_around_the_request(scan):
-    B = 3000
+@pytest.mark.parametrize("B", [63, 64, 65, 3000])
+def test_a_window_of_requests_stands_for_a_large_batch(scan, B):
+    """64 requests around a request's own are looked at, their keys times B / 64."""
     table = np.arange(B * 2).reshape(B, 2)
-    table[0] = table[511] = table[513] = table[2999] = [77, 78]
-    got = scan(np.full(B, 32), table, 64, [(0, 0), (513, 0), (1023, 1), (2999, 1)])
-    assert got == [(32 * 1024, True), (32 * 1024, True), (32 * 1024, False), (32 * 1024, False)]
+    table[0] = table[31] = table[B - 1] = [7777777, 7777778]
+    i = min(B - 2, 64)
+    got = scan(np.full(B, 32), table, 64, [(0, 0), (i, 0), (B - 1, 1)])
+    assert [s for _, s in got] == [True, False, B <= 95]
+    assert all(abs(k - 32 * B) <= 1e-5 * 32 * B for k, _ in got)
