@@ -391,19 +391,37 @@ static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int
     return SPEC_OK;
 }
 
-// W is read once when one row group covers the batch: nontemporal if the matrix is larger than the memory-side cache by so much that a call finds
-// little of it there from the call before.  Measured back to back, ordinary -> nontemporal, us: 1.16 GiB (V = 151936, H = 4096) M = 5 207 -> 191,
-// M = 40 223 -> 208; 390 MiB (100000, 2048) M = 1 68 -> 62.5, M = 80 77 -> 75.5; 312 MiB (64000, 2560) 55 -> 51, 60 -> 57; 296 MiB (151936, 1024)
-// no difference; 281 MiB (36000, 4096) 45 -> 47, 52 -> 59; 195 MiB (100000, 1024) M = 40 34 -> 38.  After 2 GiB of other reads, when nothing is
-// found, the two differ by 3 % up to 288 MiB.  With several row groups the others read W from the L2.
-// Row-major, only where rows lie a multiple of 4 KB apart (V = 151936 / 100000, M = 1: H = 4096 213 -> 204 / 150 -> 141, H = 2048 130 -> 128 /
-// 78 -> 73; but H = 2560 137 -> 142 / 93 -> 96, H = 5120 268 -> 273 / 177 -> 182).
+static int panels_per_cu(int V)
+{
+    int ranges, per_range;
+    packed_geometry(V, 1, &ranges, &per_range);
+    return per_range;
+}
+
+// W is read once when one row group covers the batch.  A matrix above 3/8 of the memory-side cache is read nontemporal: it does not push the step's other
+// operands out of that cache, and it would not be found there by the next step.  Measured on steps over three batches in turn, ordinary ->
+// nontemporal, us: W = 97 MiB (V = 40001, H = 1280) 4 requests 50.3 -> 47.2, 32 requests 81.5 -> 75.9; 156 MiB (32000, 2560) 59.3 -> 54.4, 81.8 -> 77.1;
+// 250 MiB (64000, 2048) 83.5 -> 78.7, 100.6 -> 96.9; 13 ragged requests on 122 MiB (50021, 1280) 92.5 -> 83.8; 1.16 GiB one request 267 -> 244; below
+// the line, 73 MiB 48.0 -> 47.8.  (The LM head alone, called again and again on one matrix of 100 to 280 MiB, loses 3 to 15 % by it: 195 MiB, M = 40 34 -> 38.
+// So does a batch of several row groups, which reads W from the L2 in all but one.)
+// Row-major, alone on three matrices in turn: where rows are a multiple of 2 KB, or the waves have nearly all their panel slots to fill (H = 2560, M = 1:
+// V = 64000, 16 panels of 16 59 -> 53, V = 128256, 2 x 16 113 -> 103; but V = 90000, 2 x 11 87 -> 93, V = 36000, 9 46 -> 51.5, V = 151936, 38 in 3
+// passes 138 -> 143; H = 4096 V = 90000 156 -> 152, V = 151936 215 -> 203).
+template <bool ROWS>
+static bool stream_weights(int H, int V, int pass_panels)
+{
+    if ((size_t)V * H * 2 <= kMemorySideCache * 3 / 8) return false;
+    if (!ROWS || H % 1024 == 0) return true;
+    const int p = panels_per_cu(V), passes = (p + pass_panels - 1) / pass_panels;
+    return p * 16 >= 13 * passes * pass_panels;
+}
+
 template <int TM, int RS, int NW, bool NT, int TN, bool STATS = false, bool ROWS = false>
 static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
                          float* blk_max = nullptr, int32_t* blk_arg = nullptr)
 {
     if constexpr (NT) {
-        if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 9 / 8 && (!ROWS || H % 2048 == 0))
+        if (groups == 1 && stream_weights<ROWS>(H, V, NW * TN))
             return launch_packed_as<TM, RS, NW, NT, TN, STATS, true, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
     }
     return launch_packed_as<TM, RS, NW, NT, TN, STATS, false, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
@@ -413,12 +431,6 @@ static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M,
 // panel each, their second slot re-reading it, and twice the LDS reads per panel.  Measured at V = 32000, 8 against 4 waves: H = 4096
 // M = 40 51.6 -> 47.8 us, M = 160 70 -> 60; H = 2048 M = 96 35.3 -> 32.6; row-major H = 4096 M = 80 74 -> 48, M = 160 87 -> 61.
 // With more panels 8 waves are ahead (V = 50021, H = 1280, M = 40: 27.5 against 30.5).
-static int panels_per_cu(int V)
-{
-    int ranges, per_range;
-    packed_geometry(V, 1, &ranges, &per_range);
-    return per_range;
-}
 static bool few_panels(int V) { return panels_per_cu(V) <= 8; }
 
 template <int TM>
@@ -446,17 +458,19 @@ static int launch_rows(const uint16_t* a, const uint16_t* w, float* c, int M, in
 
 // The same kernel on a row-major matrix, for spec_lm_head (M <= 160, H a multiple of 256).  Returns false if it does not take the shape: the 4-wave
 // kernel of lm_head.hip, whose passes are half as wide, serves it then.
-// That one splits a small vocabulary over more waves, and with few rows over more workgroups.  Measured against it (4-wave -> this, us):
-//   12 panels per CU and more: V = 151936, H = 4096 M = 5 227 -> 201, M = 40 249 -> 218, M = 128 309 -> 278, M = 160 329 -> 298;
-//     V = 49152 M = 1 H = 1024 20.9 -> 20.2, H = 2048 33.9 -> 34.8, H = 4096 76 -> 74, M = 160 33.9 -> 29.7, 54.8 -> 48.2, 116 -> 97
-//   8 to 11: M = 80 V = 32768 H = 2048 26.1 -> 25.5, H = 4096 51.7 -> 48.9, V = 34000 39.3 -> 38.6, 78 -> 74, M = 160 51.7 -> 44.1, 104 -> 88; but
-//     M = 1 V = 32768 H = 2048 22.6 -> 24.1, V = 34000 29.1 -> 33.4, V = 40960 31.1 -> 33.9
-//   fewer: V = 24576 H = 2048 M = 1 18.9 -> 20.3, M = 160 28.9 -> 31.7; V = 16000, H = 1024 8.8 -> 11.6, 17.0 -> 19.0; V = 2000, H = 4096 21.9 -> 33.4
+// That one splits a small vocabulary over more waves, and with few rows over more workgroups.  Measured against it (4-wave -> this, three matrices in
+// turn, us):
+//   11 panels per CU and more: V = 151936, H = 4096 M = 1 225 -> 203, M = 40 250 -> 222, M = 150 329 -> 299; V = 50021, H = 1280 M = 1 27.8 -> 27.0,
+//     M = 150 58 -> 50; V = 42000, H = 2560 M = 1 45.7 -> 44.9, M = 150 75.6 -> 62.1
+//   8: V = 32000 M = 1 H = 1024 14.6 -> 14.6, H = 2048 30.9 -> 28.1, H = 4096 62 -> 57, M = 80 17.5 -> 15.8, 36.5 -> 33.5, 64 -> 60
+//   9 and 10: V = 36000 M = 12 H = 1280 23.4 -> 23.8, H = 2560 43.8 -> 46.0, H = 4096 76 -> 73, M = 40 26.1 -> 25.4, 49.7 -> 50.5, 82 -> 78, M = 80 32.7 -> 29.7
+//   fewer (one matrix): V = 24576, H = 2048 M = 1 18.9 -> 20.3, M = 160 28.9 -> 31.7; V = 16000, H = 1024 8.8 -> 11.6, 17.0 -> 19.0; V = 2000, H = 4096 21.9 -> 33.4
 // Reading 64 bytes of each of 16 rows instead (no weaving, ordinary loads) costs the same from M = 96 on, and 222 against 199 us at M = 5.
 bool lm_head_rows_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc)
 {
     if (M > kPkMaxRows || H % (2 * kPkSlab) != 0 || (size_t)V > ((size_t)1 << 32) / (4 * (size_t)(kPkMaxRows + 16))) return false;
-    if (panels_per_cu(V) < (M <= 64 ? 12 : 8)) return false;
+    const int panels = panels_per_cu(V);
+    if (panels < 8 || (panels < 11 && panels > 8 && M <= 32)) return false;
     switch ((M + 15) / 16) {
         case 1: case 2: *rc = launch_rows<2>(a, w, c, M, H, V, s); break;
         case 3: case 4: *rc = launch_rows<4>(a, w, c, M, H, V, s); break;

@@ -67,7 +67,7 @@ def test_attention_over_more_keys_than_the_cache_holds(sv, oracle, gammas, Hq):
 @pytest.mark.parametrize("M", [1, 37, 160])
 @pytest.mark.parametrize("V", [196608, 196612, 196625])
 def test_packed_lm_head_streaming_and_cached_weights(sv, oracle, M, V):
-    """Large vocabularies of a short matrix, last panels of 1, 4 and 16 entries.  (Ordinary loads: the line of the nontemporal ones is below.)"""
+    """The vocabulary matrix by nontemporal loads above 3/8 of the memory-side cache (H = 256: more than 196608 entries)."""
     g = torch.Generator(device="cuda").manual_seed(V + M)
     hidden = torch.randn((M, 256), generator=g, device="cuda").to(torch.bfloat16)
     W = torch.randn((V, 256), generator=g, device="cuda").to(torch.bfloat16)
@@ -112,10 +112,10 @@ def _both_layouts(sv, hidden, W):
     return logits, packed
 
 
-@pytest.mark.parametrize("M", [1, 64, 65, 160])
-@pytest.mark.parametrize("V", [28672, 28673, 45056, 45057])
+@pytest.mark.parametrize("M", [1, 32, 33, 160])
+@pytest.mark.parametrize("V", [28672, 28673, 32768, 32769, 40960, 40961])
 def test_row_major_lm_head_at_the_lines_of_its_routes(sv, oracle, M, V):
-    """7 and 8, 11 and 12 panels per CU (of 256), up to 64 rows and more: the 4-wave kernel on one side, the packed kernel's row-major form on the other."""
+    """7, 8, 9 and 10, 11 panels per CU (of 256), up to 32 rows and more: the 4-wave kernel on one side, the packed kernel's row-major form on the other."""
     g = torch.Generator(device="cuda").manual_seed(V + M)
     hidden = torch.randn((M, 256), generator=g, device="cuda").to(torch.bfloat16)
     W = torch.randn((V, 256), generator=g, device="cuda").to(torch.bfloat16)
@@ -126,10 +126,10 @@ def test_row_major_lm_head_at_the_lines_of_its_routes(sv, oracle, M, V):
 
 
 @pytest.mark.parametrize("M", [5, 80, 160])
-@pytest.mark.parametrize("V,H", [(32000, 4864), (32767, 6144)])
+@pytest.mark.parametrize("V,H", [(32000, 1792), (32767, 2048)])
 def test_few_panels_and_a_matrix_beyond_the_cache(sv, oracle, V, H, M):
-    """At most 8 panels per CU (4 waves, two slabs in the ring) and nontemporal weights: packed, and row-major where H is a multiple of 2048."""
-    assert V * H * 2 > 288 << 20
+    """At most 8 panels per CU (4 waves, two slabs in the ring) and nontemporal weights, both layouts."""
+    assert V * H * 2 > 96 << 20
     g = torch.Generator(device="cuda").manual_seed(V + M)
     hidden = torch.randn((M, H), generator=g, device="cuda").to(torch.bfloat16)
     W = torch.randn((V, H), generator=g, device="cuda").to(torch.bfloat16)
@@ -147,16 +147,17 @@ def test_few_panels_and_a_matrix_beyond_the_cache(sv, oracle, V, H, M):
 
 
 @pytest.mark.parametrize("M", [1, 80, 160])
-@pytest.mark.parametrize("V", [147456, 147457])
-def test_packed_lm_head_at_the_line_of_its_nontemporal_loads(sv, oracle, M, V):
-    """The vocabulary matrix by nontemporal loads above 9/8 of the memory-side cache (H = 1024: more than 147456 entries)."""
+@pytest.mark.parametrize("V,H", [(50000, 1280), (62000, 1280), (62000, 1024)])
+def test_row_major_lm_head_by_ordinary_and_nontemporal_loads(sv, oracle, M, V, H):
+    """A matrix beyond 3/8 of the memory-side cache: rows of whole 2 KB or panel slots nearly all filled (13 and 16 of 16 per CU)."""
+    assert V * H * 2 > 96 << 20
     g = torch.Generator(device="cuda").manual_seed(V + M)
-    hidden = torch.randn((M, 1024), generator=g, device="cuda").to(torch.bfloat16)
-    W = torch.randn((V, 1024), generator=g, device="cuda").to(torch.bfloat16)
+    hidden = torch.randn((M, H), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, H), generator=g, device="cuda").to(torch.bfloat16)
     logits, packed = _both_layouts(sv, hidden, W)
     rows = torch.tensor(sorted({0, M // 2, M - 1}), device="cuda")
     ref = oracle.lm_head(wl.bf16_bits(hidden[rows]), wl.bf16_bits(W))
-    assert np.abs(packed[rows].cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(1024) * np.abs(ref).max()
+    assert np.abs(logits[rows].cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(H) * np.abs(ref).max()
     assert torch.equal(packed, logits)
 
 
