@@ -106,7 +106,7 @@ __device__ inline void lds_dma16(const void* g, void* lds_base)
     else asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(m0v) : "memory");
 }
 
-// Block summaries of the large-tile LM head (lm_head_mfma.hip): what acceptance needs from a row of logits without reading it again.  A
+// Block summaries of the large-tile LM head (lm_head_mfma_kernel.h): what acceptance needs from a row of logits without reading it again.  A
 // block is what one wave holds of a row at the end of a pass, at most 64 consecutive vocabulary entries; block index =
 // (panel range * passes per range + pass) * 4 + wave, so blocks cover increasing vocabulary ranges; blk_span[2 b],
 // blk_span[2 b + 1] = first entry and number of entries of block b (0 for a slot that holds nothing).  Per row and block:

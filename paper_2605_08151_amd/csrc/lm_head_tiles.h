@@ -1,4 +1,4 @@
-// Row groups, panel ranges and panel shares of the large-tile LM head (lm_head_mfma.hip), and which bytes of the packed matrix a wave
+// Row groups, panel ranges and panel shares of the large-tile LM head (lm_head_mfma_kernel.h), and which bytes of the packed matrix a wave
 // requests for them.  Integer arithmetic only, without device types: the kernel, its launch and a CPU test that walks whole matrices share it.
 #pragma once
 

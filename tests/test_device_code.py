@@ -16,7 +16,7 @@ pytestmark = pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="needs ROCm'
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """{demangled-ish name: [(address, instruction text)]} of every kernel of the large-tile LM head"""
+    """{(row tiles, nontemporal loads, nontemporal stores, block summaries): [(address, instruction, rest of the line)]} of the large-tile LM head"""
     if not os.path.exists(LIB):
         import __graft_entry__
         __graft_entry__.build()
@@ -32,23 +32,26 @@ def kernels(tmp_path_factory):
         for line in text.splitlines():
             head = re.match(r"[0-9a-f]+ <(\S+)>:", line)
             if head:
-                m = re.match(r"_ZN5specv19lm_head_mfma_kernelILi(\d+)ELb([01])ELb([01])E", head[1])
-                code = out.setdefault((int(m[1]), m[2] == "1", m[3] == "1"), []) if m else None
+                m = re.match(r"_ZN5specv19lm_head_mfma_kernelILi(\d+)ELb([01])ELb([01])ELb([01])E", head[1])
+                code = out.setdefault((int(m[1]), m[2] == "1", m[3] == "1", m[4] == "1"), []) if m else None
                 continue
             m = re.match(r"\s+(\S.*?)\s*// ([0-9A-F]+):(.*)", line)
             if m and code is not None:
                 code.append((int(m[2], 16), m[1].strip(), m[3]))
-    assert len(out) == 32, sorted(out)                     # 9..16 row tiles, nontemporal or not, with block summaries or not
+    # 9..16 row tiles, stores nontemporal or not, with block summaries or not; 11..16 also with nontemporal loads, without summaries
+    assert len(out) == 32 + 12, sorted(out)
     return out
 
 
-def test_logits_are_stored_nontemporal_where_asked_for(kernels):
-    """The compiler may merge a nontemporal and an ordinary store of the same value; the 16-byte stores of the logits must be what the
-    instantiation says."""
-    for (tm, nt, summary), code in kernels.items():
+def test_loads_and_stores_are_nontemporal_where_asked_for(kernels):
+    """The compiler may merge a nontemporal and an ordinary store of the same value; the 16-byte stores of the logits, and the loads of
+    the weights, must be what the instantiation says."""
+    for (tm, stream, nt, summary), code in kernels.items():
         stores = [t for _, t, _ in code if t.startswith("global_store_dwordx4")]
-        assert stores
+        loads = [t for _, t, _ in code if re.match(r"(global|buffer)_load_dwordx4", t)]       # (of W; hidden goes to LDS directly)
+        assert stores and loads
         assert all(t.endswith(" nt") == nt for t in stores), (tm, nt, summary, [t for t in stores if t.endswith(" nt") != nt][:3])
+        assert all(t.endswith(" nt") == stream for t in loads), (tm, stream, summary, [t for t in loads if t.endswith(" nt") != stream][:3])
 
 
 def _registers(text, kind):
