@@ -20,9 +20,6 @@ static bool mfma_nt(int M, int V)
     return forced == 1 || (forced == 0 && M <= 416 && V % 16 == 0);
 }
 
-// lm_head_mfma_summary.hip (the instantiations that also leave block summaries, built beside these)
-int lm_head_mfma_summary(bool nt, const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, const LmSummary& sm, hipStream_t s);
-
 // blocks per row of the summaries for this shape; 0 if the large-tile kernel does not take it
 int lm_head_mfma_blocks(int M, int H, int V)
 {
@@ -49,25 +46,12 @@ int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M
     if (summary) return lm_head_mfma_summary(nt, a, wp, c, M, H, V, L, sm, s);
     // One row group reads W once, bound by that stream: nontemporal, by the rule of the weight-streaming kernel (the tree step, M = 188, V = 151936,
     // H = 4096 378 -> 360 us, M = 216 408 -> 394; V = 64000, H = 2560 179 -> 167).
-    const bool stream = L.groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8;
-    switch (L.tm) {
-#define SPECV_MF(TMv)                                                                                             \
-        case TMv:                                                                                                 \
-            return nt ? launch_mfma<TMv, false, true, false>(a, wp, c, M, H, V, L, sm, s)                         \
-                      : launch_mfma<TMv, false, false, false>(a, wp, c, M, H, V, L, sm, s);
-#define SPECV_MF_ONE_GROUP(TMv)                                                                                   \
-        case TMv:                                                                                                 \
-            if (stream) return nt ? launch_mfma<TMv, true, true, false>(a, wp, c, M, H, V, L, sm, s)              \
-                                  : launch_mfma<TMv, true, false, false>(a, wp, c, M, H, V, L, sm, s);            \
-            return nt ? launch_mfma<TMv, false, true, false>(a, wp, c, M, H, V, L, sm, s)                         \
-                      : launch_mfma<TMv, false, false, false>(a, wp, c, M, H, V, L, sm, s);
-        SPECV_MF(9) SPECV_MF(10)                      // (more than 160 rows in one group: 11 tiles or more)
-        SPECV_MF_ONE_GROUP(11) SPECV_MF_ONE_GROUP(12) SPECV_MF_ONE_GROUP(13) SPECV_MF_ONE_GROUP(14) SPECV_MF_ONE_GROUP(15) SPECV_MF_ONE_GROUP(16)
-#undef SPECV_MF
-#undef SPECV_MF_ONE_GROUP
-        default: break;
-    }
-    return fail(SPEC_ESHAPE, "spec_lm_head_packed: no large-tile instantiation for %d row tiles per group", L.tm);
+    if (L.groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8) return lm_head_mfma_stream(nt, a, wp, c, M, H, V, L, sm, s);
+    // Several groups that read panels a multiple of 64 KB apart: global loads (buffer -> global, V = 151936 / 100000, H = 4096: M = 257 357 -> 330 /
+    // 264 -> 247 us, M = 576 622 -> 606 / 408 -> 395, M = 1152 1157 -> 1119 / 793 -> 782; H = 2048 M = 257 191 -> 179, M = 576 351 -> 328).  Elsewhere
+    // buffer loads (H = 2560: M = 576 398 -> 409 / 260 -> 265, M = 1152 757 -> 779; H = 3072 854 -> 902; H = 1024 357 -> 360).
+    if (L.groups > 1 && H % 2048 == 0) return lm_head_mfma_global(nt, a, wp, c, M, H, V, L, sm, s);
+    return lm_head_mfma_buffer(nt, a, wp, c, M, H, V, L, sm, s);
 }
 
 }  // namespace specv

@@ -1,0 +1,8 @@
+// The instantiations of the large-tile LM head with W by buffer loads.
+#include "lm_head_mfma_kernel.h"
+
+namespace specv {
+
+SPECV_MFMA_FILE(lm_head_mfma_buffer) { return launch_mfma_tiles<kBufferLoads, false, 9>(nt, a, wp, c, M, H, V, L, sm, s); }
+
+}  // namespace specv

@@ -50,9 +50,11 @@ __device__ inline void lds_dma16_off(uint32_t off, const void* base, void* lds_b
     asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
 }
 
-// STREAM: W by nontemporal loads (one row group and a matrix too large for the memory-side cache); NT: nontemporal stores of the logits (a template argument: of two stores in the branches of a flag the compiler makes one ordinary store);
+// LOADS: how W is read, see MfmaLoads; NT: nontemporal stores of the logits (a template argument: of two stores in the branches of a flag the compiler makes one ordinary store);
 // SUMMARY instantiations also leave the block summaries described at LmSummary.
-template <int TM, bool STREAM, bool NT, bool SUMMARY>
+enum MfmaLoads { kBufferLoads, kGlobalLoads, kStreamLoads };   // buffer loads; global loads; nontemporal global loads
+
+template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
 __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
     int M_all, int H, int V, int n_panels, int panels_per_wg, int groups, int tiles_lo, int groups_hi,
@@ -131,8 +133,8 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         lds_dma16_off(hoff[q], hsrc, hbuf + slot * kSlabBytes + (QN * wave + q) * 1024);
     };
 
-    // ---- W: the wave's panels of a pass, read through a buffer descriptor at its first panel (STREAM: from its address), at a scalar position (panel
-    // slot and place in the stream) plus 16 bytes per lane: a request costs no vector address arithmetic.
+    // ---- W: the wave's panels of a pass, read at a scalar position (panel slot and place in the stream) from its first panel on, through a buffer
+    // descriptor or by address, plus 16 bytes per lane: a request costs no vector address arithmetic.
     int wave_p0 = 0, wave_np = 0;
     auto pass_panels = [&](int pass, int& p0, int& np) SPECV_INLINE {
         const PanelShare s = mf_panel_share(p_begin, p_end, pass, wave);
@@ -155,7 +157,9 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         for (int tn = 0; tn < kMfTN; ++tn) wslot[tn] = mf_slot_bytes(np, tn, panel_bytes);
     };
     auto fetch_w1 = [&](int slot, int t, int tn) SPECV_INLINE {    // k-tile t of that slab, panel slot tn
-        if constexpr (STREAM) wreg[slot][t][tn] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wbase + (wpos + t * 1024 + wslot[tn]) + woff));
+        const u32x4* at = reinterpret_cast<const u32x4*>(wbase + (wpos + t * 1024 + wslot[tn]) + woff);
+        if constexpr (LOADS == kStreamLoads) wreg[slot][t][tn] = __builtin_nontemporal_load(at);
+        else if constexpr (LOADS == kGlobalLoads) wreg[slot][t][tn] = *at;
         else wreg[slot][t][tn] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff, wpos + t * 1024 + wslot[tn], 0);
     };
 
@@ -457,16 +461,32 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     __builtin_amdgcn_s_waitcnt(0x0F70);               // no direct load of this wave is still landing when the LDS is given up
 }
 
-template <int TM, bool STREAM, bool NT, bool SUMMARY>
+template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
 static int launch_mfma(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, LmSummary sm, hipStream_t s)
 {
     constexpr int SR = (TM * 16 + 31) / 32 * 32;
     const size_t smem = (size_t)kMfRing * SR * kMfPitch + (size_t)kMfWaves * 16 * kMfPatchPitch + (SUMMARY ? TM * 16 * 4 : 0);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, STREAM, NT, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
-    hipLaunchKernelGGL((lm_head_mfma_kernel<TM, STREAM, NT, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, LOADS, NT, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
+    hipLaunchKernelGGL((lm_head_mfma_kernel<TM, LOADS, NT, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
                        (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi, sm);
     return SPEC_OK;
 }
+
+// The instantiations for TM..16 row tiles of one kind of loads: a file each, built side by side.
+template <MfmaLoads LOADS, bool SUMMARY, int TM>
+static int launch_mfma_tiles(bool nt, const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, const LmSummary& sm, hipStream_t s)
+{
+    if (L.tm == TM)
+        return nt ? launch_mfma<TM, LOADS, true, SUMMARY>(a, wp, c, M, H, V, L, sm, s) : launch_mfma<TM, LOADS, false, SUMMARY>(a, wp, c, M, H, V, L, sm, s);
+    if constexpr (TM < 16) return launch_mfma_tiles<LOADS, SUMMARY, TM + 1>(nt, a, wp, c, M, H, V, L, sm, s);
+    else return fail(SPEC_ESHAPE, "spec_lm_head_packed: no large-tile instantiation for %d row tiles per group", L.tm);
+}
+
+#define SPECV_MFMA_FILE(name) int name(bool nt, const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, const LmSummary& sm, hipStream_t s)
+SPECV_MFMA_FILE(lm_head_mfma_buffer);
+SPECV_MFMA_FILE(lm_head_mfma_global);
+SPECV_MFMA_FILE(lm_head_mfma_stream);      // 11 row tiles or more (one group of more than 160 rows)
+SPECV_MFMA_FILE(lm_head_mfma_summary);     // (buffer loads)
 
 }  // namespace specv

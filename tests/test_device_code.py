@@ -16,7 +16,7 @@ pytestmark = pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="needs ROCm'
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """{(row tiles, nontemporal loads, nontemporal stores, block summaries): [(address, instruction, rest of the line)]} of the large-tile LM head"""
+    """{(row tiles, loads: 0 buffer, 1 global, 2 nontemporal global, nontemporal stores, block summaries): [(address, instruction, rest of the line)]} of the large-tile LM head"""
     if not os.path.exists(LIB):
         import __graft_entry__
         __graft_entry__.build()
@@ -32,21 +32,22 @@ def kernels(tmp_path_factory):
         for line in text.splitlines():
             head = re.match(r"[0-9a-f]+ <(\S+)>:", line)
             if head:
-                m = re.match(r"_ZN5specv19lm_head_mfma_kernelILi(\d+)ELb([01])ELb([01])ELb([01])E", head[1])
-                code = out.setdefault((int(m[1]), m[2] == "1", m[3] == "1", m[4] == "1"), []) if m else None
+                m = re.match(r"_ZN5specv19lm_head_mfma_kernelILi(\d+)ELNS_9MfmaLoadsE([012])ELb([01])ELb([01])E", head[1])
+                code = out.setdefault((int(m[1]), int(m[2]), m[3] == "1", m[4] == "1"), []) if m else None
                 continue
             m = re.match(r"\s+(\S.*?)\s*// ([0-9A-F]+):(.*)", line)
             if m and code is not None:
                 code.append((int(m[2], 16), m[1].strip(), m[3]))
-    # 9..16 row tiles, stores nontemporal or not, with block summaries or not; 11..16 also with nontemporal loads, without summaries
-    assert len(out) == 32 + 12, sorted(out)
+    # 9..16 row tiles, stores nontemporal or not: buffer loads with and without block summaries, global loads; 11..16: nontemporal loads
+    assert len(out) == 48 + 12, sorted(out)
     return out
 
 
 def test_loads_and_stores_are_nontemporal_where_asked_for(kernels):
     """The compiler may merge a nontemporal and an ordinary store of the same value; the 16-byte stores of the logits, and the loads of
     the weights, must be what the instantiation says."""
-    for (tm, stream, nt, summary), code in kernels.items():
+    for (tm, kind, nt, summary), code in kernels.items():
+        stream = kind == 2
         stores = [t for _, t, _ in code if t.startswith("global_store_dwordx4")]
         loads = [t for _, t, _ in code if re.match(r"(global|buffer)_load_dwordx4", t)]       # (of W; hidden goes to LDS directly)
         assert stores and loads
