@@ -25,6 +25,7 @@ import csv
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -101,11 +102,15 @@ def algorithmic(cfg, b):
     )
 
 
+def instantiation(full: str) -> str:
+    """'void specv::k<16, (specv::Loads)1, false>(int)' -> 'specv::k<16, 1, false>'"""
+    return re.sub(r"\((?:\w+::)*\w+\)(?=\d)", "", full.replace("void ", "")).split("(")[0]
+
+
 def short_kernel_name(full: str) -> str:
     """'void specv::lm_head_mfma_kernel<13, false, false>(...)' -> 'lm_head_mfma_kernel'; instantiations that do different work in one run are
     told apart: the packed LM head kernel on a row-major matrix, and the sums of exponentials before the residual sums of acceptance."""
-    s = full.replace("void ", "").split("(")[0]
-    name, _, args = s.partition("<")
+    name, _, args = instantiation(full).partition("<")
     name, args = name.split("::")[-1].strip(), [a.strip() for a in args.rstrip(">").split(",")]
     if name == "lm_head_packed_kernel" and args[-1] == "true":
         return name + "(row-major)"
@@ -563,7 +568,7 @@ def summarize_counters(args):
         f = sum(F[k]) / len(F[k])
         w = sum(W[k]) / len(W[k]) if k in W else 0.0
         fm, wm = f * sf * 1024 / 1e6, w * sw * 1024 / 1e6
-        rows.append((k.replace("void ", "").split("(")[0], len(F[k]), f, w, fm, wm, alg.get(short)))
+        rows.append((instantiation(k), len(F[k]), f, w, fm, wm, alg.get(short)))
         if "probe" in short or "pack_kernel" in short:   # not part of a step
             continue
         assert f"{name}:{short}" not in table, f"two kernels named {short}: key them apart before summing anything"
@@ -605,7 +610,7 @@ def summarize_sq(args):
     agg = collections.defaultdict(lambda: collections.defaultdict(list))
     for r in csv.DictReader(open(args.summarize_sq)):
         if "specv::" in r["Kernel_Name"]:
-            k = r["Kernel_Name"].split("(")[0].replace("void ", "")
+            k = instantiation(r["Kernel_Name"])
             agg[k][r["Counter_Name"]].append(float(r["Counter_Value"]))
             if r["Counter_Name"] == "GRBM_GUI_ACTIVE":
                 agg[k]["_us"].append((float(r["End_Timestamp"]) - float(r["Start_Timestamp"])) / 1e3)
@@ -673,7 +678,7 @@ def summarize_trace(args):
         o.write("Kernel-trace statistics of the library's kernels (durations in microseconds):\n\n")
         o.write("| kernel | calls | avg us | min us | max us | stddev us |\n|---|---|---|---|---|---|\n")
         for r in rows:
-            k = r["Name"].replace("void ", "").split("(")[0]
+            k = instantiation(r["Name"])
             o.write(f"| {k} | {r['Calls']} | {float(r['AverageNs']) / 1e3:.2f} | {float(r['MinNs']) / 1e3:.2f} | "
                     f"{float(r['MaxNs']) / 1e3:.2f} | {float(r['StdDev']) / 1e3:.2f} |\n")
     print(open(md).read())

@@ -13,10 +13,11 @@ def test_kernels_of_one_run_have_names_of_their_own():
            "void specv::lm_head_packed_kernel<10, 1, 8, true, 2, false, true, true>(unsigned short const*, int)",
            "void specv::accept_bonus_kernel<false, true>(specv::DecideArgs, specv::AcceptWorkspace, bool)",
            "void specv::accept_bonus_kernel<false, false>(specv::DecideArgs, specv::AcceptWorkspace, bool)",
-           "void specv::lm_head_mfma_kernel<12, true, false>(unsigned short const*)", "specv::accept_decide_kernel(specv::DecideArgs)"]
+           "void specv::lm_head_mfma_kernel<12, (specv::MfmaLoads)1, true, false>(unsigned short const*)", "specv::accept_decide_kernel(specv::DecideArgs)"]
     names = [bench.short_kernel_name(k) for k in run]
     assert names == ["lm_head_packed_kernel", "lm_head_packed_kernel(row-major)", "accept_bonus_kernel(exponentials)", "accept_bonus_kernel(residual)",
                      "lm_head_mfma_kernel", "accept_decide_kernel"]
+    assert bench.instantiation(run[4]) == "specv::lm_head_mfma_kernel<12, 1, true, false>"
 
 
 def test_kernels_that_carry_a_call_exist():
