@@ -13,9 +13,9 @@
 //   * a wave is its own latency hiding: everything it needs is requested 2.5 to 4 slabs (2-4 us) ahead, hidden fragments are read
 //     from LDS across the border of two slabs, and the stores of a tile drain under the first steps of the next one.
 // What bounds it: the issue slots (a wave issues 16 instructions in the time of 4 MFMAs, 64 cycles), and the power that the operands' way from L2
-// costs.  M = 1152, V = 151936, H = 4096 takes 1150-1190 us (1.2 PFLOP/s; 1240-1270 with vector address arithmetic, branches per group and a full stop at every
+// costs.  M = 1152, V = 151936, H = 4096 takes 1150 us (1.25 PFLOP/s; 1240-1270 with vector address arithmetic, branches per group and a full stop at every
 // slab and tile); 1119 without any store of logits, 800 with operands that stay in registers.  With one row group (161..256 rows) it is the stream of W,
-// as in the weight-streaming kernel: M = 192 270 us, 4.9 TB/s.
+// as in the weight-streaming kernel: M = 188 247 us, 5.5 TB/s.
 // The batch is cut into row groups of whole 16-row tiles, nearly equal and at most 256 rows each; the grid is groups x panel ranges, the groups of a
 // range run on the same XCD at the same time and share that range's panels through the XCD's L2, so HBM sees W once.
 // Per output element the products are added in the same order as in the other LM-head kernels (k ascending, one
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     // the next pass, so the pipeline never drains between tiles.
     // A step is 2 TM groups of 4 MFMAs (one hidden fragment against the wave's 4 panels).  A wave issues one instruction in
     // 4 cycles and a group keeps the matrix core busy for 64: everything else of a group has to fit 12 slots, so a request is
-    // one load with a scalar base and a step without branches (FOUR: a full pass, the wave owns all four panels) does no vector arithmetic.
+    // one load with a scalar base and a step does no vector arithmetic.
     // Requests of step s, in program order (fenced: the in-order completion of a wave's requests is what every wait counts on):
     //   groups 0..3            W chunk k-tile 1 of slab s+3 (its ring slot was consumed at the end of the previous step)
     //   groups 4..4+QN-1       direct loads of hidden slab s+3 into the LDS slot of slab s-1
@@ -239,21 +239,20 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     // younger requests in flight, i.e. it covers requests at least 1.75 steps old, and a direct load is needed 2.5 steps
     // after it was issued: it is never what the math waits for.
     static_assert(4 + QN <= TM && TM + 3 <= 2 * TM - 6, "the requests of a step precede its barrier");
-    // FIRST: the first slab of a pass (the products start from zero).  last_iter: the last 4 slabs of a pass.
+    // FIRST: the first slab of a pass (the products start from zero).  SLOTS: panels per wave whose products are taken.  last_iter: the last 4 slabs of a pass.
     // stores: the counted stores of a tile were issued between the requests for slab s+1 and this step.
-    auto do_step = [&](auto rc, auto first_c, auto four_c, bool last_iter, bool stores) SPECV_INLINE {
+    auto do_step = [&](auto rc, auto first_c, auto slots_c, bool last_iter, bool stores) SPECV_INLINE {
         constexpr int r = decltype(rc)::value;        // ring slot of slab s
         constexpr int rp = (r + 3) % RW;              // ring slot of slab s-1 = of slab s+3
-        constexpr bool FIRST = decltype(first_c)::value, FOUR = decltype(four_c)::value;
+        constexpr bool FIRST = decltype(first_c)::value;
+        constexpr int SLOTS = decltype(slots_c)::value;
         constexpr int g0 = r * 2 * TM;                // running group index (8 TM groups of 4 steps are a multiple of kHfRing)
         static_for<2 * TM>([&](auto ic) SPECV_INLINE {
             constexpr int i = decltype(ic)::value, t = i / TM, tm = i % TM;
             const bf16x8 h = hfq[(g0 + i) % kHfRing];
             if (tm < TM - 1 || full_tm) {             // wave-uniform
 #pragma unroll
-                for (int tn = 0; tn < kMfTN; ++tn) {
-                    // wave-uniform: slots 2 and 3 cost no MFMA where the wave does not own them (0 and 1 are always computed)
-                    if (!FOUR && tn >= kMfTN - 2 && tn >= wave_np) continue;
+                for (int tn = 0; tn < SLOTS; ++tn) {
                     if constexpr (FIRST && t == 0)
                         asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
                     else
@@ -269,9 +268,9 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
                 hfq[(g0 + i + kHfCross) % kHfRing] =
                     hfrag(std::integral_constant<int, (r + 1) % RW>{}, std::integral_constant<int, i + kHfCross - 2 * TM>{});
             }
-            if constexpr (i < 4) fetch_w1(rp, 1, i);
-            else if constexpr (i < 4 + QN) stage_h1(rp, i - 4);
-            else if constexpr (i >= TM && i < TM + 4) fetch_w1(r, 0, i - TM);
+            if constexpr (i < SLOTS) fetch_w1(rp, 1, i);
+            else if constexpr (i >= 4 && i < 4 + QN) stage_h1(rp, i - 4);
+            else if constexpr (i >= TM && i < TM + SLOTS) fetch_w1(r, 0, i - TM);
             if constexpr (i == 4) {                   // W goes on to slab s+4: after the last one of a pass, to the next pass's panels
                 wpos += 2048;
                 if (r == 0 && last_iter) open_panels(p0_next, np_next);
@@ -282,10 +281,11 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
             }
             if constexpr (i == 2 * TM - kHfCross - 1) {
                 // Slab s+1 must be complete in LDS before anybody reads it.  This wave's share was requested in groups 4.. of
-                // step s-2; younger than it are 4 W loads of that step and the 8 + QN requests of each of the two steps since.
+                // step s-2; younger than it are SLOTS W loads of that step and the 2 SLOTS + QN requests of each of the two steps since
+                // (more where those steps were of a pass with more slots).
                 // Where a tile was stored by counted stores in between, 4 for each of its TM or TM - 1 row tiles are younger still, and
                 // waiting for all but 63 (the most the counter holds) lets them drain for two steps.  No LDS read of slab s is pending either: its slot may be overwritten.
-                constexpr int kYounger = 2 * QN + 20;
+                constexpr int kYounger = 2 * QN + 5 * SLOTS;
                 constexpr int kDrain = kYounger + 4 * (TM - 1) < 63 ? kYounger + 4 * (TM - 1) : 63;
                 static_assert(kYounger < 63, "s_waitcnt vmcnt has 6 bits");
                 if (stores) __builtin_amdgcn_s_waitcnt(0x0070 | (kDrain & 15) | ((kDrain >> 4) << 14));
@@ -297,17 +297,17 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    auto do_steps = [&](auto first_c, auto four_c, bool last_iter, bool stores) SPECV_INLINE {
+    auto do_steps = [&](auto first_c, auto slots_c, bool last_iter, bool stores) SPECV_INLINE {
         constexpr bool FIRST = decltype(first_c)::value;
-        do_step(std::integral_constant<int, 0>{}, first_c, four_c, last_iter, FIRST && stores);
-        do_step(std::integral_constant<int, 1>{}, std::false_type{}, four_c, false, FIRST && stores);
-        do_step(std::integral_constant<int, 2>{}, std::false_type{}, four_c, false, false);
-        do_step(std::integral_constant<int, 3>{}, std::false_type{}, four_c, false, false);
+        do_step(std::integral_constant<int, 0>{}, first_c, slots_c, last_iter, FIRST && stores);
+        do_step(std::integral_constant<int, 1>{}, std::false_type{}, slots_c, false, FIRST && stores);
+        do_step(std::integral_constant<int, 2>{}, std::false_type{}, slots_c, false, false);
+        do_step(std::integral_constant<int, 3>{}, std::false_type{}, slots_c, false, false);
     };
     // Stores the finished tile of pass `pass`; returns whether it did so by exactly 4 stores per row tile.
-    auto store_tile = [&](int pass, int st_p0, int st_np, auto full_c) SPECV_INLINE {
-        constexpr bool FULL = decltype(full_c)::value;    // a full pass: four panels, all inside the matrix
-        const bool whole = !SUMMARY && st_np > 0 && (FULL || (st_p0 + st_np) * 16 <= V);
+    auto store_tile = [&](int pass, int st_p0, int st_np, auto slots_c) SPECV_INLINE {
+        constexpr int SLOTS = decltype(slots_c)::value;
+        const bool whole = !SUMMARY && st_np > 0 && (st_p0 + st_np) * 16 <= V;
         // acc[tn][tm][i] = C[row 16 tm + l16][entry 16 (st_p0 + tn) + 4 kg + i]
         // (SUMMARY) block of this wave and pass; its span is written once, by the first row group
         int blk = 0, count = 0;
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
             f32x4 v[4];
             auto put = [&](auto tmc) SPECV_INLINE {
 #pragma unroll
-                for (int tn = 0; tn < kMfTN; ++tn)
+                for (int tn = 0; tn < SLOTS; ++tn)
                     *reinterpret_cast<f32x4*>(patch + l16_e * kMfPatchPitch + (tn * 16 + kg_e * 4) * 4) = acc[tn][decltype(tmc)::value];
             };
             put(std::integral_constant<int, 0>{});
@@ -376,9 +376,9 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
             const uint32_t sat_step = (uint32_t)kRowsPerStore * (uint32_t)sm.blocks;
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
-                f32x4 t[kMfTN];
+                f32x4 t[SLOTS];
 #pragma unroll
-                for (int tn = 0; tn < kMfTN; ++tn) {
+                for (int tn = 0; tn < SLOTS; ++tn) {
                     t[tn] = acc[tn][tm];
                     *reinterpret_cast<f32x4*>(patch + l16_e * kMfPatchPitch + (tn * 16 + kg_e * 4) * 4) = t[tn];
                 }
@@ -433,24 +433,28 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         return whole;
     };
 
-    // Full passes are in code of their own: where ways with and without the fourth panel meet, the compiler would move the whole ring to
-    // other registers, and wait for every request in flight to do so.
+    // The last pass of a range, which has 1..16 panels, is in code of its own for two and for three panels per wave: no branches, and waits that count
+    // its requests (a wave that owns fewer repeats its last panel).  One code for any number, with a run-time test of the wave's panels in every
+    // group -> these, us: V = 151936, H = 4096 M = 188 262 -> 247, M = 576 619 -> 606, M = 1152 1161 -> 1148; V = 32000 M = 188 76 -> 59.  Where ways with
+    // and without the fourth panel meet, the compiler would also move the whole ring to other registers, and wait for every request in flight to do so.
     // In each, the first four steps stand outside the loop: there, and only there, the waits know of the stores of the tile before.
     bool stored = false;                              // a tile's counted stores precede this pass
-    auto one_pass = [&](auto four_c) SPECV_INLINE {
-        do_steps(std::true_type{}, four_c, nslab == RW, stored);
-        for (int s = RW; s < nslab; s += RW) do_steps(std::false_type{}, four_c, s + RW == nslab, false);
+    auto one_pass = [&](auto slots_c) SPECV_INLINE {
+        do_steps(std::true_type{}, slots_c, nslab == RW, stored);
+        for (int s = RW; s < nslab; s += RW) do_steps(std::false_type{}, slots_c, s + RW == nslab, false);
         // the tile is complete; the next pass's first slabs are already in flight
-        stored = store_tile(pass, wave_p0, wave_np, four_c);
+        stored = store_tile(pass, wave_p0, wave_np, slots_c);
     };
-    const int full = mf_full_passes(p_begin, p_end, V);
-    while (pass < full) {
-        one_pass(std::true_type{});
+    const int slots = mf_last_slots(n_own);
+    const int full = mf_full_passes(p_begin, p_end, V), four = slots == kMfTN ? npass : full;      // (full: npass or npass - 1)
+    while (pass < four) {
+        one_pass(std::integral_constant<int, kMfTN>{});
         ++pass;
         wave_p0 = p0_next; wave_np = np_next;
         pass_panels(min(pass + 1, npass - 1), p0_next, np_next);
     }
-    if (pass < npass) one_pass(std::false_type{});
+    if (slots == 2) one_pass(std::integral_constant<int, 2>{});
+    else if (slots == 3) one_pass(std::integral_constant<int, 3>{});
     if constexpr (SUMMARY) {                          // block slots of passes this range does not have
         if (group == 0)
             for (int b = npass * kMfWaves + tid; b < sm.passes_per_range * kMfWaves; b += 64 * kMfWaves) {

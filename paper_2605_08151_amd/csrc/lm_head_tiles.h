@@ -78,12 +78,19 @@ constexpr PanelShare mf_panel_share(int p_begin, int p_end, int pass, int wave)
     return {lo + first, (wave + 1) * m / kMfWaves - first};
 }
 
-// Passes of the range that the kernel's code for full ones serves: 16 panels, all their entries in the matrix.  All passes, where the panels divide
-// and the last one is not padded, else all but the last (V = 32000, H = 4096, one full pass per range: M = 257 69 -> 62 us, M = 416 92 -> 87
-// against its code for any number of panels, which tests the wave's share in every group).
+// Passes of the range with 16 panels, all their entries in the matrix: all, where the panels divide and the last one is not padded, else all but the
+// last.
 constexpr int mf_full_passes(int p_begin, int p_end, int V)
 {
     return (p_end - p_begin - (p_end * 16 > V ? 1 : 0)) / kMfPassPanels;
+}
+
+// Panels per wave that the code of a range's last pass serves: 2, 3 or 4 (one panel in code for one would not be faster: the pass is bound by
+// the fragments of hidden that every wave reads from LDS).
+constexpr int mf_last_slots(int n_own)
+{
+    const int m = (n_own - 1) % kMfPassPanels + 1, most = (m + kMfWaves - 1) / kMfWaves;
+    return most < 2 ? 2 : most;
 }
 
 // Byte distance of panel slot tn from the wave's first panel.  A slot past the wave's share repeats its last panel (the L2 or the
