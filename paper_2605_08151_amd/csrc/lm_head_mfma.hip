@@ -20,6 +20,17 @@ static bool mfma_nt(int M, int V)
     return forced == 1 || (forced == 0 && M <= 416 && V % 16 == 0);
 }
 
+// One row group reads W once, bound by that stream: nontemporal, by the rule of the weight-streaming kernel (the tree step, M = 188, V = 151936,
+// H = 4096 378 -> 360 us, M = 216 408 -> 394; V = 64000, H = 2560 179 -> 167).
+// Several groups that read panels a multiple of 64 KB apart: global loads (buffer -> global, V = 151936 / 100000, H = 4096: M = 257 357 -> 330 /
+// 264 -> 247 us, M = 576 622 -> 606 / 408 -> 395, M = 1152 1157 -> 1119 / 793 -> 782; H = 2048 M = 257 191 -> 179, M = 576 351 -> 328).  Elsewhere
+// buffer loads (H = 2560: M = 576 398 -> 409 / 260 -> 265, M = 1152 757 -> 779; H = 3072 854 -> 902; H = 1024 357 -> 360).
+static MfmaLoads mfma_loads(int groups, int H, int V)
+{
+    if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8) return kStreamLoads;
+    return groups > 1 && H % 2048 == 0 ? kGlobalLoads : kBufferLoads;
+}
+
 // blocks per row of the summaries for this shape; 0 if the large-tile kernel does not take it
 int lm_head_mfma_blocks(int M, int H, int V)
 {
@@ -44,14 +55,15 @@ int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M
     }
     const bool nt = mfma_nt(M, V);
     if (summary) return lm_head_mfma_summary(nt, a, wp, c, M, H, V, L, sm, s);
-    // One row group reads W once, bound by that stream: nontemporal, by the rule of the weight-streaming kernel (the tree step, M = 188, V = 151936,
-    // H = 4096 378 -> 360 us, M = 216 408 -> 394; V = 64000, H = 2560 179 -> 167).
-    if (L.groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8) return lm_head_mfma_stream(nt, a, wp, c, M, H, V, L, sm, s);
-    // Several groups that read panels a multiple of 64 KB apart: global loads (buffer -> global, V = 151936 / 100000, H = 4096: M = 257 357 -> 330 /
-    // 264 -> 247 us, M = 576 622 -> 606 / 408 -> 395, M = 1152 1157 -> 1119 / 793 -> 782; H = 2048 M = 257 191 -> 179, M = 576 351 -> 328).  Elsewhere
-    // buffer loads (H = 2560: M = 576 398 -> 409 / 260 -> 265, M = 1152 757 -> 779; H = 3072 854 -> 902; H = 1024 357 -> 360).
-    if (L.groups > 1 && H % 2048 == 0) return lm_head_mfma_global(nt, a, wp, c, M, H, V, L, sm, s);
-    return lm_head_mfma_buffer(nt, a, wp, c, M, H, V, L, sm, s);
+    if (g_lm_mfma_rows == 0 && g_lm_mfma_nt == 0) {      // (the benchmark hooks speak of groups of at most 16 tiles)
+        const MfmaLayout T = mfma_tall_layout_for(M, V, device_cu_count());
+        if (T.groups > 0) return lm_head_tile(mfma_loads(T.groups, H, V), nt, a, wp, c, M, H, V, T, s);
+    }
+    switch (mfma_loads(L.groups, H, V)) {
+        case kStreamLoads: return lm_head_mfma_stream(nt, a, wp, c, M, H, V, L, sm, s);
+        case kGlobalLoads: return lm_head_mfma_global(nt, a, wp, c, M, H, V, L, sm, s);
+        default: return lm_head_mfma_buffer(nt, a, wp, c, M, H, V, L, sm, s);
+    }
 }
 
 }  // namespace specv

@@ -4,7 +4,8 @@
 // With hundreds of rows the LM head is a dense contraction bound by the matrix cores, and what starves them is operand
 // traffic: L2 -> CU bytes per flop fall with the workgroup's tile area, LDS bytes per flop with the vocabulary width a wave
 // covers.  So: ONE wave per SIMD with the whole register file (512 registers), each wave holding a tile of
-// 16 TM rows x 64 vocabulary entries in the accumulation registers (TM <= 16: the workgroup tile is up to 256 x 256),
+// 16 TM rows x 64 vocabulary entries in the accumulation registers (TM <= 16: the workgroup tile is up to 256 x 256; 17 and 18 with the rest
+// in vector registers),
 //   * W goes from L2/HBM straight into MFMA operand registers (the packed layout is the A operand of
 //     v_mfma_f32_16x16x32_bf16 lane by lane), through a ring of 4 slabs of 64 k, each chunk requested again right
 //     after the MFMAs that consumed it: no W byte touches LDS;
@@ -13,10 +14,10 @@
 //   * a wave is its own latency hiding: everything it needs is requested 2.5 to 4 slabs (2-4 us) ahead, hidden fragments are read
 //     from LDS across the border of two slabs, and the stores of a tile drain under the first steps of the next one.
 // What bounds it: the issue slots (a wave issues 16 instructions in the time of 4 MFMAs, 64 cycles), and the power that the operands' way from L2
-// costs.  M = 1152, V = 151936, H = 4096 takes 1150 us (1.25 PFLOP/s; 1240-1270 with vector address arithmetic, branches per group and a full stop at every
+// costs.  M = 1152, V = 151936, H = 4096 takes 1097 us in groups of 18 tiles (1.31 PFLOP/s), 1150 of 15 ( 1240-1270 with vector address arithmetic, branches per group and a full stop at every
 // slab and tile); 1119 without any store of logits, 800 with operands that stay in registers.  With one row group (161..256 rows) it is the stream of W,
 // as in the weight-streaming kernel: M = 188 247 us, 5.5 TB/s.
-// The batch is cut into row groups of whole 16-row tiles, nearly equal and at most 256 rows each; the grid is groups x panel ranges, the groups of a
+// The batch is cut into row groups of whole 16-row tiles, nearly equal and at most 288 rows each; the grid is groups x panel ranges, the groups of a
 // range run on the same XCD at the same time and share that range's panels through the XCD's L2, so HBM sees W once.
 // Per output element the products are added in the same order as in the other LM-head kernels (k ascending, one
 // fp32 accumulator), so the logits are bit-identical to theirs.
@@ -33,7 +34,12 @@ namespace specv {
 constexpr int kMfSlab = 64;                    // k per slab
 constexpr int kMfPitch = kMfSlab * 2;          // bytes per hidden row in LDS; 16-byte chunk c of row r sits at c ^ ((r >> 1) & 7)
 constexpr int kMfRing = 4;                     // slabs in flight: hidden slabs in LDS = W slabs in registers
-constexpr int kMfPatchPitch = kMfTN * 64 + 16; // bytes per row of a wave's store patch
+// bytes per row of a wave's store patch: padded by 16, or for more than 16 row tiles, which leave no LDS for padding, swizzled
+constexpr int mf_patch_pitch(int tm) { return kMfTN * 64 + (tm > 16 ? 0 : 16); }
+constexpr size_t mf_lds_bytes(int tm, bool summary)
+{
+    return (size_t)kMfRing * ((tm * 16 + 31) / 32 * 32) * kMfPitch + (size_t)kMfWaves * 16 * mf_patch_pitch(tm) + (summary ? tm * 16 * 4 : 0);
+}
 
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // (a row of logits starts at any multiple of 4 bytes)
 
@@ -55,7 +61,7 @@ __device__ inline void lds_dma16_off(uint32_t off, const void* base, void* lds_b
 enum MfmaLoads { kBufferLoads, kGlobalLoads, kStreamLoads };   // buffer loads; global loads; nontemporal global loads
 
 template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
-__global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
+__device__ __forceinline__ void lm_head_mfma_tiles(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
     int M_all, int H, int V, int n_panels, int panels_per_wg, int groups, int tiles_lo, int groups_hi,
     LmSummary sm)
@@ -99,8 +105,14 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     const int nslab = H / kMfSlab;                    // a multiple of 4 (host check)
 
     unsigned char* hbuf = smem;                                        // kMfRing slabs
-    unsigned char* patch = smem + kMfRing * kSlabBytes + wave * (16 * kMfPatchPitch);
-    float* row_scale = reinterpret_cast<float*>(smem + kMfRing * kSlabBytes + kMfWaves * (16 * kMfPatchPitch));   // [TM * 16], SUMMARY only
+    constexpr int kPatchPitch = mf_patch_pitch(TM);
+    // position of the 16 bytes that hold entries 4 c .. 4 c + 3 of row r in the wave's store patch
+    auto patch_at = [&](int r, int c) SPECV_INLINE {
+        if constexpr (kPatchPitch == kMfTN * 64) c ^= r;
+        return r * kPatchPitch + c * 16;
+    };
+    unsigned char* patch = smem + kMfRing * kSlabBytes + wave * (16 * kPatchPitch);
+    float* row_scale = reinterpret_cast<float*>(smem + kMfRing * kSlabBytes + kMfWaves * (16 * kPatchPitch));   // [TM * 16], SUMMARY only
     if constexpr (SUMMARY) {
         // log2(e) / T of each row's request (0: greedy, or no such row); read again only after many barriers
         for (int r = tid; r < TM * 16; r += 64 * kMfWaves) {
@@ -171,22 +183,23 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
 
     // LDS offset of this lane's fragment of row tile 0, k-tile t inside a slab: row l16, chunk (4 t + kg) ^ ((l16 >> 1) & 7)
     // (row 16 tm + l16 has the same swizzle term: 8 tm vanishes under & 7)
-    // and the same for slots 2 and 3, so that every fragment is one of four registers plus a 16-bit immediate
+    // and the same for the other slots, so that every fragment is one of four registers (eight where two slabs are too long) plus a 16-bit immediate
     typedef __attribute__((address_space(3))) const unsigned char* LdsPtr;
-    uint32_t hf_at[2][2];
+    constexpr int kHfSlots = kSlabBytes + (TM - 1) * 16 * kMfPitch < 65536 ? 2 : 1;      // ring slots per register
+    uint32_t hf_at[RW / kHfSlots][2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            hf_at[u][t] = (uint32_t)(uintptr_t)(LdsPtr)hbuf + (uint32_t)(u * 2 * kSlabBytes + l16 * kMfPitch + (((t * 4 + kg) ^ ((l16 >> 1) & 7)) << 4));
+        for (int u = 0; u < RW / kHfSlots; ++u) {
+            hf_at[u][t] = (uint32_t)(uintptr_t)(LdsPtr)hbuf + (uint32_t)(u * kHfSlots * kSlabBytes + l16 * kMfPitch + (((t * 4 + kg) ^ ((l16 >> 1) & 7)) << 4));
             asm volatile("" : "+v"(hf_at[u][t]));     // (the compiler would keep a register per distant fragment instead)
         }
     bf16x8 hfq[kHfRing];
     auto hfrag = [&](auto rc, auto ic) SPECV_INLINE {              // fragment i = t * TM + tm of the slab in ring slot r
         constexpr int r = decltype(rc)::value, i = decltype(ic)::value;
-        static_assert(kSlabBytes + (TM - 1) * 16 * kMfPitch < 65536, "16-bit LDS offsets");
+        static_assert((kHfSlots - 1) * kSlabBytes + (TM - 1) * 16 * kMfPitch < 65536, "16-bit LDS offsets");
         return *reinterpret_cast<__attribute__((address_space(3))) const bf16x8*>(
-            (LdsPtr)(uintptr_t)hf_at[r / 2][i / TM] + ((r & 1) * kSlabBytes + (i % TM) * (16 * kMfPitch)));
+            (LdsPtr)(uintptr_t)hf_at[r / kHfSlots][i / TM] + ((r % kHfSlots) * kSlabBytes + (i % TM) * (16 * kMfPitch)));
     };
 
     int pass = 0, p0_next, np_next;
@@ -253,7 +266,11 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
             if (tm < TM - 1 || full_tm) {             // wave-uniform
 #pragma unroll
                 for (int tn = 0; tn < SLOTS; ++tn) {
-                    if constexpr (FIRST && t == 0)
+                    if constexpr (FIRST && t == 0 && tm >= 16)
+                        asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
+                    else if constexpr (tm >= 16)
+                        asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
+                    else if constexpr (FIRST && t == 0)
                         asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
                     else
                         asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[tn][tm]) : "v"(wreg[r][t][tn]), "v"(h));
@@ -333,7 +350,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
             auto put = [&](auto tmc) SPECV_INLINE {
 #pragma unroll
                 for (int tn = 0; tn < SLOTS; ++tn)
-                    *reinterpret_cast<f32x4*>(patch + l16_e * kMfPatchPitch + (tn * 16 + kg_e * 4) * 4) = acc[tn][decltype(tmc)::value];
+                    *reinterpret_cast<f32x4*>(patch + patch_at(l16_e, tn * 4 + kg_e)) = acc[tn][decltype(tmc)::value];
             };
             put(std::integral_constant<int, 0>{});
             static_for<TM>([&](auto tmc) SPECV_INLINE {
@@ -344,7 +361,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int prow = RAGGED ? min(q * 4 + srow, last) : q * 4 + srow;
-                        v[q] = *reinterpret_cast<const f32x4*>(patch + prow * kMfPatchPitch + scol * 4);
+                        v[q] = *reinterpret_cast<const f32x4*>(patch + patch_at(prow, scol >> 2));
                     }
                     if constexpr (tm + 1 < TM) { if (tm + 1 < TM - 1 || full_tm) put(std::integral_constant<int, tm + 1>{}); }
                     __builtin_amdgcn_sched_barrier(0);
@@ -380,12 +397,12 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
 #pragma unroll
                 for (int tn = 0; tn < SLOTS; ++tn) {
                     t[tn] = acc[tn][tm];
-                    *reinterpret_cast<f32x4*>(patch + l16_e * kMfPatchPitch + (tn * 16 + kg_e * 4) * 4) = t[tn];
+                    *reinterpret_cast<f32x4*>(patch + patch_at(l16_e, tn * 4 + kg_e)) = t[tn];
                 }
 #pragma unroll
                 for (int q = 0; q < 16 / kRowsPerStore; ++q) {
                     const int prow = q * kRowsPerStore + srow;
-                    const f32x4 v = *reinterpret_cast<const f32x4*>(patch + prow * kMfPatchPitch + scol * 4);
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(patch + patch_at(prow, scol >> 2));
                     if constexpr (SUMMARY) {
                         // In this layout a row's 64 entries lie in the 16 lanes of one 16-lane row, 4 consecutive entries
                         // each (the values are in registers for the store anyway; taking them from the accumulators instead
@@ -445,7 +462,9 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         // the tile is complete; the next pass's first slabs are already in flight
         stored = store_tile(pass, wave_p0, wave_np, slots_c);
     };
-    const int slots = mf_last_slots(n_own);
+    // (beyond 16 row tiles the code for three leaves the compiler short of registers: it moves accumulators inside the steps; four serve it)
+    constexpr bool THREE = TM <= 16;
+    const int slots = !THREE && mf_last_slots(n_own) == 3 ? kMfTN : mf_last_slots(n_own);
     const int full = mf_full_passes(p_begin, p_end, V), four = slots == kMfTN ? npass : full;      // (full: npass or npass - 1)
     while (pass < four) {
         one_pass(std::integral_constant<int, kMfTN>{});
@@ -454,7 +473,7 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
         pass_panels(min(pass + 1, npass - 1), p0_next, np_next);
     }
     if (slots == 2) one_pass(std::integral_constant<int, 2>{});
-    else if (slots == 3) one_pass(std::integral_constant<int, 3>{});
+    if constexpr (THREE) { if (slots == 3) one_pass(std::integral_constant<int, 3>{}); }
     if constexpr (SUMMARY) {                          // block slots of passes this range does not have
         if (group == 0)
             for (int b = npass * kMfWaves + tid; b < sm.passes_per_range * kMfWaves; b += 64 * kMfWaves) {
@@ -465,11 +484,28 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     __builtin_amdgcn_s_waitcnt(0x0F70);               // no direct load of this wave is still landing when the LDS is given up
 }
 
+// up to 16 row tiles per group
+template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
+__global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp, float* __restrict__ C, int M, int H, int V, int n_panels, int panels_per_wg,
+    int groups, int tiles_lo, int groups_hi, LmSummary sm)
+{
+    lm_head_mfma_tiles<TM, LOADS, NT, SUMMARY>(A, Wp, C, M, H, V, n_panels, panels_per_wg, groups, tiles_lo, groups_hi, sm);
+}
+
+// 17 and 18: 16 tiles of accumulators fill the accumulation registers, the others are vector registers; LDS is full to the byte.  A kernel of its own name.
+template <int TM, MfmaLoads LOADS, bool NT>
+__global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_tile_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp, float* __restrict__ C, int M, int H, int V, int n_panels, int panels_per_wg,
+    int groups, int tiles_lo, int groups_hi)
+{
+    lm_head_mfma_tiles<TM, LOADS, NT, false>(A, Wp, C, M, H, V, n_panels, panels_per_wg, groups, tiles_lo, groups_hi, LmSummary{});
+}
+
 template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
 static int launch_mfma(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, LmSummary sm, hipStream_t s)
 {
-    constexpr int SR = (TM * 16 + 31) / 32 * 32;
-    const size_t smem = (size_t)kMfRing * SR * kMfPitch + (size_t)kMfWaves * 16 * kMfPatchPitch + (SUMMARY ? TM * 16 * 4 : 0);
+    constexpr size_t smem = mf_lds_bytes(TM, SUMMARY);
     static LdsGrantTable granted = {};
     if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_mfma_kernel<TM, LOADS, NT, SUMMARY>), smem, granted, "spec_lm_head_packed")) return rc;
     hipLaunchKernelGGL((lm_head_mfma_kernel<TM, LOADS, NT, SUMMARY>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
@@ -486,6 +522,20 @@ static int launch_mfma_tiles(bool nt, const uint16_t* a, const uint16_t* wp, flo
     if constexpr (TM < 16) return launch_mfma_tiles<LOADS, SUMMARY, TM + 1>(nt, a, wp, c, M, H, V, L, sm, s);
     else return fail(SPEC_ESHAPE, "spec_lm_head_packed: no large-tile instantiation for %d row tiles per group", L.tm);
 }
+
+template <int TM, MfmaLoads LOADS, bool NT>
+static int launch_tile(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, hipStream_t s)
+{
+    constexpr size_t smem = mf_lds_bytes(TM, false);
+    static_assert(smem <= 160 * 1024, "the LDS of a CU");
+    static LdsGrantTable granted = {};
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_tile_kernel<TM, LOADS, NT>), smem, granted, "spec_lm_head_packed")) return rc;
+    hipLaunchKernelGGL((lm_head_tile_kernel<TM, LOADS, NT>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
+                       (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi);
+    return SPEC_OK;
+}
+
+int lm_head_tile(MfmaLoads loads, bool nt, const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, hipStream_t s);
 
 #define SPECV_MFMA_FILE(name) int name(bool nt, const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, const LmSummary& sm, hipStream_t s)
 SPECV_MFMA_FILE(lm_head_mfma_buffer);

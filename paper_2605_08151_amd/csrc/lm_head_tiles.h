@@ -9,6 +9,7 @@ namespace specv {
 constexpr int kMfWaves = 4;                    // waves per workgroup
 constexpr int kMfTN = 4;                       // panels (16 vocabulary entries each) per wave
 constexpr int kMfPassPanels = kMfWaves * kMfTN;
+constexpr int kMfTallTM = 18;                  // row tiles per group at most
 
 // Row groups, panel ranges and the instantiation that serves them.
 struct MfmaLayout { int groups, tiles_lo, groups_hi, tm, ranges, per_range, passes_per_range, blocks; };
@@ -32,11 +33,24 @@ constexpr long mf_group_cost(int tiles, int groups, int n_panels, int cus)
     return slots * (2 * tm + 11);
 }
 
+constexpr MfmaLayout mf_layout_of(int tiles, int groups, int n_panels, int cus)
+{
+    MfmaLayout L{};
+    L.groups = groups;
+    L.tiles_lo = tiles / groups;                                         // groups of tiles_lo + 1 first, then of tiles_lo
+    L.groups_hi = tiles % groups;
+    L.tm = L.tiles_lo + (L.groups_hi ? 1 : 0);
+    L.per_range = mf_per_range(n_panels, groups, cus);
+    L.ranges = ((n_panels + L.per_range - 1) / L.per_range + 7) / 8 * 8;
+    L.passes_per_range = (L.per_range + kMfPassPanels - 1) / kMfPassPanels;
+    L.blocks = L.ranges * L.passes_per_range * kMfWaves;
+    return L;
+}
+
 // cap_rows: rows per group at most (144..256); anything else = automatic.
 constexpr MfmaLayout mfma_layout_for(int M, int V, int cus, int cap_rows)
 {
     constexpr int kMinTM = 9, kMaxTM = 16;                               // the kernel is built for 9..16 tiles per group
-    MfmaLayout L{};
     const int tiles = (M + 15) / 16;                                     // 16-row tiles of the batch
     const int n_panels = (V + 15) / 16;
     const bool forced = cap_rows >= 16 * kMinTM && cap_rows <= 16 * kMaxTM;
@@ -55,15 +69,34 @@ constexpr MfmaLayout mfma_layout_for(int M, int V, int cus, int cap_rows)
             if (cost < best) { best = cost; groups = g; }
         }
     }
-    L.groups = groups;
-    L.tiles_lo = tiles / groups;                                         // groups of tiles_lo + 1 first, then of tiles_lo
-    L.groups_hi = tiles % groups;
-    L.tm = L.tiles_lo + (L.groups_hi ? 1 : 0);
-    L.per_range = mf_per_range(n_panels, groups, cus);
-    L.ranges = ((n_panels + L.per_range - 1) / L.per_range + 7) / 8 * 8;
-    L.passes_per_range = (L.per_range + kMfPassPanels - 1) / kMfPassPanels;
-    L.blocks = L.ranges * L.passes_per_range * kMfWaves;
-    return L;
+    return mf_layout_of(tiles, groups, n_panels, cus);
+}
+
+// The same for groups of 17 or 18 tiles, which take fewer bytes from L2 per product and, where they make the number of groups a power of two, leave no CU
+// idle (3 groups of 12 and 5 of 15 occupy 240 of 256); groups == 0: up to 16 tiles it is.
+// By tenths of a panel slot: a last pass with two panels per wave costs 0.73 of a full one, with three 0.87 (all of it beyond 16 tiles, where the code for four
+// serves it).  Measured, at most 16 / 17 and 18 tiles, us: H = 4096 V = 151936 M = 272 344 / 322, M = 544 595 / 561, M = 576 606 / 586, M = 800 815 / 796,
+// M = 1056 1070 / 1021, M = 1152 1148 / 1097; V = 128256 M = 288 301 / 268, M = 576 540 / 476, M = 1152 987 / 909; V = 32000 M = 576 138 / 127, M = 1152 261 / 235;
+// H = 2560 V = 64000 M = 272 98 / 90, M = 576 184 / 162.  Not chosen: H = 4096 V = 100000 M = 576 403 / 419 (3 full passes and one panel),
+// V = 128256 M = 800 678 / 689; H = 1024 V = 32000 M = 288 25 / 28.5.
+constexpr long mf_tall_cost(int tiles, int groups, int n_panels, int cus)
+{
+    const int per_range = mf_per_range(n_panels, groups, cus), tm = (tiles + groups - 1) / groups;
+    const int rest = per_range % kMfPassPanels, last = (rest + kMfWaves - 1) / kMfWaves;
+    const long slots10 = (long)(per_range / kMfPassPanels) * 40 + (rest == 0 ? 0 : last <= 2 ? 29 : (last == 3 && tm <= 16) ? 35 : 40);
+    return slots10 * (2 * tm + 6);
+}
+
+constexpr MfmaLayout mfma_tall_layout_for(int M, int V, int cus)
+{
+    const int tiles = (M + 15) / 16, n_panels = (V + 15) / 16;
+    long best = mf_tall_cost(tiles, mfma_layout_for(M, V, cus, 0).groups, n_panels, cus);
+    int groups = 0;
+    for (int g = (tiles + kMfTallTM - 1) / kMfTallTM; (tiles + g - 1) / g > 16; ++g) {
+        const long cost = mf_tall_cost(tiles, g, n_panels, cus);
+        if (cost < best) { best = cost; groups = g; }
+    }
+    return groups == 0 ? MfmaLayout{} : mf_layout_of(tiles, groups, n_panels, cus);
 }
 
 struct PanelShare { int p0, np; };             // first panel and number of panels, 0 .. 4; p0 is a panel of the range also where np == 0
