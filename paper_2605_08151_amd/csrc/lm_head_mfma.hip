@@ -60,9 +60,9 @@ int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M
         if (T.groups > 0) return lm_head_tile(mfma_loads(T.groups, H, V), nt, a, wp, c, M, H, V, T, s);
     }
     switch (mfma_loads(L.groups, H, V)) {
-        case kStreamLoads: return lm_head_mfma_stream(nt, a, wp, c, M, H, V, L, sm, s);
+        case kStreamLoads: return L.tm < 11 ? lm_head_tile(kStreamLoads, nt, a, wp, c, M, H, V, L, s) : lm_head_mfma_stream(nt, a, wp, c, M, H, V, L, sm, s);
         case kGlobalLoads: return lm_head_mfma_global(nt, a, wp, c, M, H, V, L, sm, s);
-        default: return lm_head_mfma_buffer(nt, a, wp, c, M, H, V, L, sm, s);
+        default: return L.tm < 9 ? lm_head_tile(kBufferLoads, nt, a, wp, c, M, H, V, L, s) : lm_head_mfma_buffer(nt, a, wp, c, M, H, V, L, sm, s);
     }
 }
 

@@ -1,4 +1,4 @@
-// spec_lm_head_packed for batches of more than 160 rows: the MFMA-bound kernel (paper, Appendix "Target side": every
+// spec_lm_head_packed for batches of more than 160 rows, and for 113 to 160 where it is ahead of the weight-streaming kernel: the MFMA-bound kernel (paper, Appendix "Target side": every
 // position of every verification candidate is scored; the hybrid ordinary-parallel batch has ~1200 positions).
 //
 // With hundreds of rows the LM head is a dense contraction bound by the matrix cores, and what starves them is operand
@@ -14,8 +14,8 @@
 //   * a wave is its own latency hiding: everything it needs is requested 2.5 to 4 slabs (2-4 us) ahead, hidden fragments are read
 //     from LDS across the border of two slabs, and the stores of a tile drain under the first steps of the next one.
 // What bounds it: the issue slots (a wave issues 16 instructions in the time of 4 MFMAs, 64 cycles), and the power that the operands' way from L2
-// costs.  M = 1152, V = 151936, H = 4096 takes 1097 us in groups of 18 tiles (1.31 PFLOP/s), 1150 of 15 ( 1240-1270 with vector address arithmetic, branches per group and a full stop at every
-// slab and tile); 1119 without any store of logits, 800 with operands that stay in registers.  With one row group (161..256 rows) it is the stream of W,
+// costs.  M = 1152, V = 151936, H = 4096 takes 1097 us in groups of 18 tiles (1.31 PFLOP/s), 1150 of 15 (1240-1270 with vector address arithmetic, branches
+// per group and a full stop at every slab and tile; 1119 without any store of logits, 800 with operands that stay in registers).  With one row group (113..288 rows) it is the stream of W,
 // as in the weight-streaming kernel: M = 188 247 us, 5.5 TB/s.
 // The batch is cut into row groups of whole 16-row tiles, nearly equal and at most 288 rows each; the grid is groups x panel ranges, the groups of a
 // range run on the same XCD at the same time and share that range's panels through the XCD's L2, so HBM sees W once.
@@ -72,7 +72,7 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
     constexpr int QN = SR / 32;                       // direct loads per wave and slab
     constexpr int kSlabBytes = SR * kMfPitch;
     // hidden fragments are read from LDS ahead of their MFMAs: kHfCross groups at the border of two steps, kHfAhead inside one
-    constexpr int kHfCross = 5, kHfAhead = 7, kHfCatchUp = kHfAhead - kHfCross, kHfRing = 8;
+    constexpr int kHfCross = TM >= 9 ? 5 : 4, kHfAhead = 7, kHfCatchUp = kHfAhead - kHfCross, kHfRing = 8;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, l16 = lane & 15, kg = lane >> 4;
@@ -251,7 +251,7 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
     // loads only (the direct loads are invisible to the compiler): a wait for a chunk requested 3.5 steps ago allows ~28
     // younger requests in flight, i.e. it covers requests at least 1.75 steps old, and a direct load is needed 2.5 steps
     // after it was issued: it is never what the math waits for.
-    static_assert(4 + QN <= TM && TM + 3 <= 2 * TM - 6, "the requests of a step precede its barrier");
+    static_assert(4 + QN <= TM && TM + 3 <= 2 * TM - kHfCross - 1, "the requests of a step precede its barrier");
     // FIRST: the first slab of a pass (the products start from zero).  SLOTS: panels per wave whose products are taken.  last_iter: the last 4 slabs of a pass.
     // stores: the counted stores of a tile were issued between the requests for slab s+1 and this step.
     auto do_step = [&](auto rc, auto first_c, auto slots_c, bool last_iter, bool stores) SPECV_INLINE {
@@ -484,7 +484,7 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
     __builtin_amdgcn_s_waitcnt(0x0F70);               // no direct load of this wave is still landing when the LDS is given up
 }
 
-// up to 16 row tiles per group
+// 9 to 16 row tiles per group
 template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
 __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp, float* __restrict__ C, int M, int H, int V, int n_panels, int panels_per_wg,
@@ -493,7 +493,8 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_mfma_kernel(
     lm_head_mfma_tiles<TM, LOADS, NT, SUMMARY>(A, Wp, C, M, H, V, n_panels, panels_per_wg, groups, tiles_lo, groups_hi, sm);
 }
 
-// 17 and 18: 16 tiles of accumulators fill the accumulation registers, the others are vector registers; LDS is full to the byte.  A kernel of its own name.
+// 8 (and 9 and 10 with nontemporal loads): one group of 113 to 160 rows; 17 and 18: 16 tiles of accumulators fill the accumulation registers, the others are
+// vector registers, and LDS is full to the byte
 template <int TM, MfmaLoads LOADS, bool NT>
 __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_tile_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp, float* __restrict__ C, int M, int H, int V, int n_panels, int panels_per_wg,

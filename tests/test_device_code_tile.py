@@ -36,7 +36,7 @@ def kernels(tmp_path_factory):
             m = re.match(r"\s+(\S.*?)\s*// ([0-9A-F]+):(.*)", line)
             if m and code is not None:
                 code.append((int(m[2], 16), m[1].strip(), m[3]))
-    assert {k[0] for k in out} == {17, 18}, sorted(out)
+    assert {k[0] for k in out} == {8, 9, 10, 17, 18}, sorted(out)
     return out
 
 

@@ -84,3 +84,29 @@ def test_tall_groups(sv, oracle, M, V, H):
     finally:
         sv.spec_set_tuning("lm_packed_tile", 0)
     assert torch.equal(other, logits[:M])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [112, 113, 128, 129, 144, 145, 160])
+@pytest.mark.parametrize("V,H", [(999, 4096), (36864, 1280), (36880, 2048), (50021, 1280), (57344, 256), (70000, 256), (64013, 1024)])
+def test_lines_between_the_weight_streaming_and_the_large_tile_kernel(sv, oracle, M, V, H):
+    """8, 9 and 10 row tiles, whole and ragged; less than a panel, 9 (ordinary and nontemporal loads), 13, 14, 16 and 18 panels per CU, aligned rows of logits and not."""
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, H), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, H), generator=g, device="cuda").to(torch.bfloat16)
+    Wp = torch.empty(sv.spec_lm_head_packed_bytes(V, H) // 2, dtype=torch.bfloat16, device="cuda")
+    sv.spec_lm_head_pack(W, Wp)
+    logits = torch.full((M + 1, V), 7.0, device="cuda")
+    sv.spec_lm_head_packed(hidden, Wp, logits[:M])
+    rows = torch.tensor(sorted({0, M // 2, M - 1}), device="cuda")
+    ref = oracle.lm_head(wl.bf16_bits(hidden[rows]), wl.bf16_bits(W))
+    assert np.abs(logits[rows].cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(H) * np.abs(ref).max()
+    assert (logits[M] == 7.0).all()
+    other = torch.empty((M, V), device="cuda")
+    sv.spec_set_tuning("lm_packed_tile", 1)
+    try:
+        sv.spec_lm_head_packed(hidden, Wp, other)
+        torch.cuda.synchronize()
+    finally:
+        sv.spec_set_tuning("lm_packed_tile", 0)
+    assert torch.equal(other, logits[:M])
