@@ -106,6 +106,15 @@ __device__ inline void lds_dma16(const void* g, void* lds_base)
     else asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(m0v) : "memory");
 }
 
+// The same with a wave-uniform base and a 32-bit offset per lane: no vector address arithmetic.
+template <bool STREAM = false>
+__device__ inline void lds_dma16_off(uint32_t off, const void* base, void* lds_base)
+{
+    const uint32_t m0v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_base;
+    if constexpr (STREAM) asm volatile("global_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
+    else asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
+}
+
 // Block summaries of the large-tile LM head (lm_head_mfma_kernel.h): what acceptance needs from a row of logits without reading it again.  A
 // block is what one wave holds of a row at the end of a pass, at most 64 consecutive vocabulary entries; block index =
 // (panel range * passes per range + pass) * 4 + wave, so blocks cover increasing vocabulary ranges; blk_span[2 b],

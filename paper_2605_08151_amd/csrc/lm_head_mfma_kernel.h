@@ -49,13 +49,6 @@ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
-// lds_dma16 with a wave-uniform base and a 32-bit offset per lane
-__device__ inline void lds_dma16_off(uint32_t off, const void* base, void* lds_base)
-{
-    const uint32_t m0v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_base;
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
-}
-
 // LOADS: how W is read, see MfmaLoads; NT: nontemporal stores of the logits (a template argument: of two stores in the branches of a flag the compiler makes one ordinary store);
 // SUMMARY instantiations also leave the block summaries described at LmSummary.
 enum MfmaLoads { kBufferLoads, kGlobalLoads, kStreamLoads };   // buffer loads; global loads; nontemporal global loads

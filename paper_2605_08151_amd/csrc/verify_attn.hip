@@ -9,7 +9,7 @@
 //   candidate positions).  A wave copies ITS two pages
 //   (K and V, 4 KB each, contiguous in HBM) straight into its private 16 KB of LDS with direct
 //   global->LDS loads (no staging registers), so the waves of a workgroup never wait for each other
-//   inside the loop; latency is hidden by the other waves resident on the SIMD.
+//   inside the loop; the next step's K is in flight under this one's softmax and its V under the next scores.
 //   Scores are computed transposed, S^T = K Q^T (v_mfma_f32_16x16x32_bf16, keys on the MFMA row
 //   axis): a lane then holds 4 keys of ONE query row, the row maximum is an in-lane max plus two
 //   cross-lane shuffles, and exp(S^T) is already the B operand of O^T += V^T P^T.  K and V stay
@@ -152,30 +152,56 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     __syncthreads();
     const bool stream_kv = STREAM && scan && __builtin_amdgcn_readfirstlane(s_stream);
 
-    // ---- this wave's two pages of a step, K and V, HBM -> LDS (always 16 direct loads: positions past the
-    // range read page 0 instead, so the wait counts below are constants) ----
+    // ---- this wave's two pages of a step, HBM -> LDS: 8 direct loads of K and 8 of V, always (positions past the range
+    // read page 0 instead, so the wait counts below are constants).  A request is a scalar base (the page) plus a lane's place in it. ----
     const int drow = lane >> 4, dpos = lane & 15;        // direct-load role: row within a group of 4, 16-byte position
-    auto issue_pages = [&](auto stream, int wbase, unsigned char* buf) {
+    uint32_t koff[4], voff[2];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        const int row = q4 * 4 + drow;                   // slot in the page = key & 15
+        koff[q4] = (uint32_t)(row * kRowBytes + ((dpos ^ row) << 4));                                       // K: chunk ch of a row is stored at position ch ^ (row & 15)
+        if (q4 < 2) voff[q4] = (uint32_t)(row * kRowBytes + (((((dpos >> 1) ^ (row & 7)) << 1) | (dpos & 1)) << 4));   // V: 32-byte chunk c at c ^ (row & 7); 8 rows on the same
+    }
+    struct StepPages { int a, b; };
+    auto step_pages = [&](int wbase) {
+        StepPages r;
+        r.a = (wbase < kend) ? __builtin_amdgcn_readfirstlane(sPT[(wbase - kbeg) / kP]) : 0;
+        r.b = (wbase + kP < kend) ? __builtin_amdgcn_readfirstlane(sPT[(wbase - kbeg) / kP + 1]) : 0;
+        return r;
+    };
+    auto issue_k_as = [&](auto stream, StepPages pages, unsigned char* buf) {
         constexpr bool kStream = decltype(stream)::value;
 #pragma unroll
         for (int pg = 0; pg < 2; ++pg) {
-            const int t0 = wbase + pg * kP;
-            const int page = (t0 < kend) ? __builtin_amdgcn_readfirstlane(sPT[(t0 - kbeg) / kP]) : 0;
-            const size_t base = ((size_t)page * p.Hkv + kvh) * (kP * kD);
+            const uint16_t* base = p.k_cache + ((size_t)(pg ? pages.b : pages.a) * p.Hkv + kvh) * (kP * kD);
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int row = q4 * 4 + drow;             // slot in the page = key & 15
-                // K: chunk ch of a row is stored at position ch ^ (row & 15)
-                lds_dma16<kStream>(p.k_cache + base + row * kD + ((dpos ^ row) << 3), buf + (pg * 16 + q4 * 4) * kRowBytes);
-                // V: 32-byte chunk c of a row is stored at position c ^ (row & 7)
-                const int src16 = ((((dpos >> 1) ^ (row & 7)) << 1) | (dpos & 1));
-                lds_dma16<kStream>(p.v_cache + base + row * kD + (src16 << 3), buf + (32 + pg * 16 + q4 * 4) * kRowBytes);
-            }
+            for (int q4 = 0; q4 < 4; ++q4) lds_dma16_off<kStream>(koff[q4], base, buf + (pg * 16 + q4 * 4) * kRowBytes);
         }
     };
+    auto issue_v_as = [&](auto stream, StepPages pages, unsigned char* buf) {
+        constexpr bool kStream = decltype(stream)::value;
+#pragma unroll
+        for (int pg = 0; pg < 2; ++pg) {
+            const uint16_t* base = p.v_cache + ((size_t)(pg ? pages.b : pages.a) * p.Hkv + kvh) * (kP * kD);
+            unsigned char* to = buf + (32 + pg * 16) * kRowBytes;
+            lds_dma16_off<kStream>(voff[0], base, to);
+            lds_dma16_off<kStream>(voff[1], base, to + 4 * kRowBytes);
+            lds_dma16_off<kStream>(voff[0], base + 8 * kD, to + 8 * kRowBytes);
+            lds_dma16_off<kStream>(voff[1], base + 8 * kD, to + 12 * kRowBytes);
+        }
+    };
+    auto issue_k = [&](StepPages pages, unsigned char* buf) {
+        if (STREAM && stream_kv) issue_k_as(std::true_type{}, pages, buf);
+        else issue_k_as(std::false_type{}, pages, buf);
+    };
+    auto issue_v = [&](StepPages pages, unsigned char* buf) {
+        if (STREAM && stream_kv) issue_v_as(std::true_type{}, pages, buf);
+        else issue_v_as(std::false_type{}, pages, buf);
+    };
     auto issue_step = [&](int wbase, unsigned char* buf) {
-        if (STREAM && stream_kv) issue_pages(std::true_type{}, wbase, buf);
-        else issue_pages(std::false_type{}, wbase, buf);
+        const StepPages pages = step_pages(wbase);
+        issue_k(pages, buf);
+        issue_v(pages, buf);
     };
     const int wfirst = kbeg + wave * 32;
     if (wfirst < kend) issue_step(wfirst, sKV);           // in flight while Q is staged
@@ -248,28 +274,23 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     for (int wbase = wfirst; wbase < kend; wbase += kTile, ++it) {
         unsigned char* sK = sKV + (NBUF == 2 ? (it & 1) * kWaveLds : 0);
         unsigned char* sV = sK + 32 * kRowBytes;
+        // One buffer: K and V are waited for, and requested again, each by itself.  The next step's K pages are requested as soon as this step's K fragments
+        // are in registers, its V pages as soon as this step's V fragments are, so that one or the other is always in flight under the arithmetic
+        // (with both waited for and requested at once, and an address per lane: 128 requests x 8 heads x 2.6k keys 270.6 -> 266.7 us, 64 x 8 x 2.6k keys of 5 rows 121.1 -> 118.9).
+        const bool more = wbase + kTile < kend;
+        StepPages next{0, 0};
         if (NBUF == 2) {
             // the other buffer was last read in the previous step; its reads have returned
             __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0)
-            if (wbase + kTile < kend) {
+            if (more) {
                 issue_step(wbase + kTile, sKV + ((it + 1) & 1) * kWaveLds);
                 __builtin_amdgcn_s_waitcnt(0x4F70);       // vmcnt(16): this step's pages have landed, the next 16 loads fly on
             } else {
                 __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
             }
         } else {
-            if (it > 0) {
-                __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): the previous step's LDS reads have returned
-                issue_step(wbase, sKV);
-            }
-            __builtin_amdgcn_s_waitcnt(0x0F70);           // vmcnt(0): this step's pages have landed
-        }
-        if (wbase + 32 > kend) {
-            // slots past the range may hold anything (even NaN patterns): P is 0 there, so V must be too
-            for (int idx = lane; idx < 32 * 16; idx += 64) {
-                const int row = idx >> 4;
-                if (wbase + row >= kend) *reinterpret_cast<u32x4*>(sV + row * kRowBytes + (idx & 15) * 16) = u32x4{0, 0, 0, 0};
-            }
+            if (more) next = step_pages(wbase + kTile);
+            __builtin_amdgcn_s_waitcnt(0x0F78);           // vmcnt(8): K has landed, V (8 younger loads) may fly on
         }
 
         // ---- S^T = K Q^T for the wave's two 16-key blocks ----
@@ -279,6 +300,10 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
 #pragma unroll
             for (int s = 0; s < 4; ++s)
                 kf[kb][s] = *reinterpret_cast<const bf16x8*>(sK + (kb * 16 + l16) * kRowBytes + (((s * 4 + g) ^ l16) << 4));
+        if (NBUF == 1 && more) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): the fragments are in registers
+            issue_k(next, sK);
+        }
         const bool need_mask = wbase + 32 > min(c + 1, kend);
         // The row tiles go through every phase together (scores, maxima, exponentials) so that the
         // dependent chains of different tiles (MFMA -> max -> cross-lane max -> exp) overlap in the one wave.
@@ -322,9 +347,7 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
             tmax[rt] = t;
         }
 #pragma unroll
-        for (int rt = 0; rt < A; ++rt) tmax[rt] = fmaxf(tmax[rt], __shfl_xor(tmax[rt], 16, 64));
-#pragma unroll
-        for (int rt = 0; rt < A; ++rt) tmax[rt] = fmaxf(tmax[rt], __shfl_xor(tmax[rt], 32, 64));
+        for (int rt = 0; rt < A; ++rt) tmax[rt] = four_rows_max(tmax[rt]);
         // Lazy reference maximum: m_run only moves when a step's maximum exceeds it by more than kMaxSlack
         // (log2 units), so exp2(s - m_run) <= 2^kMaxSlack stays well inside fp32/bf16 range and the 32
         // accumulator registers of a row tile are rescaled a handful of times per chunk instead of almost
@@ -365,19 +388,37 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
         }
         // ---- O^T += V^T P^T: lane (d = 16dt + l16, k-group g) needs keys 4g..4g+3 of both blocks at one d.
         // For the transposing read, lane r of a group supplies key 4g + r/4, d = 16dt + 4*(r%4) .. +3. ----
+        if (NBUF == 1) {
+            if (more) __builtin_amdgcn_s_waitcnt(0x0F78); // vmcnt(8): V has landed, the next step's K may fly on
+            else __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+        }
+        if (wbase + 32 > kend) {
+            // slots past the range may hold anything (even NaN patterns): P is 0 there, so V must be too
+            for (int idx = lane; idx < 32 * 16; idx += 64) {
+                const int row = idx >> 4;
+                if (wbase + row >= kend) *reinterpret_cast<u32x4*>(sV + row * kRowBytes + (idx & 15) * 16) = u32x4{0, 0, 0, 0};
+            }
+        }
         {
             const int vrow = 4 * g + (l16 >> 2);
             const unsigned char* v0 = sV + vrow * kRowBytes + 8 * (l16 & 3);
+            bf16x8 vf[8];
 #pragma unroll
             for (int dt = 0; dt < 8; ++dt) {
                 const int off = (dt ^ (vrow & 7)) << 5;
                 const s16x4 lo = lds_read_tr(v0 + off);
                 const s16x4 hi = lds_read_tr(v0 + 16 * kRowBytes + off);
                 struct { s16x4 a, b; } pair = {lo, hi};
-                const bf16x8 vf = __builtin_bit_cast(bf16x8, pair);
-#pragma unroll
-                for (int rt = 0; rt < A; ++rt) o[rt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[rt], o[rt][dt], 0, 0, 0);
+                vf[dt] = __builtin_bit_cast(bf16x8, pair);
             }
+            if (NBUF == 1 && more) {
+                __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): the fragments are in registers
+                issue_v(next, sK);
+            }
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+                for (int rt = 0; rt < A; ++rt) o[rt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf[rt], o[rt][dt], 0, 0, 0);
         }
     }
     };
