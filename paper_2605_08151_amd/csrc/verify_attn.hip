@@ -65,6 +65,9 @@ struct AttnParams {
     int max_pages, num_pages, Hq, Hkv, G, M, max_kv_len, max_q_len, chunk_target, splits;
     float scale_log2e;
     int B;
+    // Workgroups that start together take the heads of one piece: their pages are neighbours in HBM (a page of all heads is one stretch of Hkv * 4 KB), and are
+    // read at about the same time.  Pieces first -> heads first: 128 requests x 8 heads x 2.6k keys 266.7 -> 220.7 us (5.2 -> 6.3 TB/s)
+    int head_first;
     float stream_keys;         // committed keys of the batch above which its K/V is too large for the memory-side cache (0: it never is)
 };
 
@@ -99,20 +102,21 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    const int kvh = blockIdx.y;
+    // (see AttnParams::head_first)
+    const int kvh = p.head_first ? blockIdx.x : blockIdx.y, piece = p.head_first ? blockIdx.y : blockIdx.x;
     int split, i, ns_plan = 0, pb_plan = 0;
     bool scan = STREAM;
     if (p.plan_items) {
         // one workgroup per item of the balanced list; the grid is sized from a host bound
-        if ((int)blockIdx.x >= p.plan_hdr[0]) return;
+        if (piece >= p.plan_hdr[0]) return;
         scan = STREAM && p.plan_hdr[2];
-        const int* it = p.plan_items + 4 * (size_t)blockIdx.x;
+        const int* it = p.plan_items + 4 * (size_t)piece;
         i = __builtin_amdgcn_readfirstlane(it[0]);
         split = __builtin_amdgcn_readfirstlane(it[1]);
         ns_plan = __builtin_amdgcn_readfirstlane(it[2]);
         pb_plan = __builtin_amdgcn_readfirstlane(it[3]);
     } else {
-        split = blockIdx.x;
+        split = piece;
         i = blockIdx.z;
     }
     unsigned char* sKV = smem + wave * (NBUF * kWaveLds); // this wave's NBUF x (32 K rows, 32 V rows)
@@ -528,19 +532,20 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    const int kvh = blockIdx.y;
+    // (see AttnParams::head_first)
+    const int kvh = p.head_first ? blockIdx.x : blockIdx.y, piece = p.head_first ? blockIdx.y : blockIdx.x;
     int split, i, ns_plan = 0, pb_plan = 0;
     bool scan = STREAM;
     if (p.plan_items) {
-        if ((int)blockIdx.x >= p.plan_hdr[0]) return;
+        if (piece >= p.plan_hdr[0]) return;
         scan = STREAM && p.plan_hdr[2];
-        const int* it = p.plan_items + 4 * (size_t)blockIdx.x;
+        const int* it = p.plan_items + 4 * (size_t)piece;
         i = __builtin_amdgcn_readfirstlane(it[0]);
         split = __builtin_amdgcn_readfirstlane(it[1]);
         ns_plan = __builtin_amdgcn_readfirstlane(it[2]);
         pb_plan = __builtin_amdgcn_readfirstlane(it[3]);
     } else {
-        split = blockIdx.x;
+        split = piece;
         i = blockIdx.z;
     }
     unsigned char* sRing = smem;                                         // kRowsStages x (32 K rows, 32 V rows)
@@ -1200,7 +1205,7 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     const AttnPlanCfg pc = attn_plan_cfg(B, Hq, Hkv, max_kv_len, max_q_len, NR, p.chunk_target);
-    dim3 grid(p.splits, Hkv, B);
+    dim3 grid(p.splits, Hkv, B);                          // (pieces, kv heads, requests)
     if (pc.on) {
         if (pc.slots * kD > 2147483647u || (size_t)pc.max_items > 2147483647u)
             return fail(SPEC_ESHAPE, "spec_verify_attn: work list beyond 32-bit slots");
@@ -1225,6 +1230,9 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
         p.part_m = (float*)(ws + round_up(units * kD * 4, 256));
         p.part_l = (float*)(ws + round_up(units * kD * 4, 256) + round_up(units * 4, 256));
     }
+
+    p.head_first = grid.x <= 65535;                       // (the second dimension's limit)
+    if (p.head_first) grid = dim3(grid.y, grid.x, grid.z);
 
     int rc = SPEC_OK;
     switch (NR) {
