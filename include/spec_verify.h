@@ -85,8 +85,9 @@ int spec_version(void);
  *                      row a bonus token is drawn from and on rows whose test the interval leaves open; 2 = fp64
  *                      sums over every row; 3 = as 1 with an interval so wide that most tests take the fp64 path (a
  *                      test hook).  Same integers in all.
- *   "lm_kernel"       kernel used by spec_lm_head: 0 = automatic (for M <= 160 the weight-streaming kernel of
- *                      spec_lm_head_packed in its row-major form, or 1 for a vocabulary too small for it; 8 above), 1 =
+ *   "lm_kernel"       kernel used by spec_lm_head: 0 = automatic (the large-tile kernel of spec_lm_head_packed
+ *                      in its row-major form for M > 160 and most shapes from 113 rows on; below, its
+ *                      weight-streaming kernel in that form, or 1 for a vocabulary too small for it), 1 =
  *                      4-wave weight-streaming kernel, 2 = MFMA-bound with direct global->LDS loads, 3 = plain
  *                      tiled, 4..7 = variants of 1 (wave count / register-ring depth; 7 = 1), 8 = MFMA-bound with
  *                      register staging.

@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspecverify.so")
 # (the slowest to compile first)
-SOURCES = ["lm_head_mfma_summary.hip", "lm_head_mfma_buffer.hip", "lm_head_mfma_global.hip", "verify_attn.hip", "lm_head_mfma_stream.hip", "lm_head_tile.hip", "lm_head_mfma.hip", "lm_head_packed.hip", "lm_head.hip", "api.hip", "accept.hip", "kv_commit.hip", "assemble_next.hip", "draft_side.hip", "probes.hip"]
+SOURCES = ["lm_head_mfma_summary.hip", "lm_head_mfma_buffer.hip", "lm_head_mfma_global.hip", "verify_attn.hip", "lm_head_mfma_stream.hip", "lm_head_rowmajor.hip", "lm_head_tile.hip", "lm_head_mfma.hip", "lm_head_packed.hip", "lm_head.hip", "api.hip", "accept.hip", "kv_commit.hip", "assemble_next.hip", "draft_side.hip", "probes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -620,10 +620,11 @@ static int launch_big2(const uint16_t* a, const uint16_t* w, float* c, int M, in
 
 Tunable g_lm_kernel_waves{8};  // benchmark hook: waves per workgroup of the MFMA-bound kernel (4 or 8)
 // benchmark hook: 0 = automatic, 1 = weight-streaming (this file's), 2 = MFMA-bound with direct loads, 3 = plain tiled, 8 = MFMA-bound with
-// register staging (the automatic choice for M > 160), 4 = weight-streaming with 8 waves (4 x 2) and a 2-slab ring, 5/6/7 = 4 waves with
+// register staging, 4 = weight-streaming with 8 waves (4 x 2) and a 2-slab ring, 5/6/7 = 4 waves with
 // 4-slab ring / 4-slab ring + paired refills / 2-slab ring + paired refills (what 0 and 1 run).
-// For M <= 160 the automatic choice is lm_head_rows_dispatch (lm_head_packed.hip) where that takes the shape; this file's weight-streaming kernel
-// serves the smaller vocabularies, and spec_lm_head_stats.
+// The automatic choice is lm_head_rowmajor_dispatch (lm_head_mfma.hip: more than 160 rows, and most shapes from 113 rows on), then for M <= 160 lm_head_rows_dispatch
+// (lm_head_packed.hip) where that takes the shape; this file's weight-streaming kernel serves the smaller vocabularies, and spec_lm_head_stats; its MFMA-bound
+// kernels serve H that is no multiple of 256.
 Tunable g_lm_kernel{0};
 
 // vocabulary entries per workgroup and the grid of the weight-streaming kernel
@@ -666,6 +667,7 @@ static int launch_skinny_auto(const uint16_t* a, const uint16_t* w, float* c, in
     return launch_skinny<TM, 1, 2, 1>(a, w, c, M, H, V, s);
 }
 
+bool lm_head_rowmajor_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc);   // lm_head_mfma.hip
 bool lm_head_rows_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc);   // lm_head_packed.hip
 
 static bool skinny_applies(int M, int H)
@@ -724,7 +726,9 @@ extern "C" int spec_lm_head(const void* hidden, const void* W, float* logits, in
     const uint16_t* w = (const uint16_t*)W;
     const int force = g_lm_kernel;
     int rows_rc = SPEC_OK;
-    if (force == 0 && lm_head_rows_dispatch(a, w, logits, M, H, V, s, &rows_rc)) {
+    if (force == 0 && lm_head_rowmajor_dispatch(a, w, logits, M, H, V, s, &rows_rc)) {
+        if (rows_rc != SPEC_OK) return rows_rc;
+    } else if (force == 0 && lm_head_rows_dispatch(a, w, logits, M, H, V, s, &rows_rc)) {
         if (rows_rc != SPEC_OK) return rows_rc;
     } else if (skinny_applies(M, H)) {
         int rc;

@@ -51,7 +51,8 @@ __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make
 
 // LOADS: how W is read, see MfmaLoads; NT: nontemporal stores of the logits (a template argument: of two stores in the branches of a flag the compiler makes one ordinary store);
 // SUMMARY instantiations also leave the block summaries described at LmSummary.
-enum MfmaLoads { kBufferLoads, kGlobalLoads, kStreamLoads };   // buffer loads; global loads; nontemporal global loads
+// buffer loads; global loads; nontemporal global loads; the same two of a matrix that is row-major, not packed
+enum MfmaLoads { kBufferLoads, kGlobalLoads, kStreamLoads, kRowLoads, kRowStreamLoads };
 
 template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
 __device__ __forceinline__ void lm_head_mfma_tiles(
@@ -146,8 +147,12 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
         p0 = s.p0;
         np = s.np;
     };
+    // Row-major (ROWS): a load takes 128 bytes (a slab) of 8 rows, whole lines.  The two loads of a slab and panel slot, rows 0..7 and 8..15, become the operands
+    // of its two k-tiles by selections and a rotation within 16 lanes (weave_rows) when the slab's step begins.
+    constexpr bool ROWS = LOADS == kRowLoads || LOADS == kRowStreamLoads;
     const uint32_t panel_bytes = (uint32_t)H * 32u;
     const uint32_t woff = (uint32_t)lane * 16u;
+    uint32_t roff[kMfTN][2];                          // (ROWS) byte offset of this lane's 16 bytes from the wave's first row
     u32x4 wreg[RW][2][kMfTN];
     __amdgpu_buffer_rsrc_t wrsrc;
     const unsigned char* wbase = nullptr;
@@ -155,17 +160,48 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
     uint32_t wslot[kMfTN];                            // mf_slot_bytes of the wave's panel slots
     auto open_panels = [&](int p0, int np) SPECV_INLINE {
         const unsigned char* base = reinterpret_cast<const unsigned char*>(Wp) + (size_t)p0 * panel_bytes;
-        wrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (uint32_t)max(np, 1) * panel_bytes, 0x00020000);
+        if constexpr (LOADS == kBufferLoads) wrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (uint32_t)max(np, 1) * panel_bytes, 0x00020000);
         wbase = base;
         wpos = 0;
 #pragma unroll
-        for (int tn = 0; tn < kMfTN; ++tn) wslot[tn] = mf_slot_bytes(np, tn, panel_bytes);
+        for (int tn = 0; tn < kMfTN; ++tn) {
+            if constexpr (ROWS) {
+                // entries past V repeat the last one; which half of a row's 128 bytes the lane takes: see weave_rows
+                const int last = V - 1 - p0 * 16, row = min(tn, max(np - 1, 0)) * 16 + (l16 & 7);
+                roff[tn][0] = (uint32_t)min(row, last) * (uint32_t)H * 2u + (uint32_t)(kg + (l16 & 8) / 2) * 16u;
+                roff[tn][1] = (uint32_t)min(row + 8, last) * (uint32_t)H * 2u + (uint32_t)(kg + 4 - (l16 & 8) / 2) * 16u;
+            } else {
+                wslot[tn] = mf_slot_bytes(np, tn, panel_bytes);
+            }
+        }
     };
+    constexpr uint32_t kWSlab = ROWS ? kMfSlab * 2 : 2048;         // bytes from a slab to the next in a row, in a packed panel
     auto fetch_w1 = [&](int slot, int t, int tn) SPECV_INLINE {    // k-tile t of that slab, panel slot tn
-        const u32x4* at = reinterpret_cast<const u32x4*>(wbase + (wpos + t * 1024 + wslot[tn]) + woff);
-        if constexpr (LOADS == kStreamLoads) wreg[slot][t][tn] = __builtin_nontemporal_load(at);
-        else if constexpr (LOADS == kGlobalLoads) wreg[slot][t][tn] = *at;
+        const u32x4* at;
+        if constexpr (ROWS) at = reinterpret_cast<const u32x4*>(wbase + wpos + roff[tn][t]);
+        else at = reinterpret_cast<const u32x4*>(wbase + (wpos + t * 1024 + wslot[tn]) + woff);
+        if constexpr (LOADS == kStreamLoads || LOADS == kRowStreamLoads) wreg[slot][t][tn] = __builtin_nontemporal_load(at);
+        else if constexpr (LOADS != kBufferLoads) wreg[slot][t][tn] = *at;
         else wreg[slot][t][tn] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff, wpos + t * 1024 + wslot[tn], 0);
+    };
+
+    // (ROWS) Loaded, lane (l16, kg) of slot tn holds row l16 % 8, 16-byte piece kg (l16 < 8) or 4 + kg (else), and row 8 + l16 % 8, piece 4 + kg or kg; needed is row
+    // l16, pieces kg and 4 + kg: a selection, and a selection and a rotation by 8 within the 16 lanes.
+    auto weave_rows = [&](auto rc, auto slots_c) SPECV_INLINE {
+        constexpr int r = decltype(rc)::value;
+        const bool low = l16 < 8;
+#pragma unroll
+        for (int tn = 0; tn < decltype(slots_c)::value; ++tn) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t a = wreg[r][0][tn][e], b = wreg[r][1][tn][e];
+                wreg[r][0][tn][e] = low ? a : b;
+                wreg[r][1][tn][e] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(low ? b : a), 0x128, 0xF, 0xF, false);   // row_ror:8
+            }
+            asm volatile("" : "+v"(wreg[r][0][tn]), "+v"(wreg[r][1][tn]));
+        }
+        asm volatile("s_nop 1");                      // (the products are assembly statements)
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     f32x4 acc[kMfTN][TM];
@@ -214,7 +250,7 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
 #pragma unroll
             for (int tn = 0; tn < kMfTN; ++tn)
                 if (r < RW - 1 || t == 0) fetch_w1(r, t, tn);
-        if (r < RW - 1) wpos += 2048;
+        if (r < RW - 1) wpos += kWSlab;
     }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -252,6 +288,7 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
         constexpr int rp = (r + 3) % RW;              // ring slot of slab s-1 = of slab s+3
         constexpr bool FIRST = decltype(first_c)::value;
         constexpr int SLOTS = decltype(slots_c)::value;
+        if constexpr (ROWS) weave_rows(rc, slots_c);
         constexpr int g0 = r * 2 * TM;                // running group index (8 TM groups of 4 steps are a multiple of kHfRing)
         static_for<2 * TM>([&](auto ic) SPECV_INLINE {
             constexpr int i = decltype(ic)::value, t = i / TM, tm = i % TM;
@@ -282,7 +319,7 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
             else if constexpr (i >= 4 && i < 4 + QN) stage_h1(rp, i - 4);
             else if constexpr (i >= TM && i < TM + SLOTS) fetch_w1(r, 0, i - TM);
             if constexpr (i == 4) {                   // W goes on to slab s+4: after the last one of a pass, to the next pass's panels
-                wpos += 2048;
+                wpos += kWSlab;
                 if (r == 0 && last_iter) open_panels(p0_next, np_next);
             }
             if constexpr (i == TM - 1) {              // hidden goes on to slab s+4; after the last one, to slab 0 again
@@ -496,6 +533,15 @@ __global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_tile_kernel(
     lm_head_mfma_tiles<TM, LOADS, NT, false>(A, Wp, C, M, H, V, n_panels, panels_per_wg, groups, tiles_lo, groups_hi, LmSummary{});
 }
 
+// 8 to 16, W row-major
+template <int TM, MfmaLoads LOADS, bool NT>
+__global__ __launch_bounds__(64 * kMfWaves, 1) void lm_head_rowmajor_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, float* __restrict__ C, int M, int H, int V, int n_panels, int panels_per_wg,
+    int groups, int tiles_lo, int groups_hi)
+{
+    lm_head_mfma_tiles<TM, LOADS, NT, false>(A, W, C, M, H, V, n_panels, panels_per_wg, groups, tiles_lo, groups_hi, LmSummary{});
+}
+
 template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
 static int launch_mfma(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, LmSummary sm, hipStream_t s)
 {
@@ -527,6 +573,21 @@ static int launch_tile(const uint16_t* a, const uint16_t* wp, float* c, int M, i
     hipLaunchKernelGGL((lm_head_tile_kernel<TM, LOADS, NT>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, wp, c, M, H, V,
                        (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi);
     return SPEC_OK;
+}
+
+template <int TM, MfmaLoads LOADS, bool NT>
+static int launch_rowmajor(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, const MfmaLayout& L, hipStream_t s)
+{
+    if (L.tm == TM) {
+        constexpr size_t smem = mf_lds_bytes(TM, false);
+        static LdsGrantTable granted = {};
+        if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_rowmajor_kernel<TM, LOADS, NT>), smem, granted, "spec_lm_head")) return rc;
+        hipLaunchKernelGGL((lm_head_rowmajor_kernel<TM, LOADS, NT>), dim3(L.ranges * L.groups), dim3(64 * kMfWaves), smem, s, a, w, c, M, H, V,
+                           (V + 15) / 16, L.per_range, L.groups, L.tiles_lo, L.groups_hi);
+        return SPEC_OK;
+    }
+    if constexpr (TM < 16) return launch_rowmajor<TM + 1, LOADS, NT>(a, w, c, M, H, V, L, s);
+    else return fail(SPEC_ESHAPE, "spec_lm_head: no large-tile instantiation for %d row tiles per group", L.tm);
 }
 
 int lm_head_tile(MfmaLoads loads, bool nt, const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, hipStream_t s);

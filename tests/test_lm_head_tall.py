@@ -110,3 +110,26 @@ def test_lines_between_the_weight_streaming_and_the_large_tile_kernel(sv, oracle
     finally:
         sv.spec_set_tuning("lm_packed_tile", 0)
     assert torch.equal(other, logits[:M])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [113, 128, 160, 161, 256, 257, 400])
+@pytest.mark.parametrize("V,H", [(999, 4096), (20001, 256), (37003, 512), (49152, 1280), (70000, 256), (64013, 1024)])
+def test_row_major_weights_through_the_large_tile_kernel(sv, oracle, M, V, H):
+    """Ragged last panels (rows past the matrix repeat its last one), one group and two, ordinary and nontemporal loads, aligned rows of logits and not.  Same
+    order of additions as on packed weights: same bits."""
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    hidden = torch.randn((M, H), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((V, H), generator=g, device="cuda").to(torch.bfloat16)
+    logits = torch.full((M + 1, V), 7.0, device="cuda")
+    sv.spec_lm_head(hidden, W, logits[:M])
+    rows = torch.tensor(sorted({0, M // 2, M - 1}), device="cuda")
+    ref = oracle.lm_head(wl.bf16_bits(hidden[rows]), wl.bf16_bits(W))
+    assert np.abs(logits[rows].cpu().numpy() - ref).max() <= 1e-5 * math.sqrt(H) * np.abs(ref).max()
+    assert (logits[M] == 7.0).all()
+    Wp = torch.empty(sv.spec_lm_head_packed_bytes(V, H) // 2, dtype=torch.bfloat16, device="cuda")
+    sv.spec_lm_head_pack(W, Wp)
+    other = torch.empty((M, V), device="cuda")
+    sv.spec_lm_head_packed(hidden, Wp, other)
+    torch.cuda.synchronize()
+    assert torch.equal(other, logits[:M])
