@@ -1,4 +1,4 @@
-"""Builds libspecverify.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libspecverify.so (HIP, gfx950 only) with hipcc and the binding's _marshal.so with g++, in-tree."""
 from __future__ import annotations
 
 import os
@@ -9,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspecverify.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 # (the slowest to compile first)
 SOURCES = ["lm_head_mfma_summary.hip", "lm_head_mfma_buffer.hip", "lm_head_mfma_global.hip", "verify_attn.hip", "lm_head_mfma_stream.hip", "lm_head_rowmajor.hip", "lm_head_tile.hip", "lm_head_mfma.hip", "lm_head_packed.hip", "lm_head.hip", "api.hip", "accept.hip", "kv_commit.hip", "assemble_next.hip", "draft_side.hip", "probes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -34,7 +35,23 @@ def build(verbose: bool = False, jobs: int = 5) -> str:
     _drain(procs)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    build_marshal()
     return LIB
+
+
+def build_marshal() -> str:
+    """The extension module behind binding.py's per-tensor checks (host code, against the headers of the torch that is installed)."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    include = [x for d in include_paths("cuda") + [sysconfig.get_paths()["include"]] for x in ("-I", d)]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *include, os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL,
+           "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    subprocess.run(cmd, check=True)
+    return MARSHAL
 
 
 def _drain(procs):
