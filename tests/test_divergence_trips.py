@@ -1,0 +1,26 @@
+"""Divergence points at the edges of what one memory round trip compares (512 threads x 8 positions)."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import sv  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def test_divergence_at_the_edges_of_a_trip(sv, oracle):
+    at = [0, 63, 64, 511, 512, 4095, 4096, 4097, 8191, 8192, 9000]
+    lens = [max(1, t + 1) for t in at] + [4096, 4097, 9001, 0, 5]
+    rng = np.random.default_rng(5)
+    p = [rng.integers(0, 9, n).astype(np.int32) for n in lens]
+    h = [np.concatenate([x, x[:1]]) for x in p]                  # the longer one agrees all the way ...
+    for k, t in enumerate(at):
+        h[k][t] += 1                                             # ... but for one position, and everything behind it
+        h[k][t + 1:] += 1
+    indptr = lambda rows: np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)  # noqa: E731
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    delta = torch.full((len(p),), -7, dtype=torch.int32, device="cuda")
+    sv.spec_divergence(dev(np.concatenate(p)), dev(indptr(p)), dev(np.concatenate(h)), dev(indptr(h)), delta)
+    expected = at + lens[len(at):]
+    assert delta.cpu().tolist() == expected
+    assert oracle.divergence(np.concatenate(p), indptr(p), np.concatenate(h), indptr(h)).tolist() == expected
