@@ -915,6 +915,15 @@ __global__ __launch_bounds__(1024) void verify_attn_plan_kernel(AttnParams p, in
     if (tid == 0 && any_bad && p.status_flags) atomicOr(p.status_flags, SPEC_FLAG_BAD_LENGTH);
 }
 
+// The request of candidate row `row`: the number of requests that start at or before it, less one (-1: none), counted by the whole workgroup in one memory round
+// trip per 256 requests (a binary search is eight dependent trips for 256).
+__device__ inline int request_of_row(const AttnParams& p, int B, int row)
+{
+    int before = 0;
+    for (int k = 0; k < B; k += 256) before += __syncthreads_count(k + (int)threadIdx.x < B && p.qo_indptr[k + threadIdx.x] <= row);
+    return __builtin_amdgcn_readfirstlane(before) - 1;   // (the same in every lane)
+}
+
 // Merge the split partials of one (row, head) and write bf16 (and lse).  256 threads: lane group q = tid/32
 // takes splits q, q+8, ..., thread t%32 four consecutive d; the 8 groups are then summed in group order, so
 // the result does not depend on timing.
@@ -923,20 +932,18 @@ __global__ __launch_bounds__(256) void verify_attn_combine_kernel(AttnParams p, 
     __shared__ float s_num[8][kD];
     __shared__ float s_den[8];
     const int row = blockIdx.x, hq = blockIdx.y, tid = threadIdx.x, grp = tid >> 5, d4 = (tid & 31) * 4;
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (p.qo_indptr[mid] <= row) lo = mid; else hi = mid - 1;
-    }
-    const int i = lo;
-    const int n = p.qo_indptr[i + 1] - p.qo_indptr[i], c = p.seq_lens[i];
-    if (!request_ok(p.qo_indptr[i], n, c, p) || row >= p.qo_indptr[i + 1]) return;
+    const int i = request_of_row(p, B, row);
+    if (i < 0) return;
+    const int r0 = p.qo_indptr[i], n = p.qo_indptr[i + 1] - r0, c = p.seq_lens[i];
+    if (!request_ok(r0, n, c, p) || row < r0 || row >= r0 + n) return;
     const int len = c + n;
     const int ns = p.plan_req ? p.plan_req[2 * i] : (len + p.chunk_target - 1) / p.chunk_target;
-    const size_t unit = p.plan_req ? (size_t)p.plan_req[2 * i + 1] + ((size_t)(row - p.qo_indptr[i]) * p.Hq + hq) * ns
+    const size_t unit = p.plan_req ? (size_t)p.plan_req[2 * i + 1] + ((size_t)(row - r0) * p.Hq + hq) * ns
                                    : ((size_t)row * p.Hq + hq) * p.splits;
     float mx = kNegBig;
-    for (int s = 0; s < ns; ++s) mx = fmaxf(mx, p.part_m[unit + s]);
+    for (int s = tid & 31; s < ns; s += 32) mx = fmaxf(mx, p.part_m[unit + s]);
+    mx = row16_max(mx);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
     float den = 0.0f;
     for (int s = grp; s < ns; s += 8) {
@@ -956,40 +963,56 @@ __global__ __launch_bounds__(256) void verify_attn_combine_kernel(AttnParams p, 
     }
 }
 
-// The same merge for requests cut into few pieces: one workgroup per candidate row, lane group q = tid/32 takes
-// heads q, q+8, ... and walks the splits of its (row, head) in order; 8x fewer, fuller workgroups than above.
+// The same merge for requests cut into few pieces: one workgroup per candidate row and 8 heads, a lane group of 32 per head, which
+// walks the splits in order; 8x fewer, fuller workgroups than above.  Latency-bound: splits are fetched four at a time, their maxima beside their O.
+// (One workgroup for all heads of a row, one split at a time, the request by binary search: 188 rows x 32 heads in 6 pieces 13.4 us, now 5.4; 1152 rows x 8 heads
+// 9.0, now 6.7; 128 x 32 7.0, now 4.6.)
 __global__ __launch_bounds__(256) void verify_attn_combine_rows_kernel(AttnParams p, int B)
 {
-    const int row = blockIdx.x, tid = threadIdx.x, grp = tid >> 5, d4 = (tid & 31) * 4;
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (p.qo_indptr[mid] <= row) lo = mid; else hi = mid - 1;
-    }
-    const int i = lo;
-    const int n = p.qo_indptr[i + 1] - p.qo_indptr[i], c = p.seq_lens[i];
-    if (!request_ok(p.qo_indptr[i], n, c, p) || row >= p.qo_indptr[i + 1]) return;
+    const int row = blockIdx.x, tid = threadIdx.x, hq = blockIdx.y * 8 + (tid >> 5), d4 = (tid & 31) * 4;
+    const int i = request_of_row(p, B, row);
+    if (i < 0 || hq >= p.Hq) return;
+    const int r0 = p.qo_indptr[i], n = p.qo_indptr[i + 1] - r0, c = p.seq_lens[i];
+    if (!request_ok(r0, n, c, p) || row < r0 || row >= r0 + n) return;
     const int len = c + n;
     const int ns = p.plan_req ? p.plan_req[2 * i] : (len + p.chunk_target - 1) / p.chunk_target;
-    for (int hq = grp; hq < p.Hq; hq += 8) {
-        const size_t unit = p.plan_req ? (size_t)p.plan_req[2 * i + 1] + ((size_t)(row - p.qo_indptr[i]) * p.Hq + hq) * ns
-                                       : ((size_t)row * p.Hq + hq) * p.splits;
-        float mx = kNegBig;
-        for (int s = 0; s < ns; ++s) mx = fmaxf(mx, p.part_m[unit + s]);
-        f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
-        float den = 0.0f;
-        for (int s = 0; s < ns; ++s) {
-            const float w = exp2f(p.part_m[unit + s] - mx);
-            num += w * *reinterpret_cast<const f32x4*>(p.part_o + (unit + s) * kD + d4);
-            den += w * p.part_l[unit + s];
+    const size_t unit = p.plan_req ? (size_t)p.plan_req[2 * i + 1] + ((size_t)(row - r0) * p.Hq + hq) * ns
+                                   : ((size_t)row * p.Hq + hq) * p.splits;
+    float mx = kNegBig;
+    f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
+    float den = 0.0f;
+    for (int s0 = 0; s0 < ns; s0 += 4) {
+        float m[4], l[4], mx2 = mx;
+        f32x4 o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const size_t s = unit + min(s0 + k, ns - 1);
+            m[k] = p.part_m[s];
+            l[k] = p.part_l[s];
+            o[k] = *reinterpret_cast<const f32x4*>(p.part_o + s * kD + d4);
         }
-        const float inv = 1.0f / den;
-        u32x2 packed;
-        packed.x = pack_bf16x2(num.x * inv, num.y * inv);
-        packed.y = pack_bf16x2(num.z * inv, num.w * inv);
-        *reinterpret_cast<u32x2*>(p.out + ((size_t)row * p.Hq + hq) * kD + d4) = packed;
-        if (p.lse && (tid & 31) == 0) p.lse[(size_t)row * p.Hq + hq] = (mx + log2f(den)) * 0.6931471805599453f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) mx2 = fmaxf(mx2, m[k]);
+        if (s0 > 0) {                                     // (equal maxima: a factor of one)
+            const float w = exp2f(mx - mx2);
+            num *= w;
+            den *= w;
+        }
+        mx = mx2;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (s0 + k < ns) {
+                const float w = exp2f(m[k] - mx);
+                num += w * o[k];
+                den += w * l[k];
+            }
     }
+    const float inv = 1.0f / den;
+    u32x2 packed;
+    packed.x = pack_bf16x2(num.x * inv, num.y * inv);
+    packed.y = pack_bf16x2(num.z * inv, num.w * inv);
+    *reinterpret_cast<u32x2*>(p.out + ((size_t)row * p.Hq + hq) * kD + d4) = packed;
+    if (p.lse && (tid & 31) == 0) p.lse[(size_t)row * p.Hq + hq] = (mx + log2f(den)) * 0.6931471805599453f;
 }
 
 Tunable g_attn_chunk_override{0};
@@ -1267,7 +1290,7 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
     if (p.splits == 1) return SPEC_OK;                    // the main kernel wrote the output itself
     // few pieces per request (typical count in work-list mode: items per request): one workgroup per row
     const bool few = pc.on ? (pc.target_items + B) / B <= 8 : p.splits <= 16;
-    if (few) hipLaunchKernelGGL(verify_attn_combine_rows_kernel, dim3(M), dim3(256), 0, s, p, B);
+    if (few) hipLaunchKernelGGL(verify_attn_combine_rows_kernel, dim3(M, (Hq + 7) / 8), dim3(256), 0, s, p, B);
     else hipLaunchKernelGGL(verify_attn_combine_kernel, dim3(M, Hq), dim3(256), 0, s, p, B);
     return check_launch("spec_verify_attn (combine)");
 }
