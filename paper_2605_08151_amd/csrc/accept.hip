@@ -664,27 +664,25 @@ __global__ __launch_bounds__(kDecideThreads) void accept_decide_kernel(DecideArg
 }
 
 // ---- 2b. greedy decision on a candidate tree ---------------------------------------------------
-// Same merge of the per-segment maxima as above; then one thread walks from the root: at node u the target's
-// token is the argmax of row u; the walk goes on to the child of u that carries it (the lowest row among equal
+// Same merge of the per-segment maxima as above, a wave per row; then wave 0 walks from the root, lane v looking at row v (at most 64 rows): at node u the
+// target's token is the argmax of row u; the walk goes on to the child of u that carries it (the lowest row among equal
 // children) and stops where there is none.  path = the visited rows, out_tokens = their tokens then the bonus.
-__global__ __launch_bounds__(256) void accept_decide_tree_kernel(
+// (Four rows side by side and one thread walking the rows in LDS: 16 trees of up to 16 rows 8.5 us, now 4.7.)
+constexpr int kTreeThreads = 1024;
+
+__global__ __launch_bounds__(kTreeThreads) void accept_decide_tree_kernel(
     const int32_t* __restrict__ tokens, const int32_t* __restrict__ parent, const int32_t* __restrict__ qo_indptr,
     int32_t* __restrict__ accept_len, int32_t* __restrict__ out_tokens, int32_t* __restrict__ path,
     uint8_t* __restrict__ rollback, int32_t* __restrict__ stats, int M, int V, int nseg, int gamma_max,
     AcceptWorkspace w, int32_t* __restrict__ status_flags)
 {
-    __shared__ int s_arg[kMaxRows], s_bad[kMaxRows], s_tok[kMaxRows], s_par[kMaxRows];
-    const int i = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
+    __shared__ int s_arg[kMaxRows], s_bad[kMaxRows];
+    const int i = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r0 = qo_indptr[i], n = qo_indptr[i + 1] - r0;
-    int32_t* emit = out_tokens + (size_t)i * (gamma_max + 1);
-    int32_t* pth = path + (size_t)i * (gamma_max + 1);
-    for (int j = tid; j <= gamma_max; j += 256) { emit[j] = -1; pth[j] = j == 0 ? 0 : -1; }
-    if (tid == 0) { accept_len[i] = 0; if (rollback) rollback[i] = 0; }
-    if (n < 1 || n - 1 > gamma_max || r0 < 0 || r0 + n > M) {
-        if (tid == 0 && status_flags) atomicOr(status_flags, SPEC_FLAG_BAD_LENGTH);
-        return;
-    }
-    for (int j = wave; j < n; j += 4) {
+    const bool ok = n >= 1 && n - 1 <= gamma_max && r0 >= 0 && r0 + n <= M;      // (gamma_max < kMaxRows: host check)
+    int tok = 0, par = -1;
+    if (ok && wave == 0 && lane < n) { tok = tokens[r0 + lane]; par = parent[r0 + lane]; }
+    for (int j = wave; ok && j < n; j += kTreeThreads / 64) {
         const size_t base = (size_t)(r0 + j) * nseg;
         float m = -INFINITY;
         int arg = 0x7FFFFFFF, bad = 0;
@@ -698,41 +696,45 @@ __global__ __launch_bounds__(256) void accept_decide_tree_kernel(
         bad = __any(bad) || !(m > -INFINITY && m < INFINITY);
         if (lane == 0) { s_arg[j] = arg; s_bad[j] = bad; }
     }
-    if (tid < n) { s_tok[tid] = tokens[r0 + tid]; s_par[tid] = parent[r0 + tid]; }
     __syncthreads();
-    if (tid != 0) return;
-    int flags = 0;
-    for (int j = 0; j < n; ++j) {
-        if (s_bad[j]) flags |= SPEC_FLAG_BAD_LOGITS;
-        if (j > 0 && (s_tok[j] < 0 || s_tok[j] >= V)) flags |= SPEC_FLAG_BAD_TOKEN;
-        if (j == 0 ? s_par[0] != -1 : (s_par[j] < 0 || s_par[j] >= j)) flags |= SPEC_FLAG_BAD_TREE;
+    if (wave != 0) return;
+    int flags = ok ? 0 : SPEC_FLAG_BAD_LENGTH, a = 0;
+    bool back = false;
+    int emitted = -1, visited = lane == 0 ? 0 : -1;       // slot `lane` of out_tokens and of path
+    if (ok) {
+        const bool row = lane < n;
+        const int arg = row ? s_arg[lane] : -1;
+        if (__any(row && s_bad[lane])) flags |= SPEC_FLAG_BAD_LOGITS;
+        if (__any(row && lane > 0 && (tok < 0 || tok >= V))) flags |= SPEC_FLAG_BAD_TOKEN;
+        if (__any(row && (lane == 0 ? par != -1 : (par < 0 || par >= lane)))) flags |= SPEC_FLAG_BAD_TREE;
+        back = n > 1;
+        if (!flags) {
+            int u = 0;
+            for (;;) {                                    // (a child's row is above its parent's: at most n - 1 turns)
+                const int best = __builtin_amdgcn_readlane(arg, u);
+                const unsigned long long child = __ballot(row && lane > u && par == u && tok == best);
+                if (!child) break;
+                u = __ffsll((long long)child) - 1;
+                if (lane == a) emitted = best;
+                ++a;
+                if (lane == a) visited = u;
+            }
+            if (lane == a) emitted = __builtin_amdgcn_readlane(arg, u);
+            back = __any(row && lane > u && par == u);
+        }
     }
-    if (flags) {
-        if (rollback) rollback[i] = (uint8_t)(n > 1);
-        if (stats && n > 1) atomicAdd(stats + 0, 1);
-        if (status_flags) atomicOr(status_flags, flags);
-        return;
+    if (lane <= gamma_max) {
+        out_tokens[(size_t)i * (gamma_max + 1) + lane] = emitted;
+        path[(size_t)i * (gamma_max + 1) + lane] = visited;
     }
-    int u = 0, a = 0;
-    for (;;) {
-        int next = -1;
-        for (int v = u + 1; v < n; ++v)
-            if (s_par[v] == u && s_tok[v] == s_arg[u]) { next = v; break; }
-        if (next < 0) break;
-        emit[a] = s_tok[next];
-        ++a;
-        pth[a] = next;
-        u = next;
-    }
-    emit[a] = s_arg[u];
+    if (lane != 0) return;
     accept_len[i] = a;
-    int has_child = 0;
-    for (int v = u + 1; v < n; ++v) has_child |= (s_par[v] == u);
-    if (rollback) rollback[i] = (uint8_t)has_child;
-    if (stats) {
-        if (has_child) atomicAdd(stats + 0, 1);
-        atomicAdd(stats + 1, a + 1);
+    if (rollback) rollback[i] = (uint8_t)back;
+    if (stats && ok) {
+        if (back) atomicAdd(stats + 0, 1);
+        if (!flags) atomicAdd(stats + 1, a + 1);
     }
+    if (status_flags && flags) atomicOr(status_flags, flags);
 }
 
 // residual weight of vocabulary entry v on the job's row: max(0, p(v) - q(v)) in fp32, and p(v)
@@ -1192,7 +1194,7 @@ extern "C" int spec_accept_tree(const float* logits, const int32_t* tokens, cons
     carve(&w, (char*)workspace, B, M, nseg);
     hipStream_t s = (hipStream_t)stream;
     launch_row_stats(logits, nullptr, qo_indptr, B, M, V, nseg, w, stats, false, false, s);
-    hipLaunchKernelGGL(accept_decide_tree_kernel, dim3(B), dim3(256), 0, s, tokens, parent, qo_indptr, accept_len, out_tokens,
+    hipLaunchKernelGGL(accept_decide_tree_kernel, dim3(B), dim3(kTreeThreads), 0, s, tokens, parent, qo_indptr, accept_len, out_tokens,
                        path, rollback, stats, M, V, nseg, gamma_max, w, status_flags);
     return check_launch("spec_accept_tree");
 }
