@@ -16,6 +16,8 @@
 
 namespace specv {
 
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // (a row of logits starts at any multiple of 4 bytes)
+
 constexpr int kPkSlab = 128;                   // k per hidden slab in LDS
 constexpr int kPkHPitch = kPkSlab * 2;         // bytes per hidden row in LDS; 16-byte chunk ch of row r sits at position ch ^ (r & 15)
 constexpr int kPkMaxRows = 160;                // rows of hidden per row group (one workgroup's share)
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(256) void lm_head_pack_kernel(const uint16_t* __res
 template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW, bool ROWS>
 __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
-    int M_all, int H, int V, int n_panels, int panels_per_wg, bool vec_store, int groups, int rows_per_group,
+    int M_all, int H, int V, int n_panels, int panels_per_wg, int groups, int rows_per_group,
     float* __restrict__ blk_max, int32_t* __restrict__ blk_arg, int nblk, int passes_per_range)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -308,14 +310,17 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
                 asm volatile("" : "+v"(cslot));
             }
         }
-        if (vec_store) {
-            // V % 4 == 0.  The tile is turned through the wave's own LDS patch so that one store instruction writes
-            // all the wave's entries of a row (whole cache lines), 4 or 8 rows at a time, instead of 64 bytes of each of 16 rows.
-            // LDS operations of one wave execute in order, so the patch needs no barrier and no second copy.
+        {
+            // The tile is turned through the wave's own LDS patch so that one store instruction writes
+            // all the wave's entries of a row (whole cache lines where rows are aligned), 4 or 8 rows at a time, instead of 64 bytes of each of 16 rows.
+            // LDS operations of one wave execute in order, so the patch needs no barrier and no second copy.  A row starts at any multiple of 4 bytes; the last
+            // entries of one whose length is no multiple of 4 are stored one by one.  (All entries one by one there: V = 50021, H = 1280 M = 57 30.1 -> 27.0 us,
+            // M = 96 35.8 -> 31.8; V = 32001, H = 1024 M = 60 20.4 -> 16.9.)
             constexpr int kLanesPerRow = TN * 4, kRowsPerStore = 64 / kLanesPerRow;
             const int srow = lane / kLanesPerRow, scol = (lane % kLanesPerRow) * 4;     // this lane's row and entry when storing
             const int col0 = st_p0 * 16 + scol;
-            const bool col_ok = scol < st_np * 16 && col0 < V;
+            const bool mine = scol < st_np * 16, col_ok = mine && col0 + 4 <= V;
+            const int col_tail = mine && !col_ok ? V - col0 : 0;
             uint32_t off = ((uint32_t)srow * (uint32_t)V + (uint32_t)col0) * 4u;
             const uint32_t row_step = (uint32_t)kRowsPerStore * 4u * (uint32_t)V;
 #pragma unroll
@@ -330,26 +335,18 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
                     const int prow = q * kRowsPerStore + srow, row = tm * 16 + prow;
                     const f32x4 v = *reinterpret_cast<const f32x4*>(patch + prow * kPatchPitch + scol * 4);
                     if (row < M && col_ok) {
-                        f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<unsigned char*>(C) + off);
-                        if constexpr (NT) __builtin_nontemporal_store(v, dst); else *dst = v;
+                        f32x4_any* dst = reinterpret_cast<f32x4_any*>(reinterpret_cast<unsigned char*>(C) + off);
+                        if constexpr (NT) __builtin_nontemporal_store((f32x4_any)v, dst); else *dst = v;
+                    }
+                    if (row < M && col_tail > 0) {    // the matrix ends inside these four entries
+                        float* dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(C) + off);
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) if (e < col_tail) dst[e] = v[e];
                     }
                     off += row_step;                  // one running byte offset (M * V * 4 < 2^32 per launch) instead of
                     asm volatile("" : "+v"(off));     // one row address per store kept alive across the whole pass
                 }
             }
-        } else {
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    const int row = tm * 16 + l16, e = (st_p0 + tn) * 16 + kg * 4;
-                    if (row < M && tn < st_np) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (e + i < V) C[(size_t)row * V + e + i] = acc[tn][tm][i];
-                    }
-                    acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
         }
         if (!more) break;
     }
@@ -385,9 +382,8 @@ static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int
     int ranges, per_range;
     packed_geometry(V, groups, &ranges, &per_range);
     const int ppr = (per_range + NW * TN - 1) / (NW * TN);
-    const bool vec_store = (V % 4 == 0);
     hipLaunchKernelGGL((lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW, ROWS>), dim3(ranges * groups), dim3(64 * NW), smem, s, a, wp, c, M, H, V,
-                       (V + 15) / 16, per_range, vec_store, groups, BM, blk_max, blk_arg, ranges * ppr, ppr);
+                       (V + 15) / 16, per_range, groups, BM, blk_max, blk_arg, ranges * ppr, ppr);
     return SPEC_OK;
 }
 
