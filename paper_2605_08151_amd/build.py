@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -11,28 +12,33 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspecverify.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
 # (the slowest to compile first)
-SOURCES = ["lm_head_mfma_summary.hip", "lm_head_mfma_buffer.hip", "lm_head_mfma_global.hip", "verify_attn.hip", "lm_head_mfma_stream.hip", "lm_head_rowmajor.hip", "lm_head_tile.hip", "lm_head_mfma.hip", "lm_head_packed.hip", "lm_head.hip", "api.hip", "accept.hip", "kv_commit.hip", "assemble_next.hip", "draft_side.hip", "probes.hip"]
+SOURCES = ["lm_head_rowmajor.hip", "lm_head_rowmajor_stream.hip", "lm_head_mfma_summary.hip", "lm_head_tile.hip", "lm_head_mfma_buffer.hip", "lm_head_mfma_global.hip", "lm_head_mfma_stream.hip",
+           "verify_attn.hip", "lm_head_mfma.hip", "lm_head_packed.hip", "lm_head.hip", "api.hip", "accept.hip", "kv_commit.hip", "assemble_next.hip", "draft_side.hip", "probes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-def build(verbose: bool = False, jobs: int = 5) -> str:
+def build(verbose: bool = False, jobs: int = 7) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    procs = []
-    objs = []
-    for src in SOURCES:
+
+    def compile_one(src):
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        objs.append(obj)
         cmd = [hipcc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        if len(procs) >= jobs:
-            _drain(procs)
-    _drain(procs)
+        done = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        text = "\n".join(l for l in done.stdout.splitlines() if "packed-fp32-ops" not in l)
+        if text.strip():
+            sys.stderr.write(text + "\n")
+        if done.returncode != 0:
+            raise RuntimeError(f"hipcc failed on {src}")
+        return obj
+
+    with ThreadPoolExecutor(jobs) as pool:                # (a process each; the next starts when one ends)
+        objs = list(pool.map(compile_one, SOURCES))
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
     build_marshal()
@@ -52,18 +58,6 @@ def build_marshal() -> str:
            "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     subprocess.run(cmd, check=True)
     return MARSHAL
-
-
-def _drain(procs):
-    while procs:
-        src, p = procs.pop(0)
-        out, _ = p.communicate()
-        text = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
-        if p.returncode != 0:
-            sys.stderr.write(text + "\n")
-            raise RuntimeError(f"hipcc failed on {src}")
-        if text.strip():
-            sys.stderr.write(text + "\n")
 
 
 if __name__ == "__main__":
