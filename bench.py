@@ -41,8 +41,8 @@ NAMES = ("verify_attn", "lm_head", "accept", "kv_commit")
 KERNEL_OF_CALL = {
     ("verify_attn", True): ("verify_attn_rows_kernel", "verify_attn_kernel"),
     ("verify_attn", False): ("verify_attn_rows_kernel", "verify_attn_kernel"),
-    ("lm_head", True): ("lm_head_mfma_kernel", "lm_head_packed_kernel"),
-    ("lm_head", False): ("lm_head_big2_kernel", "lm_head_big_kernel", "lm_head_packed_kernel(row-major)", "lm_head_skinny_kernel", "lm_head_tiled_kernel"),
+    ("lm_head", True): ("lm_head_mfma_kernel", "lm_head_tile_kernel", "lm_head_packed_kernel"),
+    ("lm_head", False): ("lm_head_rowmajor_kernel", "lm_head_big2_kernel", "lm_head_big_kernel", "lm_head_packed_kernel(row-major)", "lm_head_skinny_kernel", "lm_head_tiled_kernel"),
     ("accept", True): ("accept_row_stats_kernel",), ("accept", False): ("accept_row_stats_kernel",),
     ("kv_commit", True): ("kv_commit_kernel",), ("kv_commit", False): ("kv_commit_kernel",),
 }
@@ -537,7 +537,8 @@ def _algorithmic_by_kernel(cfg_name):
     n_stoch = int((b["temperature"] > 0).sum())
     return {"verify_attn_kernel": alg["attn_bytes"] / 1e6, "verify_attn_rows_kernel": alg["attn_bytes"] / 1e6,
             "lm_head_packed_kernel": alg["lm_bytes"] / 1e6, "lm_head_packed_kernel(row-major)": alg["lm_bytes"] / 1e6,
-            "lm_head_mfma_kernel": alg["lm_bytes"] / 1e6, "lm_head_big2_kernel": alg["lm_bytes"] / 1e6,
+            "lm_head_mfma_kernel": alg["lm_bytes"] / 1e6, "lm_head_tile_kernel": alg["lm_bytes"] / 1e6,
+            "lm_head_rowmajor_kernel": alg["lm_bytes"] / 1e6, "lm_head_big2_kernel": alg["lm_bytes"] / 1e6,
             "lm_head_skinny_kernel": alg["lm_bytes"] / 1e6,
             "accept_row_stats_kernel": b["M"] * cfg.V * 4 / 1e6,
             "accept_bonus_kernel(exponentials)": n_stoch * cfg.V * 4 / 1e6, "accept_bonus_kernel(residual)": n_stoch * 2 * cfg.V * 4 / 1e6}
@@ -667,7 +668,7 @@ def summarize_trace(args):
     name = args.config
     rows = [r for r in csv.DictReader(open(args.summarize_trace)) if "specv::" in r["Name"]]
     rows.sort(key=lambda r: -float(r["TotalDurationNs"]))
-    cmd = args.profile_cmd or f"python3 bench.py --config {name} --steps 30 --warmup 5 --no-cpu-baseline --no-per-config"
+    cmd = args.profile_cmd or f"python3 bench.py --config {name} --steps 20 --warmup 5 --no-cpu-baseline --no-per-config --no-peaks"
     md = os.path.join(ROOT, "profiles", f"step_{name}_kernel_trace.md")
     with open(md, "w") as o:
         o.write(f"# Verification step, workload '{name}': rocprofv3 kernel trace\n\n")
