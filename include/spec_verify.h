@@ -97,7 +97,8 @@ int spec_version(void);
  *   "lm_packed_wide"   that kernel with passes of 512 vocabulary entries over row groups of at most 80 rows:
  *                      0 = automatic (off), 1 = always, 2 = never.
  *   "lm_packed_tile"   which kernel spec_lm_head_packed runs for M > 160: 0 = automatic (the large-tile MFMA-bound
- *                      kernel), 1 = the weight-streaming kernel over row groups of at most 160 rows.
+ *                      kernel, which also serves most shapes from 113 rows on), 1 = the weight-streaming
+ *                      kernel over row groups of at most 160 rows.
  *   "lm_mfma_rows"     rows per row group of that large-tile kernel at most, 144..256; 0 = automatic.
  *   "lm_mfma_nt"       its logits stores nontemporal: 0 = automatic (at most 416 rows and V a multiple of 16), 1 = always,
  *                      2 = never.
