@@ -513,7 +513,7 @@ int lm_head_mfma_blocks(int M, int H, int V);
 //   17 panels per CU and more: V = 151936, H = 4096 M = 113 224 -> 211, M = 128 230 -> 214, M = 144 248 -> 221, M = 160 260 -> 224; V = 100000 M = 160 172 -> 153;
 //     V = 68000, H = 1280 M = 120 55.1 -> 49.7, M = 160 60.8 -> 54.6; V = 131072, H = 1024 M = 128 64.8 -> 65.0, M = 160 69.5 -> 68.8
 //   13 to 16: V = 64000, H = 2560 M = 113 61.4 -> 62.9, M = 160 64.6 -> 68.4; V = 57344, H = 1280 M = 160 37.9 -> 41.1, H = 4096 96.3 -> 90.9;
-//     but V = 64013, H = 2560 M = 128 76 -> 66 (rows of logits that are not aligned cost this kernel a store per entry)
+//     but rows of logits that are not aligned V = 64013, H = 2560 M = 128 69 -> 66, M = 160 76 -> 69, V = 57345, H = 1280 40.1 -> 36.4, 45.7 -> 40.0
 //   10 to 12: V = 49152 M = 128 H = 1280 32.8 -> 31.1, H = 4096 79 -> 72; V = 40000, H = 1024 M = 128 19.7 -> 19.2
 //   9: V = 36864 M = 128 H = 2048 39.6 -> 37.0, but H = 1280 (94 MB, ordinary loads) 23.0 -> 25.9
 //   5 to 8: V = 32000, H = 1024 M = 128 19.7 -> 19.8, M = 160 21.3 -> 20.8, H = 2560 35.8 -> 37.9, 40.8 -> 39.8, H = 4096 52 -> 50, 62 -> 53

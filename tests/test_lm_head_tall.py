@@ -114,7 +114,7 @@ def test_lines_between_the_weight_streaming_and_the_large_tile_kernel(sv, oracle
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("M", [113, 128, 160, 161, 256, 257, 400])
-@pytest.mark.parametrize("V,H", [(999, 4096), (20001, 256), (37003, 512), (49152, 1280), (70000, 256), (64013, 1024)])
+@pytest.mark.parametrize("V,H", [(999, 4096), (20001, 256), (32001, 512), (37003, 512), (49152, 1280), (70000, 256), (64013, 1024)])
 def test_row_major_weights_through_the_large_tile_kernel(sv, oracle, M, V, H):
     """Ragged last panels (rows past the matrix repeat its last one), one group and two, ordinary and nontemporal loads, aligned rows of logits and not.  Same
     order of additions as on packed weights: same bits."""
