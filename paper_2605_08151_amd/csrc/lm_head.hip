@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256 * MS, 1) void lm_head_skinny_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// MFMA-bound kernel for M > 160 rows (large or deeply speculating batches: 576 to ~1200 rows).
+// MFMA-bound kernel for M > 160 rows (large or deeply speculating batches: 576 to ~1200 rows), where H is no multiple of 256.
 //   * (64*TMW) x 256 output tile per workgroup, 4 waves in a 2 x 2 grid, each wave TMW x 4 tiles of
 //     v_mfma_f32_32x32x16_bf16 (up to 256 accumulator registers).
 //   * K advances in slabs of 32 through a ring of 4 LDS stages filled by direct HBM/L2 -> LDS loads
