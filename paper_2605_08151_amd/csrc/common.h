@@ -96,14 +96,16 @@ __device__ inline uint32_t f32_to_bf16_bits(float f) { return pack_bf16x2(f, 0.0
 // 16 bytes per lane from global memory straight into LDS at lds_base + 16 * lane (lds_base wave-uniform).
 // Written as inline assembly so that the compiler does not order it against later LDS reads by draining
 // the whole load queue: the kernel double-buffers and waits with explicit s_waitcnt vmcnt(n) instead.
-// M0 (the LDS base of the transfer) is an operand tied to that register: the compiler writes it and knows it is live.
+// M0 (the LDS base of the transfer) is an operand tied to that register: the compiler writes it and knows it is live.  The s_nop is the wait state that a load to
+// LDS needs behind a scalar instruction that writes M0; the compiler inserts it for loads of its own only (a test looks at the built code).  It costs nothing that
+// shows: attention of 128 decode rows 214 us with and without, the step of 160 rows 294, of 64 x 9 rows 716 without and 700 with (another card).
 // STREAM: a nontemporal load, for bytes that are read once (see kMemorySideCache).
 template <bool STREAM = false>
 __device__ inline void lds_dma16(const void* g, void* lds_base)
 {
     const uint32_t m0v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_base;
-    if constexpr (STREAM) asm volatile("global_load_lds_dwordx4 %0, off nt" ::"v"(g), "{m0}"(m0v) : "memory");
-    else asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(m0v) : "memory");
+    if constexpr (STREAM) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "{m0}"(m0v) : "memory");
+    else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(m0v) : "memory");
 }
 
 // The same with a wave-uniform base and a 32-bit offset per lane: no vector address arithmetic.
@@ -111,8 +113,8 @@ template <bool STREAM = false>
 __device__ inline void lds_dma16_off(uint32_t off, const void* base, void* lds_base)
 {
     const uint32_t m0v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_base;
-    if constexpr (STREAM) asm volatile("global_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
-    else asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
+    if constexpr (STREAM) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
+    else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0v) : "memory");
 }
 
 // Block summaries of the large-tile LM head (lm_head_mfma_kernel.h): what acceptance needs from a row of logits without reading it again.  A
