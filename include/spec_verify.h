@@ -93,9 +93,10 @@ int spec_version(void);
  *                      register staging.
  *   "lm_big_waves"     waves per workgroup of the MFMA-bound kernels of spec_lm_head: 4 or 8 (default).
  *   "lm_packed_waves"  waves per workgroup of the weight-streaming kernel of spec_lm_head_packed: 4 or 8; 0 = automatic (8, or
- *                      4 of half the width where a CU has at most 8 panels of 16 entries).
+ *                      4 of half the width where a CU has at most 8 panels of 16 entries).  Any other value than 0 also keeps
+ *                      batches of 113 to 160 rows with that kernel.
  *   "lm_packed_wide"   that kernel with passes of 512 vocabulary entries over row groups of at most 80 rows:
- *                      0 = automatic (off), 1 = always, 2 = never.
+ *                      0 = automatic (off), 1 = always (batches of 113 to 160 rows too), 2 = never.
  *   "lm_packed_tile"   which kernel spec_lm_head_packed runs for M > 160: 0 = automatic (the large-tile MFMA-bound
  *                      kernel, which also serves most shapes from 113 rows on), 1 = the weight-streaming
  *                      kernel over row groups of at most 160 rows.
