@@ -1,0 +1,18 @@
+// Rules on the number of requests in a batch.  Plain arithmetic without device types: the launches, their kernels and a CPU test share it.
+#pragma once
+
+namespace specv {
+
+// Threads per pair of sequences in divergence_kernel, and positions per thread in one memory round trip.  Few pairs wait for round trips: many positions in each.
+// With more pairs than CUs they hide each other's waits, and what counts is what is read for nothing behind an early difference.  Pairs of 3000 tokens that
+// differ at 10 / 600 / 2999, and of 16000 at the end, us, in the order 512 x 8, 512 x 2, 256 x 4 (one position of 256 threads before):
+//   B = 128 3.3 / 3.3 / 3.2, 13.9 (4.1 / 4.8 / 6.5, 37.9); 256 3.9 / 3.9 / 3.9, 13.8 against 2.7 / 2.6 / 4.6, 17.9
+//   B = 384 4.5 / 4.5 / 4.5, 15.7 against 2.8 / 2.8 / 5.1, 19.9; 1024 6.5 / 6.5 / 6.4 against 3.6 / 3.6 / 6.6, 31 against 3.8 / 3.8 / 7.8, 44 (5.4 / 5.7 / 9.8, 55)
+//   B = 2048 6.0 / 6.0 / 11.2, 60 against 5.2 / 5.2 / 9.9, 54 (7.9 / 8.0 / 11.1, 63); 8192 46.6 / 46.5 / 46.2 against 15.6 / 15.8 / 43.5 (23 / 25 / 51)
+struct DivergenceShape { int threads, per; };
+constexpr DivergenceShape divergence_shape(int B, int cus)
+{
+    return B <= cus ? DivergenceShape{512, 8} : B <= 4 * cus ? DivergenceShape{512, 2} : DivergenceShape{256, 4};
+}
+
+}  // namespace specv

@@ -1,16 +1,15 @@
 // Draft-side primitives (paper, Appendix "Draft side": "Message handling and update", "State recovery";
 // Method, "Draft-side context compression", eq. token_eviction).  Integer-only ragged work; none of it is on the
 // target's critical path, so the kernels are plain: one workgroup per request, coalesced token reads.
+#include "batch_rules.h"
 #include "common.h"
 
 namespace specv {
 
 // delta_i = min{ t : p_i[t] != h_i[t] }, or the shorter length when one sequence is a prefix of the other.
-// A chain of memory round trips: 4096 positions are compared per trip (one position per thread and trip, 256 in all: 128 pairs of 3000 tokens
-// 6.5 us, now 3.2; of 16000 38, now 14).
-constexpr int kDivThreads = 512, kDivPer = 8;
-
-__global__ __launch_bounds__(kDivThreads) void divergence_kernel(
+// A chain of memory round trips, THREADS * PER positions in each (see divergence_shape).
+template <int THREADS, int PER>
+__global__ __launch_bounds__(THREADS) void divergence_kernel(
     const int32_t* __restrict__ p_tokens, const int32_t* __restrict__ p_indptr,
     const int32_t* __restrict__ h_tokens, const int32_t* __restrict__ h_indptr, int32_t* __restrict__ delta)
 {
@@ -21,22 +20,23 @@ __global__ __launch_bounds__(kDivThreads) void divergence_kernel(
     if (tid == 0) s_first = n > 0 ? n : 0;
     __syncthreads();
     // chunks in order: the first one with a difference ends the walk for the whole workgroup
-    for (int base = 0; base < n; base += kDivThreads * kDivPer) {
-        bool differs[kDivPer];
+    for (int base = 0; base < n; base += THREADS * PER) {
+        const int m = n - base;
+        bool differs[PER];
 #pragma unroll
-        for (int k = 0; k < kDivPer; ++k) {
-            const int t = base + k * kDivThreads + tid;
-            differs[k] = t < n && p_tokens[p0 + t] != h_tokens[h0 + t];
+        for (int k = 0; k < PER; ++k) {
+            const int t = k * THREADS + tid;
+            differs[k] = t < m && p_tokens[p0 + base + t] != h_tokens[h0 + base + t];
         }
         int first = -1;                                   // the wave's first difference
 #pragma unroll
-        for (int k = kDivPer - 1; k >= 0; --k) {
-            const unsigned long long m = __ballot(differs[k]);
-            if (m) first = base + k * kDivThreads + wave0 + __builtin_ctzll(m);
+        for (int k = PER - 1; k >= 0; --k) {
+            const unsigned long long d = __ballot(differs[k]);
+            if (d) first = base + k * THREADS + wave0 + __builtin_ctzll(d);
         }
         if (first >= 0 && tid == wave0) atomicMin(&s_first, first);
         if (__syncthreads_or(first >= 0)) break;
-        if (n - base <= kDivThreads * kDivPer) break;     // (base stays below 2^31)
+        if (n - base <= THREADS * PER) break;             // (base stays below 2^31)
     }
     __syncthreads();
     if (tid == 0) delta[i] = s_first;
@@ -160,7 +160,11 @@ extern "C" int spec_divergence(const int32_t* p_tokens, const int32_t* p_indptr,
     if (B < 0) return fail(SPEC_EINVAL, "spec_divergence: negative B=%d", B);
     if (B == 0) return SPEC_OK;
     if (!p_tokens || !p_indptr || !h_tokens || !h_indptr || !delta) return fail(SPEC_EINVAL, "spec_divergence: NULL pointer argument");
-    hipLaunchKernelGGL(divergence_kernel, dim3(B), dim3(kDivThreads), 0, (hipStream_t)stream, p_tokens, p_indptr, h_tokens, h_indptr, delta);
+    hipStream_t s = (hipStream_t)stream;
+    const DivergenceShape shape = divergence_shape(B, device_cu_count());
+    if (shape.threads == 256) hipLaunchKernelGGL((divergence_kernel<256, 4>), dim3(B), dim3(256), 0, s, p_tokens, p_indptr, h_tokens, h_indptr, delta);
+    else if (shape.per == 2) hipLaunchKernelGGL((divergence_kernel<512, 2>), dim3(B), dim3(512), 0, s, p_tokens, p_indptr, h_tokens, h_indptr, delta);
+    else hipLaunchKernelGGL((divergence_kernel<512, 8>), dim3(B), dim3(512), 0, s, p_tokens, p_indptr, h_tokens, h_indptr, delta);
     return check_launch("spec_divergence");
 }
 

@@ -24,3 +24,23 @@ def test_divergence_at_the_edges_of_a_trip(sv, oracle):
     expected = at + lens[len(at):]
     assert delta.cpu().tolist() == expected
     assert oracle.divergence(np.concatenate(p), indptr(p), np.concatenate(h), indptr(h)).tolist() == expected
+
+
+@pytest.mark.parametrize("per_cu", [1, 4])
+def test_divergence_of_many_sequences(sv, oracle, per_cu):
+    """More pairs than CUs, and more than four per CU: trips of 1024 positions by 512 threads and by 256, a difference at every edge."""
+    edges = [0, 1, 63, 64, 255, 256, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 3000]
+    rng = np.random.default_rng(6)
+    B = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + 5
+    at = [edges[i % len(edges)] for i in range(B)]
+    p = [rng.integers(0, 9, t + 1 + i % 3).astype(np.int32) for i, t in enumerate(at)]
+    h = [x.copy() for x in p]
+    for i, t in enumerate(at):
+        if i % 5:                                                # (every fifth agrees to its end)
+            h[i][t:] += 1
+    indptr = lambda rows: np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)  # noqa: E731
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    delta = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    sv.spec_divergence(dev(np.concatenate(p)), dev(indptr(p)), dev(np.concatenate(h)), dev(indptr(h)), delta)
+    assert delta.cpu().tolist() == oracle.divergence(np.concatenate(p), indptr(p), np.concatenate(h), indptr(h)).tolist()
+    assert delta.cpu().tolist() == [len(x) if i % 5 == 0 else t for i, (x, t) in enumerate(zip(p, at))]
