@@ -15,4 +15,10 @@ constexpr DivergenceShape divergence_shape(int B, int cus)
     return B <= cus ? DivergenceShape{512, 8} : B <= 4 * cus ? DivergenceShape{512, 2} : DivergenceShape{256, 4};
 }
 
+// Up to so many requests attention's merge kernels count those that start before their row, 256 in a round trip; beyond, a binary search is ahead, whose dependent
+// round trips other workgroups hide, and which reads few bytes.  Requests of one row that are split by their bound, 8 heads, whole call, us, count -> search:
+// B = 2048 83 -> 82, 4096 169 -> 159, 8192 365 -> 320, 16384 820 -> 630, 65535 5715 -> 2605; of two rows, 32 heads: 2048 352 -> 343, 4096 759 -> 686, 8192 1770 -> 1439.
+// At B = 1024 43 with either.
+constexpr int kMergeCounted = 1024;
+
 }  // namespace specv

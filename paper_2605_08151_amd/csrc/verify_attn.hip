@@ -17,6 +17,7 @@
 //   the transposing LDS read (ds_read_b64_tr_b16), Q fragments are re-read from a shared LDS copy.
 //   Every chunk writes an unnormalised fp32 partial (O, running max, sum); a second kernel merges the
 //   partials of a row in split order (deterministic) and writes bf16.
+#include "batch_rules.h"
 #include "common.h"
 #include "kv_stream.h"
 
@@ -954,9 +955,17 @@ __global__ __launch_bounds__(1024) void verify_attn_plan_kernel(AttnParams p, in
 }
 
 // The request of candidate row `row`: the number of requests that start at or before it, less one (-1: none), counted by the whole workgroup in one memory round
-// trip per 256 requests (a binary search is eight dependent trips for 256).
+// trip per 256 requests (a binary search is eight dependent trips for 256; it serves batches of more than kMergeCounted).
 __device__ inline int request_of_row(const AttnParams& p, int B, int row)
 {
+    if (B > kMergeCounted) {
+        int lo = -1, hi = B - 1;                          // the largest request that starts at or before the row
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (p.qo_indptr[mid] <= row) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    }
     int before = 0;
     for (int k = 0; k < B; k += 256) before += __syncthreads_count(k + (int)threadIdx.x < B && p.qo_indptr[k + threadIdx.x] <= row);
     return __builtin_amdgcn_readfirstlane(before) - 1;   // (the same in every lane)
