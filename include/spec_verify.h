@@ -86,7 +86,7 @@ int spec_version(void);
  *                      sums over every row; 3 = as 1 with an interval so wide that most tests take the fp64 path (a
  *                      test hook).  Same integers in all.
  *   "lm_kernel"       kernel used by spec_lm_head: 0 = automatic (the large-tile kernel of spec_lm_head_packed
- *                      in its row-major form for M > 160 and most shapes from 113 rows on; below, its
+ *                      in its row-major form for most shapes from 113 rows on, 8 for the others of M > 160; below, its
  *                      weight-streaming kernel in that form, or 1 for a vocabulary too small for it), 1 =
  *                      4-wave weight-streaming kernel, 2 = MFMA-bound with direct global->LDS loads, 3 = plain
  *                      tiled, 4..7 = variants of 1 (wave count / register-ring depth; 7 = 1), 8 = MFMA-bound with

@@ -5,6 +5,7 @@
 // Both operands are K-contiguous ("NT" product), which is the MFMA operand order: lane l of a
 // 32x32x16 step holds 8 consecutive k of row l%32 (A) or of vocabulary entry l%32 (B), k-group l/32.
 #include "common.h"
+#include "lm_head_tiles.h"
 
 namespace specv {
 
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(256 * MS, 1) void lm_head_skinny_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// MFMA-bound kernel for M > 160 rows (large or deeply speculating batches: 576 to ~1200 rows), where H is no multiple of 256.
+// MFMA-bound kernel for M > 160 rows (large or deeply speculating batches: 576 to ~1200 rows), where H is no multiple of 256, or the large-tile kernel is behind.
 //   * (64*TMW) x 256 output tile per workgroup, 4 waves in a 2 x 2 grid, each wave TMW x 4 tiles of
 //     v_mfma_f32_32x32x16_bf16 (up to 256 accumulator registers).
 //   * K advances in slabs of 32 through a ring of 4 LDS stages filled by direct HBM/L2 -> LDS loads
@@ -622,9 +623,9 @@ Tunable g_lm_kernel_waves{8};  // benchmark hook: waves per workgroup of the MFM
 // benchmark hook: 0 = automatic, 1 = weight-streaming (this file's), 2 = MFMA-bound with direct loads, 3 = plain tiled, 8 = MFMA-bound with
 // register staging, 4 = weight-streaming with 8 waves (4 x 2) and a 2-slab ring, 5/6/7 = 4 waves with
 // 4-slab ring / 4-slab ring + paired refills / 2-slab ring + paired refills (what 0 and 1 run).
-// The automatic choice is lm_head_rowmajor_dispatch (lm_head_mfma.hip: more than 160 rows, and most shapes from 113 rows on), then for M <= 160 lm_head_rows_dispatch
+// The automatic choice is lm_head_rowmajor_dispatch (lm_head_mfma.hip: most shapes from 113 rows on), then for M <= 160 lm_head_rows_dispatch
 // (lm_head_packed.hip) where that takes the shape; this file's weight-streaming kernel serves the smaller vocabularies, and spec_lm_head_stats; its MFMA-bound
-// kernels serve H that is no multiple of 256.
+// kernels serve H that is no multiple of 256, and the larger batches where they are ahead (lm_rowmajor_large_tile).
 Tunable g_lm_kernel{0};
 
 // vocabulary entries per workgroup and the grid of the weight-streaming kernel
@@ -739,10 +740,9 @@ extern "C" int spec_lm_head(const void* hidden, const void* W, float* logits, in
         else rc = launch_skinny_auto<10>(a, w, logits, M, H, V, s);
         if (rc != SPEC_OK) return rc;
     } else if ((force == 8 || (force == 0 && M > 160)) && H % (2 * kB2BK) == 0) {
-        const int waste192 = (M + 191) / 192 * 192 - M, waste256 = (M + 255) / 256 * 256 - M;
         int rc;
-        if (g_lm_kernel_waves == 4) rc = waste192 <= waste256 ? launch_big2<3, 4>(a, w, logits, M, H, V, s) : launch_big2<4, 4>(a, w, logits, M, H, V, s);
-        else rc = waste192 <= waste256 ? launch_big2<3, 8>(a, w, logits, M, H, V, s) : launch_big2<4, 8>(a, w, logits, M, H, V, s);
+        if (g_lm_kernel_waves == 4) rc = lm_big2_rows(M) == 192 ? launch_big2<3, 4>(a, w, logits, M, H, V, s) : launch_big2<4, 4>(a, w, logits, M, H, V, s);
+        else rc = lm_big2_rows(M) == 192 ? launch_big2<3, 8>(a, w, logits, M, H, V, s) : launch_big2<4, 8>(a, w, logits, M, H, V, s);
         if (rc != SPEC_OK) return rc;
     } else if ((force == 2 || (force == 0 && M > 160)) && H % kBigBK == 0 && H >= kBigBK * kBigStages) {   // H % 128 != 0 ends here
         // row tiles of 192 or 256: whichever wastes fewer padded rows

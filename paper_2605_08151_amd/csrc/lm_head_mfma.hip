@@ -68,22 +68,11 @@ int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M
 
 int lm_head_rowmajor(bool stream, bool nt, const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, const MfmaLayout& L, hipStream_t s);
 
-// The same on a row-major matrix, for spec_lm_head.  Returns false if it does not take the shape, or other kernels are ahead.
-// More than 160 rows: always (the kernels with 32 x 32 products of lm_head.hip -> this, us: V = 151936, H = 4096 M = 192 371 -> 296, M = 320 536 -> 451, M = 576 800 -> 744,
-// M = 1152 1489 -> 1368; V = 64000, H = 2560 M = 200 99 -> 86; V = 32000, H = 4096 M = 256 112 -> 84; V = 2000, H = 2048 M = 224 52 -> 32).  113 to 160 rows, against the
-// weight-streaming kernels, by panels per CU:
-//   17 and more: V = 151936 M = 128 H = 4096 284 -> 249, H = 1280 107 -> 99.5; V = 128256, H = 2048 135 -> 133; V = 68000, H = 2560 113 -> 103
-//   13 to 16: V = 64000, H = 2560 M = 128 70 -> 73; rows of logits not aligned V = 61001, H = 2048 M = 128 65.7 -> 60.8, M = 160 72.7 -> 63.9, V = 53249, H = 4096 108.5 -> 109.3
-//   9 to 12: V = 36864 M = 128 H = 1280 32.9 -> 30.1, H = 4096 89 -> 79; V = 45056, H = 1280 33.6 -> 33.7; V = 49152, H = 2048 55.7 -> 54.3
-//   8: V = 32000 M = 128 H = 1024 17.0 -> 17.9, H = 4096 64.8 -> 64.7; V = 32001, H = 2560 44.1 -> 49.1
-//   fewer: aligned as 8; not aligned V = 24001, H = 1280 M = 128 24.6 -> 22.3, V = 20001, H = 2048 M = 160 34.7 -> 32.0, V = 8001, H = 4096 34.5 -> 45
+// The same on a row-major matrix, for spec_lm_head.  Returns false if it does not take the shape, or other kernels are ahead (see lm_rowmajor_large_tile).
 bool lm_head_rowmajor_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc)
 {
-    if (M <= 112 || H % (kMfRing * kMfSlab) != 0 || (size_t)V > ((size_t)1 << 32) / (4 * (size_t)(304 + 16))) return false;
-    if (M <= 160) {
-        const int panels = mf_per_range((V + 15) / 16, 1, device_cu_count());
-        if (panels < 5 || panels == 8 || (V % 4 == 0 && (panels < 8 || (panels > 12 && panels <= 16)))) return false;
-    }
+    static_assert(kMfRing * kMfSlab == 256, "the rule's multiple of H");
+    if (!lm_rowmajor_large_tile(M, H, V, device_cu_count())) return false;
     const MfmaLayout L = mfma_layout_for(M, V, device_cu_count(), 0);
     *rc = lm_head_rowmajor(mfma_loads(L.groups, H, V) == kStreamLoads, M <= 416 && V % 16 == 0, a, w, c, M, H, V, L, s);
     return true;

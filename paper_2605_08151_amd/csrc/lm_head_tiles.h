@@ -2,6 +2,7 @@
 // requests for them.  Integer arithmetic only, without device types: the kernel, its launch and a CPU test that walks whole matrices share it.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 
 namespace specv {
@@ -79,12 +80,16 @@ constexpr MfmaLayout mfma_layout_for(int M, int V, int cus, int cap_rows)
 // M = 1056 1070 / 1021, M = 1152 1148 / 1097; V = 128256 M = 288 301 / 268, M = 576 540 / 476, M = 1152 987 / 909; V = 32000 M = 576 138 / 127, M = 1152 261 / 235;
 // H = 2560 V = 64000 M = 272 98 / 90, M = 576 184 / 162.  Not chosen: H = 4096 V = 100000 M = 576 403 / 419 (3 full passes and one panel),
 // V = 128256 M = 800 678 / 689; H = 1024 V = 32000 M = 288 25 / 28.5.
+constexpr long mf_slots10(int per_range, int tm)
+{
+    const int rest = per_range % kMfPassPanels, last = (rest + kMfWaves - 1) / kMfWaves;
+    return (long)(per_range / kMfPassPanels) * 40 + (rest == 0 ? 0 : last <= 2 ? 29 : (last == 3 && tm <= 16) ? 35 : 40);
+}
+
 constexpr long mf_tall_cost(int tiles, int groups, int n_panels, int cus)
 {
     const int per_range = mf_per_range(n_panels, groups, cus), tm = (tiles + groups - 1) / groups;
-    const int rest = per_range % kMfPassPanels, last = (rest + kMfWaves - 1) / kMfWaves;
-    const long slots10 = (long)(per_range / kMfPassPanels) * 40 + (rest == 0 ? 0 : last <= 2 ? 29 : (last == 3 && tm <= 16) ? 35 : 40);
-    return slots10 * (2 * tm + 6);
+    return mf_slots10(per_range, tm) * (2 * tm + 6);
 }
 
 constexpr MfmaLayout mfma_tall_layout_for(int M, int V, int cus)
@@ -97,6 +102,42 @@ constexpr MfmaLayout mfma_tall_layout_for(int M, int V, int cus)
         if (cost < best) { best = cost; groups = g; }
     }
     return groups == 0 ? MfmaLayout{} : mf_layout_of(tiles, groups, n_panels, cus);
+}
+
+// Rows of a tile of the kernel with 32 x 32 products (lm_head_big2_kernel), whichever of the two pads less; a tile is 256 vocabulary entries wide.
+constexpr int lm_big2_rows(int M) { return (M + 191) / 192 * 192 <= (M + 255) / 256 * 256 ? 192 : 256; }
+
+// Whether row-major weights go through the large-tile kernel.  More than 160 rows, against the kernel with 32 x 32 products, us:
+//   one row group: V = 151936, H = 4096 M = 192 371 -> 296; V = 64000, H = 2560 M = 200 99 -> 86; V = 32000, H = 4096 M = 256 112 -> 84; V = 2000, H = 2048 M = 224 52 -> 32;
+//     13 to 15 panels per CU, one pass that wastes slots, only where the other one pads the rows (193 to 224) or W's stream weighs: V = 50021, H = 2048 M = 177 58 -> 63, M = 208 69 -> 67,
+//     M = 256 70 -> 75, H = 4096 118 -> 114, 133 -> 121, 135 -> 136; V = 57344, H = 1024 M = 177 32.0 -> 36.6.
+//     H = 256, up to 192 rows: V = 4000 M = 177 9.7 -> 10.8, V = 12001 10.8 -> 12.3, V = 40001 13.9 -> 14.6; but V = 24000 12.0 -> 11.5, V = 151936 44 -> 35
+//   several: by the time of a workgroup's tiles, the rounds of the other kernel's tiles over the CUs times their rows against the panel slots of a range times 2 tm + 11 (see
+//     mf_group_cost).  Per unit this kernel is the faster one by 0.64 (0.69 where rows are no power of two apart: the other one reads those faster).  Taken:
+//     V = 151936, H = 4096 M = 320 536 -> 451, M = 1152 1489 -> 1368; V = 50021, H = 2560 M = 768 249 -> 204.  Not taken: M = 576 V = 64000, H = 2560 212 -> 258, V = 128256,
+//     H = 2560 414 -> 475, V = 151936, H = 2048 414 -> 431; M = 1152 V = 64000, H = 2048 332 -> 349, V = 100000, H = 3072 765 -> 798.  Of 800 shapes of H = 1024 to 8192, M = 257 to
+//     4096, V = 8001 to 151936 the slower one is taken by more than 2 % in 33, by 6 % at most (five groups on 240 of 256 CUs above all).
+//     H = 256, where a range is one pass with three or four panels per wave and the other kernel one round: V = 28002 M = 300 14.3 -> 16.1, V = 8000 M = 1152 13.6 -> 15.2
+// 113 to 160 rows, against the weight-streaming kernels, by panels per CU:
+//   17 and more: V = 151936 M = 128 H = 4096 284 -> 249, H = 1280 107 -> 99.5; V = 128256, H = 2048 135 -> 133; V = 68000, H = 2560 113 -> 103
+//   13 to 16: V = 64000, H = 2560 M = 128 70 -> 73; rows of logits not aligned V = 61001, H = 2048 M = 128 65.7 -> 60.8, M = 160 72.7 -> 63.9, V = 53249, H = 4096 108.5 -> 109.3
+//   9 to 12: V = 36864 M = 128 H = 1280 32.9 -> 30.1, H = 4096 89 -> 79; V = 45056, H = 1280 33.6 -> 33.7; V = 49152, H = 2048 55.7 -> 54.3
+//   8: V = 32000 M = 128 H = 1024 17.0 -> 17.9, H = 4096 64.8 -> 64.7; V = 32001, H = 2560 44.1 -> 49.1
+//   fewer, aligned: not measured, as 8; not aligned V = 24001, H = 1280 M = 128 24.6 -> 22.3, V = 20001, H = 2048 M = 160 34.7 -> 32.0, V = 8001, H = 4096 34.5 -> 45
+constexpr bool lm_rowmajor_large_tile(int M, int H, int V, int cus)
+{
+    if (M <= 112 || H % 256 != 0 || (size_t)V > ((size_t)1 << 32) / (4 * (size_t)(304 + 16))) return false;
+    const int n_panels = (V + 15) / 16, panels = mf_per_range(n_panels, 1, cus);
+    if (M <= 160) return !(panels < 5 || panels == 8 || (V % 4 == 0 && (panels < 8 || (panels > 12 && panels <= 16))));
+    const MfmaLayout L = mfma_layout_for(M, V, cus, 0);
+    if (L.groups == 1) {
+        if (panels >= 13 && panels <= 15 && H < 4096) return M > 192 && M <= 224;
+        return H >= 512 || M > 192 || (panels >= 6 && panels <= 8) || panels > 16;
+    }
+    const int rows = lm_big2_rows(M);
+    const long tiles = (long)((M + rows - 1) / rows) * ((V + 255) / 256), rounds = (tiles + cus - 1) / cus;
+    if (H < 512 && rounds == 1 && L.per_range > 10 && L.per_range <= kMfPassPanels) return false;
+    return rounds * rows * 5000 >= ((H & (H - 1)) == 0 ? 642 : 692) * mf_slots10(L.per_range, L.tm) * (2 * L.tm + 11);
 }
 
 struct PanelShare { int p0, np; };             // first panel and number of panels, 0 .. 4; p0 is a panel of the range also where np == 0
