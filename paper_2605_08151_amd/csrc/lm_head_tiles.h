@@ -123,12 +123,18 @@ constexpr int lm_big2_rows(int M) { return (M + 191) / 192 * 192 <= (M + 255) / 
 //   13 to 16: V = 64000, H = 2560 M = 128 70 -> 73; rows of logits not aligned V = 61001, H = 2048 M = 128 65.7 -> 60.8, M = 160 72.7 -> 63.9, V = 53249, H = 4096 108.5 -> 109.3
 //   9 to 12: V = 36864 M = 128 H = 1280 32.9 -> 30.1, H = 4096 89 -> 79; V = 45056, H = 1280 33.6 -> 33.7; V = 49152, H = 2048 55.7 -> 54.3
 //   8: V = 32000 M = 128 H = 1024 17.0 -> 17.9, H = 4096 64.8 -> 64.7; V = 32001, H = 2560 44.1 -> 49.1
-//   fewer, aligned: not measured, as 8; not aligned V = 24001, H = 1280 M = 128 24.6 -> 22.3, V = 20001, H = 2048 M = 160 34.7 -> 32.0, V = 8001, H = 4096 34.5 -> 45
-constexpr bool lm_rowmajor_large_tile(int M, int H, int V, int cus)
+//   fewer, aligned: not measured, as 8; not aligned V = 24001, H = 1280 M = 128 24.6 -> 22.3, V = 20001, H = 2048 M = 160 34.7 -> 32.0, V = 8001, H = 4096 34.5 -> 45; but not where this
+//     kernel reads W nontemporal and the memory-side cache holds much of it from one call to the next (over three matrices in turn V = 24001, H = 2560, 117 MiB, M = 128 41.7 -> 44.5; two in
+//     turn V = 20001, H = 4096, 156 MiB 52.9 -> 54.9, V = 24001, H = 4096, 188 MiB 58.6 -> 57.8, V = 28001, 219 MiB 64 -> 61)
+constexpr bool lm_rowmajor_large_tile(int M, int H, int V, int cus, size_t cache = (size_t)256 << 20)
 {
     if (M <= 112 || H % 256 != 0 || (size_t)V > ((size_t)1 << 32) / (4 * (size_t)(304 + 16))) return false;
     const int n_panels = (V + 15) / 16, panels = mf_per_range(n_panels, 1, cus);
-    if (M <= 160) return !(panels < 5 || panels == 8 || (V % 4 == 0 && (panels < 8 || (panels > 12 && panels <= 16))));
+    if (M <= 160) {
+        if (panels < 5 || panels == 8 || (V % 4 == 0 && (panels < 8 || (panels > 12 && panels <= 16)))) return false;
+        const size_t bytes = (size_t)V * H * 2;
+        return panels > 8 || bytes <= cache * 3 / 8 || bytes > cache * 5 / 8;
+    }
     const MfmaLayout L = mfma_layout_for(M, V, cus, 0);
     if (L.groups == 1) {
         if (panels >= 13 && panels <= 15 && H < 4096) return M > 192 && M <= 224;

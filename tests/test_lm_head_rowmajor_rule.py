@@ -24,7 +24,9 @@ int main()
         {192, 4096, 151936, true}, {200, 2560, 64000, true}, {300, 1024, 64000, true}, {400, 2048, 50021, true}, {768, 2560, 50021, true}, {1152, 4096, 151936, true}, {2048, 1024, 100000, true},
         {576, 2560, 64000, false}, {576, 4096, 64000, false}, {576, 1280, 128256, false}, {576, 2560, 128256, false}, {576, 2048, 151936, false}, {576, 5120, 128256, false},
         {768, 2560, 64000, false}, {1152, 2048, 64000, false}, {1152, 2560, 32000, false}, {1152, 3072, 100000, false}, {1206, 2560, 50021, false},
-        {177, 256, 4000, false}, {192, 256, 12001, false}, {208, 256, 12001, true}, {177, 512, 4000, true}, {300, 256, 28002, false}, {1152, 256, 8000, false}, {257, 256, 20001, true}};
+        {177, 256, 4000, false}, {192, 256, 12001, false}, {208, 256, 12001, true}, {177, 512, 4000, true}, {300, 256, 28002, false}, {1152, 256, 8000, false}, {257, 256, 20001, true},
+        {128, 1280, 24001, true}, {160, 2048, 20001, true}, {128, 2560, 24001, false}, {160, 2560, 20001, false}, {128, 2048, 28001, false}, {128, 4096, 28001, true}, {128, 4096, 8001, false},
+        {128, 2560, 24000, false}, {128, 2560, 64000, false}, {128, 2560, 64001, true}, {128, 4096, 151936, true}, {112, 4096, 151936, false}};
     for (const auto& m : measured) CHECK(lm_rowmajor_large_tile(m.M, m.H, m.V, 256) == m.large, "M=%d H=%d V=%d", m.M, m.H, m.V);
     const int Vs[] = {1, 17, 999, 8200, 32000, 50021, 128256, 151937}, cuss[] = {8, 64, 256, 304}, Hs[] = {64, 256, 320, 512, 2560, 4096};
     int taken = 0;
