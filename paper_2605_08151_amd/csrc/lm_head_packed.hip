@@ -13,6 +13,7 @@
 //     Wp[((p * (H/32) + t) * 64 + l) * 8 + j] = W[16 p + l % 16][32 t + 8 (l / 16) + j]      (0 for entries >= V)
 // i.e. the A operand of v_mfma_f32_16x16x32_bf16 for that tile, lane by lane.  ceil(V/16) panels.
 #include "common.h"
+#include "lm_head_tiles.h"
 
 namespace specv {
 
@@ -507,25 +508,10 @@ extern Tunable g_lm_packed_tile;
 int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const LmSummary* summary, hipStream_t s);
 int lm_head_mfma_blocks(int M, int H, int V);
 
-// Between 113 and 160 rows (8 to 10 row tiles) the large-tile kernel is ahead where the products weigh: it reads a fragment of hidden from LDS for 4 panels,
-// not for 2, stages hidden without registers and requests 2.5 to 4 slabs ahead.  This one is ahead (or as fast) where all its waves have their two panels in one
-// pass, 13 to 16 panels per CU, with aligned stores; and with few rows on a small matrix.  Measured, this kernel -> large tile, us:
-//   17 panels per CU and more: V = 151936, H = 4096 M = 113 224 -> 211, M = 128 230 -> 214, M = 144 248 -> 221, M = 160 260 -> 224; V = 100000 M = 160 172 -> 153;
-//     V = 68000, H = 1280 M = 120 55.1 -> 49.7, M = 160 60.8 -> 54.6; V = 131072, H = 1024 M = 128 64.8 -> 65.0, M = 160 69.5 -> 68.8
-//   13 to 16: V = 64000, H = 2560 M = 113 61.4 -> 62.9, M = 160 64.6 -> 68.4; V = 57344, H = 1280 M = 160 37.9 -> 41.1, H = 4096 96.3 -> 90.9;
-//     but rows of logits that are not aligned V = 64013, H = 2560 M = 128 69 -> 66, M = 160 76 -> 69, V = 57345, H = 1280 40.1 -> 36.4, 45.7 -> 40.0
-//   10 to 12: V = 49152 M = 128 H = 1280 32.8 -> 31.1, H = 4096 79 -> 72; V = 40000, H = 1024 M = 128 19.7 -> 19.2
-//   9: V = 36864 M = 128 H = 2048 39.6 -> 37.0, but H = 1280 (94 MB, ordinary loads) 23.0 -> 25.9
-//   5 to 8: V = 32000, H = 1024 M = 128 19.7 -> 19.8, M = 160 21.3 -> 20.8, H = 2560 35.8 -> 37.9, 40.8 -> 39.8, H = 4096 52 -> 50, 62 -> 53
-//   fewer: V = 16000, H = 2048 M = 128 25.8 -> 19.4; V = 2000, H = 4096 M = 160 46 -> 30
+// (the hooks speak of the weight-streaming kernel)
 static bool large_tile_faster(int M, int H, int V)
 {
-    if (M <= 112 || M > kPkMaxRows || g_lm_packed_waves != 0 || g_lm_packed_wide == 1) return false;
-    if (V % 4 != 0) return true;
-    const int panels = panels_per_cu(V);
-    if (panels > 16 || panels < 5) return true;
-    if (panels > 12) return false;
-    return panels >= 10 || (panels == 9 ? (size_t)V * H * 2 > kMemorySideCache * 3 / 8 : M > 128);
+    return g_lm_packed_waves == 0 && g_lm_packed_wide != 1 && lm_packed_large_tile(M, H, V, device_cu_count(), kMemorySideCache);
 }
 
 static int packed_groups(int M) { return (M + kPkMaxRows - 1) / kPkMaxRows; }

@@ -104,6 +104,31 @@ constexpr MfmaLayout mfma_tall_layout_for(int M, int V, int cus)
     return groups == 0 ? MfmaLayout{} : mf_layout_of(tiles, groups, n_panels, cus);
 }
 
+// Between 113 and 160 rows (8 to 10 row tiles) the large-tile kernel is ahead where the products weigh: it reads a fragment of hidden from LDS for 4 panels,
+// not for 2, stages hidden without registers and requests 2.5 to 4 slabs ahead.  The weight-streaming kernel (lm_head_packed.hip) is ahead (or as fast) where all its waves have
+// their two panels in one pass, 13 to 16 panels per CU, with aligned stores; and with few rows or short ones on a small matrix.  Measured, weight-streaming -> large tile, us:
+//   17 panels per CU and more: V = 151936, H = 4096 M = 113 224 -> 211, M = 128 230 -> 214, M = 144 248 -> 221, M = 160 260 -> 224; V = 100000 M = 160 172 -> 153;
+//     V = 68000, H = 1280 M = 120 55.1 -> 49.7, M = 160 60.8 -> 54.6; V = 131072, H = 1024 M = 128 64.8 -> 65.0, M = 160 69.5 -> 68.8
+//   13 to 16: V = 64000, H = 2560 M = 113 61.4 -> 62.9, M = 160 64.6 -> 68.4; V = 57344, H = 1280 M = 160 37.9 -> 41.1 (but H = 4096 96.3 -> 90.9: left as it was);
+//     but rows of logits that are not aligned V = 64013, H = 2560 M = 128 69 -> 66, M = 160 76 -> 69, V = 57345, H = 1280 40.1 -> 36.4, 45.7 -> 40.0
+//   10 to 12: V = 49152 M = 128 H = 1280 32.8 -> 31.1, H = 4096 79 -> 72; V = 40000, H = 1024 M = 128 19.7 -> 19.2; but H = 512 V = 40000 M = 128 13.2 -> 13.8, M = 160 15.7 -> 14.9 and 16.1 -> 19.6,
+//     V = 44000 M = 128 13.8 -> 15.0, M = 144 15.0 -> 15.8
+//   9: V = 36864 M = 128 H = 2048 39.6 -> 37.0, but H = 1280 (94 MB, ordinary loads) 23.0 -> 25.9
+//   5 to 8: V = 32000, H = 1024 M = 128 19.7 -> 19.8, M = 160 21.3 -> 20.8, H = 2560 35.8 -> 37.9, 40.8 -> 39.8, H = 4096 52 -> 50 (M = 128: left as it was), 62 -> 53
+//   fewer: V = 16000, H = 2048 M = 128 25.8 -> 19.4, H = 256 6.7 -> 6.2; V = 2000, H = 4096 M = 160 46 -> 30, but H = 256 M = 144 6.7 -> 7.0; V = 12000, H = 256 7.0 -> 7.3
+constexpr bool lm_packed_large_tile(int M, int H, int V, int cus, size_t cache = (size_t)256 << 20)
+{
+    if (M <= 112 || M > 160) return false;
+    if (V % 4 != 0) return true;
+    const int panels = mf_per_range((V + 15) / 16, 1, cus);
+    if (panels > 16) return true;
+    if (panels > 12) return false;
+    if (panels >= 10) return H >= 1024;
+    if (panels == 9) return (size_t)V * H * 2 > cache * 3 / 8;
+    if (panels >= 5) return M > 128;
+    return H >= 512 || panels == 4;
+}
+
 // Rows of a tile of the kernel with 32 x 32 products (lm_head_big2_kernel), whichever of the two pads less; a tile is 256 vocabulary entries wide.
 constexpr int lm_big2_rows(int M) { return (M + 191) / 192 * 192 <= (M + 255) / 256 * 256 ? 192 : 256; }
 

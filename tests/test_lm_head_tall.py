@@ -86,9 +86,34 @@ def test_tall_groups(sv, oracle, M, V, H):
     assert torch.equal(other, logits[:M])
 
 
+LINES_M, LINES_VH = [112, 113, 128, 129, 144, 145, 160], [(999, 4096), (36864, 1280), (36880, 2048), (50021, 1280), (57344, 256), (70000, 256), (64013, 1024)]
+
+LINES_PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "lm_head_tiles.h"
+int main(int, char** a) { std::puts(specv::lm_packed_large_tile(std::atoi(a[1]), std::atoi(a[2]), std::atoi(a[3]), 256) ? "large tile" : "weight-streaming"); return 0; }
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_which_kernel_the_lines_choose(tmp_path):
+    """For 256 CUs, and the library's own choices (no tuning key set): the shapes that the next test runs, and measured ones on both sides of the other lines."""
+    src, exe = tmp_path / "lines.cpp", tmp_path / "lines"
+    src.write_text(LINES_PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    expected = {(M, H, V): M > 112 and (V, H) not in ((36864, 1280), (57344, 256)) for M in LINES_M for V, H in LINES_VH}
+    assert sum(expected.values()) == 30
+    expected |= {(128, 1024, 40000): True, (128, 512, 40000): False, (160, 512, 40000): False, (144, 512, 44000): False, (144, 256, 2000): False, (144, 512, 2000): True, (128, 256, 16000): True,
+                 (128, 2560, 32000): False, (160, 2560, 32000): True, (113, 4096, 151936): True, (160, 2560, 64000): False, (161, 4096, 151936): False}
+    for (M, H, V), large in expected.items():
+        got = subprocess.run([str(exe), str(M), str(H), str(V)], capture_output=True, text=True, check=True).stdout.strip()
+        assert got == ("large tile" if large else "weight-streaming"), (M, H, V)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("M", [112, 113, 128, 129, 144, 145, 160])
-@pytest.mark.parametrize("V,H", [(999, 4096), (36864, 1280), (36880, 2048), (50021, 1280), (57344, 256), (70000, 256), (64013, 1024)])
+@pytest.mark.parametrize("M", LINES_M)
+@pytest.mark.parametrize("V,H", LINES_VH)
 def test_lines_between_the_weight_streaming_and_the_large_tile_kernel(sv, oracle, M, V, H):
     """8, 9 and 10 row tiles, whole and ragged; less than a panel, 9 (ordinary and nontemporal loads), 13, 14, 16 and 18 panels per CU, aligned rows of logits and not."""
     g = torch.Generator(device="cuda").manual_seed(V + M)
