@@ -15,6 +15,8 @@
 #include "common.h"
 #include "lm_head_tiles.h"
 
+#include <type_traits>
+
 namespace specv {
 
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // (a row of logits starts at any multiple of 4 bytes)
@@ -316,38 +318,44 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
             // all the wave's entries of a row (whole cache lines where rows are aligned), 4 or 8 rows at a time, instead of 64 bytes of each of 16 rows.
             // LDS operations of one wave execute in order, so the patch needs no barrier and no second copy.  A row starts at any multiple of 4 bytes; the last
             // entries of one whose length is no multiple of 4 are stored one by one.  (All entries one by one there: V = 50021, H = 1280 M = 57 30.1 -> 27.0 us,
-            // M = 96 35.8 -> 31.8; V = 32001, H = 1024 M = 60 20.4 -> 16.9.)
+            // M = 96 35.8 -> 31.8; V = 32001, H = 1024 M = 60 20.4 -> 16.9.)  Whole rows have code of their own: through that with the tails V = 64000, H = 512 M = 144 20.7 -> 21.6,
+            // V = 44000 15.1 -> 15.7, H = 256 M = 112 10.0 -> 10.3.
             constexpr int kLanesPerRow = TN * 4, kRowsPerStore = 64 / kLanesPerRow;
             const int srow = lane / kLanesPerRow, scol = (lane % kLanesPerRow) * 4;     // this lane's row and entry when storing
             const int col0 = st_p0 * 16 + scol;
-            const bool mine = scol < st_np * 16, col_ok = mine && col0 + 4 <= V;
-            const int col_tail = mine && !col_ok ? V - col0 : 0;
             uint32_t off = ((uint32_t)srow * (uint32_t)V + (uint32_t)col0) * 4u;
             const uint32_t row_step = (uint32_t)kRowsPerStore * 4u * (uint32_t)V;
+            auto store_rows = [&](auto ragged) {
+                constexpr bool kRagged = decltype(ragged)::value;
+                const bool mine = scol < st_np * 16, col_ok = mine && (kRagged ? col0 + 4 <= V : col0 < V);
+                const int col_tail = kRagged && mine && !col_ok ? V - col0 : 0;
+                typedef typename std::conditional<kRagged, f32x4_any, f32x4>::type Quad;
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
+                for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    *reinterpret_cast<f32x4*>(patch + l16 * kPatchPitch + (tn * 16 + kg * 4) * 4) = acc[tn][tm];
-                    acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-#pragma unroll
-                for (int q = 0; q < 16 / kRowsPerStore; ++q) {
-                    const int prow = q * kRowsPerStore + srow, row = tm * 16 + prow;
-                    const f32x4 v = *reinterpret_cast<const f32x4*>(patch + prow * kPatchPitch + scol * 4);
-                    if (row < M && col_ok) {
-                        f32x4_any* dst = reinterpret_cast<f32x4_any*>(reinterpret_cast<unsigned char*>(C) + off);
-                        if constexpr (NT) __builtin_nontemporal_store((f32x4_any)v, dst); else *dst = v;
+                    for (int tn = 0; tn < TN; ++tn) {
+                        *reinterpret_cast<f32x4*>(patch + l16 * kPatchPitch + (tn * 16 + kg * 4) * 4) = acc[tn][tm];
+                        acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
                     }
-                    if (row < M && col_tail > 0) {    // the matrix ends inside these four entries
-                        float* dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(C) + off);
 #pragma unroll
-                        for (int e = 0; e < 3; ++e) if (e < col_tail) dst[e] = v[e];
+                    for (int q = 0; q < 16 / kRowsPerStore; ++q) {
+                        const int prow = q * kRowsPerStore + srow, row = tm * 16 + prow;
+                        const f32x4 v = *reinterpret_cast<const f32x4*>(patch + prow * kPatchPitch + scol * 4);
+                        if (row < M && col_ok) {
+                            Quad* dst = reinterpret_cast<Quad*>(reinterpret_cast<unsigned char*>(C) + off);
+                            if constexpr (NT) __builtin_nontemporal_store((Quad)v, dst); else *dst = v;
+                        }
+                        if (kRagged && row < M && col_tail > 0) {     // the matrix ends inside these four entries
+                            float* dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(C) + off);
+#pragma unroll
+                            for (int e = 0; e < 3; ++e) if (e < col_tail) dst[e] = v[e];
+                        }
+                        off += row_step;              // one running byte offset (M * V * 4 < 2^32 per launch) instead of
+                        asm volatile("" : "+v"(off)); // one row address per store kept alive across the whole pass
                     }
-                    off += row_step;                  // one running byte offset (M * V * 4 < 2^32 per launch) instead of
-                    asm volatile("" : "+v"(off));     // one row address per store kept alive across the whole pass
                 }
-            }
+            };
+            if (V % 4 == 0) store_rows(std::false_type{}); else store_rows(std::true_type{});
         }
         if (!more) break;
     }
