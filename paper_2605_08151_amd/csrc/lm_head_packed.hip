@@ -438,6 +438,12 @@ static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M,
 // With more panels 8 waves are ahead (V = 50021, H = 1280, M = 40: 27.5 against 30.5).
 static bool few_panels(int V) { return panels_per_cu(V) <= 8; }
 
+// The logits are stored nontemporal for one and two row groups, also where rows share lines with their neighbours (V no multiple of 16): followed by the acceptance that reads them,
+// as in a step, ordinary -> nontemporal, us: V = 50021, H = 1280 M = 57 36.2 -> 35.6, M = 96 41.8 -> 41.8 (the LM head alone 26.2 -> 27.0, 30.3 -> 31.9); V = 100001, H = 4096 M = 57
+// 160.7 -> 147.3, V = 151935 250 -> 228; row-major V = 64013, H = 4096 110.0 -> 110.6, V = 151935 272 -> 248.  But a vocabulary of at most 2 panels per CU, whose stores are all there is
+// between the last product and the end: V = 2001, H = 1280 M = 16 6.0 -> 6.4, M = 57 8.6 -> 9.1, M = 96 11.7 -> 12.3; V = 8001 M = 16 6.5 -> 6.9, M = 57 9.6 -> 10.1.
+static bool ordinary_stores(int H, int V) { return V % 16 != 0 && panels_per_cu(V) <= 2 && (size_t)V * H * 2 <= kMemorySideCache * 3 / 8; }
+
 template <int TM>
 static int launch_packed_auto(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
                               float* blk_max, int32_t* blk_arg)
@@ -450,7 +456,10 @@ static int launch_packed_auto(const uint16_t* a, const uint16_t* wp, float* c, i
     // W ring is 5 us slower with either); at M = 40 both take 218 us; at M = 576 and 1152 8 waves are 5 % ahead
     if (g_lm_packed_waves == 4) return launch_packed<TM, 1, 4, true, 4>(a, wp, c, M, H, V, groups, s);
     if (groups > 2) return launch_packed<TM, 1, 8, false, 2>(a, wp, c, M, H, V, groups, s);
-    if (groups == 1 && g_lm_packed_waves != 8 && few_panels(V)) return launch_packed<TM, 2, 4, true, 2>(a, wp, c, M, H, V, groups, s);
+    if (groups == 1 && g_lm_packed_waves != 8 && few_panels(V)) {
+        if (ordinary_stores(H, V)) return launch_packed<TM, 2, 4, false, 2>(a, wp, c, M, H, V, groups, s);
+        return launch_packed<TM, 2, 4, true, 2>(a, wp, c, M, H, V, groups, s);
+    }
     return launch_packed<TM, 1, 8, true, 2>(a, wp, c, M, H, V, groups, s);
 }
 
