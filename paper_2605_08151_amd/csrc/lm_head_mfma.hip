@@ -57,7 +57,7 @@ int lm_head_mfma_dispatch(const uint16_t* a, const uint16_t* wp, float* c, int M
     if (summary) return lm_head_mfma_summary(nt, a, wp, c, M, H, V, L, sm, s);
     if (g_lm_mfma_rows == 0 && g_lm_mfma_nt == 0) {      // (the benchmark hooks speak of groups of at most 16 tiles)
         const MfmaLayout T = mfma_tall_layout_for(M, V, device_cu_count());
-        if (T.groups > 0) return lm_head_tile(mfma_loads(T.groups, H, V), nt, a, wp, c, M, H, V, T, s);
+        if (T.groups > 0 && mfma_tall_pays(T, H)) return lm_head_tile(mfma_loads(T.groups, H, V), nt, a, wp, c, M, H, V, T, s);
     }
     switch (mfma_loads(L.groups, H, V)) {
         case kStreamLoads: return L.tm < 11 ? lm_head_tile(kStreamLoads, nt, a, wp, c, M, H, V, L, s) : lm_head_mfma_stream(nt, a, wp, c, M, H, V, L, sm, s);

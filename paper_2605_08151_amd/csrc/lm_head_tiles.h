@@ -104,6 +104,14 @@ constexpr MfmaLayout mfma_tall_layout_for(int M, int V, int cus)
     return groups == 0 ? MfmaLayout{} : mf_layout_of(tiles, groups, n_panels, cus);
 }
 
+// Whether the products weigh enough for them: what a tile costs besides (its operands' first slabs, its stores) grows with its height.  At most 16 / 17 and 18 tiles, us, one group: H = 256 V = 64000
+// M = 260 19.4 / 22.2, V = 128256 M = 288 39 / 43; H = 512 V = 128256 60 / 64, V = 100000 55.6 / 52.2; H = 768 V = 50021 34.3 / 32.8, V = 128256 79 / 76, V = 64000 35.5 / 36.7.
+// Several groups: H = 256 V = 32000 M = 560, one pass, 19.8 / 21.0, V = 64000, two, 44.6 / 36.1, V = 128256 M = 1152 191 / 146; H = 512 V = 32000 M = 560 29.5 / 29.8, M = 1152 53 / 51.
+constexpr bool mfma_tall_pays(const MfmaLayout& L, int H)
+{
+    return L.groups == 1 ? H >= 768 : H >= 512 || L.per_range > kMfPassPanels;
+}
+
 // Between 113 and 160 rows (8 to 10 row tiles) the large-tile kernel is ahead where the products weigh: it reads a fragment of hidden from LDS for 4 panels,
 // not for 2, stages hidden without registers and requests 2.5 to 4 slabs ahead.  The weight-streaming kernel (lm_head_packed.hip) is ahead (or as fast) where all its waves have
 // their two panels in one pass, 13 to 16 panels per CU, with aligned stores; and with few rows or short ones on a small matrix.  Measured, weight-streaming -> large tile, us:

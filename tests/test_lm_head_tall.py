@@ -23,6 +23,9 @@ int main()
 {
     const struct { int M, V, groups; } expected[] = {{272, 151936, 1}, {576, 151936, 2}, {1152, 151936, 4}, {576, 100000, 0}, {288, 32000, 0}, {1204, 151936, 0}, {256, 151936, 0}, {161, 500, 0}};
     for (const auto& e : expected) CHECK(mfma_tall_layout_for(e.M, e.V, 256).groups == e.groups, "M=%d V=%d: %d groups", e.M, e.V, mfma_tall_layout_for(e.M, e.V, 256).groups);
+    const struct { int M, H, V; bool pays; } short_rows[] = {{260, 256, 64000, false}, {288, 512, 128256, false}, {257, 768, 60021, true}, {288, 1024, 62003, true},
+        {560, 256, 32000, false}, {576, 256, 130000, true}, {560, 512, 32000, true}, {1152, 256, 128256, true}};
+    for (const auto& e : short_rows) CHECK(mfma_tall_layout_for(e.M, e.V, 256).groups > 0 && mfma_tall_pays(mfma_tall_layout_for(e.M, e.V, 256), e.H) == e.pays, "M=%d H=%d V=%d", e.M, e.H, e.V);
     const int Vs[] = {1, 17, 999, 8200, 32000, 50021, 128256, 151937}, cuss[] = {8, 64, 256, 304};
     int tall = 0;
     for (int M = 161; M <= 2000; M += 7) for (int V : Vs) for (int cus : cuss) {
@@ -60,7 +63,7 @@ def test_tall_layouts_own_every_row_and_panel_once(tmp_path):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,V,H", [(257, 60021, 256), (272, 64000, 2560), (273, 64016, 1280), (288, 62003, 1024), (288, 100000, 512), (529, 32000, 1024), (561, 32000, 2048),
+@pytest.mark.parametrize("M,V,H", [(257, 60021, 768), (272, 64000, 2560), (273, 64016, 1280), (288, 62003, 1024), (288, 100000, 768), (529, 32000, 1024), (561, 32000, 2048),
                                    (576, 31003, 512), (560, 32000, 512), (576, 130000, 256), (576, 137001, 256), (1057, 31000, 1024), (1152, 31999, 2048)])
 def test_tall_groups(sv, oracle, M, V, H):
     """One, two and four groups; 17 and 18 tiles, the last one whole and ragged, groups of one tile fewer beside them; the three kinds of loads of W, stores nontemporal and
