@@ -20,16 +20,7 @@ static bool mfma_nt(int M, int V)
     return forced == 1 || (forced == 0 && M <= 416 && V % 16 == 0);
 }
 
-// One row group reads W once, bound by that stream: nontemporal, by the rule of the weight-streaming kernel (the tree step, M = 188, V = 151936,
-// H = 4096 378 -> 360 us, M = 216 408 -> 394; V = 64000, H = 2560 179 -> 167).
-// Several groups that read panels a multiple of 64 KB apart: global loads (buffer -> global, V = 151936 / 100000, H = 4096: M = 257 357 -> 330 /
-// 264 -> 247 us, M = 576 622 -> 606 / 408 -> 395, M = 1152 1157 -> 1119 / 793 -> 782; H = 2048 M = 257 191 -> 179, M = 576 351 -> 328).  Elsewhere
-// buffer loads (H = 2560: M = 576 398 -> 409 / 260 -> 265, M = 1152 757 -> 779; H = 3072 854 -> 902; H = 1024 357 -> 360).
-static MfmaLoads mfma_loads(int groups, int H, int V)
-{
-    if (groups == 1 && (size_t)V * H * 2 > kMemorySideCache * 3 / 8) return kStreamLoads;
-    return groups > 1 && H % 2048 == 0 ? kGlobalLoads : kBufferLoads;
-}
+static MfmaLoads mfma_loads(int groups, int H, int V) { return mfma_loads_for(groups, H, V, kMemorySideCache); }
 
 // blocks per row of the summaries for this shape; 0 if the large-tile kernel does not take it
 int lm_head_mfma_blocks(int M, int H, int V)

@@ -51,8 +51,6 @@ __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make
 
 // LOADS: how W is read, see MfmaLoads; NT: nontemporal stores of the logits (a template argument: of two stores in the branches of a flag the compiler makes one ordinary store);
 // SUMMARY instantiations also leave the block summaries described at LmSummary.
-// buffer loads; global loads; nontemporal global loads; the same two of a matrix that is row-major, not packed
-enum MfmaLoads { kBufferLoads, kGlobalLoads, kStreamLoads, kRowLoads, kRowStreamLoads };
 
 template <int TM, MfmaLoads LOADS, bool NT, bool SUMMARY>
 __device__ __forceinline__ void lm_head_mfma_tiles(

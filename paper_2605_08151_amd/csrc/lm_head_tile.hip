@@ -18,7 +18,7 @@ static int launch_tile_count(const uint16_t* a, const uint16_t* wp, float* c, in
 
 int lm_head_tile(MfmaLoads loads, bool nt, const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, const MfmaLayout& L, hipStream_t s)
 {
-    if (L.tm != 17 && L.tm != 18 && L.tm > 10) return fail(SPEC_ESHAPE, "spec_lm_head_packed: no instantiation for %d row tiles per group", L.tm);
+    if (!mf_tile_built(loads, L.tm)) return fail(SPEC_ESHAPE, "spec_lm_head_packed: no instantiation for %d row tiles per group", L.tm);
     switch (loads) {
         case kStreamLoads: return nt ? launch_tile_count<kStreamLoads, true>(a, wp, c, M, H, V, L, s) : launch_tile_count<kStreamLoads, false>(a, wp, c, M, H, V, L, s);
         case kGlobalLoads: return launch_tile_count<kGlobalLoads, false>(a, wp, c, M, H, V, L, s);

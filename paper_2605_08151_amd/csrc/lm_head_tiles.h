@@ -112,6 +112,27 @@ constexpr bool mfma_tall_pays(const MfmaLayout& L, int H)
     return L.groups == 1 ? H >= 768 : H >= 512 || L.per_range > kMfPassPanels;
 }
 
+// How W is read: buffer loads; global loads; nontemporal global loads; the same two of a matrix that is row-major, not packed
+enum MfmaLoads { kBufferLoads, kGlobalLoads, kStreamLoads, kRowLoads, kRowStreamLoads };
+
+// One row group reads W once, bound by that stream: nontemporal, by the rule of the weight-streaming kernel (the tree step, M = 188, V = 151936,
+// H = 4096 378 -> 360 us, M = 216 408 -> 394; V = 64000, H = 2560 179 -> 167).
+// Several groups that read panels a multiple of 64 KB apart: global loads (buffer -> global, V = 151936 / 100000, H = 4096: M = 257 357 -> 330 /
+// 264 -> 247 us, M = 576 622 -> 606 / 408 -> 395, M = 1152 1157 -> 1119 / 793 -> 782; H = 2048 M = 257 191 -> 179, M = 576 351 -> 328).  Elsewhere
+// buffer loads (H = 2560: M = 576 398 -> 409 / 260 -> 265, M = 1152 757 -> 779; H = 3072 854 -> 902; H = 1024 357 -> 360).
+constexpr MfmaLoads mfma_loads_for(int groups, int H, int V, size_t cache = (size_t)256 << 20)
+{
+    if (groups == 1 && (size_t)V * H * 2 > cache * 3 / 8) return kStreamLoads;
+    return groups > 1 && H % 2048 == 0 ? kGlobalLoads : kBufferLoads;
+}
+
+// The instantiations of lm_head_tile.hip; lm_head_mfma_buffer.hip and _global.hip have 9 to 16 row tiles, _stream.hip 11 to 16.
+constexpr bool mf_tile_built(MfmaLoads loads, int tm)
+{
+    if (loads > kStreamLoads) return false;
+    return tm == 17 || tm == 18 || (tm == 8 && loads != kGlobalLoads) || ((tm == 9 || tm == 10) && loads == kStreamLoads);
+}
+
 // Between 113 and 160 rows (8 to 10 row tiles) the large-tile kernel is ahead where the products weigh: it reads a fragment of hidden from LDS for 4 panels,
 // not for 2, stages hidden without registers and requests 2.5 to 4 slabs ahead.  The weight-streaming kernel (lm_head_packed.hip) is ahead (or as fast) where all its waves have
 // their two panels in one pass, 13 to 16 panels per CU, with aligned stores; and with few rows or short ones on a small matrix.  Measured, weight-streaming -> large tile, us:

@@ -15,6 +15,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 PROGRAM = r"""
 #include <cstdio>
+#include <initializer_list>
 #include <vector>
 #include "lm_head_tiles.h"
 using namespace specv;
@@ -47,6 +48,21 @@ int main()
         for (int n : owner) CHECK(n == 1, "M=%d V=%d: a panel owned %d times", M, V, n);
     }
     CHECK(tall > 100, "%d layouts", tall);
+    // every call reaches an instantiation that is built; what is not built is refused
+    for (int tm = 1; tm <= 20; ++tm)
+        for (MfmaLoads loads : {kBufferLoads, kGlobalLoads, kStreamLoads, kRowLoads, kRowStreamLoads}) {
+            const bool built = loads <= kStreamLoads && (tm == 17 || tm == 18 || (tm == 8 && loads != kGlobalLoads) || ((tm == 9 || tm == 10) && loads == kStreamLoads));
+            CHECK(mf_tile_built(loads, tm) == built, "loads %d, %d tiles", (int)loads, tm);
+        }
+    for (int M = 113; M <= 2000; M += M < 320 ? 1 : 7) for (int V : Vs) for (int cus : cuss) for (int H : {256, 768, 2048, 4096}) {
+        if (M <= 160 && !lm_packed_large_tile(M, H, V, cus)) continue;
+        MfmaLayout L = mfma_tall_layout_for(M, V, cus);
+        const bool tall_one = L.groups > 0 && mfma_tall_pays(L, H);
+        if (!tall_one) L = mfma_layout_for(M, V, cus, 0);
+        const MfmaLoads loads = mfma_loads_for(L.groups, H, V);
+        const bool in_tile_file = tall_one || (loads == kStreamLoads ? L.tm < 11 : loads == kBufferLoads && L.tm < 9);
+        CHECK(in_tile_file ? mf_tile_built(loads, L.tm) : L.tm >= (loads == kStreamLoads ? 11 : 9) && L.tm <= 16, "M=%d V=%d H=%d: loads %d, %d tiles", M, V, H, (int)loads, L.tm);
+    }
     std::puts("ok");
     return 0;
 }
