@@ -17,6 +17,7 @@
 //   the transposing LDS read (ds_read_b64_tr_b16), Q fragments are re-read from a shared LDS copy.
 //   Every chunk writes an unnormalised fp32 partial (O, running max, sum); a second kernel merges the
 //   partials of a row in split order (deterministic) and writes bf16.
+#include "attn_lds.h"
 #include "batch_rules.h"
 #include "common.h"
 #include "kv_stream.h"
@@ -181,8 +182,8 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     __shared__ int s_stream;
     if (STREAM && scan) kv_scan<NW>(p, i, kbeg / kP, p.plan_items != nullptr, &s_stream);
     const bool tree = p.parent != nullptr;
-    int32_t* sPar = sPT + (min(p.chunk_target, p.max_kv_len) / kP + 1);
-    unsigned long long* sAnc = reinterpret_cast<unsigned long long*>(sPar + 64);   // [NR * 16], 8-byte aligned
+    int32_t* sPar = sPT + attn_page_slots(min(p.chunk_target, p.max_kv_len));
+    unsigned long long* sAnc = reinterpret_cast<unsigned long long*>(sPar + kAttnParents);   // [NR * 16], 8-byte aligned
     constexpr int kQLoads = (NR * 16 * 16 + kThreads - 1) / kThreads;              // 16-byte chunks of Q per thread
     u32x4 qv[kQLoads];
 #pragma unroll
@@ -633,9 +634,9 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
     const bool tree = p.parent != nullptr;
     int limit = row_ok ? (tree ? kend : min(c + qj + 1, kend)) : 0;      // the row sees key positions t < limit
     // tree verification: bit a of anc is set iff candidate a is on this row's path to the root (a chain: all ones)
-    int32_t* sPar = sPT + (min(p.chunk_target, p.max_kv_len) / kP + 1);
+    int32_t* sPar = sPT + attn_page_slots(min(p.chunk_target, p.max_kv_len));
     // (the masks live in LDS and are read in the few stages that reach the candidates, as in the kernel above)
-    unsigned long long* sAnc = reinterpret_cast<unsigned long long*>(sPar + 64);   // [NW * 16]
+    unsigned long long* sAnc = reinterpret_cast<unsigned long long*>(sPar + kAttnParents);   // [NW * 16]
     if (tree) {
         int bad_tree = 0;
         if (tid < n) {
@@ -1137,7 +1138,7 @@ static AttnPlanCfg attn_plan_cfg(int B, int Hq, int Hkv, int max_kv_len, int max
 static size_t attn_smem_bytes(int NR, int NW, int NBUF, int chunk_keys)
 {
     // K/V buffers, Q, page ids, parents, masks, the waves' maxima and sums
-    return (size_t)NW * NBUF * kWaveLds + (size_t)NR * 16 * kRowBytes + (size_t)(chunk_keys / kP + 1) * 4 + 64 * 4 + 8 + (size_t)NR * 16 * 8 + (size_t)2 * NW * NR * 16 * 4;
+    return (size_t)NW * NBUF * kWaveLds + (size_t)NR * 16 * kRowBytes + attn_mask_offset(chunk_keys) + (size_t)NR * 16 * 8 + (size_t)2 * NW * NR * 16 * 4;
 }
 
 template <int NR, int NW, int NBUF, bool FINAL, bool STREAM>
@@ -1161,7 +1162,7 @@ Tunable g_attn_rows_ring{0};  // benchmark hook: K/V stages per workgroup of the
 
 static size_t attn_rows_smem_bytes(int chunk_keys, int ring)
 {
-    return (size_t)ring * kRowsStageBytes + (size_t)(chunk_keys / kP + 1) * 4 + 64 * 4 + 8 + 8 * 16 * 8;
+    return (size_t)ring * kRowsStageBytes + attn_mask_offset(chunk_keys) + 8 * 16 * 8;
 }
 
 template <int NW, bool FINAL, int RING, bool STREAM>
