@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void lm_head_pack_kernel(const uint16_t* __res
 // SW: W by nontemporal loads (one row group and a matrix too large for the memory-side cache);
 // STATS: also leave per-block maxima for greedy acceptance.
 // ------------------------------------------------------------------------------------------------
-template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW, bool ROWS>
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW, bool RAGGED, bool ROWS>
 __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
     const uint16_t* __restrict__ A_all, const uint16_t* __restrict__ Wp, float* __restrict__ C_all,
     int M_all, int H, int V, int n_panels, int panels_per_wg, int groups, int rows_per_group,
@@ -318,44 +318,40 @@ __global__ __launch_bounds__(64 * NW, 1) void lm_head_packed_kernel(
             // all the wave's entries of a row (whole cache lines where rows are aligned), 4 or 8 rows at a time, instead of 64 bytes of each of 16 rows.
             // LDS operations of one wave execute in order, so the patch needs no barrier and no second copy.  A row starts at any multiple of 4 bytes; the last
             // entries of one whose length is no multiple of 4 are stored one by one.  (All entries one by one there: V = 50021, H = 1280 M = 57 30.1 -> 27.0 us,
-            // M = 96 35.8 -> 31.8; V = 32001, H = 1024 M = 60 20.4 -> 16.9.)  Whole rows have code of their own: through that with the tails V = 64000, H = 512 M = 144 20.7 -> 21.6,
-            // V = 44000 15.1 -> 15.7, H = 256 M = 112 10.0 -> 10.3.
+            // M = 96 35.8 -> 31.8; V = 32001, H = 1024 M = 60 20.4 -> 16.9.)  Whole rows (not RAGGED) have kernels of their own: through the code with tails V = 64000, H = 512 M = 144
+            // 20.7 -> 21.6, V = 44000 15.1 -> 15.7; with both codes in one kernel V = 32000, H = 1024 M = 20 12.8 -> 13.2.
             constexpr int kLanesPerRow = TN * 4, kRowsPerStore = 64 / kLanesPerRow;
             const int srow = lane / kLanesPerRow, scol = (lane % kLanesPerRow) * 4;     // this lane's row and entry when storing
             const int col0 = st_p0 * 16 + scol;
             uint32_t off = ((uint32_t)srow * (uint32_t)V + (uint32_t)col0) * 4u;
             const uint32_t row_step = (uint32_t)kRowsPerStore * 4u * (uint32_t)V;
-            auto store_rows = [&](auto ragged) {
-                constexpr bool kRagged = decltype(ragged)::value;
-                const bool mine = scol < st_np * 16, col_ok = mine && (kRagged ? col0 + 4 <= V : col0 < V);
-                const int col_tail = kRagged && mine && !col_ok ? V - col0 : 0;
-                typedef typename std::conditional<kRagged, f32x4_any, f32x4>::type Quad;
+            const bool mine = scol < st_np * 16, col_ok = mine && (RAGGED ? col0 + 4 <= V : col0 < V);
+            const int col_tail = RAGGED && mine && !col_ok ? V - col0 : 0;
+            typedef typename std::conditional<RAGGED, f32x4_any, f32x4>::type Quad;
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm) {
+            for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
-                    for (int tn = 0; tn < TN; ++tn) {
-                        *reinterpret_cast<f32x4*>(patch + l16 * kPatchPitch + (tn * 16 + kg * 4) * 4) = acc[tn][tm];
-                        acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    }
-#pragma unroll
-                    for (int q = 0; q < 16 / kRowsPerStore; ++q) {
-                        const int prow = q * kRowsPerStore + srow, row = tm * 16 + prow;
-                        const f32x4 v = *reinterpret_cast<const f32x4*>(patch + prow * kPatchPitch + scol * 4);
-                        if (row < M && col_ok) {
-                            Quad* dst = reinterpret_cast<Quad*>(reinterpret_cast<unsigned char*>(C) + off);
-                            if constexpr (NT) __builtin_nontemporal_store((Quad)v, dst); else *dst = v;
-                        }
-                        if (kRagged && row < M && col_tail > 0) {     // the matrix ends inside these four entries
-                            float* dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(C) + off);
-#pragma unroll
-                            for (int e = 0; e < 3; ++e) if (e < col_tail) dst[e] = v[e];
-                        }
-                        off += row_step;              // one running byte offset (M * V * 4 < 2^32 per launch) instead of
-                        asm volatile("" : "+v"(off)); // one row address per store kept alive across the whole pass
-                    }
+                for (int tn = 0; tn < TN; ++tn) {
+                    *reinterpret_cast<f32x4*>(patch + l16 * kPatchPitch + (tn * 16 + kg * 4) * 4) = acc[tn][tm];
+                    acc[tn][tm] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
-            };
-            if (V % 4 == 0) store_rows(std::false_type{}); else store_rows(std::true_type{});
+#pragma unroll
+                for (int q = 0; q < 16 / kRowsPerStore; ++q) {
+                    const int prow = q * kRowsPerStore + srow, row = tm * 16 + prow;
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(patch + prow * kPatchPitch + scol * 4);
+                    if (row < M && col_ok) {
+                        Quad* dst = reinterpret_cast<Quad*>(reinterpret_cast<unsigned char*>(C) + off);
+                        if constexpr (NT) __builtin_nontemporal_store((Quad)v, dst); else *dst = v;
+                    }
+                    if (RAGGED && row < M && col_tail > 0) {      // the matrix ends inside these four entries
+                        float* dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(C) + off);
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) if (e < col_tail) dst[e] = v[e];
+                    }
+                    off += row_step;                  // one running byte offset (M * V * 4 < 2^32 per launch) instead of
+                    asm volatile("" : "+v"(off));     // one row address per store kept alive across the whole pass
+                }
+            }
         }
         if (!more) break;
     }
@@ -380,18 +376,18 @@ static void packed_geometry(int V, int groups, int* ranges, int* per_range)
     *ranges = ((n_panels + *per_range - 1) / *per_range + 7) / 8 * 8;
 }
 
-template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW, bool ROWS>
+template <int TM, int RS, int NW, bool NT, int TN, bool STATS, bool SW, bool RAGGED, bool ROWS>
 static int launch_packed_as(const uint16_t* a, const uint16_t* wp, float* c, int M, int H, int V, int groups, hipStream_t s,
                             float* blk_max, int32_t* blk_arg)
 {
     constexpr int BM = TM * 16;
     const size_t smem = 2 * (size_t)BM * kPkHPitch + NW * 16 * (TN * 64 + 16) + (STATS ? (size_t)BM * NW * 8 : 0);
     static LdsGrantTable granted = {};
-    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW, ROWS>), smem, granted, ROWS ? "spec_lm_head" : "spec_lm_head_packed")) return rc;
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW, RAGGED, ROWS>), smem, granted, ROWS ? "spec_lm_head" : "spec_lm_head_packed")) return rc;
     int ranges, per_range;
     packed_geometry(V, groups, &ranges, &per_range);
     const int ppr = (per_range + NW * TN - 1) / (NW * TN);
-    hipLaunchKernelGGL((lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW, ROWS>), dim3(ranges * groups), dim3(64 * NW), smem, s, a, wp, c, M, H, V,
+    hipLaunchKernelGGL((lm_head_packed_kernel<TM, RS, NW, NT, TN, STATS, SW, RAGGED, ROWS>), dim3(ranges * groups), dim3(64 * NW), smem, s, a, wp, c, M, H, V,
                        (V + 15) / 16, per_range, groups, BM, blk_max, blk_arg, ranges * ppr, ppr);
     return SPEC_OK;
 }
@@ -427,9 +423,11 @@ static int launch_packed(const uint16_t* a, const uint16_t* wp, float* c, int M,
 {
     if constexpr (NT) {
         if (groups == 1 && stream_weights<ROWS>(H, V, NW * TN))
-            return launch_packed_as<TM, RS, NW, NT, TN, STATS, true, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
+            return V % 4 == 0 ? launch_packed_as<TM, RS, NW, NT, TN, STATS, true, false, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg)
+                              : launch_packed_as<TM, RS, NW, NT, TN, STATS, true, true, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
     }
-    return launch_packed_as<TM, RS, NW, NT, TN, STATS, false, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
+    return V % 4 == 0 ? launch_packed_as<TM, RS, NW, NT, TN, STATS, false, false, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg)
+                      : launch_packed_as<TM, RS, NW, NT, TN, STATS, false, true, ROWS>(a, wp, c, M, H, V, groups, s, blk_max, blk_arg);
 }
 
 // A vocabulary of at most 8 panels per CU (V <= 32768 on 256 CUs) is one pass of 4 waves with 2 panels each and a 2-slab ring; 8 waves would have one
