@@ -22,6 +22,7 @@
 #include "common.h"
 #include "kv_stream.h"
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -72,6 +73,7 @@ struct AttnParams {
     int head_first;
     // Fixed chunks, at most 64 requests, more workgroups than CUs: the requests with the longest contexts go first (see longest_first)
     int by_length;
+    int page_slots;            // see attn_page_slots
     float stream_keys;         // committed keys of the batch above which its K/V is too large for the memory-side cache (0: it never is)
 };
 
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
     __shared__ int s_stream;
     if (STREAM && scan) kv_scan<NW>(p, i, kbeg / kP, p.plan_items != nullptr, &s_stream);
     const bool tree = p.parent != nullptr;
-    int32_t* sPar = sPT + attn_page_slots(min(p.chunk_target, p.max_kv_len));
+    int32_t* sPar = sPT + p.page_slots;
     unsigned long long* sAnc = reinterpret_cast<unsigned long long*>(sPar + kAttnParents);   // [NR * 16], 8-byte aligned
     constexpr int kQLoads = (NR * 16 * 16 + kThreads - 1) / kThreads;              // 16-byte chunks of Q per thread
     u32x4 qv[kQLoads];
@@ -634,7 +636,7 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
     const bool tree = p.parent != nullptr;
     int limit = row_ok ? (tree ? kend : min(c + qj + 1, kend)) : 0;      // the row sees key positions t < limit
     // tree verification: bit a of anc is set iff candidate a is on this row's path to the root (a chain: all ones)
-    int32_t* sPar = sPT + attn_page_slots(min(p.chunk_target, p.max_kv_len));
+    int32_t* sPar = sPT + p.page_slots;
     // (the masks live in LDS and are read in the few stages that reach the candidates, as in the kernel above)
     unsigned long long* sAnc = reinterpret_cast<unsigned long long*>(sPar + kAttnParents);   // [NW * 16]
     if (tree) {
@@ -1318,6 +1320,7 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
         p.part_l = (float*)(ws + round_up(units * kD * 4, 256) + round_up(units * 4, 256));
     }
 
+    p.page_slots = attn_page_slots(std::min(p.chunk_target, p.max_kv_len));
     p.by_length = !pc.on && B > 1 && B <= 64 && (long)p.splits * Hkv * B > device_cu_count();
     p.head_first = grid.x <= 65535;                       // (the second dimension's limit)
     if (p.head_first) grid = dim3(grid.y, grid.x, grid.z);
