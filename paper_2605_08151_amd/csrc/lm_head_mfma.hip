@@ -63,7 +63,7 @@ int lm_head_rowmajor(bool stream, bool nt, const uint16_t* a, const uint16_t* w,
 bool lm_head_rowmajor_dispatch(const uint16_t* a, const uint16_t* w, float* c, int M, int H, int V, hipStream_t s, int* rc)
 {
     static_assert(kMfRing * kMfSlab == 256, "the rule's multiple of H");
-    if (!lm_rowmajor_large_tile(M, H, V, device_cu_count(), kMemorySideCache)) return false;
+    if (M <= 112 || !lm_rowmajor_large_tile(M, H, V, device_cu_count(), kMemorySideCache)) return false;    // (rows first: the number of CUs is a call into the runtime)
     const MfmaLayout L = mfma_layout_for(M, V, device_cu_count(), 0);
     *rc = lm_head_rowmajor(mfma_loads(L.groups, H, V) == kStreamLoads, M <= 416 && V % 16 == 0, a, w, c, M, H, V, L, s);
     return true;

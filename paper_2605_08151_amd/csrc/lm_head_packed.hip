@@ -526,7 +526,8 @@ int lm_head_mfma_blocks(int M, int H, int V);
 // (the hooks speak of the weight-streaming kernel)
 static bool large_tile_faster(int M, int H, int V)
 {
-    return g_lm_packed_waves == 0 && g_lm_packed_wide != 1 && lm_packed_large_tile(M, H, V, device_cu_count(), kMemorySideCache);
+    // (rows first: the number of CUs is a call into the runtime)
+    return M > 112 && M <= kPkMaxRows && g_lm_packed_waves == 0 && g_lm_packed_wide != 1 && lm_packed_large_tile(M, H, V, device_cu_count(), kMemorySideCache);
 }
 
 static int packed_groups(int M) { return (M + kPkMaxRows - 1) / kPkMaxRows; }
