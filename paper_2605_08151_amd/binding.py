@@ -11,12 +11,17 @@ import os
 
 import torch
 
+_HERE = os.path.dirname(os.path.abspath(__file__))
+_BUILD = "`python -c 'import __graft_entry__ as g; g.build()'`"
+
 try:
     from . import _marshal
 except ImportError as e:                              # as with the library: no fallback
-    raise ImportError("paper_2605_08151_amd/_marshal.so is not built; run `python -c 'import __graft_entry__ as g; g.build()'`") from e
+    _path = os.path.join(_HERE, "_marshal.so")
+    if not os.path.exists(_path):
+        raise ImportError(f"{_path} is not built; run {_BUILD}") from e
+    raise ImportError(f"{_path} does not load ({e}): it is built against one torch, this one is {torch.__version__}; run {_BUILD} again") from e
 
-_HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libspecverify.so")
 
 EXPORTS = (

@@ -1,4 +1,7 @@
-"""Builds libspecverify.so (HIP, gfx950 only) with hipcc and the binding's _marshal.so with g++, in-tree."""
+"""Builds libspecverify.so (HIP, gfx950 only) with hipcc and the binding's _marshal.so with g++, in-tree.
+
+_marshal.so is host code against the headers of the torch that is installed: it has to be built again for another one.  libspecverify.so has no torch types.
+"""
 from __future__ import annotations
 
 import os
@@ -47,10 +50,13 @@ def build(verbose: bool = False, jobs: int = 7) -> str:
 
 def build_marshal() -> str:
     """The extension module behind binding.py's per-tensor checks (host code, against the headers of the torch that is installed)."""
+    import shutil
     import sysconfig
 
     import torch
     from torch.utils.cpp_extension import include_paths
+    if shutil.which("g++") is None:
+        raise RuntimeError("the binding's _marshal.so needs g++")
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     include = [x for d in include_paths("cuda") + [sysconfig.get_paths()["include"]] for x in ("-I", d)]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",

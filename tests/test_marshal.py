@@ -42,3 +42,25 @@ def test_addresses_and_streams():
     with torch.cuda.stream(side):
         assert binding._stream() == side.cuda_stream
     assert binding._stream() != side.cuda_stream
+
+
+def test_the_import_says_why_the_module_is_missing(tmp_path):
+    """Not built, or built and not loadable (against another torch, say): two errors."""
+    import os
+    import shutil
+    import subprocess
+    import sys
+    package = tmp_path / "pkg"
+    package.mkdir()
+    (package / "__init__.py").write_text("")
+    shutil.copy(binding.__file__, package / "binding.py")
+
+    def error():
+        done = subprocess.run([sys.executable, "-c", "import pkg.binding"], cwd=tmp_path, capture_output=True, text=True, env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+        assert done.returncode != 0
+        return done.stderr.strip().splitlines()[-1]
+
+    assert "_marshal.so is not built" in error()
+    (package / "_marshal.so").write_bytes(b"\x7fELF, but no library")
+    last = error()
+    assert "does not load" in last and torch.__version__ in last and "not built" not in last
