@@ -3,7 +3,7 @@
 
 namespace specv {
 
-Tunable g_lm_packed_tile{0};   // benchmark hook: 0 = automatic (this kernel for M > 160), 1 = the weight-streaming kernel over row groups
+Tunable g_lm_packed_tile{0};   // benchmark hook: 0 = automatic (this kernel for M > 160 and by lm_packed_large_tile from 113 on), 1 = the weight-streaming kernel over row groups
 Tunable g_lm_mfma_nt{0};       // benchmark hook: nontemporal logits stores, 0 = automatic (see mfma_nt), 1 = always, 2 = never
 Tunable g_lm_mfma_rows{0};     // benchmark hook: rows per group of this kernel at most (144..256), 0 = automatic (256)
 

@@ -275,9 +275,10 @@ __device__ __forceinline__ void lm_head_mfma_tiles(
     // not follow a vector instruction that wrote its operand by less than 2 wait states.  Before the first step of a pass, where copies do stand,
     // the MFMAs bring their own s_nop; that nothing else is in the way, around the branches for the last row tile and for panel slots above all, is
     // checked on the built code by a test (s_nops at those branches too: M = 768, V = 32000, H = 4096 161 -> 164 us, M = 1152 263 -> 279).  Those waits count W
-    // loads only (the direct loads are invisible to the compiler): a wait for a chunk requested 3.5 steps ago allows ~28
-    // younger requests in flight, i.e. it covers requests at least 1.75 steps old, and a direct load is needed 2.5 steps
-    // after it was issued: it is never what the math waits for.
+    // loads only (the direct loads are invisible to the compiler): a wait for a chunk allows 7 SLOTS younger requests in flight, of the 2 SLOTS + QN of a step, direct loads
+    // among them.  With 4 slots that is 1.75 steps at 8 direct loads a step and 1.65 at 9 (17 and 18 tiles), less than the 2.5 steps a direct load has, which thus is seldom what the math
+    // waits for; in a last pass of two panels per wave it is 1.1 to 1.75, and the math does wait for direct loads before they are needed.  That slab s+1 is complete in LDS is not
+    // left to this: the counted wait in front of its barrier says so.
     static_assert(4 + QN <= TM && TM + 3 <= 2 * TM - kHfCross - 1, "the requests of a step precede its barrier");
     // FIRST: the first slab of a pass (the products start from zero).  SLOTS: panels per wave whose products are taken.  last_iter: the last 4 slabs of a pass.
     // stores: the counted stores of a tile were issued between the requests for slab s+1 and this step.

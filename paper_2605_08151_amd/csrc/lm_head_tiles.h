@@ -25,7 +25,8 @@ constexpr int mf_per_range(int n_panels, int groups, int cus)
 }
 
 // Time of a workgroup in units of half a row tile's products for one panel per wave: a pass costs as many panel slots as its fullest wave owns
-// (two at least), each 2 tm + 11 (the products, and the operands and the epilogue that do not depend on the rows).
+// (two at least), each 2 tm + 11 (the products, and the operands and the epilogue that do not depend on the rows).  It chooses among groups of up to 16 tiles, and was fitted when all passes
+// went through the code for four panels per wave; a last pass with up to two now costs 0.73 of a full one (mf_slots10), not the half that stands here.
 constexpr long mf_group_cost(int tiles, int groups, int n_panels, int cus)
 {
     const int per_range = mf_per_range(n_panels, groups, cus), tm = (tiles + groups - 1) / groups;
