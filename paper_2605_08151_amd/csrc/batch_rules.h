@@ -10,9 +10,10 @@ namespace specv {
 //   B = 384 4.5 / 4.5 / 4.5, 15.7 against 2.8 / 2.8 / 5.1, 19.9; 1024 6.5 / 6.5 / 6.4 against 3.6 / 3.6 / 6.6, 31 against 3.8 / 3.8 / 7.8, 44 (5.4 / 5.7 / 9.8, 55)
 //   B = 2048 6.0 / 6.0 / 11.2, 60 against 5.2 / 5.2 / 9.9, 54 (7.9 / 8.0 / 11.1, 63); 8192 46.6 / 46.5 / 46.2 against 15.6 / 15.8 / 43.5 (23 / 25 / 51)
 struct DivergenceShape { int threads, per; };
-constexpr DivergenceShape divergence_shape(int B, int cus)
+// (256 CUs taken for granted: asking the runtime for the device would cost as much as the rule gives)
+constexpr DivergenceShape divergence_shape(int B)
 {
-    return B <= cus ? DivergenceShape{512, 8} : B <= 4 * cus ? DivergenceShape{512, 2} : DivergenceShape{256, 4};
+    return B <= 256 ? DivergenceShape{512, 8} : B <= 4 * 256 ? DivergenceShape{512, 2} : DivergenceShape{256, 4};
 }
 
 // Up to so many requests attention's merge kernels count those that start before their row, 256 in a round trip; beyond, a binary search is ahead, whose dependent

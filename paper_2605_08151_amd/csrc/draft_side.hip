@@ -161,7 +161,7 @@ extern "C" int spec_divergence(const int32_t* p_tokens, const int32_t* p_indptr,
     if (B == 0) return SPEC_OK;
     if (!p_tokens || !p_indptr || !h_tokens || !h_indptr || !delta) return fail(SPEC_EINVAL, "spec_divergence: NULL pointer argument");
     hipStream_t s = (hipStream_t)stream;
-    const DivergenceShape shape = divergence_shape(B, device_cu_count());
+    const DivergenceShape shape = divergence_shape(B);
     if (shape.threads == 256) hipLaunchKernelGGL((divergence_kernel<256, 4>), dim3(B), dim3(256), 0, s, p_tokens, p_indptr, h_tokens, h_indptr, delta);
     else if (shape.per == 2) hipLaunchKernelGGL((divergence_kernel<512, 2>), dim3(B), dim3(512), 0, s, p_tokens, p_indptr, h_tokens, h_indptr, delta);
     else hipLaunchKernelGGL((divergence_kernel<512, 8>), dim3(B), dim3(512), 0, s, p_tokens, p_indptr, h_tokens, h_indptr, delta);

@@ -19,9 +19,9 @@ using namespace specv;
 int main()
 {
     // many positions per round trip where few pairs wait for it; elsewhere little is read behind an early difference; only shapes that are built
-    for (int cus = 8; cus <= 304; cus += 8) for (int B = 1; B <= 9 * cus; ++B) {
-        const DivergenceShape s = divergence_shape(B, cus);
-        CHECK(s.threads * s.per == (B <= cus ? 4096 : 1024), "B=%d: %d x %d", B, s.threads, s.per);
+    for (int B = 1; B <= 9 * 256; ++B) {
+        const DivergenceShape s = divergence_shape(B);
+        CHECK(s.threads * s.per == (B <= 256 ? 4096 : 1024), "B=%d: %d x %d", B, s.threads, s.per);
         CHECK((s.threads == 512 && (s.per == 8 || s.per == 2)) || (s.threads == 256 && s.per == 4), "B=%d: %d x %d", B, s.threads, s.per);
     }
     CHECK(kMergeCounted >= 256 && kMergeCounted <= 2048, "requests are counted up to %d", kMergeCounted);
