@@ -1,6 +1,8 @@
 // Rules on the number of requests in a batch.  Plain arithmetic without device types: the launches, their kernels and a CPU test share it.
 #pragma once
 
+#include <cstdint>
+
 namespace specv {
 
 // Threads per pair of sequences in divergence_kernel, and positions per thread in one memory round trip.  Few pairs wait for round trips: many positions in each.
@@ -21,5 +23,33 @@ constexpr DivergenceShape divergence_shape(int B)
 // B = 2048 83 -> 82, 4096 169 -> 159, 8192 365 -> 320, 16384 820 -> 630, 65535 5715 -> 2605; of two rows, 32 heads: 2048 352 -> 343, 4096 759 -> 686, 8192 1770 -> 1439.
 // At B = 1024 43 with either.
 constexpr int kMergeCounted = 1024;
+
+// Attention in fixed chunks: a request has `splits` places of Hkv workgroups in the grid, by the stated bound, and as many pieces as it is long; what is left over ends at once.
+// Workgroups go round the 8 XCDs in grid order, and inside an XCD round its 4 shader engines.  With piece k in place k of every request and Hkv * splits a multiple of a power of two,
+// requests that fill only their first places lie on the same ones (4 kv heads, 2 places, 1 piece: all work on four XCDs).  So the pieces of a request begin `turn` places
+// on, one more with every group of requests that fills a multiple of 32 workgroups.  Only where a request's places are at most 32 workgroups: with more there was as much
+// lost as gained (1550 shapes, lengths that differ or half the bound: 28 faster by more than 3 %, 26 slower); up to 32, of 4700 such shapes 1207 faster, 69 slower.
+// Pieces first in the grid -> heads first -> heads first with the turn, us, contexts of half the bound: 128 requests of 5 rows, 2855 keys, 4 heads 167 -> 197 -> 121; 510 of 1 row,
+// 2317 keys, 4 heads 553 -> 622 -> 394; 31 of 1 row, 6512 keys, 2 heads 52 -> 59 -> 44.  Pieces first is still ahead by more than 3 % in 20 of 7800: few requests whose
+// pieces, about one per CU, meet on one shader engine (9 requests x 2 heads, 9 of 17 places: 64 -> 98).
+struct PieceTurn { int shift; uint32_t magic; };
+
+constexpr PieceTurn piece_turn(int Hkv, int splits)
+{
+    long unit = (long)Hkv * splits;
+    if (splits < 2 || unit > 32) return {31, 0};          // no turn: request numbers are below 65536
+    int shift = 5;                                        // log2(32 / gcd(32, Hkv * splits))
+    for (; unit % 2 == 0; unit /= 2) --shift;
+    return {shift, (uint32_t)(0x100000000ull / (uint32_t)splits) + 1};
+}
+
+// The piece at place `place` of request i.  (x mod splits by a multiplication: exact for x below 2^16 and splits up to 32, since x * (magic * splits - 2^32) < 2^32.)
+constexpr int piece_of_place(PieceTurn t, int splits, int place, int i)
+{
+    const uint32_t x = (uint32_t)i >> t.shift;
+    const int turn = (int)(x - (uint32_t)((uint64_t)x * t.magic >> 32) * (uint32_t)splits);
+    const int piece = place - turn;
+    return piece < 0 ? piece + splits : piece;
+}
 
 }  // namespace specv

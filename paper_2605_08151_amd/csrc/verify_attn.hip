@@ -71,6 +71,7 @@ struct AttnParams {
     // Workgroups that start together take the heads of one piece: their pages are neighbours in HBM (a page of all heads is one stretch of Hkv * 4 KB), and are
     // read at about the same time.  Pieces first -> heads first: 128 requests x 8 heads x 2.6k keys 266.7 -> 220.7 us (5.2 -> 6.3 TB/s)
     int head_first;
+    PieceTurn turn;            // fixed chunks: which piece of its request a place in the grid stands for
     // Fixed chunks, at most 64 requests, more workgroups than CUs: the requests with the longest contexts go first (see longest_first)
     int by_length;
     int page_slots;            // see attn_page_slots
@@ -142,8 +143,8 @@ __global__ __launch_bounds__(NW * 64) void verify_attn_kernel(AttnParams p)
         ns_plan = __builtin_amdgcn_readfirstlane(it[2]);
         pb_plan = __builtin_amdgcn_readfirstlane(it[3]);
     } else {
-        split = piece;
         i = blockIdx.z;
+        split = FINAL ? piece : piece_of_place(p.turn, p.splits, piece, i);
     }
     unsigned char* sKV = smem + wave * (NBUF * kWaveLds); // this wave's NBUF x (32 K rows, 32 V rows)
     unsigned char* sQ = smem + NW * NBUF * kWaveLds;      // shared: NR*16 query rows
@@ -581,8 +582,8 @@ __global__ __launch_bounds__(NW * 64, (NW <= 5 ? 4 : (NW == 6 ? 3 : 2))) void ve
         ns_plan = __builtin_amdgcn_readfirstlane(it[2]);
         pb_plan = __builtin_amdgcn_readfirstlane(it[3]);
     } else {
-        split = piece;
         i = blockIdx.z;
+        split = FINAL ? piece : piece_of_place(p.turn, p.splits, piece, i);
     }
     unsigned char* sRing = smem;                                         // kRowsStages x (32 K rows, 32 V rows)
     int32_t* sPT = reinterpret_cast<int32_t*>(smem + kRowsStages * kRowsStageBytes);   // page ids of this chunk
@@ -1322,6 +1323,7 @@ extern "C" int spec_verify_attn_tree(const void* q, const void* k_cache, const v
 
     p.page_slots = attn_page_slots(std::min(p.chunk_target, p.max_kv_len));
     p.by_length = !pc.on && B > 1 && B <= 64 && (long)p.splits * Hkv * B > device_cu_count();
+    p.turn = piece_turn(Hkv, p.splits);
     p.head_first = grid.x <= 65535;                       // (the second dimension's limit)
     if (p.head_first) grid = dim3(grid.y, grid.x, grid.z);
 
