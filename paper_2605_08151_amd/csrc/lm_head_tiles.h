@@ -168,7 +168,8 @@ constexpr int lm_big2_rows(int M) { return (M + 191) / 192 * 192 <= (M + 255) / 
 //     M = 256 70 -> 75, H = 4096 118 -> 114, 133 -> 121, 135 -> 136; V = 57344, H = 1024 M = 177 32.0 -> 36.6.
 //     H = 256, up to 192 rows: V = 4000 M = 177 9.7 -> 10.8, V = 12001 10.8 -> 12.3, V = 40001 13.9 -> 14.6; but V = 24000 12.0 -> 11.5, V = 151936 44 -> 35
 //   several: by the time of a workgroup's tiles, the rounds of the other kernel's tiles over the CUs times their rows against the panel slots of a range times 2 tm + 11 (see
-//     mf_group_cost).  Per unit this kernel is the faster one by 0.64 (0.69 where rows are no power of two apart: the other one reads those faster).  Taken:
+//     mf_group_cost).  Per unit this kernel is the faster one by 0.64 (0.69 where rows are no power of two apart: the other one reads those faster; 0.62 either way from 1 GiB of W on:
+//     V = 151936 M = 576 H = 4096 793 -> 741, H = 6144 1169 -> 1125, H = 8192 1521 -> 1409, M = 1152 H = 6144 2173 -> 2061).  Taken:
 //     V = 151936, H = 4096 M = 320 536 -> 451, M = 1152 1489 -> 1368; V = 50021, H = 2560 M = 768 249 -> 204.  Not taken: M = 576 V = 64000, H = 2560 212 -> 258, V = 128256,
 //     H = 2560 414 -> 475, V = 151936, H = 2048 414 -> 431; M = 1152 V = 64000, H = 2048 332 -> 349, V = 100000, H = 3072 765 -> 798.  Of 800 shapes of H = 1024 to 8192, M = 257 to
 //     4096, V = 8001 to 151936 the slower one is taken by more than 2 % in 33, by 6 % at most (five groups on 240 of 256 CUs above all).
@@ -198,7 +199,8 @@ constexpr bool lm_rowmajor_large_tile(int M, int H, int V, int cus, size_t cache
     const int rows = lm_big2_rows(M);
     const long tiles = (long)((M + rows - 1) / rows) * ((V + 255) / 256), rounds = (tiles + cus - 1) / cus;
     if (H < 512 && rounds == 1 && L.per_range > 10 && L.per_range <= kMfPassPanels) return false;
-    return rounds * rows * 5000 >= ((H & (H - 1)) == 0 ? 642 : 692) * mf_slots10(L.per_range, L.tm) * (2 * L.tm + 11);
+    const int per_unit = (size_t)V * H * 2 >= cache * 4 ? 619 : (H & (H - 1)) == 0 ? 642 : 692;
+    return rounds * rows * 5000 >= per_unit * mf_slots10(L.per_range, L.tm) * (2 * L.tm + 11);
 }
 
 struct PanelShare { int p0, np; };             // first panel and number of panels, 0 .. 4; p0 is a panel of the range also where np == 0

@@ -22,6 +22,7 @@ int main()
 {
     const struct { int M, H, V; bool large; } measured[] = {
         {192, 4096, 151936, true}, {200, 2560, 64000, true}, {300, 1024, 64000, true}, {400, 2048, 50021, true}, {768, 2560, 50021, true}, {1152, 4096, 151936, true}, {2048, 1024, 100000, true},
+        {576, 4096, 151936, true}, {576, 6144, 151936, true}, {576, 8192, 151936, true}, {1152, 6144, 151936, true}, {768, 6144, 128256, true}, {576, 6144, 128256, false},
         {576, 2560, 64000, false}, {576, 4096, 64000, false}, {576, 1280, 128256, false}, {576, 2560, 128256, false}, {576, 2048, 151936, false}, {576, 5120, 128256, false},
         {768, 2560, 64000, false}, {1152, 2048, 64000, false}, {1152, 2560, 32000, false}, {1152, 3072, 100000, false}, {1206, 2560, 50021, false},
         {177, 256, 4000, false}, {192, 256, 12001, false}, {208, 256, 12001, true}, {177, 512, 4000, true}, {300, 256, 28002, false}, {1152, 256, 8000, false}, {257, 256, 20001, true},
